@@ -350,9 +350,9 @@ typedef struct {
   int32_t use_graph;              /* 1: capture once and replay as a HIP graph; 0: launch
                                      directly, with timing events around the bucket
                                      launches */
-  int32_t lazy_clash;             /* 0: decide every torsion sample's clash test in the
-                                     scoring pass (pruned pair list); 1: test only the
-                                     winner and drop it while it clashes */
+  int32_t lazy_clash;             /* torsion scans, 0: clash tests drop whole groups of
+                                     samples before any is scored; 1: only samples that
+                                     beat the best so far are tested */
 } lg_tuning;
 
 lg_status lg_set_tuning(lg_pocket pocket, const lg_tuning* tuning);

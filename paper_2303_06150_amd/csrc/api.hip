@@ -20,15 +20,16 @@
 #include "lg_internal.h"
 
 namespace lg {
-hipError_t launch_dock_plain(int nslot, int spl, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D,
-                             int lig, hipStream_t st);
-hipError_t launch_dock_bucket(int nslot, int spl, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
-                              const DockDev& D, const QueueDev& Q, hipStream_t st);
-hipError_t occupancy_dock_bucket(int nslot, int spl, int wpb, int tab_len, int* blocks_per_cu);
+hipError_t launch_dock_plain(int nslot, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D, int lig,
+                             hipStream_t st);
+hipError_t launch_dock_bucket(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
+                              const QueueDev& Q, hipStream_t st);
+size_t dock_lds_bytes(int nslot, int wpb, int tab_len, int angles);
+hipError_t occupancy_dock_bucket(int nslot, int wpb, int tab_len, int angles, int* blocks_per_cu);
 hipError_t launch_valu_probe(int kind, int blocks, int iters, float* out, hipStream_t st);
-hipError_t launch_dock_sites(int nslot, int spl, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
-                             const DockDev& D, const QueueDev& Q, const SitesDev& Sd, hipStream_t st);
-hipError_t attributes_dock_bucket(int nslot, int spl, hipFuncAttributes* attr);
+hipError_t launch_dock_sites(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
+                             const QueueDev& Q, const SitesDev& Sd, hipStream_t st);
+hipError_t attributes_dock_bucket(int nslot, hipFuncAttributes* attr);
 hipError_t launch_topk(int nslot, const LigDev& Lg, const DockDev& D, int n, int k, float* score, int32_t* rid,
                        float* ox, float* oy, float* oz, float* all_scores, float* pivot, hipStream_t st);
 hipError_t launch_score(const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
@@ -40,6 +41,8 @@ hipError_t rank_static_scratch(void** out, size_t* bytes);
 hipError_t launch_pad(const float* src, int nx, int ny, int nz, float out, float* dst, hipStream_t st);
 hipError_t launch_brick(const float* padded, int px, int py, int pz, int nbx, int nby, int nbz, float out,
                         float* brick, hipStream_t st);
+hipError_t launch_dilate(const GridDev& G, const float* padded, hipStream_t st);
+hipError_t launch_grid_max(const float* padded, long long n, uint32_t* out, hipStream_t st);
 hipError_t launch_bucketing(const int32_t* atom_offset, const int32_t* tors_offset, int n, const ClusterBounds& cb,
                             int32_t* cls, int32_t* counts, int32_t* start, int32_t* fill, int32_t* perm,
                             int32_t* cursors, hipStream_t st);
@@ -66,6 +69,8 @@ using lghost::guarded;
     hipError_t e_ = (call);                                                                   \
     if (e_ != hipSuccess) return fail(LG_ERR_DEVICE, "%s failed: %s", #call, hipGetErrorString(e_)); \
   } while (0)
+
+constexpr size_t kMaxDilated = (size_t)1 << 25;   // padded nodes of the largest grid with dilated copies
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -110,6 +115,7 @@ struct lg_pocket_s {
   lg_pocket_desc desc{};
   float* padded = nullptr;
   float* brick = nullptr;
+  char* dil = nullptr;             // dilated copies of the brick grid, then the grid's largest |value|
   lg::GridDev grid{};
   void* ws = nullptr;
   size_t ws_bytes = 0;
@@ -254,14 +260,47 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
   }
   if (s == LG_OK && lg::launch_brick(p->padded, nx + 2, ny + 2, nz + 2, nbx, nby, nbz, desc->out_value, p->brick, st) != hipSuccess)
     s = fail(LG_ERR_DEVICE, "brick kernel launch failed");
+  lg::GridDev& G = p->grid;
+  for (int a = 0; a < 3; ++a) {
+    G.n[a] = (&desc->nx)[a];
+    G.nb8[a] = (G.n[a] + 2 + 7) / 8;
+    G.nb4[a] = (G.n[a] + 2 + 3) / 4;
+  }
+  // the dilated copies only save work: grids of more than 2^25 nodes, or a device
+  // short of memory, do without, and so do grids with values that are not finite
+  size_t stride = (size_t)128 * G.nb4[0] * G.nb4[1] * G.nb4[2];
+  for (int e = 0; e < 3; ++e)
+    stride = std::max(stride, (size_t)128 * (G.n[e] + 2) * G.nb8[(e + 1) % 3] * G.nb8[(e + 2) % 3]);
+  stride = align256(stride);
+  uint32_t vmax_bits = 0xFFFFFFFFu;
+  if (s == LG_OK && padded <= kMaxDilated) {
+    if (hipMalloc((void**)&p->dil, lg::kDilated * stride + 256) != hipSuccess) {
+      (void)hipGetLastError();
+      p->dil = nullptr;
+    } else {
+      uint32_t* vmax = reinterpret_cast<uint32_t*>(p->dil + lg::kDilated * stride);
+      if (lg::launch_grid_max(p->padded, (long long)padded, vmax, st) != hipSuccess ||
+          hipMemcpyAsync(&vmax_bits, vmax, sizeof vmax_bits, hipMemcpyDeviceToHost, st) != hipSuccess ||
+          hipStreamSynchronize(st) != hipSuccess)
+        s = fail(LG_ERR_DEVICE, "reading the grid's largest value failed");
+    }
+  }
+  const bool finite = vmax_bits < 0x7F800000u;
+  G.vmax = HUGE_VALF;
+  if (finite) std::memcpy(&G.vmax, &vmax_bits, sizeof G.vmax);
+  G.bound_scale = finite && G.vmax > 1e-30f ? G.vmax / 32000.f : 1.f;
+  G.dil = finite ? p->dil : nullptr;
+  G.dil_stride = (uint32_t)stride;
+  if (s == LG_OK && G.dil && lg::launch_dilate(G, p->padded, st) != hipSuccess)
+    s = fail(LG_ERR_DEVICE, "dilation kernel launch failed");
   if (s == LG_OK && hipStreamSynchronize(st) != hipSuccess) s = fail(LG_ERR_DEVICE, "stream synchronise failed");
   if (s != LG_OK) {
     (void)hipFree(p->padded);
     if (p->brick) (void)hipFree(p->brick);
+    if (p->dil) (void)hipFree(p->dil);
     delete p;
     return s;
   }
-  lg::GridDev& G = p->grid;
   G.stride[0] = 1;
   G.stride[1] = nx + 2;
   G.stride[2] = (nx + 2) * (ny + 2);
@@ -269,7 +308,6 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
   G.gb = reinterpret_cast<const char*>(p->padded);
   for (int a = 0; a < 3; ++a) G.bs[a] = 4 * G.stride[a];
   G.b0 = 4 * (1 + G.stride[1] + G.stride[2]);
-  G.n[0] = nx; G.n[1] = ny; G.n[2] = nz;
   for (int a = 0; a < 3; ++a) {
     G.o[a] = desc->origin[a];
     G.fn[a] = (float)G.n[a];
@@ -283,10 +321,21 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
   G.tab_base[0] = 0;
   G.tab_base[1] = nx + 2;
   G.tab_base[2] = (nx + 2) + (ny + 2);
-  G.tab_len = (nx + 2) + (ny + 2) + (nz + 2);
+  int entries = (nx + 2) + (ny + 2) + (nz + 2);
+  G.tab_bounds = padded <= kMaxDilated;   // by size alone: sites of equal dimensions share the tables
+  for (int a = 0; a < 3 && G.tab_bounds; ++a) {
+    G.tab_q[a] = entries;
+    entries += G.n[a] + 2;
+    G.tab_c[a] = entries;
+    entries += G.n[a] + 2;
+  }
+  G.tab_p = entries;
+  if (G.tab_bounds) entries += std::max(nx, std::max(ny, nz)) + 2;
+  G.tab_len = entries;
   if (hipStreamCreateWithFlags(&p->capture, hipStreamNonBlocking) != hipSuccess) {
     (void)hipFree(p->padded);
     (void)hipFree(p->brick);
+    if (p->dil) (void)hipFree(p->dil);
     delete p;
     return fail(LG_ERR_DEVICE, "stream creation failed");
   }
@@ -303,6 +352,7 @@ lg_status lg_free_pocket(lg_pocket p) {
   if (p->ws) (void)hipFree(p->ws);
   if (p->padded) (void)hipFree(p->padded);
   if (p->brick) (void)hipFree(p->brick);
+  if (p->dil) (void)hipFree(p->dil);
   delete p;
   return LG_OK;
 }
@@ -409,19 +459,19 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
   D.angles = P->angle_table;
   D.final_scores = (float*)(ws + o_final);
   D.moves = (uint16_t*)(ws + o_moves);
+  D.clash = P->clash_dist2 > 0.f ? std::sqrt(P->clash_dist2) : 0.f;
   D.lazy_clash = tu.lazy_clash;
   D.trace = O->trace;
   D.trace_w = 6 + (O->trace ? O->trace_kmax : 0);
   const lg::LigDev Lg = lig_dev(L);
   const int topk_slots = std::max(1, (max_atoms + 63) / 64);   // replay instance for the largest ligand
   const int spl = spl_for(D.A, D.T);
-  if (spl > 16) return fail(LG_ERR_LIMIT, "samples per lane %d > 16", spl);
 
   if (P->mode == LG_PLAIN) {
     // the plain method: one launch per ligand, kernel sized for the largest class
     const int nslot = LG_MAX_ATOMS / 64;
     for (int i = 0; i < n; ++i)
-      LG_HIP(lg::launch_dock_plain(nslot, spl, tu.plain_waves_per_block, p->grid, Lg, D, i, st));
+      LG_HIP(lg::launch_dock_plain(nslot, tu.plain_waves_per_block, p->grid, Lg, D, i, st));
     LG_HIP(lg::launch_topk(topk_slots, Lg, D, n, P->top_k, O->score, O->restart_id, O->x, O->y, O->z, O->all_scores,
                            O->pivot, st));
     return LG_OK;
@@ -466,10 +516,10 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
       const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
       const int wpb = tu.waves_per_block[nslot - 1];
       int bpc = 0;
-      LG_HIP(lg::occupancy_dock_bucket(nslot, spl, wpb, p->grid.tab_len, &bpc));
+      LG_HIP(lg::occupancy_dock_bucket(nslot, wpb, p->grid.tab_len, D.A, &bpc));
       if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots, %d samples/lane) cannot be resident", nslot, spl);
       hipFuncAttributes attr;
-      LG_HIP(lg::attributes_dock_bucket(nslot, spl, &attr));
+      LG_HIP(lg::attributes_dock_bucket(nslot, &attr));
       for (int cr = cb.nr - 1; cr >= 0; --cr) {
         lg_bucket_stat b;
         b.bucket = ca * cb.nr + cr;
@@ -479,7 +529,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
         b.samples_per_lane = spl;
         b.waves_per_block = wpb;
         b.vgprs = attr.numRegs;
-        b.lds_bytes = (int32_t)((size_t)((p->grid.tab_len + 3) & ~3) * 4 + (size_t)wpb * lg::dock_wave_float4(nslot) * 16);
+        b.lds_bytes = (int32_t)lg::dock_lds_bytes(nslot, wpb, p->grid.tab_len, D.A);
         b.blocks_per_cu = bpc;
         b.blocks = bpc * p->cus * tu.grid_scale;
         b.ligands = -1;
@@ -509,7 +559,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
       const lg_bucket_stat& b = launches[l];
       if (timed) e = hipEventRecord(p->events[1 + 2 * l], cs);
       lg::QueueDev Q{perm, start, cursors, b.bucket, tu.restart_chunk};
-      if (e == hipSuccess) e = lg::launch_dock_bucket(b.slots, spl, b.waves_per_block, b.blocks, p->grid, Lg, D, Q, cs);
+      if (e == hipSuccess) e = lg::launch_dock_bucket(b.slots, b.waves_per_block, b.blocks, p->grid, Lg, D, Q, cs);
       if (e == hipSuccess && timed) e = hipEventRecord(p->events[2 + 2 * l], cs);
     }
     if (e == hipSuccess && timed) e = hipEventRecord(p->events[1 + 2 * nl], cs);
@@ -861,31 +911,13 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
   const size_t o_cls = lay.take((size_t)n * sizeof(int32_t));
   const size_t o_perm = lay.take((size_t)n * sizeof(int32_t));
   const size_t o_cnt = lay.take((size_t)(4 * B + 1) * sizeof(int32_t));
-  const size_t o_grids = lay.take((size_t)n_sites * sizeof(lg::SiteGrid));
+  const size_t o_sites = lay.take((size_t)n_sites * sizeof(lg::DockArgs));
   s = ensure_ws(p, lay.off);
   if (s != LG_OK) return s;
   char* ws = (char*)p->ws;
   int max_atoms = 0, max_tors = 0;
   s = check_on_device(p, L, (int32_t*)(ws + o_stats), st, &max_atoms, &max_tors);
   if (s != LG_OK) return s;
-  std::vector<lg::SiteGrid> grids(n_sites);
-  for (int si = 0; si < n_sites; ++si) {
-    const lg::GridDev& g = pockets[si]->grid;
-    lg::SiteGrid& sg = grids[si];
-    sg.g0 = g.g0;
-    sg.gb = g.gb;
-    sg.gk = g.gk;
-    for (int a = 0; a < 3; ++a) {
-      sg.c0[a] = g.c0[a];
-      sg.o[a] = g.o[a];
-    }
-    sg.out = g.out;
-    for (int a = 0; a < 3; ++a) sg.c[a] = pockets[si]->desc.center[a];
-  }
-  lg::SiteGrid* dgrids = (lg::SiteGrid*)(ws + o_grids);
-  LG_HIP(hipMemcpyAsync(dgrids, grids.data(), grids.size() * sizeof(lg::SiteGrid), hipMemcpyHostToDevice, st));
-  LG_HIP(hipStreamSynchronize(st));
-
   lg::DockDev D;
   D.R = R;
   D.A = P->angle_samples;
@@ -899,13 +931,23 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
   D.angles = P->angle_table;
   D.final_scores = (float*)(ws + o_final);
   D.moves = (uint16_t*)(ws + o_moves);
+  D.clash = P->clash_dist2 > 0.f ? std::sqrt(P->clash_dist2) : 0.f;
   D.lazy_clash = tu.lazy_clash;
   D.trace = nullptr;
   D.trace_w = 6;
-  lg::SitesDev Sd{dgrids, n_sites, site_major ? 1 : 0, (size_t)n * R, (size_t)moves_per_site};
   const lg::LigDev Lg = lig_dev(L);
-  const int spl = spl_for(D.A, D.T);
-  if (spl > 16) return fail(LG_ERR_LIMIT, "samples per lane %d > 16", spl);
+  std::vector<lg::DockArgs> sites((size_t)n_sites, lg::DockArgs{p->grid, Lg, D});
+  for (int si = 0; si < n_sites; ++si) {
+    lg::DockArgs& x = sites[si];
+    x.G = pockets[si]->grid;
+    for (int a = 0; a < 3; ++a) x.D.c[a] = pockets[si]->desc.center[a];
+    x.D.final_scores = D.final_scores + (size_t)si * n * R;
+    x.D.moves = D.moves + (size_t)si * moves_per_site;
+  }
+  lg::DockArgs* dsites = (lg::DockArgs*)(ws + o_sites);
+  LG_HIP(hipMemcpyAsync(dsites, sites.data(), sites.size() * sizeof(lg::DockArgs), hipMemcpyHostToDevice, st));
+  LG_HIP(hipStreamSynchronize(st));   // the table's host copy ends with this call
+  lg::SitesDev Sd{dsites, n_sites, site_major ? 1 : 0};
 
   lg::ClusterBounds cb;
   std::memset(&cb, 0, sizeof cb);
@@ -926,19 +968,16 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
     const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
     const int wpb = tu.waves_per_block[nslot - 1];
     int bpc = 0;
-    LG_HIP(lg::occupancy_dock_bucket(nslot, spl, wpb, p->grid.tab_len, &bpc));
-    if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots, %d samples/lane) cannot be resident", nslot, spl);
+    LG_HIP(lg::occupancy_dock_bucket(nslot, wpb, p->grid.tab_len, D.A, &bpc));
+    if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots) cannot be resident", nslot);
     for (int cr = cb.nr - 1; cr >= 0; --cr) {
       lg::QueueDev Q{perm, start, cursors, ca * cb.nr + cr, tu.restart_chunk};
-      LG_HIP(lg::launch_dock_sites(nslot, spl, wpb, bpc * p->cus * tu.grid_scale, p->grid, Lg, D, Q, Sd, st));
+      LG_HIP(lg::launch_dock_sites(nslot, wpb, bpc * p->cus * tu.grid_scale, p->grid, Lg, D, Q, Sd, st));
     }
   }
   const int topk_slots = std::max(1, (max_atoms + 63) / 64);
   for (int si = 0; si < n_sites; ++si) {
-    lg::DockDev Ds = D;
-    for (int a = 0; a < 3; ++a) Ds.c[a] = pockets[si]->desc.center[a];
-    Ds.final_scores = D.final_scores + (size_t)si * Sd.scores_stride;
-    Ds.moves = D.moves + (size_t)si * Sd.moves_stride;
+    const lg::DockDev& Ds = sites[si].D;
     const lg_dock_out& O = outs[si];
     LG_HIP(lg::launch_topk(topk_slots, Lg, Ds, n, P->top_k, O.score, O.restart_id, O.x, O.y, O.z, O.all_scores,
                            O.pivot, st));

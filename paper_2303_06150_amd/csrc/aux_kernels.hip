@@ -3,11 +3,16 @@
 // and validation kernels.
 #include "lg_device.h"
 
+#include <algorithm>
 #include <climits>
 
 namespace lg {
 
 
+
+__global__ void zero_kernel(int32_t* p, int n) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
+}
 
 // One wavefront per pose: score = sum over atoms in atom order; optional
 // gradient with respect to (t, omega, theta) at zero (force / torque form).
@@ -122,16 +127,93 @@ hipError_t launch_brick(const float* padded, int px, int py, int pz, int nbx, in
   return hipGetLastError();
 }
 
+// Byte offset of padded node (x[0], x[1], x[2]) in a dilated copy: bricks of
+// 8 x 8 nodes of the plane across axis e, or of 4 x 4 x 4 nodes (e = 3).
+__device__ __forceinline__ size_t dilated_off(const GridDev& G, int e, const int (&x)[3]) {
+  if (e == 3)
+    return 128 * (((size_t)(x[2] >> 2) * G.nb4[1] + (x[1] >> 2)) * G.nb4[0] + (x[0] >> 2)) +
+           2 * (((x[2] & 3) * 4 + (x[1] & 3)) * 4 + (x[0] & 3));
+  const int p = (e + 1) % 3, q = (e + 2) % 3;
+  return 128 * (((size_t)x[e] * G.nb8[q] + (x[q] >> 3)) * G.nb8[p] + (x[p] >> 3)) + 2 * ((x[q] & 7) * 8 + (x[p] & 7));
+}
+
+// Whole multiple of scale at or above v.
+__device__ __forceinline__ int round_up_to(float v, float scale) {
+  int q = (int)ceilf(v / scale);
+  if ((float)q * scale < v) ++q;
+  return q;
+}
+
+// One step of the dilated copies: the largest of the source's nodes at offsets lo
+// and hi along the copy's axes (two of a plane, all three of a cube), clamped to
+// the padded extent.  Windows of 2, 3, 4 and 6 nodes are built from those before
+// (2 of the grid's own values, 3 and 4 of twos, 6 of fours), four or eight reads
+// a node.
+__global__ void dilate_kernel(GridDev G, const float* padded, const char* src, int e, int lo, int hi, char* dst) {
+  const int px[3] = {G.n[0] + 2, G.n[1] + 2, G.n[2] + 2};
+  const int total = px[0] * px[1] * px[2];
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    const int x[3] = {i % px[0], (i / px[0]) % px[1], i / (px[0] * px[1])};
+    int best = INT_MIN;
+    for (int k = 0; k < 8; ++k) {
+      if (e < 3 && ((k >> e) & 1)) continue;
+      int y[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        y[a] = a == e ? x[a] : min(max(x[a] + ((k >> a) & 1 ? hi : lo), 0), px[a] - 1);
+      const int v = src ? *reinterpret_cast<const int16_t*>(src + dilated_off(G, e, y))
+                        : round_up_to(padded[((size_t)y[2] * px[1] + y[1]) * px[0] + y[0]], G.bound_scale);
+      best = max(best, v);
+    }
+    *reinterpret_cast<int16_t*>(dst + dilated_off(G, e, x)) = (int16_t)best;
+  }
+}
+
+// G: the finished description of the grid, dil included.
+hipError_t launch_dilate(const GridDev& G, const float* padded, hipStream_t st) {
+  char* dil = const_cast<char*>(G.dil);
+  auto copy = [&](int i) { return dil + (size_t)i * G.dil_stride; };
+  const long long total = (long long)(G.n[0] + 2) * (G.n[1] + 2) * (G.n[2] + 2);
+  const int blocks = (int)std::min<long long>((total + 255) / 256, 8192);
+  auto step = [&](int from, int e, int lo, int hi, int to) {
+    hipLaunchKernelGGL(dilate_kernel, dim3(blocks), dim3(256), 0, st, G, padded, from < 0 ? nullptr : copy(from), e, lo,
+                       hi, copy(to));
+  };
+  for (int e = 0; e < 3; ++e) {
+    step(-1, e, 0, 1, 4 * e);              // 2 x 2
+    step(4 * e, e, 0, 1, 4 * e + 1);       // 3 x 3
+    step(4 * e, e, 0, 2, 4 * e + 2);       // 4 x 4
+    step(4 * e + 2, e, 0, 2, 4 * e + 3);   // 6 x 6
+  }
+  step(-1, 3, 0, 1, 12);    // i .. i + 1
+  step(12, 3, -1, 1, 13);   // i - 1 .. i + 2
+  step(13, 3, -1, 1, 14);   // i - 2 .. i + 3
+  return hipGetLastError();
+}
+
+// Bits of the largest |value|: NaN above infinity above every finite value.
+__global__ void grid_max_kernel(const float* v, long long n, uint32_t* out) {
+  uint32_t best = 0;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+    const uint32_t b = __float_as_uint(v[i]) & 0x7FFFFFFFu;
+    best = b > best ? b : best;
+  }
+  const int wave = wave_reduce_i32((int)best, OpMax());
+  if (lane_id() == 0) atomicMax(out, (uint32_t)wave);
+}
+
+hipError_t launch_grid_max(const float* padded, long long n, uint32_t* out, hipStream_t st) {
+  hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<int32_t*>(out), 1);
+  hipLaunchKernelGGL(grid_max_kernel, dim3(256), dim3(256), 0, st, padded, n, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_pad(const float* src, int nx, int ny, int nz, float out, float* dst, hipStream_t st) {
   hipLaunchKernelGGL(pad_kernel, dim3(1024), dim3(256), 0, st, src, nx, ny, nz, out, dst);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------- input preparation (buckets)
-__global__ void zero_kernel(int32_t* p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
-}
-
 __global__ void classify_kernel(const int32_t* atom_offset, const int32_t* tors_offset, int n, ClusterBounds cb,
                                 int32_t* cls, int32_t* counts) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;

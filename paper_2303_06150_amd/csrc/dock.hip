@@ -2,15 +2,17 @@
 // scans, greedy torsion scans with the intramolecular clash check, nearest-voxel
 // scan scores, trilinear final score, per-ligand top-k.
 //
-// Mapping.  One wavefront docks one restart (ligand, r).  A scan's samples are
-// spread over the 64 lanes (sample j = lane + 64 q, q < SPL); each lane loops
-// over the atoms of the scan, reading per-atom scan data that the wavefront
-// staged in LDS (broadcast reads), and accumulates nearest-voxel values
-// gathered from the L2-resident grid.  The pose lives in registers, atom
-// a = 64 s + lane in slot s < NSLOT.  The best sample comes from a DPP/readlane
-// reduction (lowest index among equal scores).  Torsion samples are tested for
-// intramolecular clashes in the scoring pass against a pruned list of the
-// pairs that can clash at some angle.
+// Mapping.  One wavefront docks one restart (ligand, r).  A scan first bounds the
+// score of every group of neighbouring samples (one group per lane) from above,
+// then scores the samples of the groups whose bound exceeds the current pose's
+// score, one sample per lane: the selected sample is that of a scan over every
+// sample, at about half the lookups.  Each lane loops over the atoms of the
+// scan, reading per-atom scan data that the wavefront staged in LDS (broadcast
+// reads), and accumulates nearest-voxel values gathered from the L2-resident
+// grid.  The pose lives in registers, atom a = 64 s + lane in slot s < NSLOT.
+// The best sample comes from a DPP/readlane reduction (lowest index among equal
+// scores).  Torsion samples are tested for intramolecular clashes against a
+// pruned list of the pairs that can clash at some angle.
 //
 // Outputs.  Each restart records its final score and the selected sample of
 // every scan (a few bytes per scan); the per-ligand top-k then rebuilds the k
@@ -34,73 +36,14 @@ struct PoseReg {
   float piv[3];
 };
 
-template <int SPL>
-struct SampleReg {
-  float c[SPL], s[SPL], d[SPL];
-  uint32_t valid_a, valid_t;   // bit q: sample lane + 64 q exists
-  bool half_turn;              // A = 64 SPL and sample j + A/2 is sample j turned by pi:
-                               // (cos, sin) of the two are exact negatives
-  bool quarter_turn;           // A = 64 SPL and samples j + A/4, j + A/2, j + 3A/4 are j
-                               // turned by pi/2, pi, 3pi/2: (-s, c), (-c, -s), (s, -c) exactly
-  bool unit;                   // every angle sample has |cos| <= 1 and |sin| <= 1
-};
-
-
-
-
-
-template <int SPL>
-__device__ __forceinline__ int wave_argmax(const float (&acc)[SPL], uint32_t alive) {
-  const int lane = lane_id();
-  int best = INT_MIN, bj = INT_MAX;
-#pragma unroll
-  for (int q = 0; q < SPL; ++q) {
-    int k = orderable(acc[q]);
-    if (((alive >> q) & 1u) && k > best) { best = k; bj = lane + 64 * q; }
-  }
-  int wmax = wave_reduce_i32(best, OpMax());
-  return wave_reduce_i32(best == wmax ? bj : INT_MAX, OpMin());
-}
-
-
-
-// acc[q] += gather(t)[q] over t < n, with the gathers of atom t+1 issued before
-// the values of atom t are added (two register buffers, no copies).
-template <int Q, int NA, class F>
-__device__ __forceinline__ void pipelined_sum(int n, F gather, float (&acc)[NA], int qoff = 0) {
-  float v0[Q], v1[Q];
-  gather(0, v0);
-  int t = 1;
-  for (; t + 1 < n; t += 2) {
-    gather(t, v1);
-    __builtin_amdgcn_sched_barrier(0);   // keep the loads of atom t ahead of the sums of atom t-1
-#pragma unroll
-    for (int q = 0; q < Q; ++q) acc[q + qoff] += v0[q];
-    gather(t + 1, v0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) acc[q + qoff] += v1[q];
-  }
-  if (t < n) {
-    gather(t, v1);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) acc[q + qoff] += v0[q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) acc[q + qoff] += v1[q];
-  } else {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) acc[q + qoff] += v0[q];
-  }
-}
-
 // ---- moves: the selected sample of a scan applied to the pose ----------------
-// Rotation by sample j about lab axis E through the pivot.
+// Rotation by sample j, (cos, sin) = ang[j], about lab axis E through the pivot.
 template <int NSLOT, int E>
-__device__ __forceinline__ void apply_rot(const DockDev& D, PoseReg<NSLOT>& p, int j) {
+__device__ __forceinline__ void apply_rot(const float2* ang, PoseReg<NSLOT>& p, int j) {
   constexpr int P = (E + 1) % 3, Q = (E + 2) % 3;
   if (j == 0) return;
   const float pP = p.piv[P], pQ = p.piv[Q];
-  const float c = D.angles[2 * j], sn = D.angles[2 * j + 1];
+  const float c = ang[j].x, sn = ang[j].y;
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
     float vp = p.x[P][s] - pP, vq = p.x[Q][s] - pQ;
@@ -175,132 +118,296 @@ __device__ __forceinline__ void moving_atoms(const uint32_t (&mk)[NSLOT], int N,
   }
 }
 
+// Square root for radii that only bound something: the hardware's one-ulp root.
+// The margins around them (0.05 A of the pair prune, thousandths of a node of
+// the windows) are orders of magnitude above an ulp of a radius; no exact test
+// uses a root.
+__device__ __forceinline__ float prune_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+
+// ---- samples of a launch -------------------------------------------------------
+// A scan's samples are taken in groups of neighbours, at most 64 groups, one per
+// lane.  What every scan of a launch needs to know of them; uniform but for the
+// lane's group centre.
+struct Samples {
+  int A;              // angle samples
+  int GA, nga;        // rotations and torsions: samples per group, groups
+  int GT, ngt;        // translations, in order of displacement
+  int tsub;           // lanes that share a translation group in the bound pass (log2): 0, 1, 2
+  int gt0;            // translation group of sample 0
+  bool bound_t;       // a translation group's samples span less than one node
+  float dlow;         // least displacement of the lane's translation group
+  float radius;       // largest |(cos, sin)| of a sample (1 up to rounding)
+  float chord;        // every sample of a group lies within chord of its centre, in (cos, sin)
+  float cc, cs;       // centre of the lane's group: the mean of its two middle samples
+  const float2* ang;  // (cos, sin) of every sample, in LDS
+};
+
+__device__ __forceinline__ void load_samples(const GridDev& G, const DockDev& D, const float2* ang, Samples& sm) {
+  const int lane = lane_id();
+  sm.ang = ang;
+  sm.A = D.A;
+  sm.GA = (D.A + 63) >> 6;
+  sm.nga = (D.A + sm.GA - 1) / sm.GA;
+  const int j0 = lane * sm.GA, cnt = min(sm.GA, D.A - j0);
+  float far2 = 0.f, len2 = 0.f;
+  bool odd = false;
+  sm.cc = 1.f;
+  sm.cs = 0.f;
+  if (cnt > 0) {
+    const float2 a = ang[j0 + ((cnt - 1) >> 1)], b = ang[j0 + (cnt >> 1)];
+    sm.cc = 0.5f * (a.x + b.x);
+    sm.cs = 0.5f * (a.y + b.y);
+    for (int q = 0; q < cnt; ++q) {
+      const float2 s = ang[j0 + q];
+      const float dc = s.x - sm.cc, ds = s.y - sm.cs, d2 = fmaf(dc, dc, ds * ds);
+      len2 = fmaxf(len2, fmaf(s.x, s.x, s.y * s.y));
+      odd = odd || !(d2 < 1e30f) || !(len2 < 1e30f);
+      far2 = fmaxf(far2, d2);
+    }
+  }
+  // non-negative floats order as ints; a table with NaN or huge entries has no
+  // bound (every test against these fails)
+  const float w2 = __int_as_float(wave_reduce_i32(__float_as_int(far2), OpMax()));
+  const float r2 = __int_as_float(wave_reduce_i32(__float_as_int(len2), OpMax()));
+  const bool none = wave_any(odd);
+  sm.chord = none ? __builtin_inff() : prune_sqrt(w2) * 1.0001f + 1e-6f;
+  sm.radius = none ? __builtin_inff() : prune_sqrt(r2) * 1.0001f;
+  // a group may not span a whole node: 16 groups where that holds, else 32 or 64
+  const float step = fabsf(D.delta) * G.inv_h;
+  sm.tsub = 2;
+  for (;; --sm.tsub) {
+    sm.GT = (D.T + (64 >> sm.tsub) - 1) >> (6 - sm.tsub);
+    sm.bound_t = (float)(sm.GT - 1) * step <= 0.998f;
+    if (sm.bound_t || sm.tsub == 0) break;
+  }
+  if (D.T <= 64) {   // one pass scores every sample
+    sm.GT = 1;
+    sm.bound_t = false;
+  }
+  sm.ngt = (D.T + sm.GT - 1) / sm.GT;
+  const int mlo = D.T >= 2 ? D.T / 2 - D.T : 0;
+  sm.gt0 = -mlo / sm.GT;
+  const int g = lane & ((64 >> sm.tsub) - 1);
+  const int m0 = min(g * sm.GT, D.T - 1) + mlo, m1 = min(g * sm.GT + sm.GT - 1, D.T - 1) + mlo;
+  sm.dlow = fminf(D.delta * (float)m0, D.delta * (float)m1);
+}
+
+// n / d of small whole numbers, 0 <= n < 2^13, 1 <= d <= 64, from r = 1 / d (a few
+// ulps off): n + 1/2 over d is at least 1/128 from any whole number.
+__device__ __forceinline__ int small_div(int n, float r) { return (int)(((float)n + 0.5f) * r); }
+
+// A uniform value in a vector register: arithmetic with a scalar operand issues
+// at half rate.
+__device__ __forceinline__ float in_vgpr(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// The selected sample of a scan: the largest score of an admissible sample, the
+// lowest index among equal ones; sample 0, the current pose with score s0, is
+// always admissible (ZERO: its group is among `alive` and it is scored with the
+// others).  `alive` holds the groups (bit g: samples g G .. g G + G - 1
+// in the scan's own order) that may beat s0, `bound` the lane's group's upper
+// bound.  Each pass scores the samples of the next 64 / G groups, one per lane,
+// in order of the groups; groups whose bound falls below the best score since
+// found drop out.  index(pos) is the sample at a position of the scan's order,
+// score(j) its exact score, refuse(j, better) the lanes whose sample is not
+// admissible (asked only for samples that beat the best so far).  Dropping a
+// group changes no result: a bound is at least the score of every sample of
+// its group, rounding included (upper_bound).
+template <bool ZERO, class Index, class Score, class Refuse>
+__device__ __forceinline__ int select_sample(uint64_t alive, float bound, int G, int n, float s0, Index index,
+                                             Score score, Refuse refuse) {
+  const int lane = lane_id();
+  const float rG = __builtin_amdgcn_rcpf((float)G);
+  const int per = __builtin_amdgcn_readfirstlane(small_div(64, rG));
+  const int idx = small_div(lane, rG), sub = lane - idx * G;
+  int best = ZERO ? INT_MIN : orderable(s0), bj = ZERO ? INT_MAX : 0;
+  while (alive) {
+    // the next groups: the lane that holds the r-th of them passes its number to lane r
+    const bool in = (alive >> lane) & 1u;
+    const int before =
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(alive >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)alive, 0u));
+    const bool now = in && before < per;
+    const uint64_t taken = __ballot(now);
+    const int cnt = __popcll(taken);
+    const int rest = lane - (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(taken >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)taken, 0u));
+    const int held = __builtin_amdgcn_ds_permute((now ? before : cnt + rest) << 2, lane);
+    const int g = __builtin_amdgcn_ds_bpermute(idx << 2, held);
+    const int pos = g * G + sub;
+    const bool valid = idx < cnt && idx < per && pos < n;
+    const int j = index(valid ? pos : 0);
+    const int key = orderable(score(j));
+    bool better = valid && (ZERO || j != 0) && (key > best || (key == best && j < bj));
+    if (wave_any(better)) {
+      const bool no = refuse(j, better);   // every lane takes part
+      better = better && !no;
+      const int wmax = wave_reduce_i32(better ? key : INT_MIN, OpMax());
+      const int wj = wave_reduce_i32(better && key == wmax ? j : INT_MAX, OpMin());
+      if (wj != INT_MAX) {
+        best = wmax;
+        bj = wj;
+      }
+    }
+    alive &= ~taken;
+    if (alive && bj != INT_MAX) alive &= __ballot(!(bound < __int_as_float(best ^ ((best >> 31) & 0x7FFFFFFF))));
+  }
+  return bj;
+}
+
+// How far apart two FP32 sums of the same n grid values can be, whatever their
+// orders of addition (zero on grids whose sums are exact; the bound holds for all).
+__device__ __forceinline__ float sum_slack(const GridDev& G, int n) { return G.vmax * (float)(n * n) * 4.8e-7f; }
+
+// A bound on the FP32 sum of n grid values from the sum of their dilated copies
+// (whole numbers below 2^24).
+__device__ __forceinline__ float upper_bound(const GridDev& G, int n, int sum) {
+  return fmaf((float)sum, G.bound_scale, sum_slack(G, n));
+}
+
+// Groups that may hold a sample better than s0 (a NaN bound or score keeps them all).
+__device__ __forceinline__ uint64_t groups_above(float bound, float s0, int groups) {
+  return __ballot(lane_id() < groups && !(bound <= s0));
+}
+
+// acc + value(0) + value(1) + ... + value(n - 1), added in that order; U values are
+// fetched ahead of the U being added (two register buffers, no copies).
+template <int U, class V, class F>
+__device__ __forceinline__ V ordered_sum(V acc, int n, F value) {
+  V v0[U], v1[U];
+  int t = 0;
+  const int full = n - n % U;
+  if (full > 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) v0[u] = value(u);
+    t = U;
+    for (; t + U < full; t += 2 * U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) v1[u] = value(t + u);
+      __builtin_amdgcn_sched_barrier(0);   // keep these fetches ahead of the sums before them
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v0[u];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v0[u] = value(t + U + u);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v1[u];
+    }
+    if (t < full) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) v1[u] = value(t + u);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v0[u];
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v1[u];
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v0[u];
+    }
+  }
+  for (int k = full; k < n; ++k) acc += value(k);
+  return acc;
+}
+
+// The sum over n atoms of value(in, t): `in` says whether every node index is
+// known to lie inside the padded grid, so that none needs its clamp (the usual
+// case; the other one takes the plain loop).
+template <int U, class V, class F>
+__device__ __forceinline__ V scan_sum(bool inside, V acc, int n, F value) {
+  if (inside) return ordered_sum<U>(acc, n, [&](int t) { return value(std::true_type{}, t); });
+#pragma unroll 1
+  for (int t = 0; t < n; ++t) acc += value(std::false_type{}, t);
+  return acc;
+}
+
+template <class In>
+__device__ __forceinline__ int node_index(In, float f, float fn) {
+  return In::value ? floor_node(f) : clamp_node(f, fn);
+}
+
 // ---- rigid rotation scan about lab axis E through the pivot ------------------
-template <int NSLOT, int SPL, int E>
-__device__ int rot_scan(const GridDev& G, const DockDev& D, PoseReg<NSLOT>& p, int N, float4* scr,
-                        const SampleReg<SPL>& sm, const int* tab) {
+// Bound pass: an atom at distance r from the axis stays within chord * r of its
+// place at the group's centre, so every node a group's samples read lies in a
+// window of w x w nodes of the rotation plane, w - 1 >= 2 chord r / h; the grid
+// copies dilated over such windows (GridDev::dil) give the largest value in one
+// lookup of 16 bits, in bricks of the rotation plane.  About a third of the groups
+// survive (240 k scans of mixed ligands: 0.67, 0.34, 0.23 in sweeps 1, 2, 3),
+// 2.6, 1.8 and 1.4 passes of 64 samples instead of 4.
+template <int NSLOT, int E>
+__device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, float4* scr, float4* aux,
+                                        const Samples& sm, const int* tab) {
+  const GridDev G = grid_of(S);
   constexpr int P = (E + 1) % 3, Q = (E + 2) % 3;
   const int lane = lane_id();
-  const float pP = p.piv[P], pQ = p.piv[Q];
-  const float cP = G.c0[P], cQ = G.c0[Q], ih = G.inv_h, fnP = G.fn[P], fnQ = G.fn[Q];
+  const float pP = in_vgpr(p.piv[P]), pQ = in_vgpr(p.piv[Q]);
+  const float cP = in_vgpr(G.c0[P]), cQ = in_vgpr(G.c0[Q]), ih = in_vgpr(G.inv_h), fnP = G.fn[P], fnQ = G.fn[Q];
+  const int* tP = tab + G.tab_base[P] + 1;
+  const int* tQ = tab + G.tab_base[Q] + 1;
+  const char* gk = G.gk;
   float s0 = 0.f;
-  // With |cos|, |sin| <= 1 a rotated offset is at most |vp| + |vq| per axis
-  // (B below covers the rounding of the two products and their sum), and the
-  // node map is monotone: when both ends of every atom's range map inside
-  // [-1, n], no sample needs the clamp of the node index.
-  bool inside = true;
+  // An atom stays within its distance from the axis, and the node map is
+  // monotone: when both ends of every atom's range, widened by four nodes
+  // (rounding and the windows), map inside [-1, n], no sample and no window needs
+  // the clamp of the node index.
+  bool inside = true, level = G.dil != nullptr && sm.GA > 1;
+  const float fp = fmaf(pP, ih, cP), fq = fmaf(pQ, ih, cQ);
+  const float ferr = fmaf(1e-6f * ih, fabsf(pP) + fabsf(pQ), 2e-3f);
+  const float reach = fminf(fminf(fp + 1.f, fnP - fp), fminf(fq + 1.f, fnQ - fq)) - 4.f;
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
     const int a = s * 64 + lane;
     if (a < N) {
-      float vp = p.x[P][s] - pP, vq = p.x[Q][s] - pQ;
-      int ie = clamp_node(fmaf(p.x[E][s], G.inv_h, G.c0[E]), G.fn[E]);
-      scr[a] = make_float4(vp, vq, __int_as_float(boff(tab + G.tab_base[E] + 1, ie)), 0.f);
-      s0 += nearest(G, p.x[0][s], p.x[1][s], p.x[2][s]);
-      const float B = (fabsf(vp) + fabsf(vq)) * (1.f + 0x1p-20f);
-      inside = inside && fmaf(pP - B, ih, cP) >= -1.f && fmaf(pP + B, ih, cP) <= fnP &&
-               fmaf(pQ - B, ih, cQ) >= -1.f && fmaf(pQ + B, ih, cQ) <= fnQ;
+      const float vp = p.x[P][s] - pP, vq = p.x[Q][s] - pQ;
+      const int ie = clamp_node(fmaf(p.x[E][s], ih, G.c0[E]), G.fn[E]);
+      const int part = boff(tab + G.tab_base[E] + 1, ie);
+      scr[a] = make_float4(vp, vq, __int_as_float(part), 0.f);
+      s0 += grid_at(gk, part + boff(tP, clamp_node(fmaf(p.x[P][s], ih, cP), fnP)) +
+                            boff(tQ, clamp_node(fmaf(p.x[Q][s], ih, cQ), fnQ)));
+      const float r = prune_sqrt(fmaf(vp, vp, vq * vq)) * (1.0001f * ih);
+      inside = inside && sm.radius * r <= reach;
+      const float del = fmaf(sm.chord, r, ferr);
+      const int l = del <= 0.5f ? 0 : del <= 1.f ? 1 : del <= 1.5f ? 2 : 3;
+      level = level && del <= 2.5f;
+      aux[2 * a] = make_float4(vp * ih, vq * ih, fp - del, fq - del);
+      reinterpret_cast<uint32_t*>(aux + 2 * a + 1)[0] =
+          (uint32_t)__mul24(ie + 1, 128 * G.nb8[P] * G.nb8[Q]) + (uint32_t)(4 * E + l) * G.dil_stride;
     }
   }
-  inside = sm.unit && !wave_any(!inside);
+  inside = !wave_any(!inside);
+  level = !wave_any(!level);
   s0 = wave_sum(s0);
   wave_sync();
-  float acc[SPL];
-#pragma unroll
-  for (int q = 0; q < SPL; ++q) acc[q] = 0.f;
-  const int* tP = tab + G.tab_base[P] + 1;
-  const int* tQ = tab + G.tab_base[Q] + 1;
-  const char* gk = G.gk;
-  // gathers of atom t+1 are issued before the values of atom t are summed
-  auto gather = [&](int t, float (&out)[SPL]) {
-    const float4 d = scr[t];
-    const int part = __float_as_int(d.z);
-#pragma unroll
-    for (int q = 0; q < SPL; ++q) {
-      float np = fmaf(sm.c[q], d.x, -(sm.s[q] * d.y));
-      float nq = fmaf(sm.s[q], d.x, sm.c[q] * d.y);
-      float xp = pP + np, xq = pQ + nq;
-      int ip = clamp_node(fmaf(xp, ih, cP), fnP);
-      int iq = clamp_node(fmaf(xq, ih, cQ), fnQ);
-      out[q] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-    }
-  };
-  // samples j and j + A/2: with (cos, sin) negated the rotated offsets are the
-  // exact negatives (fma and products are sign-symmetric), so one 2-D rotation
-  // serves both; a zero's sign cannot change the node
-  auto gather_half_turn = [&](int t, float (&out)[SPL]) {
-    const float4 d = scr[t];
-    const int part = __float_as_int(d.z);
-#pragma unroll
-    for (int q = 0; q < SPL / 2; ++q) {
-      float np = fmaf(sm.c[q], d.x, -(sm.s[q] * d.y));
-      float nq = fmaf(sm.s[q], d.x, sm.c[q] * d.y);
-      int ip = clamp_node(fmaf(pP + np, ih, cP), fnP);
-      int iq = clamp_node(fmaf(pQ + nq, ih, cQ), fnQ);
-      out[q] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-      ip = clamp_node(fmaf(pP - np, ih, cP), fnP);
-      iq = clamp_node(fmaf(pQ - nq, ih, cQ), fnQ);
-      out[q + SPL / 2] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-    }
-  };
-  // samples j + A/4 and j + 3A/4 in the same way: with (cos, sin) = (-s, c) the
-  // rotated offsets are (-nq, np), with (s, -c) they are (nq, -np), exactly
-  auto gather_quarter_turn = [&](int t, float (&out)[SPL]) {
-    const float4 d = scr[t];
-    const int part = __float_as_int(d.z);
-    constexpr int Q4 = SPL / 4;
-#pragma unroll
-    for (int q = 0; q < Q4; ++q) {
-      const float np = fmaf(sm.c[q], d.x, -(sm.s[q] * d.y));
-      const float nq = fmaf(sm.s[q], d.x, sm.c[q] * d.y);
-      int ip = clamp_node(fmaf(pP + np, ih, cP), fnP);
-      int iq = clamp_node(fmaf(pQ + nq, ih, cQ), fnQ);
-      out[q] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-      ip = clamp_node(fmaf(pP - nq, ih, cP), fnP);
-      iq = clamp_node(fmaf(pQ + np, ih, cQ), fnQ);
-      out[q + Q4] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-      ip = clamp_node(fmaf(pP - np, ih, cP), fnP);
-      iq = clamp_node(fmaf(pQ - nq, ih, cQ), fnQ);
-      out[q + 2 * Q4] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-      ip = clamp_node(fmaf(pP + nq, ih, cP), fnP);
-      iq = clamp_node(fmaf(pQ - np, ih, cQ), fnQ);
-      out[q + 3 * Q4] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-    }
-  };
-  // the same, every node index known to lie in range (no clamp)
-  auto gather_quarter_turn_inside = [&](int t, float (&out)[SPL]) {
-    const float4 d = scr[t];
-    const int part = __float_as_int(d.z);
-    constexpr int Q4 = SPL / 4;
-#pragma unroll
-    for (int q = 0; q < Q4; ++q) {
-      const float np = fmaf(sm.c[q], d.x, -(sm.s[q] * d.y));
-      const float nq = fmaf(sm.s[q], d.x, sm.c[q] * d.y);
-      int ip = floor_node(fmaf(pP + np, ih, cP));
-      int iq = floor_node(fmaf(pQ + nq, ih, cQ));
-      out[q] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-      ip = floor_node(fmaf(pP - nq, ih, cP));
-      iq = floor_node(fmaf(pQ + np, ih, cQ));
-      out[q + Q4] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-      ip = floor_node(fmaf(pP - np, ih, cP));
-      iq = floor_node(fmaf(pQ - nq, ih, cQ));
-      out[q + 2 * Q4] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-      ip = floor_node(fmaf(pP + nq, ih, cP));
-      iq = floor_node(fmaf(pQ - np, ih, cQ));
-      out[q + 3 * Q4] = grid_at(gk, part + boff(tP, ip) + boff(tQ, iq));
-    }
-  };
-  if (SPL % 4 == 0 && sm.quarter_turn && inside)
-    pipelined_sum<SPL>(N, gather_quarter_turn_inside, acc);
-  else if (SPL % 4 == 0 && sm.quarter_turn)
-    pipelined_sum<SPL>(N, gather_quarter_turn, acc);
-  else if (SPL % 2 == 0 && sm.half_turn)
-    pipelined_sum<SPL>(N, gather_half_turn, acc);
-  else
-    pipelined_sum<SPL>(N, gather, acc);
-  if (lane == 0) acc[0] = s0;   // sample 0 is the current pose
-  const int j = wave_argmax(acc, sm.valid_a);
-  apply_rot<NSLOT, E>(D, p, j);
+  float bound = __builtin_inff();
+  if (level) {
+    const float c = sm.cc, sn = sm.cs;
+    const char* dil = G.dil;
+    const int* dP = tab + G.tab_p + 1;
+    const int* dQ = tab + G.tab_q[Q] + 1;
+    bound = upper_bound(G, N, scan_sum<4>(inside, 0, N, [&](auto in, int t) {
+      const float4 k = aux[2 * t];
+      const uint32_t part = reinterpret_cast<const uint32_t*>(aux + 2 * t + 1)[0];
+      const int ip = node_index(in, fmaf(c, k.x, fmaf(-sn, k.y, k.z)), fnP);
+      const int iq = node_index(in, fmaf(sn, k.x, fmaf(c, k.y, k.w)), fnQ);
+      return bound_at(dil, part + boff(dP, ip) + boff(dQ, iq));
+    }));
+  }
+  const int j = select_sample<false>(
+      groups_above(bound, s0, sm.nga), bound, sm.GA, sm.A, s0, [](int pos) { return pos; },
+      [&](int js) {
+        const float2 cs = sm.ang[js];
+        return scan_sum<4>(inside, 0.f, N, [&](auto in, int t) {
+          const float4 d = scr[t];
+          const float np = fmaf(cs.x, d.x, -(cs.y * d.y));
+          const float nq = fmaf(cs.y, d.x, cs.x * d.y);
+          const int ip = node_index(in, fmaf(pP + np, ih, cP), fnP);
+          const int iq = node_index(in, fmaf(pQ + nq, ih, cQ), fnQ);
+          return grid_at(gk, __float_as_int(d.z) + boff(tP, ip) + boff(tQ, iq));
+        });
+      },
+      [](int, bool) { return false; });
+  apply_rot<NSLOT, E>(sm.ang, p, j);
   wave_sync();
   return j;
 }
@@ -313,23 +420,40 @@ __device__ __forceinline__ float lds_load(uint32_t addr) {
   return *(const __attribute__((address_space(3))) float*)(uintptr_t)addr;
 }
 
+// Maximum of two floats as one v_max_f32 (fmaxf quiets signalling NaNs first).
+__device__ __forceinline__ float larger(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
 // ---- rigid translation scan along lab axis E ---------------------------------
 // A translation moves an atom along E only, so its T samples read nodes of one
 // grid line: those between the nodes of the smallest and the largest
 // displacement (the node index is monotone in the displacement), span nodes at
-// most.  The wavefront reads each atom's run of nodes once -- 64 / span atoms
-// per gather instruction, into an LDS stage -- and every sample then takes its
-// value from the stage: the same value, node and sum order as a direct gather
-// per sample, with a fraction of the gather instructions.  Runs longer than a
-// wavefront (very wide translation ranges) fall back to direct gathers, and so
-// does STAGE = false (the plain launch, where a lone wavefront per SIMD would
-// wait on every group's nodes).
-template <int NSLOT, int SPL, int E, bool STAGE>
-__device__ int trans_scan(const GridDev& G, const DockDev& D, PoseReg<NSLOT>& p, int N, float4* scr, float* stage,
-                          const SampleReg<SPL>& sm, const int* tab) {
+// most.  The wavefront reads each atom's run of nodes once -- 64 / (span + 1)
+// atoms per gather instruction -- into an LDS stage, which holds every run of
+// a ligand of average size, and takes all further values from there: the same
+// value, node and sum order as a direct gather per sample.
+// Bound pass: the samples of a group (in order of displacement) span less than
+// one node, so the larger of two neighbouring nodes of the run bounds each.
+// 16 groups and four lanes per group, which share the atoms: their partial sums
+// are added in another order than the scores', so the bound is widened by what
+// rounding can make of that (none on grids whose sums are exact).  About 0.25 of
+// the groups survive; 1.6, 1.25, 1.14 passes (sweeps 1, 2, 3) instead of 4.
+// Runs longer than a wavefront (very wide translation ranges) fall back to
+// direct gathers of every sample, and so does STAGE = false (the plain launch,
+// where a lone wavefront per SIMD would wait on every group's nodes).
+template <int NSLOT, int E, bool STAGE>
+__device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, float4* scr, float* stage,
+                                          const Samples& sm, const int* tab) {
+  const GridDev G = grid_of(S);
+  const DockDev D = dock_of(S);
   constexpr int P = (E + 1) % 3, Q = (E + 2) % 3;
   const int lane = lane_id();
-  const float cE = G.c0[E], ih = G.inv_h, fnE = G.fn[E];
+  const float cE = in_vgpr(G.c0[E]), ih = in_vgpr(G.inv_h), fnE = G.fn[E];
+  const int* tE = tab + G.tab_base[E] + 1;
+  const char* gk = G.gk;
   // displacement delta * m of sample j (m = j, or j - T past T / 2) is monotone in
   // m, so every sample's lies between those of the two extreme m
   const int mlo = D.T >= 2 ? D.T / 2 - D.T : 0, mhi = D.T >= 2 ? D.T / 2 - 1 : 0;
@@ -337,101 +461,119 @@ __device__ int trans_scan(const GridDev& G, const DockDev& D, PoseReg<NSLOT>& p,
   const float dmin = fminf(da, db), dmax = fmaxf(da, db);
   int span = 0;
   bool inside = true;
+  float s0 = 0.f;
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
     const int a = s * 64 + lane;
     if (a < N) {
-      int ip = clamp_node(fmaf(p.x[P][s], G.inv_h, G.c0[P]), G.fn[P]);
-      int iq = clamp_node(fmaf(p.x[Q][s], G.inv_h, G.c0[Q]), G.fn[Q]);
+      const int ip = clamp_node(fmaf(p.x[P][s], ih, G.c0[P]), G.fn[P]);
+      const int iq = clamp_node(fmaf(p.x[Q][s], ih, G.c0[Q]), G.fn[Q]);
       const int part = boff(tab + G.tab_base[P] + 1, ip) + boff(tab + G.tab_base[Q] + 1, iq);
       const int lo = clamp_node(fmaf(p.x[E][s] + dmin, ih, cE), fnE);
       const int hi = clamp_node(fmaf(p.x[E][s] + dmax, ih, cE), fnE);
       span = max(span, hi - lo + 1);
       inside = inside && lo >= 0 && hi < G.n[E];   // every sample's f in [0, n): no clamp needed
       scr[a] = make_float4(p.x[E][s], __int_as_float(part), __int_as_float(lo), 0.f);
+      s0 += grid_at(gk, part + boff(tE, clamp_node(fmaf(p.x[E][s], ih, cE), fnE)));
     }
   }
   span = wave_reduce_i32(span, OpMax());
   inside = !wave_any(!inside);
   wave_sync();
-  float acc[SPL];
-#pragma unroll
-  for (int q = 0; q < SPL; ++q) acc[q] = 0.f;
-  const int* tE = tab + G.tab_base[E] + 1;
-  const char* gk = G.gk;
-  if (!STAGE || span > 64) {
-    auto gather = [&](int t, float (&out)[SPL]) {
-      const float4 d = scr[t];
-      const int part = __float_as_int(d.y);
-#pragma unroll
-      for (int q = 0; q < SPL; ++q) {
-        float xe = d.x + sm.d[q];
-        int ie = clamp_node(fmaf(xe, ih, cE), fnE);
-        out[q] = grid_at(gk, part + boff(tE, ie));
-      }
-    };
-    pipelined_sum<SPL>(N, gather, acc);
+  const uint64_t all = sm.ngt < 64 ? (1ull << sm.ngt) - 1u : ~0ull;
+  auto displacement = [&](int j) { return D.delta * (float)(j < D.T / 2 ? j : j - D.T); };
+  auto index = [&](int pos) { return pos + mlo < 0 ? pos + mlo + D.T : pos + mlo; };   // position: order of displacement
+  auto none = [](int, bool) { return false; };
+  int j;
+  if (!STAGE || span > 63) {
+    j = select_sample<true>(
+        all, __builtin_inff(), sm.GT, D.T, 0.f, index,
+        [&](int js) {
+          const float d = displacement(js);
+          return scan_sum<4>(inside, 0.f, N, [&](auto in, int t) {
+            const float4 k = scr[t];
+            return grid_at(gk, __float_as_int(k.y) + boff(tE, node_index(in, fmaf(k.x + d, ih, cE), fnE)));
+          });
+        },
+        none);
   } else {
-    const int per = 64 / span;               // atoms whose runs one gather instruction reads
-    const int tt = lane / span, ii = lane - tt * span;
+    const int run = span + 1;                          // nodes staged per atom: its run and one more
+    const float rrun = __builtin_amdgcn_rcpf((float)run);
+    const int room = __builtin_amdgcn_readfirstlane(small_div(stage_floats(NSLOT), rrun));   // atoms whose runs the stage holds
+    const int per = __builtin_amdgcn_readfirstlane(small_div(64, rrun));                     // atoms read by one gather instruction
+    const int tt = small_div(lane, rrun), ii = lane - tt * run;
     const int imax = (int)fnE;
-    // lane (tt, ii): node lo + ii of atom g * per + tt (clamped into the grid;
-    // positions past an atom's own run are never read)
-    auto stage_load = [&](int g) {
-      const int t = g * per + tt;
-      float v = 0.f;
-      if (tt < per && t < N) {
-        const float4 d = scr[t];
-        v = grid_at(gk, __float_as_int(d.y) + boff(tE, min(__float_as_int(d.z) + ii, imax)));
-      }
-      return v;
-    };
-    const int groups = (N + per - 1) / per;
-    auto staged = [&](auto clamp_tag) {
-      constexpr bool CLAMP = decltype(clamp_tag)::value;
-      float next = stage_load(0);
-      for (int g = 0; g < groups; ++g) {
-        float* buf = stage + (g & 1) * 64;    // two buffers: this group's stage is written while
-        buf[lane] = next;                     // the previous group's reads are retired
-        wave_sync();
-        if (g + 1 < groups) next = stage_load(g + 1);
-        const int t0 = g * per, t1 = min(N, t0 + per);
-        for (int t = t0; t < t1; ++t) {
-          const float4 d = scr[t];
-          // LDS byte address of the atom's run, shifted so that node ie (in [lo, lo +
-          // span)) is at run + 4 ie
-          uint32_t run = lds_addr(buf) + 4u * (uint32_t)((t - t0) * span - __float_as_int(d.z));
-          asm volatile("" : "+v"(run));   // one base per atom: each sample then adds 4 ie in one shift-add
-          int ie[SPL];
-          float v[SPL];
+    // runs of atoms t0 .. t1 - 1: atom t's node lo + i (clamped into the grid) at
+    // stage[(t - t0) * run + i]; scr[t].w becomes the LDS byte address of its node 0
+    auto fill = [&](int t0, int t1) {
+      wave_sync();
+      const int first = tt < per ? t0 + tt : t1;
+      for (int t = first; t < t1; t += 4 * per) {
+        float v[4];
 #pragma unroll
-          for (int q = 0; q < SPL; ++q) {
-            const float f = fmaf(d.x + sm.d[q], ih, cE);
-            ie[q] = CLAMP ? clamp_node(f, fnE) : floor_node(f);
-          }
-#pragma unroll
-          for (int q = 0; q < SPL; ++q) v[q] = lds_load(run + 4u * (uint32_t)ie[q]);
-#pragma unroll
-          for (int q = 0; q < SPL; ++q) acc[q] += v[q];
+        for (int u = 0; u < 4; ++u) {
+          const float4 k = scr[min(t + u * per, t1 - 1)];
+          v[u] = grid_at(gk, __float_as_int(k.y) + boff(tE, min(__float_as_int(k.z) + ii, imax)));
+          if (ii == 0 && t + u * per < t1)
+            reinterpret_cast<uint32_t*>(scr + t + u * per)[3] =
+                lds_addr(stage) + 4u * (uint32_t)((t + u * per - t0) * run - __float_as_int(k.z));
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (t + u * per < t1) stage[(t + u * per - t0) * run + ii] = v[u];
       }
+      wave_sync();
     };
-    if (inside)
-      staged(std::false_type{});
-    else
-      staged(std::true_type{});
+    const bool once = room >= N;
+    if (once) fill(0, N);
+    auto place = [&](auto in, const float4& k, float d) {
+      return __float_as_uint(k.w) + 4u * (uint32_t)node_index(in, fmaf(k.x + d, ih, cE), fnE);
+    };
+    float bound = __builtin_inff();
+    uint64_t alive = all;
+    if (sm.bound_t) {
+      const int part = lane >> (6 - sm.tsub), step = 1 << sm.tsub;
+      const float d = sm.dlow;
+      float acc = 0.f;
+      for (int t0 = 0; t0 < N; t0 += room) {
+        const int t1 = min(N, t0 + room);
+        if (!once) fill(t0, t1);
+        auto windows = [&](auto in) {
+#pragma unroll 2
+          for (int t = t0 + part; t < t1; t += step) {
+            const uint32_t at = place(in, scr[t], d);
+            acc += larger(lds_load(at), lds_load(at + 4u));
+          }
+        };
+        if (inside)
+          windows(std::true_type{});
+        else
+          windows(std::false_type{});
+      }
+      if (sm.tsub == 2) acc += __shfl_xor(acc, 16);
+      if (sm.tsub >= 1) acc += __shfl_xor(acc, 32);
+      bound = acc + sum_slack(G, N);
+      // sample 0's group stays: its own score decides between equal samples
+      alive = groups_above(bound, wave_sum(s0), sm.ngt) | 1ull << sm.gt0;
+    }
+    j = select_sample<true>(
+        alive, bound, sm.GT, D.T, 0.f, index,
+        [&](int js) {
+          const float d = displacement(js);
+          float acc = 0.f;
+          for (int t0 = 0; t0 < N; t0 += room) {
+            const int t1 = min(N, t0 + room);
+            if (!once) fill(t0, t1);
+            acc = scan_sum<4>(inside, acc, t1 - t0, [&](auto in, int t) { return lds_load(place(in, scr[t0 + t], d)); });
+          }
+          return acc;
+        },
+        none);
   }
-  const int j = wave_argmax(acc, sm.valid_t);
   apply_trans<NSLOT, E>(D, p, j);
   wave_sync();
   return j;
 }
-
-// Square root for the pair prune's radii: the hardware's one-ulp root.  The
-// prune only has to keep every pair that can clash, and its 0.05 A margin is
-// orders of magnitude above an ulp of a radius (the exact clash test itself
-// uses no root).
-__device__ __forceinline__ float prune_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
 // Minimum of two floats as one v_min_f32: fminf's quieting of signalling NaNs
 // costs two more instructions per call on a loop-carried value.  A NaN operand
@@ -444,225 +586,236 @@ __device__ __forceinline__ float vmin(float a, float b) {
 }
 
 // ---- greedy torsion scan of bond k with the clash check ----------------------
-// Admissibility of every sample is decided in the scoring pass.  A moving atom
-// sweeps a circle about the bond axis; a (moving, static) pair whose circle never
-// comes within clash distance + margin of the static atom cannot clash at any
-// angle (the margin is far above the FP32 deviation of the computed rotation from
-// the exact circle), so only the remaining "risky" pairs are tested, with the
-// oracle's d^2 formula.  The pairs are listed in LDS grouped by moving atom; if
-// a scan has more risky pairs than the list holds, the winner is instead tested
-// against every pair and dropped while it clashes (same result, slower).
-template <int NSLOT, int SPL>
-__device__ int tors_scan(const GridDev& G, const LigDev& Lg, const DockDev& D, PoseReg<NSLOT>& p, int N,
-                         int toff, int k, const uint32_t* mkl, float4* scr, float4* pairs,
-                         const SampleReg<SPL>& sm, const int* tab) {
-  constexpr int PAIR_CAP = 128 * NSLOT;
+// A moving atom sweeps a circle about the bond axis; a (moving, static) pair whose
+// circle never comes within clash distance + margin of the static atom cannot
+// clash at any angle (the margin is far above the FP32 deviation of the computed
+// rotation from the exact circle), so only the remaining "risky" pairs are
+// tested.  They are listed in LDS grouped by moving atom; a scan with more pairs
+// than the list holds takes them in several lists of whole moving atoms.
+// Bound pass, at the groups' centres: as in the rotation scan with cubic windows;
+// and a group all of whose samples clash is dropped: a pair closer than the clash
+// distance less chord * r (r: the moving atom's distance from the axis) at the
+// centre clashes at every sample.  Better scores are mostly found where the
+// fragment runs into the rest, so that test matters: 0.26, 0.13, 0.10 of the
+// groups survive (sweeps 1, 2, 3) against 0.65, 0.46, 0.40 without it; 1.3, 1.1,
+// 1.03 passes of 64 samples instead of 4.  The exact pair tests then run only
+// for samples that beat the best so far.
+template <int NSLOT>
+__device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, int toff, int k, const uint32_t* mkl,
+                                         float4* scr, float4* pairs, const Samples& sm, const int* tab) {
+  const GridDev G = grid_of(S);
+  const DockDev D = dock_of(S);
+  constexpr int PAIR_CAP = pair_cap(NSLOT);
+  float4* aux = pairs + PAIR_CAP;   // per moving atom: axial position, radius, squared distance of the group clash test, level
   const int lane = lane_id();
   uint32_t mk[NSLOT];   // fragment masks of this lane's atoms, kept in LDS between scans
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) mk[s] = mkl[s * 64 + lane];
-  const BondAxis A = bond_axis(Lg, p, toff, k);
+  const BondAxis A = bond_axis(ligands_of(S), p, toff, k);
   const int a = A.a, b = A.b;
-  const float xa = A.xa, ya = A.ya, za = A.za, ux = A.ux, uy = A.uy, uz = A.uz;
+  const float xa = in_vgpr(A.xa), ya = in_vgpr(A.ya), za = in_vgpr(A.za), ux = A.ux, uy = A.uy, uz = A.uz;
+  const float ih = in_vgpr(G.inv_h), clash2 = D.clash2;
+  const float cx = in_vgpr(G.c0[0]), cy = in_vgpr(G.c0[1]), cz = in_vgpr(G.c0[2]);
 
-  // moving atoms of F_k other than b, compacted into scr; their current score;
-  // axial position h and radius r of every static atom about the bond axis
-  bool mv[NSLOT], st[NSLOT];
-  float hs[NSLOT], rs[NSLOT];
+  // moving atoms of F_k other than b, compacted into scr and aux; their current score
+  bool mv[NSLOT];
   int m = 0;
   float s0 = 0.f;
+  // every place of a moving atom lies within |h u| + radius rho of a: when that
+  // cube, widened by four nodes, is inside the padded grid, no node index needs
+  // its clamp
+  bool inside = true, level = G.dil != nullptr && sm.GA > 1;
+  const float ulen = prune_sqrt(fmaf(ux, ux, fmaf(uy, uy, uz * uz))) * 1.0001f;
+  const float f0 = fmaf(xa, ih, cx), f1 = fmaf(ya, ih, cy), f2 = fmaf(za, ih, cz);
+  const float reach = fminf(fminf(fminf(f0 + 1.f, G.fn[0] - f0), fminf(f1 + 1.f, G.fn[1] - f1)),
+                            fminf(f2 + 1.f, G.fn[2] - f2)) - 4.f;
+  const float ferr = 1e-6f * (fabsf(xa) + fabsf(ya) + fabsf(za));   // rounding of positions far from the origin
   moving_atoms(mk, N, k, b, mv);
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
-    const int at = s * 64 + lane;
-    const bool in = at < N;
-    const bool inf = in && ((mk[s] >> k) & 1u);
-    st[s] = in && !inf && at != a;
     const float vx = p.x[0][s] - xa, vy = p.x[1][s] - ya, vz = p.x[2][s] - za;
-    hs[s] = vx * ux + vy * uy + vz * uz;
-    rs[s] = prune_sqrt(fmaxf(vx * vx + vy * vy + vz * vz - hs[s] * hs[s], 0.f));
     const uint64_t bal = __ballot(mv[s]);
-    const int pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+    const int at = m + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
     if (mv[s]) {
-      scr[m + pre] = make_float4(vx, vy, vz, 0.f);
       s0 += nearest(G, p.x[0][s], p.x[1][s], p.x[2][s]);
+      const float h = vx * ux + vy * uy + vz * uz, v2 = vx * vx + vy * vy + vz * vz;
+      const float r = prune_sqrt(fmaxf(v2 - h * h, 0.f));
+      // M v = c (v - h u) + s (u x v) + h u: the circle's radius is the length of
+      // the parts that cos and sin multiply (equal for a unit axis)
+      const float ax = vx - ux * h, ay = vy - uy * h, az = vz - uz * h;
+      const float bx = uy * vz - uz * vy, by = uz * vx - ux * vz, bz = ux * vy - uy * vx;
+      const float rho = prune_sqrt(fmaxf(ax * ax + ay * ay + az * az, bx * bx + by * by + bz * bz)) * 1.0001f;
+      inside = inside && fmaf(sm.radius, rho, ulen * fabsf(h)) * ih <= reach;
+      const float arc = sm.chord * rho;
+      const float del = fmaf(arc + ferr, ih, 4e-3f);
+      const int l = del <= 0.5f ? 0 : del <= 1.5f ? 1 : 2;
+      level = level && del <= 2.5f;
+      const float gap = D.clash - arc - ferr - 2e-3f;
+      scr[at] = make_float4(vx, vy, vz, 0.f);
+      aux[at] = make_float4(h, r, gap > 0.f ? gap * gap : 0.f, __int_as_float(l << 24));
     }
     m += __popcll(bal);
   }
+  if (m == 0) return 0;
   s0 = wave_sum(s0);
+  inside = !wave_any(!inside);
+  level = !wave_any(!level);
   wave_sync();
 
-  // risky pairs, grouped by moving atom t; scr[t].w = first pair | count << 16
-  int npairs = 0;
-  for (int t = 0; t < m; ++t) {
-    const float4 v = scr[t];
-    const float ht = v.x * ux + v.y * uy + v.z * uz;
-    const float rt = prune_sqrt(fmaxf(v.x * v.x + v.y * v.y + v.z * v.z - ht * ht, 0.f));
-    const int first = npairs;
+  // risky pairs of the moving atoms t0 .. t1 - 1, with the atom's group clash
+  // distance; scr[t].w = first pair | count << 16 | level << 24.  Returns t1:
+  // whole atoms until the next one's pairs would not fit (one atom's always do).
+  auto list_pairs = [&](int t0) {
+    float hs[NSLOT], rs[NSLOT];   // of the static atoms
+    bool st[NSLOT];
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) {
-      const float dh = ht - hs[s], dr = rt - rs[s];
-      const bool risky = st[s] && fmaf(dr, dr, dh * dh) < D.clash_r2;
-      const uint64_t bal = __ballot(risky);
-      const int pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-      if (risky && npairs + pre < PAIR_CAP) pairs[npairs + pre] = make_float4(p.x[0][s], p.x[1][s], p.x[2][s], 0.f);
-      npairs += __popcll(bal);
+      const int at = s * 64 + lane;
+      st[s] = at < N && !((mkl[at] >> k) & 1u) && at != a;
+      const float vx = p.x[0][s] - xa, vy = p.x[1][s] - ya, vz = p.x[2][s] - za;
+      hs[s] = vx * ux + vy * uy + vz * uz;
+      rs[s] = prune_sqrt(fmaxf(vx * vx + vy * vy + vz * vz - hs[s] * hs[s], 0.f));
     }
-    if (lane == 0) reinterpret_cast<int*>(scr + t)[3] = min(first, PAIR_CAP) | ((npairs - first) << 16);
-  }
-  const bool overflow = npairs > PAIR_CAP || D.lazy_clash;
-  wave_sync();
-
-  float acc[SPL];
+    wave_sync();   // reads of an earlier list are done
+    int npairs = 0, t = t0;
+    for (; t < m; ++t) {
+      const float4 x = aux[t];
+      uint64_t bal[NSLOT];
+      int count = 0;
 #pragma unroll
-  for (int q = 0; q < SPL; ++q) acc[q] = 0.f;
-  uint32_t clash = 0u;   // bit q: sample lane + 64 q clashes
-  constexpr int QG = SPL < 2 ? SPL : 2;   // samples whose matrices are held at once
-  const float ih = G.inv_h, clash2 = D.clash2;
+      for (int s = 0; s < NSLOT; ++s) {
+        const float dh = x.x - hs[s], dr = x.y - rs[s];
+        bal[s] = __ballot(st[s] && fmaf(dr, dr, dh * dh) < D.clash_r2);
+        count += __popcll(bal[s]);
+      }
+      if (npairs + count > PAIR_CAP) break;
+      if (lane == 0) reinterpret_cast<int*>(scr + t)[3] = npairs | (count << 16) | __float_as_int(x.w);
+#pragma unroll
+      for (int s = 0; s < NSLOT; ++s) {
+        const int pre =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[s] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal[s], 0u));
+        if ((bal[s] >> lane) & 1u) pairs[npairs + pre] = make_float4(p.x[0][s], p.x[1][s], p.x[2][s], x.z);
+        npairs += __popcll(bal[s]);
+      }
+    }
+    wave_sync();
+    return t;
+  };
+
   const char* gk = G.gk;
   const int* tX = tab + G.tab_base[0] + 1;
   const int* tY = tab + G.tab_base[1] + 1;
   const int* tZ = tab + G.tab_base[2] + 1;
-  if (m > 0) {
-#pragma unroll
-    for (int g = 0; g < SPL; g += QG) {
-      float M[QG][9];
-#pragma unroll
-      for (int q = 0; q < QG; ++q) torsion_matrix(ux, uy, uz, sm.c[g + q], sm.s[g + q], M[q]);
-      auto gather = [&](int t, float (&out)[QG]) {
-        const float4 v = scr[t];
-        float X[QG], Y[QG], Z[QG];
-#pragma unroll
-        for (int q = 0; q < QG; ++q) {
-          float y0, y1, y2;
-          mat_apply(M[q], v.x, v.y, v.z, y0, y1, y2);
-          X[q] = xa + y0;
-          Y[q] = ya + y1;
-          Z[q] = za + y2;
-          int ix = clamp_node(fmaf(X[q], ih, G.c0[0]), G.fn[0]);
-          int iy = clamp_node(fmaf(Y[q], ih, G.c0[1]), G.fn[1]);
-          int iz = clamp_node(fmaf(Z[q], ih, G.c0[2]), G.fn[2]);
-          out[q] = grid_at(gk, boff(tX, ix) + boff(tY, iy) + boff(tZ, iz));
+  float bound = __builtin_inff();
+  int listed = 0;   // atoms of the list in LDS, when it holds every pair
+  uint64_t dead = 0u;
+  if (level) {
+    float M[9];
+    torsion_matrix(ux, uy, uz, sm.cc, sm.cs, M);
+    const char* dil = G.dil + 12 * (size_t)G.dil_stride;
+    const int* cX = tab + G.tab_c[0] + 1;
+    const int* cY = tab + G.tab_c[1] + 1;
+    const int* cZ = tab + G.tab_c[2] + 1;
+    const float k0 = cx - 0.5f, k1 = cy - 0.5f, k2 = cz - 0.5f;   // windows reach from half a node below
+    bool hit = false;
+    auto window = [&](auto in, int t) {
+      const float4 v = scr[t];
+      const float X = fmaf(M[0], v.x, fmaf(M[1], v.y, fmaf(M[2], v.z, xa)));
+      const float Y = fmaf(M[3], v.x, fmaf(M[4], v.y, fmaf(M[5], v.z, ya)));
+      const float Z = fmaf(M[6], v.x, fmaf(M[7], v.y, fmaf(M[8], v.z, za)));
+      const int ix = node_index(in, fmaf(X, ih, k0), G.fn[0]);
+      const int iy = node_index(in, fmaf(Y, ih, k1), G.fn[1]);
+      const int iz = node_index(in, fmaf(Z, ih, k2), G.fn[2]);
+      const int seg = __builtin_amdgcn_readfirstlane(__float_as_int(v.w));
+      const int w = bound_at(dil + (uint32_t)(seg >> 24) * G.dil_stride, boff(cX, ix) + boff(cY, iy) + boff(cZ, iz));
+      const int p0 = seg & 0xFFFF, p1 = p0 + ((seg >> 16) & 0xFF);
+      if (p1 > p0 && !D.lazy_clash) {
+        float dmin = __builtin_inff(), gap2 = 0.f;
+        for (int pi = p0; pi < p1; ++pi) {
+          const float4 c = pairs[pi];
+          const float dx = X - c.x, dy = Y - c.y, dz = Z - c.z;
+          dmin = vmin(dmin, fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+          gap2 = c.w;
         }
-        if (!overflow) {
-          // the segment is the same on every lane: a scalar loop; the least d^2
-          // over the atom's pairs decides its clash bits (min is exact)
-          const int seg = __builtin_amdgcn_readfirstlane(__float_as_int(v.w));
-          const int p0 = seg & 0xFFFF, p1 = p0 + (seg >> 16);
-          if (p1 > p0) {
-            float dmin[QG];
-#pragma unroll
-            for (int q = 0; q < QG; ++q) dmin[q] = __builtin_inff();
+        hit = hit || dmin < gap2;
+      }
+      return w;
+    };
+    int sum = 0, late = 0;
+    for (int t0 = 0; t0 < m;) {
+      const int t1 = list_pairs(t0);
+      if (t0 == 0 && t1 == m) listed = m;
+      // each value is added an atom later: its fetch runs under the pair tests
+      if (inside) {
+        for (int t = t0; t < t1; ++t) {
+          sum += late;
+          late = window(std::true_type{}, t);
+        }
+      } else {
+        for (int t = t0; t < t1; ++t) {
+          sum += late;
+          late = window(std::false_type{}, t);
+        }
+      }
+      t0 = t1;
+    }
+    bound = upper_bound(G, m, sum + late);
+    dead = __ballot(hit);
+  }
+  float Mj[9];
+  const int j = select_sample<false>(
+      groups_above(bound, s0, sm.nga) & ~dead, bound, sm.GA, sm.A, s0, [](int pos) { return pos; },
+      [&](int js) {
+        const float2 cs = sm.ang[js];
+        float M[9];
+        torsion_matrix(ux, uy, uz, cs.x, cs.y, M);
+        return scan_sum<2>(inside, 0.f, m, [&](auto in, int t) {
+          const float4 v = scr[t];
+          float y0, y1, y2;
+          mat_apply(M, v.x, v.y, v.z, y0, y1, y2);
+          const int ix = node_index(in, fmaf(xa + y0, ih, cx), G.fn[0]);
+          const int iy = node_index(in, fmaf(ya + y1, ih, cy), G.fn[1]);
+          const int iz = node_index(in, fmaf(za + y2, ih, cz), G.fn[2]);
+          return grid_at(gk, boff(tX, ix) + boff(tY, iy) + boff(tZ, iz));
+        });
+      },
+      [&](int js, bool better) {
+        const float2 cs = sm.ang[js];
+        float M[9];
+        torsion_matrix(ux, uy, uz, cs.x, cs.y, M);
+        bool hit = false;
+        for (int t0 = 0; t0 < m;) {
+          const int t1 = listed ? m : list_pairs(t0);
+          if (t0 == 0 && t1 == m) listed = m;
+          for (int t = t0; t < t1; ++t) {
+            const float4 v = scr[t];
+            // the segment is the same on every lane: a scalar loop; the least d^2
+            // over the atom's pairs decides (min is exact)
+            const int seg = __builtin_amdgcn_readfirstlane(__float_as_int(v.w));
+            const int p0 = seg & 0xFFFF, p1 = p0 + ((seg >> 16) & 0xFF);
+            if (p1 == p0) continue;
+            float y0, y1, y2;
+            mat_apply(M, v.x, v.y, v.z, y0, y1, y2);
+            const float X = xa + y0, Y = ya + y1, Z = za + y2;
+            float dmin = __builtin_inff();
             for (int pi = p0; pi < p1; ++pi) {
               const float4 c = pairs[pi];
-#pragma unroll
-              for (int q = 0; q < QG; ++q) {
-                float dx = X[q] - c.x, dy = Y[q] - c.y, dz = Z[q] - c.z;
-                dmin[q] = vmin(dmin[q], fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
-              }
+              const float dx = X - c.x, dy = Y - c.y, dz = Z - c.z;
+              dmin = vmin(dmin, fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
             }
-#pragma unroll
-            for (int q = 0; q < QG; ++q)
-              if (dmin[q] < clash2) clash |= 1u << (g + q);
+            hit = hit || dmin < clash2;
+            if (!wave_any(better && !hit)) return hit;
           }
+          t0 = t1;
         }
-      };
-      pipelined_sum<QG>(m, gather, acc, g);
-    }
+        return hit;
+      });
+  if (j != 0) {
+    torsion_matrix(ux, uy, uz, sm.ang[j].x, sm.ang[j].y, Mj);
+    apply_tors(p, A, Mj, mv);
   }
-  if (lane == 0) {
-    acc[0] = s0;        // sample 0 is the current pose,
-    clash &= ~1u;       // always admissible
-  }
-
-  int j;
-  float Mj[9];
-  if (!overflow) {
-    j = wave_argmax(acc, sm.valid_a & ~clash);
-    if (j != 0) torsion_matrix(ux, uy, uz, D.angles[2 * j], D.angles[2 * j + 1], Mj);
-  } else {
-    // best sample; a winner that clashes is dropped and the next best taken
-    float4* cand = pairs;
-    uint32_t alive = sm.valid_a;
-    for (;;) {
-      j = wave_argmax(acc, alive);
-      if (j == 0) break;
-      torsion_matrix(ux, uy, uz, D.angles[2 * j], D.angles[2 * j + 1], Mj);
-      for (int t = lane; t < m; t += 64) {
-        const float4 v = scr[t];
-        float y0, y1, y2;
-        mat_apply(Mj, v.x, v.y, v.z, y0, y1, y2);
-        cand[t] = make_float4(xa + y0, ya + y1, za + y2, 0.f);
-      }
-      wave_sync();
-      bool hit = false;
-      for (int t = 0; t < m; ++t) {
-        const float4 c = cand[t];
-#pragma unroll
-        for (int s = 0; s < NSLOT; ++s) {
-          float dx = c.x - p.x[0][s], dy = c.y - p.x[1][s], dz = c.z - p.x[2][s];
-          float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-          hit |= st[s] && d2 < clash2;
-        }
-      }
-      if (!wave_any(hit)) break;
-      if (lane == (j & 63)) alive &= ~(1u << (j >> 6));
-      wave_sync();
-    }
-  }
-  if (j != 0) apply_tors(p, A, Mj, mv);
   wave_sync();
   return j;
-}
-
-template <int SPL>
-__device__ void load_samples(const DockDev& D, SampleReg<SPL>& sm) {
-  const int lane = lane_id();
-  sm.valid_a = 0u;
-  sm.valid_t = 0u;
-  sm.half_turn = false;
-  sm.quarter_turn = false;
-#pragma unroll
-  for (int q = 0; q < SPL; ++q) {
-    const int j = lane + 64 * q;
-    if (j < D.A) {
-      sm.c[q] = D.angles[2 * j];
-      sm.s[q] = D.angles[2 * j + 1];
-      sm.valid_a |= 1u << q;
-    } else {
-      sm.c[q] = 1.f;
-      sm.s[q] = 0.f;
-    }
-    if (j < D.T) {
-      const int m = j < D.T / 2 ? j : j - D.T;
-      sm.d[q] = D.delta * (float)m;
-      sm.valid_t |= 1u << q;
-    } else {
-      sm.d[q] = 0.f;
-    }
-  }
-  {
-    bool u = true;
-#pragma unroll
-    for (int q = 0; q < SPL; ++q) u = u && fabsf(sm.c[q]) <= 1.f && fabsf(sm.s[q]) <= 1.f;
-    sm.unit = !wave_any(!u);
-  }
-  if (SPL % 2 == 0 && D.A == 64 * SPL) {
-    bool pair = true;
-#pragma unroll
-    for (int q = 0; q < SPL / 2; ++q)
-      pair = pair && sm.c[q + SPL / 2] == -sm.c[q] && sm.s[q + SPL / 2] == -sm.s[q];
-    sm.half_turn = !wave_any(!pair);
-  }
-  if (SPL % 4 == 0 && D.A == 64 * SPL) {
-    constexpr int Q4 = SPL / 4;
-    bool quad = true;
-#pragma unroll
-    for (int q = 0; q < Q4; ++q)
-      quad = quad && sm.c[q + Q4] == -sm.s[q] && sm.s[q + Q4] == sm.c[q] && sm.c[q + 2 * Q4] == -sm.c[q] &&
-             sm.s[q + 2 * Q4] == -sm.s[q] && sm.c[q + 3 * Q4] == sm.s[q] && sm.s[q + 3 * Q4] == -sm.c[q];
-    sm.quarter_turn = !wave_any(!quad);
-  }
 }
 
 template <int NSLOT>
@@ -737,42 +890,57 @@ __device__ __forceinline__ uint16_t* move_record(const DockDev& D, int lig, int 
   return D.moves + (size_t)D.R * D.S * (6 * (size_t)lig + toff) + (size_t)r * D.S * (6 + K);
 }
 
+// LDS of a block: the brick offset tables, the samples' (cos, sin), then per
+// wavefront the scan data of 64*NSLOT atoms, the regions of the scans (risky
+// torsion pairs and moving atoms, staged grid values, bound-pass data) and the
+// fragment masks.
+struct BlockLds {
+  int* tab;
+  float2* ang;
+  float4* scr;
+  float4* cand;
+  uint32_t* mkl;
+};
+
 // One restart: placement, S sweeps, final trilinear score, outputs.
-template <int NSLOT, int SPL, bool STAGE = true>
-__device__ void dock_restart(const GridDev& G, const LigDev& Lg, const DockDev& D, const SampleReg<SPL>& sm,
-                             const LigReg<NSLOT>& L, int lig, int r, float4* scr, float4* cand,
-                             const uint32_t* mkl, const int* tab) {
+template <int NSLOT, bool STAGE = true>
+__device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const LigReg<NSLOT>& L, int lig, int r,
+                                             const BlockLds& B) {
   const int lane = lane_id();
   const int N = L.N;
   PoseReg<NSLOT> p;
-  place_pose(Lg, D, L, r, p);
-
-  int16_t* tr = D.trace ? D.trace + ((size_t)lig * D.R + r) * (size_t)D.S * D.trace_w : nullptr;
-  uint16_t* mrec = move_record(D, lig, L.toff, L.K, r);
-  for (int sw = 0; sw < D.S; ++sw) {
-    int jr0 = rot_scan<NSLOT, SPL, 0>(G, D, p, N, scr, sm, tab);
-    int jr1 = rot_scan<NSLOT, SPL, 1>(G, D, p, N, scr, sm, tab);
-    int jr2 = rot_scan<NSLOT, SPL, 2>(G, D, p, N, scr, sm, tab);
-    float* stage = reinterpret_cast<float*>(cand);
-    int jt0 = trans_scan<NSLOT, SPL, 0, STAGE>(G, D, p, N, scr, stage, sm, tab);
-    int jt1 = trans_scan<NSLOT, SPL, 1, STAGE>(G, D, p, N, scr, stage, sm, tab);
-    int jt2 = trans_scan<NSLOT, SPL, 2, STAGE>(G, D, p, N, scr, stage, sm, tab);
-    int16_t* trow = tr ? tr + (size_t)sw * D.trace_w : nullptr;
-    uint16_t* mrow = mrec + (size_t)sw * (6 + L.K);
+  place_pose(ligands_of(S), dock_of(S), L, r, p);
+  const int sweeps = S->D.S;
+  float* stage = reinterpret_cast<float*>(B.cand);
+  for (int sw = 0; sw < sweeps; ++sw) {
+    int j[6];
+    j[0] = rot_scan<NSLOT, 0>(S, p, N, B.scr, B.cand, sm, B.tab);
+    j[1] = rot_scan<NSLOT, 1>(S, p, N, B.scr, B.cand, sm, B.tab);
+    j[2] = rot_scan<NSLOT, 2>(S, p, N, B.scr, B.cand, sm, B.tab);
+    j[3] = trans_scan<NSLOT, 0, STAGE>(S, p, N, B.scr, stage, sm, B.tab);
+    j[4] = trans_scan<NSLOT, 1, STAGE>(S, p, N, B.scr, stage, sm, B.tab);
+    j[5] = trans_scan<NSLOT, 2, STAGE>(S, p, N, B.scr, stage, sm, B.tab);
+    const DockDev D = dock_of(S);
+    uint16_t* mrow = move_record(D, lig, L.toff, L.K, r) + (size_t)sw * (6 + L.K);
+    int16_t* trow = D.trace ? D.trace + (((size_t)lig * D.R + r) * (size_t)sweeps + sw) * D.trace_w : nullptr;
     if (lane == 0) {
-      mrow[0] = (uint16_t)jr0; mrow[1] = (uint16_t)jr1; mrow[2] = (uint16_t)jr2;
-      mrow[3] = (uint16_t)jt0; mrow[4] = (uint16_t)jt1; mrow[5] = (uint16_t)jt2;
-    }
-    if (trow && lane == 0) {
-      trow[0] = (int16_t)jr0; trow[1] = (int16_t)jr1; trow[2] = (int16_t)jr2;
-      trow[3] = (int16_t)jt0; trow[4] = (int16_t)jt1; trow[5] = (int16_t)jt2;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) mrow[q] = (uint16_t)j[q];
+      if (trow) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) trow[q] = (int16_t)j[q];
+      }
     }
     for (int k = 0; k < L.K; ++k) {
-      int jk = tors_scan<NSLOT, SPL>(G, Lg, D, p, N, L.toff, k, mkl, scr, cand, sm, tab);
-      if (lane == 0) mrow[6 + k] = (uint16_t)jk;
-      if (trow && lane == 0) trow[6 + k] = (int16_t)jk;
+      const int jk = tors_scan<NSLOT>(S, p, N, L.toff, k, B.mkl, B.scr, B.cand, sm, B.tab);
+      if (lane == 0) {
+        mrow[6 + k] = (uint16_t)jk;
+        if (trow) trow[6 + k] = (int16_t)jk;
+      }
     }
   }
+  const GridDev G = grid_of(S);
+  const DockDev D = dock_of(S);
 
   // final trilinear score, summed in atom order
   float v[NSLOT];
@@ -794,15 +962,16 @@ template <int NSLOT>
 __device__ void replay_restart(const LigDev& Lg, const DockDev& D, const LigReg<NSLOT>& L, int lig, int r,
                                PoseReg<NSLOT>& p) {
   place_pose(Lg, D, L, r, p);
+  const float2* ang = reinterpret_cast<const float2*>(D.angles);
   const uint16_t* mrec = move_record(D, lig, L.toff, L.K, r);
   // recorded indices are below A (rotations, torsions) and T (translations); the
   // clamps only keep table reads in range
   const int amax = D.A - 1, tmax = D.T - 1;
   for (int sw = 0; sw < D.S; ++sw) {
     const uint16_t* mrow = mrec + (size_t)sw * (6 + L.K);
-    apply_rot<NSLOT, 0>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[0]), amax));
-    apply_rot<NSLOT, 1>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[1]), amax));
-    apply_rot<NSLOT, 2>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[2]), amax));
+    apply_rot<NSLOT, 0>(ang, p, min((int)__builtin_amdgcn_readfirstlane(mrow[0]), amax));
+    apply_rot<NSLOT, 1>(ang, p, min((int)__builtin_amdgcn_readfirstlane(mrow[1]), amax));
+    apply_rot<NSLOT, 2>(ang, p, min((int)__builtin_amdgcn_readfirstlane(mrow[2]), amax));
     apply_trans<NSLOT, 0>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[3]), tmax));
     apply_trans<NSLOT, 1>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[4]), tmax));
     apply_trans<NSLOT, 2>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[5]), tmax));
@@ -819,31 +988,40 @@ __device__ void replay_restart(const LigDev& Lg, const DockDev& D, const LigReg<
   }
 }
 
-// Plain method: one launch per ligand; wavefront w of the grid docks restart w.
-// LDS of a block: the brick offset tables, then per wavefront the scan data of
-// 64*NSLOT atoms, a list of 128*NSLOT risky torsion pairs and the fragment masks.
-__device__ __forceinline__ int tab_words(const GridDev& G) { return (G.tab_len + 3) & ~3; }
+// The running kernel's first argument.
+__device__ __forceinline__ ArgsPtr kernel_args() { return (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); }
 
-template <int NSLOT, int SPL>
-__global__ __launch_bounds__(256) void dock_plain_kernel(GridDev G, LigDev Lg, DockDev D, int lig) {
-  extern __shared__ float4 lds[];
-  int* tab = reinterpret_cast<int*>(lds);
-  fill_brick_tables(G, tab);
+// Plain method: one launch per ligand; wavefront w of the grid docks restart w.
+template <int NSLOT>
+__device__ __forceinline__ BlockLds block_lds(const GridDev& G, const DockDev& D, float4* lds) {
+  BlockLds b;
+  b.tab = reinterpret_cast<int*>(lds);
+  const int head = (G.tab_len + 3) / 4;
+  b.ang = reinterpret_cast<float2*>(lds + head);
+  b.scr = lds + head + (D.A + 1) / 2 + (size_t)(threadIdx.x >> 6) * dock_wave_float4(NSLOT);
+  b.cand = b.scr + 64 * NSLOT;
+  b.mkl = reinterpret_cast<uint32_t*>(b.scr + dock_wave_float4(NSLOT) - 16 * NSLOT);
+  fill_brick_tables(G, b.tab);
+  for (int j = threadIdx.x; j < D.A; j += blockDim.x) b.ang[j] = make_float2(D.angles[2 * j], D.angles[2 * j + 1]);
   __syncthreads();
+  return b;
+}
+
+template <int NSLOT>
+__global__ __launch_bounds__(256) void dock_plain_kernel(DockArgs X, int lig) {
+  extern __shared__ float4 lds[];
+  const BlockLds B = block_lds<NSLOT>(X.G, X.D, lds);
   const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  float4* scr = lds + tab_words(G) / 4 + (size_t)wave * dock_wave_float4(NSLOT);
-  float4* cand = scr + 64 * NSLOT;
-  uint32_t* mkl = reinterpret_cast<uint32_t*>(scr + 3 * 64 * NSLOT);
   const int r = blockIdx.x * nwaves + wave;
-  if (r >= D.R) return;
-  SampleReg<SPL> sm;
-  load_samples(D, sm);
+  if (r >= X.D.R) return;
+  Samples sm;
+  load_samples(X.G, X.D, B.ang, sm);
   LigReg<NSLOT> L;
-  load_ligand(Lg, lig, L);
-  store_masks(L, mkl);
+  load_ligand(X.Lg, lig, L);
+  store_masks(L, B.mkl);
   // one wavefront per restart: the staged translation scan's read-then-use of
   // each group's nodes would expose their latency, so the gathers stay direct
-  dock_restart<NSLOT, SPL, false>(G, Lg, D, sm, L, lig, r, scr, cand, mkl, tab);
+  dock_restart<NSLOT, false>(kernel_args(), sm, L, lig, r, B);
 }
 
 // Bucketed method: persistent; wavefronts pull (ligand, restart chunk) items of
@@ -851,40 +1029,31 @@ __global__ __launch_bounds__(256) void dock_plain_kernel(GridDev G, LigDev Lg, D
 // target per instance (wavefronts per SIMD), chosen by measurement: the register
 // budget it implies makes the compiler spill a few values to scratch, which
 // costs less than the latency the extra wavefronts hide.
-constexpr int bucket_waves_per_simd(int nslot) { return nslot == 1 ? 6 : nslot == 2 ? 5 : 4; }
+constexpr int bucket_waves_per_simd(int nslot) { return nslot == 1 ? 5 : 4; }
 
 // Restarts per work item: the tuning's chunk, or fewer when the launch would
-// have less than 16 items per wavefront.  A longer chunk saves ligand loads; a
-// shorter one keeps every wavefront of a small launch at work and its last items
-// short.  Whole calls with the tuning's chunk of eight against this rule: one
-// ligand of 256 restarts 2 065 against 441 us, 64 small ligands of 32 restarts
-// 1 382 against 415 us, 4 000 ligands in three size classes 165.6 against
-// 115.7 ms; 20 000 ligands keep the tuning's chunk.
+// have less than 16 items per wavefront.  A longer chunk saves ligand loads (a
+// chunk of one costs under 1 % against eight); a shorter one keeps every
+// wavefront of a small launch at work and its last items short.
 __device__ __forceinline__ int restart_chunk(int chunk, long long restarts, int waves_per_block) {
   const long long share = restarts / (16LL * gridDim.x * waves_per_block);
   return share < 1 ? 1 : share < chunk ? (int)share : chunk;
 }
 
-template <int NSLOT, int SPL>
+template <int NSLOT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bucket_waves_per_simd(NSLOT))))
-void dock_bucket_kernel(GridDev G, LigDev Lg, DockDev D, QueueDev Q) {
+void dock_bucket_kernel(DockArgs X, QueueDev Q) {
   extern __shared__ float4 lds[];
   const int b0 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket]);
   const int b1 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket + 1]);
   if (b0 == b1) return;   // no ligand of this class in the batch
-  int* tab = reinterpret_cast<int*>(lds);
-  fill_brick_tables(G, tab);
-  __syncthreads();
-  const int wave = threadIdx.x >> 6;
-  float4* scr = lds + tab_words(G) / 4 + (size_t)wave * dock_wave_float4(NSLOT);
-  float4* cand = scr + 64 * NSLOT;
-  uint32_t* mkl = reinterpret_cast<uint32_t*>(scr + 3 * 64 * NSLOT);
+  const BlockLds B = block_lds<NSLOT>(X.G, X.D, lds);
   const int lane = lane_id();
-  const int chunk = restart_chunk(Q.chunk, (long long)(b1 - b0) * D.R, blockDim.x >> 6);
-  const int nch = (D.R + chunk - 1) / chunk;
+  const int chunk = restart_chunk(Q.chunk, (long long)(b1 - b0) * X.D.R, blockDim.x >> 6);
+  const int nch = (X.D.R + chunk - 1) / chunk;
   const long long n_items = (long long)(b1 - b0) * nch;
-  SampleReg<SPL> sm;
-  load_samples(D, sm);
+  Samples sm;
+  load_samples(X.G, X.D, B.ang, sm);
   int cur_lig = -1;
   LigReg<NSLOT> L;
   for (;;) {
@@ -895,47 +1064,40 @@ void dock_bucket_kernel(GridDev G, LigDev Lg, DockDev D, QueueDev Q) {
     const int li = item / nch, ch = item - li * nch;
     const int lig = __builtin_amdgcn_readfirstlane(Q.perm[b0 + li]);
     if (lig != cur_lig) {
-      load_ligand(Lg, lig, L);
-      store_masks(L, mkl);
+      load_ligand(X.Lg, lig, L);
+      store_masks(L, B.mkl);
       cur_lig = lig;
     }
-    const int r0 = ch * chunk, r1 = min(D.R, r0 + chunk);
+    const int r0 = ch * chunk, r1 = min(X.D.R, r0 + chunk);
     if (L.N > 64 * NSLOT) {
       // cannot happen with the host's plan (instances sized for the largest
       // ligand); marks the restarts instead of touching memory out of range
-      for (int r = r0 + lane; r < r1; r += 64) D.final_scores[(size_t)lig * D.R + r] = __builtin_nanf("");
+      for (int r = r0 + lane; r < r1; r += 64) X.D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
       continue;
     }
-    for (int r = r0; r < r1; ++r) dock_restart(G, Lg, D, sm, L, lig, r, scr, cand, mkl, tab);
+    for (int r = r0; r < r1; ++r) dock_restart<NSLOT>(kernel_args(), sm, L, lig, r, B);
   }
 }
 
 // Several docking sites: the bucket kernel's loop over items (site, ligand of
-// the bucket, restart chunk); each item docks against its site's grid and
-// records into the site's scores and moves.  The brick tables depend on the
+// the bucket, restart chunk); each item works on its site's entry of the table.  The brick tables depend on the
 // grid dimensions only, shared by every site.
-template <int NSLOT, int SPL>
+template <int NSLOT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bucket_waves_per_simd(NSLOT))))
-void dock_sites_kernel(GridDev G, LigDev Lg, DockDev D, QueueDev Q, SitesDev Sd) {
+void dock_sites_kernel(DockArgs X, QueueDev Q, SitesDev Sd) {
   extern __shared__ float4 lds[];
   const int b0 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket]);
   const int b1 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket + 1]);
   if (b0 == b1) return;   // no ligand of this class in the batch
-  int* tab = reinterpret_cast<int*>(lds);
-  fill_brick_tables(G, tab);
-  __syncthreads();
-  const int wave = threadIdx.x >> 6;
-  float4* scr = lds + tab_words(G) / 4 + (size_t)wave * dock_wave_float4(NSLOT);
-  float4* cand = scr + 64 * NSLOT;
-  uint32_t* mkl = reinterpret_cast<uint32_t*>(scr + 3 * 64 * NSLOT);
+  const BlockLds B = block_lds<NSLOT>(X.G, X.D, lds);
   const int lane = lane_id();
   const int nlig = b1 - b0;
-  const int chunk = restart_chunk(Q.chunk, (long long)nlig * D.R * Sd.n_sites, blockDim.x >> 6);
-  const int nch = (D.R + chunk - 1) / chunk;
+  const int chunk = restart_chunk(Q.chunk, (long long)nlig * X.D.R * Sd.n_sites, blockDim.x >> 6);
+  const int nch = (X.D.R + chunk - 1) / chunk;
   const long long per_site = (long long)nlig * nch;
   const long long n_items = per_site * Sd.n_sites;
-  SampleReg<SPL> sm;
-  load_samples(D, sm);
+  Samples sm;
+  load_samples(X.G, X.D, B.ang, sm);
   int cur_lig = -1;
   LigReg<NSLOT> L;
   for (;;) {
@@ -957,39 +1119,17 @@ void dock_sites_kernel(GridDev G, LigDev Lg, DockDev D, QueueDev Q, SitesDev Sd)
     }
     const int lig = __builtin_amdgcn_readfirstlane(Q.perm[b0 + li]);
     if (lig != cur_lig) {
-      load_ligand(Lg, lig, L);
-      store_masks(L, mkl);
+      load_ligand(X.Lg, lig, L);
+      store_masks(L, B.mkl);
       cur_lig = lig;
     }
-    // the site's fields as uniform words: a plain load of Sd.grids would be
-    // held in vector registers for the whole item
-    GridDev Gs = G;
-    DockDev Ds = D;
-    {
-      const int* w = reinterpret_cast<const int*>(Sd.grids + site);
-      int v[sizeof(SiteGrid) / 4];
-#pragma unroll
-      for (int k = 0; k < (int)(sizeof(SiteGrid) / 4); ++k) v[k] = __builtin_amdgcn_readfirstlane(w[k]);
-      SiteGrid sg;
-      __builtin_memcpy(&sg, v, sizeof sg);
-      Gs.g0 = sg.g0;
-      Gs.gb = sg.gb;
-      Gs.gk = sg.gk;
-      for (int a = 0; a < 3; ++a) {
-        Gs.c0[a] = sg.c0[a];
-        Gs.o[a] = sg.o[a];
-      }
-      Gs.out = sg.out;
-      for (int a = 0; a < 3; ++a) Ds.c[a] = sg.c[a];
-    }
-    Ds.final_scores = D.final_scores + (size_t)site * Sd.scores_stride;
-    Ds.moves = D.moves + (size_t)site * Sd.moves_stride;
-    const int r0 = ch * chunk, r1 = min(D.R, r0 + chunk);
+    const ArgsPtr S = (ArgsPtr)(Sd.sites + __builtin_amdgcn_readfirstlane(site));
+    const int r0 = ch * chunk, r1 = min(X.D.R, r0 + chunk);
     if (L.N > 64 * NSLOT) {
-      for (int r = r0 + lane; r < r1; r += 64) Ds.final_scores[(size_t)lig * D.R + r] = __builtin_nanf("");
+      for (int r = r0 + lane; r < r1; r += 64) S->D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
       continue;
     }
-    for (int r = r0; r < r1; ++r) dock_restart(Gs, Lg, Ds, sm, L, lig, r, scr, cand, mkl, tab);
+    for (int r = r0; r < r1; ++r) dock_restart<NSLOT>(S, sm, L, lig, r, B);
   }
 }
 
@@ -1043,77 +1183,69 @@ __global__ __launch_bounds__(256) void topk_kernel(LigDev Lg, DockDev D, int n, 
 }
 
 // ---------------------------------------------------------------- dispatch
-// LDS per block: the brick offset tables, then per wavefront the scan data,
-// torsion candidates and fragment masks of 64*NSLOT atoms.
-static size_t lds_bytes(int nslot, int wpb, int tab_len) {
-  return (size_t)((tab_len + 3) & ~3) * sizeof(int) + (size_t)wpb * dock_wave_float4(nslot) * sizeof(float4);
+size_t dock_lds_bytes(int nslot, int wpb, int tab_len, int angles) {
+  return ((size_t)(tab_len + 3) / 4 + (size_t)(angles + 1) / 2 + (size_t)wpb * dock_wave_float4(nslot)) * sizeof(float4);
 }
 
-#define LG_DISPATCH(nslot, spl, CALL)                                          \
-  switch (nslot * 100 + spl) {                                                 \
-    case 101: CALL(1, 1); case 102: CALL(1, 2); case 104: CALL(1, 4);          \
-    case 108: CALL(1, 8); case 116: CALL(1, 16);                               \
-    case 201: CALL(2, 1); case 202: CALL(2, 2); case 204: CALL(2, 4);          \
-    case 208: CALL(2, 8); case 216: CALL(2, 16);                               \
-    case 301: CALL(3, 1); case 302: CALL(3, 2); case 304: CALL(3, 4);          \
-    case 308: CALL(3, 8); case 316: CALL(3, 16);                               \
-    case 401: CALL(4, 1); case 402: CALL(4, 2); case 404: CALL(4, 4);          \
-    case 408: CALL(4, 8); case 416: CALL(4, 16);                               \
-    default: return hipErrorInvalidValue;                                      \
+#define LG_DISPATCH(nslot, CALL)              \
+  switch (nslot) {                            \
+    case 1: CALL(1); case 2: CALL(2);         \
+    case 3: CALL(3); case 4: CALL(4);         \
+    default: return hipErrorInvalidValue;     \
   }
 
-hipError_t launch_dock_plain(int nslot, int spl, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D,
-                             int lig, hipStream_t st) {
+hipError_t launch_dock_plain(int nslot, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D, int lig,
+                             hipStream_t st) {
   const int blocks = (D.R + wpb - 1) / wpb;
-#define CALL(NS, SP)                                                                            \
-  {                                                                                             \
-    hipLaunchKernelGGL((dock_plain_kernel<NS, SP>), dim3(blocks), dim3(64 * wpb),               \
-                       lds_bytes(NS, wpb, G.tab_len), st, G, Lg, D, lig);                              \
-    return hipGetLastError();                                                                   \
+#define CALL(NS)                                                                                     \
+  {                                                                                                  \
+    hipLaunchKernelGGL(dock_plain_kernel<NS>, dim3(blocks), dim3(64 * wpb),                          \
+                       dock_lds_bytes(NS, wpb, G.tab_len, D.A), st, DockArgs{G, Lg, D}, lig);        \
+    return hipGetLastError();                                                                        \
   }
-  LG_DISPATCH(nslot, spl, CALL)
+  LG_DISPATCH(nslot, CALL)
 #undef CALL
 }
 
-hipError_t launch_dock_bucket(int nslot, int spl, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
-                              const DockDev& D, const QueueDev& Q, hipStream_t st) {
-#define CALL(NS, SP)                                                                            \
-  {                                                                                             \
-    hipLaunchKernelGGL((dock_bucket_kernel<NS, SP>), dim3(blocks), dim3(64 * wpb),              \
-                       lds_bytes(NS, wpb, G.tab_len), st, G, Lg, D, Q);                                \
-    return hipGetLastError();                                                                   \
+hipError_t launch_dock_bucket(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
+                              const QueueDev& Q, hipStream_t st) {
+#define CALL(NS)                                                                                     \
+  {                                                                                                  \
+    hipLaunchKernelGGL(dock_bucket_kernel<NS>, dim3(blocks), dim3(64 * wpb),                         \
+                       dock_lds_bytes(NS, wpb, G.tab_len, D.A), st, DockArgs{G, Lg, D}, Q);          \
+    return hipGetLastError();                                                                        \
   }
-  LG_DISPATCH(nslot, spl, CALL)
+  LG_DISPATCH(nslot, CALL)
 #undef CALL
 }
 
-hipError_t launch_dock_sites(int nslot, int spl, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
-                             const DockDev& D, const QueueDev& Q, const SitesDev& Sd, hipStream_t st) {
-#define CALL(NS, SP)                                                                            \
-  {                                                                                             \
-    hipLaunchKernelGGL((dock_sites_kernel<NS, SP>), dim3(blocks), dim3(64 * wpb),               \
-                       lds_bytes(NS, wpb, G.tab_len), st, G, Lg, D, Q, Sd);                     \
-    return hipGetLastError();                                                                   \
+hipError_t launch_dock_sites(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
+                             const QueueDev& Q, const SitesDev& Sd, hipStream_t st) {
+#define CALL(NS)                                                                                     \
+  {                                                                                                  \
+    hipLaunchKernelGGL(dock_sites_kernel<NS>, dim3(blocks), dim3(64 * wpb),                          \
+                       dock_lds_bytes(NS, wpb, G.tab_len, D.A), st, DockArgs{G, Lg, D}, Q, Sd);      \
+    return hipGetLastError();                                                                        \
   }
-  LG_DISPATCH(nslot, spl, CALL)
+  LG_DISPATCH(nslot, CALL)
 #undef CALL
 }
 
 // Resident blocks per compute unit of a bucket kernel instance (the b of Eq. 1).
-hipError_t occupancy_dock_bucket(int nslot, int spl, int wpb, int tab_len, int* blocks_per_cu) {
-#define CALL(NS, SP)                                                                                  \
-  {                                                                                                   \
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, dock_bucket_kernel<NS, SP>,    \
-                                                        64 * wpb, lds_bytes(NS, wpb, tab_len));            \
+hipError_t occupancy_dock_bucket(int nslot, int wpb, int tab_len, int angles, int* blocks_per_cu) {
+#define CALL(NS)                                                                                        \
+  {                                                                                                     \
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, dock_bucket_kernel<NS>, 64 * wpb, \
+                                                        dock_lds_bytes(NS, wpb, tab_len, angles));      \
   }
-  LG_DISPATCH(nslot, spl, CALL)
+  LG_DISPATCH(nslot, CALL)
 #undef CALL
 }
 
-hipError_t attributes_dock_bucket(int nslot, int spl, hipFuncAttributes* attr) {
-#define CALL(NS, SP) \
-  { return hipFuncGetAttributes(attr, reinterpret_cast<const void*>(dock_bucket_kernel<NS, SP>)); }
-  LG_DISPATCH(nslot, spl, CALL)
+hipError_t attributes_dock_bucket(int nslot, hipFuncAttributes* attr) {
+#define CALL(NS) \
+  { return hipFuncGetAttributes(attr, reinterpret_cast<const void*>(dock_bucket_kernel<NS>)); }
+  LG_DISPATCH(nslot, CALL)
 #undef CALL
 }
 

@@ -24,7 +24,7 @@ struct GridDev {
   const char* gk;
   int nb[3];        // bricks per axis
   int tab_base[3];  // first entry of each axis table in the LDS table array
-  int tab_len;      // (nx+2)+(ny+2)+(nz+2) entries
+  int tab_len;      // entries of all the LDS tables
   float c0[3];      // nearest-node map: f = fma(x, inv_h, c0), c0 = fma(-o, inv_h, 0.5)
   int n[3];
   int stride[3];    // 1, nx+2, (nx+2)(ny+2)
@@ -33,7 +33,23 @@ struct GridDev {
   float fn1[3];     // (float)(n-1) per axis, trilinear range
   float inv_h;
   float out;
+  // Upper bounds for the scans: 16-bit copies of the padded grid, dilated (node i
+  // holds the largest value of a window) and rounded up to whole multiples of
+  // bound_scale.  Copy 4 e + l: w x w nodes i .. i + w - 1 of the plane across
+  // axis e, w = 2, 3, 4, 6, in bricks of 8 x 8 nodes of that plane.  Copy 12 + l:
+  // w^3 nodes i - w/2 + 1 .. i + w/2, w = 2, 4, 6, in bricks of 4 x 4 x 4.  A
+  // brick is a 128-byte line.  nullptr where there are none (very large grids,
+  // non-finite values).
+  const char* dil;
+  uint32_t dil_stride;   // bytes per copy
+  float bound_scale;
+  float vmax;            // largest |value| of the grid, infinite if one is not finite
+  int nb8[3], nb4[3];    // bricks of 8 and of 4 nodes per axis
+  int tab_p, tab_q[3], tab_c[3];   // first entries of their offset tables (see fill_brick_tables)
+  int tab_bounds;                  // the tables hold them
 };
+
+constexpr int kDilated = 15;   // dilated copies
 
 struct LigDev {
   const int32_t* atom_offset;
@@ -51,7 +67,8 @@ struct DockDev {
   int R, A, T, S;
   float delta, clash2;
   float clash_r2;          // (sqrt(clash2) + margin)^2: pairs farther apart on their circles never clash
-  int lazy_clash;          // 1: no pair list, test only the winner of each torsion scan
+  float clash;             // sqrt(clash2), 0 if that is not positive
+  int lazy_clash;          // 1: no clash tests of whole groups, only of samples that beat the best so far
   float c[3];
   const float* restarts;   // [R][12]
   const float* angles;     // [A][2]
@@ -74,38 +91,50 @@ struct RefineDev {
   float* score;
 };
 
-// What differs between sites that share grid dimensions and spacing: the
-// grid copies, the origin (and the nearest-node offsets built from it), the
-// value outside the box and the site centre that placement moves ligands to.
-// Sixteen 32-bit words, read into scalar registers.
-struct SiteGrid {
-  const float* g0;
-  const char* gb;
-  const char* gk;
-  float c0[3];
-  float o[3];
-  float out;
-  float c[3];
+// What a docking wavefront works on: the first kernel argument, or a site's entry
+// in device memory.  The scans read it through this pointer, anew in each scan
+// (uniform scalar loads): held in scalar registers over the whole restart loop,
+// its 80 words would spill into vector lanes and come back through the vector
+// ALU at every use.
+struct DockArgs {
+  GridDev G;
+  LigDev Lg;
+  DockDev D;
 };
+typedef const __attribute__((address_space(4))) DockArgs* ArgsPtr;
+
+template <class T>
+__device__ __forceinline__ T fresh_copy(const __attribute__((address_space(4))) T* p) {
+  asm volatile("" : "+s"(p));   // loaded here
+  T v;
+  __builtin_memcpy(&v, (const T*)p, sizeof v);
+  return v;
+}
+__device__ __forceinline__ GridDev grid_of(ArgsPtr S) { return fresh_copy(&S->G); }
+__device__ __forceinline__ LigDev ligands_of(ArgsPtr S) { return fresh_copy(&S->Lg); }
+__device__ __forceinline__ DockDev dock_of(ArgsPtr S) { return fresh_copy(&S->D); }
 
 // Several docking sites in one launch: grids of identical dimensions and
-// spacing (so one set of brick tables serves all); per site its own final
-// scores and move records.  Items are (site, ligand, chunk), site by site or
-// with the sites interleaved per ligand.
+// spacing (so one set of brick tables serves all); per site its own grid copies,
+// origin, centre, final scores and move records.  Items are (site, ligand,
+// chunk), site by site or with the sites interleaved per ligand.
 struct SitesDev {
-  const SiteGrid* grids;    // device [n_sites]
+  const DockArgs* sites;    // device [n_sites]
   int n_sites;
   int site_major;           // 1: site by site; 0: every site of a ligand in turn
-  size_t scores_stride;     // floats of final scores per site
-  size_t moves_stride;      // move-record entries per site
 };
 
 // Persistent work source of one bucket: items are (ligand of the bucket,
 // chunk of `chunk` restarts), pulled from `cursor` by whole wavefronts.
-// LDS of a docking wavefront, in float4: scan data of 64*nslot atoms, two
-// regions of 64*nslot float4 (risky torsion pairs or staged grid values), the
-// ligand's fragment masks (one 32-bit word per atom).
-constexpr int dock_wave_float4(int nslot) { return 3 * 64 * nslot + 16 * nslot; }
+// LDS of a docking wavefront, in float4: scan data of 64*nslot atoms, risky
+// torsion pairs, data of the moving atoms, the ligand's fragment masks (one
+// 32-bit word per atom).  The two middle regions together hold the bound-pass
+// data of a rotation scan (two float4 per atom) or the staged nodes of a
+// translation scan.  The pair list takes what leaves the instances their
+// occupancy (a list holds at least every pair of one atom).
+constexpr int pair_cap(int nslot) { return nslot == 1 ? 128 : 64 * nslot; }
+constexpr int dock_wave_float4(int nslot) { return 2 * 64 * nslot + pair_cap(nslot) + 16 * nslot; }
+constexpr int stage_floats(int nslot) { return 4 * (pair_cap(nslot) + 64 * nslot); }
 
 struct QueueDev {
   const int32_t* perm;          // ligand ids grouped by bucket
@@ -163,18 +192,31 @@ struct OpAddF {
 
 __device__ __forceinline__ float wave_sum(float v) { return __int_as_float(wave_reduce_i32(__float_as_int(v), OpAddF())); }
 
-// Per-axis byte-offset tables of the brick layout, indexed by padded node
-// coordinate p in [0, n+1]: x (p>>2)*128 + (p&3)*4, y (p>>2)*128*nbx + (p&3)*16,
-// z (p>>1)*128*nbx*nby + (p&1)*64.  Filled by all threads of a block.
+// Per-axis byte-offset tables of the brick layouts, indexed by padded node
+// coordinate p in [0, n+1]; filled by all threads of a block.
+//   grid (4 x 4 x 2 floats), axes x, y, z at tab_base:
+//     (p>>2)*128 + (p&3)*4, (p>>2)*128*nbx + (p&3)*16, (p>>1)*128*nbx*nby + (p&1)*64
+//   dilated planes (8 x 8 of 16 bits): the plane across axis e has first axis
+//     e + 1 and second axis e + 2 (mod 3); first: (p>>3)*128 + (p&7)*2 at tab_p, for
+//     every axis; second: (p>>3)*128*nb8[first] + (p&7)*16 at tab_q[axis]
+//   dilated cubes (4 x 4 x 4 of 16 bits) at tab_c:
+//     (p>>2)*128 + (p&3)*2, (p>>2)*128*nb4x + (p&3)*8, (p>>2)*128*nb4x*nb4y + (p&3)*32
 __device__ __forceinline__ void fill_brick_tables(const GridDev& G, int* tab) {
-  for (int k = threadIdx.x; k < G.tab_len; k += blockDim.x) {
-    int a = k < G.tab_base[1] ? 0 : (k < G.tab_base[2] ? 1 : 2);
-    int p = k - G.tab_base[a];
-    int v;
-    if (a == 0) v = (p >> 2) * 128 + (p & 3) * 4;
-    else if (a == 1) v = (p >> 2) * 128 * G.nb[0] + (p & 3) * 16;
-    else v = (p >> 1) * 128 * G.nb[0] * G.nb[1] + (p & 1) * 64;
-    tab[k] = v;
+  const int longest = max(G.n[0], max(G.n[1], G.n[2])) + 2;
+  for (int p = threadIdx.x; p < longest; p += blockDim.x) {
+    if (G.tab_bounds) tab[G.tab_p + p] = (p >> 3) * 128 + (p & 7) * 2;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if (p >= G.n[a] + 2) continue;
+      tab[G.tab_base[a] + p] = a == 0   ? (p >> 2) * 128 + (p & 3) * 4
+                               : a == 1 ? (p >> 2) * 128 * G.nb[0] + (p & 3) * 16
+                                        : (p >> 1) * 128 * G.nb[0] * G.nb[1] + (p & 1) * 64;
+      if (!G.tab_bounds) continue;
+      tab[G.tab_q[a] + p] = (p >> 3) * 128 * G.nb8[(a + 2) % 3] + (p & 7) * 16;
+      tab[G.tab_c[a] + p] = a == 0   ? (p >> 2) * 128 + (p & 3) * 2
+                            : a == 1 ? (p >> 2) * 128 * G.nb4[0] + (p & 3) * 8
+                                     : (p >> 2) * 128 * G.nb4[0] * G.nb4[1] + (p & 3) * 32;
+    }
   }
 }
 
@@ -185,6 +227,11 @@ __device__ __forceinline__ int mad24(int a, int b, int c) { return __mul24(a, b)
 // scalar base address).
 __device__ __forceinline__ float grid_at(const char* gb, int off) {
   return *reinterpret_cast<const float*>(gb + (uint32_t)off);
+}
+
+// Bound of a dilated copy at a byte offset, in units of bound_scale.
+__device__ __forceinline__ int bound_at(const char* dil, uint32_t off) {
+  return *reinterpret_cast<const int16_t*>(dil + off);
 }
 
 // Order-preserving map of a float to a signed int (total order on non-NaN).
