@@ -186,6 +186,7 @@ __device__ __forceinline__ int wave_reduce_i32(int v, Op op) {
 
 struct OpMax { __device__ int operator()(int a, int b) const { return a > b ? a : b; } };
 struct OpMin { __device__ int operator()(int a, int b) const { return a < b ? a : b; } };
+struct OpAdd { __device__ int operator()(int a, int b) const { return a + b; } };
 struct OpAddF {
   __device__ int operator()(int a, int b) const { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }
 };

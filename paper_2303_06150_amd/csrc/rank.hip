@@ -2,18 +2,27 @@
 // docked ligands' scores): the top m of n groups by each group's best value,
 // equal values ordered by lower group index.
 //
-// Keys.  Group i with best value v gets one 64-bit key: the upper word orders
-// the values (larger value, larger key; -0 counts as +0), the lower word is
+// Keys.  Group i with best value v has a 64-bit key: the upper word orders the
+// values (larger value, larger key; -0 counts as +0), the lower word is
 // 0xFFFFFFFF - i, so equal values rank the lower index first.  Keys are
-// distinct, so "the top m" is a set and no sort stability is needed.
+// distinct, so "the top m" is a set and no sort stability is needed.  Only the
+// upper words are stored; the lower ones follow from the position.
 //
-// Steps.  (1) keys and best members; (2) radix select of the m-th largest key,
-// one byte per pass from the top (histogram of the keys that still match the
-// selected prefix, then one thread walks the 256 bins from the top), stopping as
-// soon as the selected bin holds exactly the keys still needed; (3) compaction
-// of the m keys >= that threshold (wave-aggregated counter); (4) a descending
-// bitonic sort of the m keys, in LDS for m <= 4096, else tile sorts in LDS plus
-// global merge steps; (5) ids, values and members of the sorted keys.
+// Steps.  (1) upper words, with the histogram of their top 11 bits; (2) radix
+// select of the m-th largest key by six digits of 11, 11, 10 bits of each word:
+// every pass first picks the digit's bin from the histogram of the pass before
+// (each block for itself), then counts the next digit of the keys that match,
+// and does nothing once few enough keys are left to finish by comparison;
+// (3) compaction of the keys at or above the last threshold; (4) m <= 4096: the
+// place of each of the at most 4096 candidates is the number of larger ones,
+// counted in LDS, and the result goes straight to its place; larger m: a
+// descending bitonic sort of the m keys (tile sorts in LDS, global merge steps).
+//
+// What bounds it: the launches (nine of 2 to 6 us), then the read of the scores
+// (29 us for 32 MB).  One million groups of eight values, m = 1000, a whole call:
+// 156 us with byte digits (a histogram and a pick launch each, 64-bit keys read
+// up to nine times) and a sort of the candidates by one block, 59 us as it is.
+// At most 4096 groups: one launch.
 #include "lg.h"
 #include "lg_internal.h"
 
@@ -39,88 +48,230 @@ __device__ __forceinline__ float key_value(uint64_t k) {
 
 __device__ __forceinline__ int key_index(uint64_t k) { return (int)(0xFFFFFFFFu - (uint32_t)k); }
 
-// Per group: best value (first member on equal values) and its key.
-__global__ void rank_keys_kernel(const float* score, int n, int group, uint64_t* keys, int32_t* member) {
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += stride) {
-    const float* s = score + i * group;
-    float best = s[0];
-    int bm = 0;
-    for (int q = 1; q < group; ++q)
-      if (s[q] > best) { best = s[q]; bm = q; }
-    keys[i] = rank_key(best, (int)i);
-    member[i] = bm;
-  }
+// Best value of a group and the first member that has it.
+__device__ __forceinline__ float group_best(const float* s, int group, int* member) {
+  float best = s[0];
+  int bm = 0;
+  for (int q = 1; q < group; ++q)
+    if (s[q] > best) { best = s[q]; bm = q; }
+  *member = bm;
+  return best;
 }
+
+// Digits of the 64-bit key from the top: 11, 11, 10 bits of the value word, then
+// of the index word.
+constexpr int kDigits = 6, kBins = 2048;
+__device__ __forceinline__ int digit_shift(int d) { return d == 0 ? 53 : d == 1 ? 42 : d == 2 ? 32 : d == 3 ? 21 : d == 4 ? 10 : 0; }
+__device__ __forceinline__ uint32_t digit_mask(int d) { return d % 3 == 2 ? 1023u : 2047u; }
 
 __global__ void rank_init_kernel(RankState* st, uint32_t* hist, int m) {
-  if (threadIdx.x == 0) {
-    st->prefix = 0;
-    st->mask = 0;
-    st->need = (uint32_t)m;
-    st->done = 0;
-    st->count = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st[0].prefix = 0;
+    st[0].mask = 0;
+    st[0].need = (uint32_t)m;
+    st[0].done = 0;
+    st[0].count = 0;
+    st[kDigits].count = 0;   // candidates
   }
-  hist[threadIdx.x] = 0;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kDigits * kBins; i += gridDim.x * blockDim.x) hist[i] = 0;
 }
 
-// Histogram of byte `shift` of the keys that match the selected prefix.
-__global__ __launch_bounds__(256) void rank_hist_kernel(const uint64_t* keys, int n, const RankState* st,
-                                                        uint32_t* hist, int shift) {
-  if (st->done) return;
-  __shared__ uint32_t lh[256];
-  lh[threadIdx.x] = 0;
+__device__ __forceinline__ void add_bins(const uint32_t* lh, uint32_t* hist) {
   __syncthreads();
-  const uint64_t prefix = st->prefix, mask = st->mask;
+  for (int b = threadIdx.x; b < kBins; b += blockDim.x)
+    if (lh[b]) atomicAdd(&hist[b], lh[b]);
+}
+
+// Value words of all groups and the histogram of their top digit.  A block takes
+// 256 groups at a time: their values are one stretch, read coalesced into LDS
+// (groups of up to kStageGroup values; larger ones are long stretches themselves).
+constexpr int kStageGroup = 24;
+
+__global__ __launch_bounds__(256) void rank_keys_kernel(const float* score, int n, int group, uint32_t* words,
+                                                        uint32_t* hist) {
+  __shared__ uint32_t lh[kBins];
+  __shared__ float vals[256 * kStageGroup];
+  for (int b = threadIdx.x; b < kBins; b += blockDim.x) lh[b] = 0;
+  __syncthreads();
+  const bool stage = group <= kStageGroup;
+  for (long long g0 = blockIdx.x * 256LL; g0 < n; g0 += gridDim.x * 256LL) {
+    const int groups = (int)min(256LL, n - g0);
+    if (stage) {
+      const float* src = score + g0 * group;
+      for (int t = threadIdx.x; t < groups * group; t += 256) vals[t] = src[t];
+      __syncthreads();
+    }
+    if ((int)threadIdx.x < groups) {
+      int member;
+      const float v = stage ? group_best(vals + (int)threadIdx.x * group, group, &member)
+                            : group_best(score + (g0 + threadIdx.x) * group, group, &member);
+      const uint32_t w = (uint32_t)(rank_key(v, 0) >> 32);
+      words[g0 + threadIdx.x] = w;
+      atomicAdd(&lh[w >> 21], 1u);
+    }
+    if (stage) __syncthreads();
+  }
+  add_bins(lh, hist);
+}
+
+// Digit d's bin of the key of rank `need` (counting from the largest) among the
+// keys matching the state's prefix, by all 256 threads of a block: the state
+// with the prefix extended by it.  Done once the keys at or above the extended
+// prefix are at most `room` (m for an exact selection): then those are the
+// candidates.
+__device__ __forceinline__ RankState rank_pick(RankState st, const uint32_t* hist, int d, uint32_t room, uint32_t m) {
+  __shared__ uint32_t above_s[257];
+  __shared__ RankState out;
+  if (st.done) return st;
+  constexpr int PER = kBins / 256;
+  // bins from the top: thread t has bins kBins - 1 - PER t downwards
+  uint32_t mine[PER], sum = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    mine[k] = hist[kBins - 1 - PER * (int)threadIdx.x - k];
+    sum += mine[k];
+  }
+  // exclusive prefix of the sums over the block
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  uint32_t incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o *= 2) {
+    const uint32_t v = __shfl_up(incl, o);
+    if (lane >= o) incl += v;
+  }
+  if (lane == 63) above_s[wave] = incl;
+  __syncthreads();
+  uint32_t above = incl - sum;
+  for (int w = 0; w < wave; ++w) above += above_s[w];
+  if (above < st.need && above + sum >= st.need) {   // exactly one thread
+    int k = 0;
+#pragma unroll
+    for (; k < PER - 1; ++k) {
+      if (above + mine[k] >= st.need) break;
+      above += mine[k];
+    }
+    const uint32_t bin = (uint32_t)(kBins - 1 - PER * (int)threadIdx.x - k);
+    uint32_t held = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) held = q == k ? mine[q] : held;
+    RankState r = st;
+    r.need = st.need - above;
+    r.prefix |= (uint64_t)bin << digit_shift(d);
+    r.mask |= (uint64_t)digit_mask(d) << digit_shift(d);
+    r.done = m - r.need + held <= room ? 1u : 0u;   // larger keys, and those of this bin
+    r.count = 0;
+    out = r;
+  }
+  __syncthreads();
+  return out;
+}
+
+// Digit d - 1 picked, digit d counted among the keys that match it.
+__global__ __launch_bounds__(256) void rank_digit_kernel(const uint32_t* words, int n, RankState* states,
+                                                         uint32_t* hist, int d, uint32_t room, uint32_t m) {
+  __shared__ uint32_t lh[kBins];
+  const RankState st = rank_pick(states[d - 1], hist + (d - 1) * kBins, d - 1, room, m);
+  if (blockIdx.x == 0 && threadIdx.x == 0) states[d] = st;
+  if (st.done) return;
+  for (int b = threadIdx.x; b < kBins; b += blockDim.x) lh[b] = 0;
+  __syncthreads();
+  const int shift = digit_shift(d);
+  const uint32_t bins = digit_mask(d);
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint64_t k = keys[i];
-    if ((k & mask) == prefix) atomicAdd(&lh[(k >> shift) & 255u], 1u);
+    const uint64_t k = ((uint64_t)words[i] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
+    if ((k & st.mask) == st.prefix) atomicAdd(&lh[(uint32_t)(k >> shift) & bins], 1u);
   }
-  __syncthreads();
-  if (lh[threadIdx.x]) atomicAdd(&hist[threadIdx.x], lh[threadIdx.x]);
+  add_bins(lh, hist + d * kBins);
 }
 
-// The bin of the key of rank `need` (counting from the largest) among the keys
-// matching the prefix; extends the prefix by it.  Done once that bin holds
-// exactly the keys still needed: then the threshold is the prefix with zero
-// lower bits, and the keys >= it are the top m.
-__global__ __launch_bounds__(256) void rank_pick_kernel(RankState* st, uint32_t* hist, int shift) {
-  if (threadIdx.x == 0 && !st->done) {
-    uint32_t above = 0;
-    int b = 255;
-    for (; b > 0; --b) {
-      if (above + hist[b] >= st->need) break;
-      above += hist[b];
-    }
-    st->need -= above;
-    st->prefix |= (uint64_t)b << shift;
-    st->mask |= (uint64_t)255u << shift;
-    if (hist[b] == st->need) st->done = 1;
+// The keys at or above the threshold (at most `room`), in any order, and their
+// number; `fill` keys after them set to 0 (for the bitonic sort).  Each block
+// counts the keys of its stretch, takes their places with one addition to the
+// global counter (a contended addition costs about 30 ns) and reads them again.
+__global__ __launch_bounds__(256) void rank_compact_kernel(const uint32_t* words, int n, RankState* states,
+                                                           const uint32_t* hist, uint64_t* cand, uint32_t room,
+                                                           uint32_t m, long long fill) {
+  __shared__ uint32_t taken, base;
+  const RankState st = rank_pick(states[kDigits - 1], hist + (kDigits - 1) * kBins, kDigits - 1, room, m);
+  const uint64_t t = st.prefix;
+  const long long per = ((n + (long long)gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
+  const long long i0 = blockIdx.x * per, i1 = min((long long)n, i0 + per);
+  auto key = [&](long long i) { return ((uint64_t)words[i] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i); };
+  if (threadIdx.x == 0) taken = 0;
+  __syncthreads();
+  uint32_t mine = 0;
+  for (long long i = i0 + threadIdx.x; i < i1; i += 256) mine += key(i) >= t ? 1u : 0u;
+  mine = (uint32_t)wave_reduce_i32((int)mine, OpAdd());
+  if (lane_id() == 0 && mine) atomicAdd(&taken, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    base = taken ? atomicAdd(&states[kDigits].count, taken) : 0;   // zeroed with the histograms
+    taken = 0;
   }
   __syncthreads();
-  hist[threadIdx.x] = 0;
+  for (long long i = i0 + threadIdx.x; i < i1; i += 256) {
+    const uint64_t k = key(i);
+    if (k < t) continue;
+    const uint32_t at = base + atomicAdd(&taken, 1u);
+    if (at < room) cand[at] = k;
+  }
+  for (long long i = m + blockIdx.x * 256LL + threadIdx.x; i < fill; i += gridDim.x * 256LL) cand[i] = 0;
 }
 
-// The keys >= threshold (exactly m of them), in any order; [m, padded) set to 0.
-__global__ __launch_bounds__(256) void rank_compact_kernel(const uint64_t* keys, int n, RankState* st, uint64_t* cand,
-                                                           int m, long long padded) {
-  const uint64_t t = st->prefix;
-  const int lane = lane_id();
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long base = blockIdx.x * (long long)blockDim.x + threadIdx.x - lane; base < n; base += stride) {
-    const long long i = base + lane;
-    const uint64_t k = i < n ? keys[i] : 0;
-    const bool sel = i < n && k >= t;
-    const uint64_t bal = __ballot(sel);
-    if (bal == 0) continue;
-    uint32_t first = 0;
-    if (lane == 0) first = atomicAdd(&st->count, (uint32_t)__popcll(bal));
-    first = __builtin_amdgcn_readfirstlane(first);
-    const uint32_t pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-    if (sel && first + pre < (uint32_t)m) cand[first + pre] = k;
+// Result q: group, value and member of key k.
+__device__ __forceinline__ void rank_store(uint64_t k, int q, const float* score, int n, int group, int32_t* top_idx,
+                                           float* top_score, int32_t* top_member) {
+  const int i = key_index(k);
+  top_idx[q] = i;
+  top_score[q] = key_value(k);
+  if (top_member) {
+    int member = -1;
+    if (i >= 0 && i < n) group_best(score + (long long)i * group, group, &member);
+    top_member[q] = member;
   }
-  for (long long i = m + blockIdx.x * (long long)blockDim.x + threadIdx.x; i < padded; i += stride) cand[i] = 0;
+}
+
+// Places of the `count` keys in LDS by counting the larger ones: the block places
+// kPlaces of them, 16 threads to a key, and stores those of the top m.
+constexpr int kPlaces = 16;
+
+__device__ __forceinline__ void rank_place(const uint64_t* s, int count, const float* score, int n, int group, int m,
+                                           int32_t* top_idx, float* top_score, int32_t* top_member) {
+  const int c = blockIdx.x * kPlaces + ((int)threadIdx.x >> 4), part = threadIdx.x & 15;
+  const uint64_t k = c < count ? s[c] : 0;
+  int larger = 0;
+#pragma unroll 4
+  for (int t = part; t < count; t += 16) larger += s[t] > k ? 1 : 0;
+#pragma unroll
+  for (int o = 1; o < 16; o *= 2) larger += __shfl_xor(larger, o);
+  if (part == 0 && c < count && larger < m) rank_store(k, larger, score, n, group, top_idx, top_score, top_member);
+}
+
+// At most kTile candidates.
+__global__ __launch_bounds__(256) void rank_place_kernel(const uint64_t* cand, const RankState* states,
+                                                         const float* score, int n, int group, int m,
+                                                         int32_t* top_idx, float* top_score, int32_t* top_member) {
+  __shared__ uint64_t s[kTile];
+  const int count = min((int)states[kDigits].count, kTile);
+  if ((int)blockIdx.x * kPlaces >= count) return;
+  for (int t = threadIdx.x; t < count; t += 256) s[t] = cand[t];
+  __syncthreads();
+  rank_place(s, count, score, n, group, m, top_idx, top_score, top_member);
+}
+
+// The whole ranking of at most kTile groups in one launch: every block takes all
+// keys from the scores (n * group values out of the L2, a few microseconds, where
+// each launch of the selection costs about as much) and places kPlaces.
+__global__ __launch_bounds__(256) void rank_small_kernel(const float* score, int n, int group, int m,
+                                                         int32_t* top_idx, float* top_score, int32_t* top_member) {
+  __shared__ uint64_t s[kTile];
+  for (int t = threadIdx.x; t < n; t += 256) {
+    int member;
+    s[t] = rank_key(group_best(score + (long long)t * group, group, &member), t);
+  }
+  __syncthreads();
+  rank_place(s, n, score, n, group, m, top_idx, top_score, top_member);
 }
 
 // One compare-exchange of the descending bitonic network: stage k, distance j.
@@ -162,15 +313,10 @@ __global__ __launch_bounds__(256) void rank_merge_kernel(uint64_t* a, long long 
   }
 }
 
-__global__ void rank_out_kernel(const uint64_t* sorted, const int32_t* member, int n, int m, int32_t* top_idx,
-                                float* top_score, int32_t* top_member) {
+__global__ void rank_out_kernel(const uint64_t* sorted, const float* score, int n, int group, int m,
+                                int32_t* top_idx, float* top_score, int32_t* top_member) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= m) return;
-  const uint64_t k = sorted[q];
-  const int i = key_index(k);
-  top_idx[q] = i;
-  top_score[q] = key_value(k);
-  if (top_member) top_member[q] = (i >= 0 && i < n) ? member[i] : -1;
+  if (q < m) rank_store(sorted[q], q, score, n, group, top_idx, top_score, top_member);
 }
 
 long long pow2_at_least(long long m) {
@@ -181,9 +327,10 @@ long long pow2_at_least(long long m) {
 
 constexpr size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
+// Candidates: kTile, or the power of two that the bitonic sort needs.
 constexpr size_t scratch_bytes(size_t n, size_t pow2_m) {
-  return up256(sizeof(RankState)) + up256(256 * sizeof(uint32_t)) + up256(n * 8) + up256(n * 4) +
-         up256(pow2_m * 8);
+  return up256((kDigits + 1) * sizeof(RankState)) + up256(kDigits * kBins * sizeof(uint32_t)) + up256(n * 4) +
+         up256((pow2_m > (size_t)kTile ? pow2_m : (size_t)kTile) * 8);
 }
 
 // Fixed device scratch of lg_rank_static, sized for its largest accepted call
@@ -225,39 +372,47 @@ hipError_t rank_static_scratch(void** out, size_t* bytes) {
 hipError_t launch_rank(const float* score, int n, int group, int m, void* work, int32_t* top_idx,
                        float* top_score, int32_t* top_member, hipStream_t st) {
   if (n <= 0 || m <= 0) return hipSuccess;
-  auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  if (n <= kTile && group <= 64) {   // a block's share of larger groups would outlast the launches it saves
+    hipLaunchKernelGGL(rank_small_kernel, dim3((n + kPlaces - 1) / kPlaces), dim3(256), 0, st, score, n, group, m, top_idx,
+                       top_score, top_member);
+    return hipGetLastError();
+  }
   char* w = (char*)work;
-  RankState* state = (RankState*)w;
-  w += up(sizeof(RankState));
+  RankState* states = (RankState*)w;
+  w += up256((kDigits + 1) * sizeof(RankState));
   uint32_t* hist = (uint32_t*)w;
-  w += up(256 * sizeof(uint32_t));
-  uint64_t* keys = (uint64_t*)w;
-  w += up((size_t)n * 8);
-  int32_t* member = (int32_t*)w;
-  w += up((size_t)n * 4);
+  w += up256(kDigits * kBins * sizeof(uint32_t));
+  uint32_t* words = (uint32_t*)w;
+  w += up256((size_t)n * 4);
   uint64_t* cand = (uint64_t*)w;
   const long long padded = pow2_at_least(m);
-  const int blocks = (int)std::min<long long>(((long long)n + 255) / 256, 2048);
-  hipLaunchKernelGGL(rank_keys_kernel, dim3(blocks), dim3(256), 0, st, score, n, group, keys, member);
-  hipLaunchKernelGGL(rank_init_kernel, dim3(1), dim3(256), 0, st, state, hist, m);
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(rank_hist_kernel, dim3(blocks), dim3(256), 0, st, keys, n, state, hist, shift);
-    hipLaunchKernelGGL(rank_pick_kernel, dim3(1), dim3(256), 0, st, state, hist, shift);
+  // m <= kTile: a quarter more candidates than wanted will do (placing them costs
+  // less than another digit); more: exactly the top m
+  const bool one_tile = m <= kTile;
+  const uint32_t room = one_tile ? (uint32_t)std::min(kTile, m + std::max(256, m / 4)) : (uint32_t)m;
+  // at most two blocks per compute unit (each adds its histogram to the global
+  // one), at least four groups per thread
+  const int blocks = (int)std::max<long long>(1, std::min<long long>(((long long)n + 1023) / 1024, 512));
+  hipLaunchKernelGGL(rank_init_kernel, dim3(12), dim3(256), 0, st, states, hist, m);
+  hipLaunchKernelGGL(rank_keys_kernel, dim3(blocks), dim3(256), 0, st, score, n, group, words, hist);
+  for (int d = 1; d < kDigits; ++d)
+    hipLaunchKernelGGL(rank_digit_kernel, dim3(blocks), dim3(256), 0, st, words, n, states, hist, d, room, (uint32_t)m);
+  hipLaunchKernelGGL(rank_compact_kernel, dim3(std::min(blocks, 256)), dim3(256), 0, st, words, n, states, hist, cand, room,
+                     (uint32_t)m, one_tile ? 0LL : padded);
+  if (one_tile) {
+    hipLaunchKernelGGL(rank_place_kernel, dim3((room + kPlaces - 1) / kPlaces), dim3(256), 0, st, cand, states, score, n, group, m, top_idx,
+                       top_score, top_member);
+    return hipGetLastError();
   }
-  hipLaunchKernelGGL(rank_compact_kernel, dim3(blocks), dim3(256), 0, st, keys, n, state, cand, m, padded);
-  if (padded <= kTile) {
-    hipLaunchKernelGGL(rank_tile_kernel, dim3(1), dim3(kSortThreads), 0, st, cand, (int)padded, 2LL, padded);
-  } else {
-    const int tiles = (int)(padded / kTile);
-    const int mblocks = (int)std::min<long long>(padded / 2 / 256, 4096);
-    hipLaunchKernelGGL(rank_tile_kernel, dim3(tiles), dim3(kSortThreads), 0, st, cand, kTile, 2LL, (long long)kTile);
-    for (long long k = 2LL * kTile; k <= padded; k *= 2) {
-      for (long long j = k / 2; j >= kTile; j /= 2)
-        hipLaunchKernelGGL(rank_merge_kernel, dim3(mblocks), dim3(256), 0, st, cand, padded, k, j);
-      hipLaunchKernelGGL(rank_tile_kernel, dim3(tiles), dim3(kSortThreads), 0, st, cand, kTile, k, k);
-    }
+  const int tiles = (int)(padded / kTile);
+  const int mblocks = (int)std::min<long long>(padded / 2 / 256, 4096);
+  hipLaunchKernelGGL(rank_tile_kernel, dim3(tiles), dim3(kSortThreads), 0, st, cand, kTile, 2LL, (long long)kTile);
+  for (long long k = 2LL * kTile; k <= padded; k *= 2) {
+    for (long long j = k / 2; j >= kTile; j /= 2)
+      hipLaunchKernelGGL(rank_merge_kernel, dim3(mblocks), dim3(256), 0, st, cand, padded, k, j);
+    hipLaunchKernelGGL(rank_tile_kernel, dim3(tiles), dim3(kSortThreads), 0, st, cand, kTile, k, k);
   }
-  hipLaunchKernelGGL(rank_out_kernel, dim3((m + 255) / 256), dim3(256), 0, st, cand, member, n, m, top_idx,
+  hipLaunchKernelGGL(rank_out_kernel, dim3((m + 255) / 256), dim3(256), 0, st, cand, score, n, group, m, top_idx,
                      top_score, top_member);
   return hipGetLastError();
 }
