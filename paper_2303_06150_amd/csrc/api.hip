@@ -22,14 +22,14 @@
 namespace lg {
 hipError_t launch_dock_plain(int nslot, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D, int lig,
                              hipStream_t st);
-hipError_t launch_dock_bucket(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
-                              const QueueDev& Q, hipStream_t st);
+hipError_t launch_dock_bucket(int nslot, bool lone, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
+                              const DockDev& D, const QueueDev& Q, hipStream_t st);
 size_t dock_lds_bytes(int nslot, int wpb, int tab_len, int angles);
-hipError_t occupancy_dock_bucket(int nslot, int wpb, int tab_len, int angles, int* blocks_per_cu);
+hipError_t occupancy_dock_bucket(int nslot, bool lone, int wpb, int tab_len, int angles, int* blocks_per_cu);
 hipError_t launch_valu_probe(int kind, int blocks, int iters, float* out, hipStream_t st);
 hipError_t launch_dock_sites(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
                              const QueueDev& Q, const SitesDev& Sd, hipStream_t st);
-hipError_t attributes_dock_bucket(int nslot, hipFuncAttributes* attr);
+hipError_t attributes_dock_bucket(int nslot, bool lone, hipFuncAttributes* attr);
 hipError_t launch_topk(int nslot, const LigDev& Lg, const DockDev& D, int n, int k, float* score, int32_t* rid,
                        float* ox, float* oy, float* oz, float* all_scores, float* pivot, hipStream_t st);
 hipError_t launch_score(const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
@@ -508,18 +508,23 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
   // every atom cluster must fit its kernel instance: the last one takes the rest
   cb.atom[cb.na - 1] = LG_MAX_ATOMS;
 
+  // at most two wavefronts per SIMD (four SIMDs per compute unit): the instance
+  // with more fetches in flight, one wavefront per block, so that all compute
+  // units' caches take part (one ligand of 256 restarts: 256 blocks, not 64)
+  const long long items = (long long)n * R;
+  const bool lone = items <= 8LL * p->cus;
   auto plan = [&](std::vector<lg_bucket_stat>& launches) -> lg_status {
     // Eq. 1: resident blocks per CU of each instance give the persistent grid
     for (int ca = cb.na - 1; ca >= 0; --ca) {
       // the instance holds the cluster's largest possible ligand: its bound, or the
       // batch's largest ligand if that is smaller (the last bound is LG_MAX_ATOMS)
       const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
-      const int wpb = tu.waves_per_block[nslot - 1];
+      const int wpb = lone ? 1 : tu.waves_per_block[nslot - 1];
       int bpc = 0;
-      LG_HIP(lg::occupancy_dock_bucket(nslot, wpb, p->grid.tab_len, D.A, &bpc));
+      LG_HIP(lg::occupancy_dock_bucket(nslot, lone, wpb, p->grid.tab_len, D.A, &bpc));
       if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots, %d samples/lane) cannot be resident", nslot, spl);
       hipFuncAttributes attr;
-      LG_HIP(lg::attributes_dock_bucket(nslot, &attr));
+      LG_HIP(lg::attributes_dock_bucket(nslot, lone, &attr));
       for (int cr = cb.nr - 1; cr >= 0; --cr) {
         lg_bucket_stat b;
         b.bucket = ca * cb.nr + cr;
@@ -531,7 +536,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
         b.vgprs = attr.numRegs;
         b.lds_bytes = (int32_t)lg::dock_lds_bytes(nslot, wpb, p->grid.tab_len, D.A);
         b.blocks_per_cu = bpc;
-        b.blocks = bpc * p->cus * tu.grid_scale;
+        b.blocks = (int)std::min<long long>((long long)bpc * p->cus * tu.grid_scale, (items + wpb - 1) / wpb);
         b.ligands = -1;
         b.ms = -1.f;
         launches.push_back(b);
@@ -559,7 +564,9 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
       const lg_bucket_stat& b = launches[l];
       if (timed) e = hipEventRecord(p->events[1 + 2 * l], cs);
       lg::QueueDev Q{perm, start, cursors, b.bucket, tu.restart_chunk};
-      if (e == hipSuccess) e = lg::launch_dock_bucket(b.slots, b.waves_per_block, b.blocks, p->grid, Lg, D, Q, cs);
+      const int ca = b.bucket / cb.nr;
+      if (e == hipSuccess && (ca == 0 || cb.atom[ca - 1] < max_atoms))   // else no ligand of the batch is that large
+        e = lg::launch_dock_bucket(b.slots, lone, b.waves_per_block, b.blocks, p->grid, Lg, D, Q, cs);
       if (e == hipSuccess && timed) e = hipEventRecord(p->events[2 + 2 * l], cs);
     }
     if (e == hipSuccess && timed) e = hipEventRecord(p->events[1 + 2 * nl], cs);
@@ -968,8 +975,9 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
     const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
     const int wpb = tu.waves_per_block[nslot - 1];
     int bpc = 0;
-    LG_HIP(lg::occupancy_dock_bucket(nslot, wpb, p->grid.tab_len, D.A, &bpc));
+    LG_HIP(lg::occupancy_dock_bucket(nslot, false, wpb, p->grid.tab_len, D.A, &bpc));
     if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots) cannot be resident", nslot);
+    if (ca > 0 && cb.atom[ca - 1] >= max_atoms) continue;   // no ligand of the batch is that large
     for (int cr = cb.nr - 1; cr >= 0; --cr) {
       lg::QueueDev Q{perm, start, cursors, ca * cb.nr + cr, tu.restart_chunk};
       LG_HIP(lg::launch_dock_sites(nslot, wpb, bpc * p->cus * tu.grid_scale, p->grid, Lg, D, Q, Sd, st));

@@ -25,6 +25,7 @@
 // the final trilinear sum runs in atom order.
 #include "lg_device.h"
 
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -37,13 +38,13 @@ struct PoseReg {
 };
 
 // ---- moves: the selected sample of a scan applied to the pose ----------------
-// Rotation by sample j, (cos, sin) = ang[j], about lab axis E through the pivot.
+// Rotation by sample j, (cos, sin) = cs, about lab axis E through the pivot.
 template <int NSLOT, int E>
-__device__ __forceinline__ void apply_rot(const float2* ang, PoseReg<NSLOT>& p, int j) {
+__device__ __forceinline__ void apply_rot(float2 cs, PoseReg<NSLOT>& p, int j) {
   constexpr int P = (E + 1) % 3, Q = (E + 2) % 3;
   if (j == 0) return;
   const float pP = p.piv[P], pQ = p.piv[Q];
-  const float c = ang[j].x, sn = ang[j].y;
+  const float c = cs.x, sn = cs.y;
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
     float vp = p.x[P][s] - pP, vq = p.x[Q][s] - pQ;
@@ -75,11 +76,12 @@ struct BondAxis {
 };
 
 template <int NSLOT>
-__device__ __forceinline__ BondAxis bond_axis(const LigDev& Lg, const PoseReg<NSLOT>& p, int toff, int k) {
+__device__ __forceinline__ BondAxis bond_axis(uint32_t ab, float inv_len, const PoseReg<NSLOT>& p, int k) {
   BondAxis A;
-  A.a = __builtin_amdgcn_readfirstlane(Lg.tors_atoms[2 * (toff + k)]);
-  A.b = __builtin_amdgcn_readfirstlane(Lg.tors_atoms[2 * (toff + k) + 1]);
-  const float il = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Lg.inv_len[toff + k])));
+  const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)ab, k);
+  A.a = (int)(v & 0xFFFFu);
+  A.b = (int)(v >> 16);
+  const float il = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv_len), k));
   A.xa = atom_value(p.x[0], A.a);
   A.ya = atom_value(p.x[1], A.a);
   A.za = atom_value(p.x[2], A.a);
@@ -335,7 +337,7 @@ __device__ __forceinline__ int node_index(In, float f, float fn) {
 // lookup of 16 bits, in bricks of the rotation plane.  About a third of the groups
 // survive (240 k scans of mixed ligands: 0.67, 0.34, 0.23 in sweeps 1, 2, 3),
 // 2.6, 1.8 and 1.4 passes of 64 samples instead of 4.
-template <int NSLOT, int E>
+template <int NSLOT, int E, int U>
 __device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, float4* scr, float4* aux,
                                         const Samples& sm, const int* tab) {
   const GridDev G = grid_of(S);
@@ -385,7 +387,7 @@ __device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, flo
     const char* dil = G.dil;
     const int* dP = tab + G.tab_p + 1;
     const int* dQ = tab + G.tab_q[Q] + 1;
-    bound = upper_bound(G, N, scan_sum<4>(inside, 0, N, [&](auto in, int t) {
+    bound = upper_bound(G, N, scan_sum<U>(inside, 0, N, [&](auto in, int t) {
       const float4 k = aux[2 * t];
       const uint32_t part = reinterpret_cast<const uint32_t*>(aux + 2 * t + 1)[0];
       const int ip = node_index(in, fmaf(c, k.x, fmaf(-sn, k.y, k.z)), fnP);
@@ -397,7 +399,7 @@ __device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, flo
       groups_above(bound, s0, sm.nga), bound, sm.GA, sm.A, s0, [](int pos) { return pos; },
       [&](int js) {
         const float2 cs = sm.ang[js];
-        return scan_sum<4>(inside, 0.f, N, [&](auto in, int t) {
+        return scan_sum<U>(inside, 0.f, N, [&](auto in, int t) {
           const float4 d = scr[t];
           const float np = fmaf(cs.x, d.x, -(cs.y * d.y));
           const float nq = fmaf(cs.y, d.x, cs.x * d.y);
@@ -407,7 +409,7 @@ __device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, flo
         });
       },
       [](int, bool) { return false; });
-  apply_rot<NSLOT, E>(sm.ang, p, j);
+  apply_rot<NSLOT, E>(sm.ang[j], p, j);
   wave_sync();
   return j;
 }
@@ -444,7 +446,7 @@ __device__ __forceinline__ float larger(float a, float b) {
 // Runs longer than a wavefront (very wide translation ranges) fall back to
 // direct gathers of every sample, and so does STAGE = false (the plain launch,
 // where a lone wavefront per SIMD would wait on every group's nodes).
-template <int NSLOT, int E, bool STAGE>
+template <int NSLOT, int E, bool STAGE, int U>
 __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, float4* scr, float* stage,
                                           const Samples& sm, const int* tab) {
   const GridDev G = grid_of(S);
@@ -490,7 +492,7 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
         all, __builtin_inff(), sm.GT, D.T, 0.f, index,
         [&](int js) {
           const float d = displacement(js);
-          return scan_sum<4>(inside, 0.f, N, [&](auto in, int t) {
+          return scan_sum<U>(inside, 0.f, N, [&](auto in, int t) {
             const float4 k = scr[t];
             return grid_at(gk, __float_as_int(k.y) + boff(tE, node_index(in, fmaf(k.x + d, ih, cE), fnE)));
           });
@@ -564,7 +566,7 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
           for (int t0 = 0; t0 < N; t0 += room) {
             const int t1 = min(N, t0 + room);
             if (!once) fill(t0, t1);
-            acc = scan_sum<4>(inside, acc, t1 - t0, [&](auto in, int t) { return lds_load(place(in, scr[t0 + t], d)); });
+            acc = scan_sum<U>(inside, acc, t1 - t0, [&](auto in, int t) { return lds_load(place(in, scr[t0 + t], d)); });
           }
           return acc;
         },
@@ -600,8 +602,8 @@ __device__ __forceinline__ float vmin(float a, float b) {
 // groups survive (sweeps 1, 2, 3) against 0.65, 0.46, 0.40 without it; 1.3, 1.1,
 // 1.03 passes of 64 samples instead of 4.  The exact pair tests then run only
 // for samples that beat the best so far.
-template <int NSLOT>
-__device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, int toff, int k, const uint32_t* mkl,
+template <int NSLOT, int U>
+__device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, uint32_t ab, float inv_len, int k, const uint32_t* mkl,
                                          float4* scr, float4* pairs, const Samples& sm, const int* tab) {
   const GridDev G = grid_of(S);
   const DockDev D = dock_of(S);
@@ -611,7 +613,7 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, in
   uint32_t mk[NSLOT];   // fragment masks of this lane's atoms, kept in LDS between scans
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) mk[s] = mkl[s * 64 + lane];
-  const BondAxis A = bond_axis(ligands_of(S), p, toff, k);
+  const BondAxis A = bond_axis(ab, inv_len, p, k);
   const int a = A.a, b = A.b;
   const float xa = in_vgpr(A.xa), ya = in_vgpr(A.ya), za = in_vgpr(A.za), ux = A.ux, uy = A.uy, uz = A.uz;
   const float ih = in_vgpr(G.inv_h), clash2 = D.clash2;
@@ -769,7 +771,7 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, in
         const float2 cs = sm.ang[js];
         float M[9];
         torsion_matrix(ux, uy, uz, cs.x, cs.y, M);
-        return scan_sum<2>(inside, 0.f, m, [&](auto in, int t) {
+        return scan_sum<U>(inside, 0.f, m, [&](auto in, int t) {
           const float4 v = scr[t];
           float y0, y1, y2;
           mat_apply(M, v.x, v.y, v.z, y0, y1, y2);
@@ -823,6 +825,8 @@ struct LigReg {
   int N, K, abase, toff;
   uint32_t mk[NSLOT];
   float P0[3];
+  uint32_t ab;   // lane k: bond k's atoms, a | b << 16, and its inverse length (read
+  float il;      // back with readlane: a load per torsion scan would wait on the L2)
 };
 
 template <int NSLOT>
@@ -840,6 +844,8 @@ __device__ void load_ligand(const LigDev& Lg, int lig, LigReg<NSLOT>& L) {
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) L.P0[c] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Lg.ref[3 * lig + c])));
+  L.ab = lane < L.K ? (uint32_t)Lg.tors_atoms[2 * (L.toff + lane)] | (uint32_t)Lg.tors_atoms[2 * (L.toff + lane) + 1] << 16 : 0u;
+  L.il = lane < L.K ? Lg.inv_len[L.toff + lane] : 0.f;
 }
 
 // The fragment masks of the ligand's atoms into the wavefront's LDS: read by
@@ -903,7 +909,9 @@ struct BlockLds {
 };
 
 // One restart: placement, S sweeps, final trilinear score, outputs.
-template <int NSLOT, bool STAGE = true>
+// U: values in flight per buffer of the scans' sums (and half of it in the torsion
+// scans, whose fragments are small).
+template <int NSLOT, bool STAGE, int U>
 __device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const LigReg<NSLOT>& L, int lig, int r,
                                              const BlockLds& B) {
   const int lane = lane_id();
@@ -914,12 +922,12 @@ __device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const
   float* stage = reinterpret_cast<float*>(B.cand);
   for (int sw = 0; sw < sweeps; ++sw) {
     int j[6];
-    j[0] = rot_scan<NSLOT, 0>(S, p, N, B.scr, B.cand, sm, B.tab);
-    j[1] = rot_scan<NSLOT, 1>(S, p, N, B.scr, B.cand, sm, B.tab);
-    j[2] = rot_scan<NSLOT, 2>(S, p, N, B.scr, B.cand, sm, B.tab);
-    j[3] = trans_scan<NSLOT, 0, STAGE>(S, p, N, B.scr, stage, sm, B.tab);
-    j[4] = trans_scan<NSLOT, 1, STAGE>(S, p, N, B.scr, stage, sm, B.tab);
-    j[5] = trans_scan<NSLOT, 2, STAGE>(S, p, N, B.scr, stage, sm, B.tab);
+    j[0] = rot_scan<NSLOT, 0, U>(S, p, N, B.scr, B.cand, sm, B.tab);
+    j[1] = rot_scan<NSLOT, 1, U>(S, p, N, B.scr, B.cand, sm, B.tab);
+    j[2] = rot_scan<NSLOT, 2, U>(S, p, N, B.scr, B.cand, sm, B.tab);
+    j[3] = trans_scan<NSLOT, 0, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
+    j[4] = trans_scan<NSLOT, 1, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
+    j[5] = trans_scan<NSLOT, 2, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
     const DockDev D = dock_of(S);
     uint16_t* mrow = move_record(D, lig, L.toff, L.K, r) + (size_t)sw * (6 + L.K);
     int16_t* trow = D.trace ? D.trace + (((size_t)lig * D.R + r) * (size_t)sweeps + sw) * D.trace_w : nullptr;
@@ -932,7 +940,7 @@ __device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const
       }
     }
     for (int k = 0; k < L.K; ++k) {
-      const int jk = tors_scan<NSLOT>(S, p, N, L.toff, k, B.mkl, B.scr, B.cand, sm, B.tab);
+      const int jk = tors_scan<NSLOT, U / 2>(S, p, N, L.ab, L.il, k, B.mkl, B.scr, B.cand, sm, B.tab);
       if (lane == 0) {
         mrow[6 + k] = (uint16_t)jk;
         if (trow) trow[6 + k] = (int16_t)jk;
@@ -957,30 +965,40 @@ __device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const
 }
 
 // The pose of restart r after its recorded moves: placement, then every
-// sweep's rotations, translations and torsions with the selected samples.
+// sweep's rotations, translations and torsions with the selected samples.  A
+// sweep's record is one load (lane q: entry q) and one more for the (cos, sin)
+// of its samples; the moves themselves touch no memory.
 template <int NSLOT>
 __device__ void replay_restart(const LigDev& Lg, const DockDev& D, const LigReg<NSLOT>& L, int lig, int r,
                                PoseReg<NSLOT>& p) {
   place_pose(Lg, D, L, r, p);
-  const float2* ang = reinterpret_cast<const float2*>(D.angles);
+  const int lane = lane_id();
   const uint16_t* mrec = move_record(D, lig, L.toff, L.K, r);
-  // recorded indices are below A (rotations, torsions) and T (translations); the
-  // clamps only keep table reads in range
-  const int amax = D.A - 1, tmax = D.T - 1;
   for (int sw = 0; sw < D.S; ++sw) {
     const uint16_t* mrow = mrec + (size_t)sw * (6 + L.K);
-    apply_rot<NSLOT, 0>(ang, p, min((int)__builtin_amdgcn_readfirstlane(mrow[0]), amax));
-    apply_rot<NSLOT, 1>(ang, p, min((int)__builtin_amdgcn_readfirstlane(mrow[1]), amax));
-    apply_rot<NSLOT, 2>(ang, p, min((int)__builtin_amdgcn_readfirstlane(mrow[2]), amax));
-    apply_trans<NSLOT, 0>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[3]), tmax));
-    apply_trans<NSLOT, 1>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[4]), tmax));
-    apply_trans<NSLOT, 2>(D, p, min((int)__builtin_amdgcn_readfirstlane(mrow[5]), tmax));
+    // recorded indices are below A (rotations, torsions) and T (translations); the
+    // clamps only keep table reads in range
+    const bool shift = lane >= 3 && lane < 6;
+    const int mine = lane < 6 + L.K ? min((int)mrow[lane], (shift ? D.T : D.A) - 1) : 0;
+    const int jt = shift ? 0 : mine;
+    const float c = D.angles[2 * jt], sn = D.angles[2 * jt + 1];
+    auto entry = [&](int q) { return __builtin_amdgcn_readlane(mine, q); };
+    auto turn = [&](int q) {
+      return make_float2(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), q)),
+                         __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sn), q)));
+    };
+    apply_rot<NSLOT, 0>(turn(0), p, entry(0));
+    apply_rot<NSLOT, 1>(turn(1), p, entry(1));
+    apply_rot<NSLOT, 2>(turn(2), p, entry(2));
+    apply_trans<NSLOT, 0>(D, p, entry(3));
+    apply_trans<NSLOT, 1>(D, p, entry(4));
+    apply_trans<NSLOT, 2>(D, p, entry(5));
     for (int k = 0; k < L.K; ++k) {
-      const int j = min((int)__builtin_amdgcn_readfirstlane(mrow[6 + k]), amax);
-      if (j == 0) continue;
-      const BondAxis A = bond_axis(Lg, p, L.toff, k);
+      if (entry(6 + k) == 0) continue;
+      const BondAxis A = bond_axis(L.ab, L.il, p, k);
+      const float2 cs = turn(6 + k);
       float Mj[9];
-      torsion_matrix(A.ux, A.uy, A.uz, D.angles[2 * j], D.angles[2 * j + 1], Mj);
+      torsion_matrix(A.ux, A.uy, A.uz, cs.x, cs.y, Mj);
       bool mv[NSLOT];
       moving_atoms(L.mk, L.N, k, A.b, mv);
       apply_tors(p, A, Mj, mv);
@@ -1021,15 +1039,20 @@ __global__ __launch_bounds__(256) void dock_plain_kernel(DockArgs X, int lig) {
   store_masks(L, B.mkl);
   // one wavefront per restart: the staged translation scan's read-then-use of
   // each group's nodes would expose their latency, so the gathers stay direct
-  dock_restart<NSLOT, false>(kernel_args(), sm, L, lig, r, B);
+  dock_restart<NSLOT, false, 4>(kernel_args(), sm, L, lig, r, B);
 }
 
 // Bucketed method: persistent; wavefronts pull (ligand, restart chunk) items of
 // one size bucket from an atomic cursor until the bucket is drained.  Occupancy
-// target per instance (wavefronts per SIMD), chosen by measurement: the register
-// budget it implies makes the compiler spill a few values to scratch, which
-// costs less than the latency the extra wavefronts hide.
+// target per instance (wavefronts per SIMD), chosen by measurement: 8 000 mixed
+// ligands take 163 ms at 5 per SIMD (96 VGPRs), 166 at 6, 174 at 7.
 constexpr int bucket_waves_per_simd(int nslot) { return nslot == 1 ? 5 : 4; }
+
+// LONE: the instance for launches of at most two wavefronts per SIMD, where a
+// wavefront waits for each of its fetches alone: more of them in flight, in the
+// registers that nobody else needs.
+template <bool LONE>
+constexpr int in_flight() { return LONE ? 8 : 4; }
 
 // Restarts per work item: the tuning's chunk, or fewer when the launch would
 // have less than 16 items per wavefront.  A longer chunk saves ligand loads (a
@@ -1040,8 +1063,8 @@ __device__ __forceinline__ int restart_chunk(int chunk, long long restarts, int 
   return share < 1 ? 1 : share < chunk ? (int)share : chunk;
 }
 
-template <int NSLOT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bucket_waves_per_simd(NSLOT))))
+template <int NSLOT, bool LONE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LONE ? 2 : bucket_waves_per_simd(NSLOT))))
 void dock_bucket_kernel(DockArgs X, QueueDev Q) {
   extern __shared__ float4 lds[];
   const int b0 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket]);
@@ -1075,7 +1098,7 @@ void dock_bucket_kernel(DockArgs X, QueueDev Q) {
       for (int r = r0 + lane; r < r1; r += 64) X.D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
       continue;
     }
-    for (int r = r0; r < r1; ++r) dock_restart<NSLOT>(kernel_args(), sm, L, lig, r, B);
+    for (int r = r0; r < r1; ++r) dock_restart<NSLOT, true, in_flight<LONE>()>(kernel_args(), sm, L, lig, r, B);
   }
 }
 
@@ -1129,26 +1152,20 @@ void dock_sites_kernel(DockArgs X, QueueDev Q, SitesDev Sd) {
       for (int r = r0 + lane; r < r1; r += 64) S->D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
       continue;
     }
-    for (int r = r0; r < r1; ++r) dock_restart<NSLOT>(S, sm, L, lig, r, B);
+    for (int r = r0; r < r1; ++r) dock_restart<NSLOT, true, 4>(S, sm, L, lig, r, B);
   }
 }
 
-// Per-ligand top-k over restarts (score descending, equal scores: lower r);
-// the kept poses and pivots rebuilt from their recorded moves.  One wavefront
-// per ligand.
-template <int NSLOT>
-__global__ __launch_bounds__(256) void topk_kernel(LigDev Lg, DockDev D, int n, int k, float* score,
-                                                    int32_t* rid, float* ox, float* oy, float* oz,
-                                                    float* all_scores, float* opiv) {
+// Per-ligand top-k over restarts (score descending, equal scores: lower r).  One
+// wavefront per ligand.
+__global__ __launch_bounds__(256) void topk_kernel(DockDev D, int n, int k, float* score, int32_t* rid,
+                                                   float* all_scores) {
   const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id();
   const int lig = blockIdx.x * nwaves + wave;
   if (lig >= n) return;
   const float* fs = D.final_scores + (size_t)lig * D.R;
   if (all_scores)
     for (int r = lane; r < D.R; r += 64) all_scores[(size_t)lig * D.R + r] = fs[r];
-  LigReg<NSLOT> L;
-  load_ligand(Lg, lig, L);
-  if (L.N > 64 * NSLOT) return;   // cannot happen: the instance is sized for the largest ligand
   int pk = INT_MAX, pr = -1;   // previous selection (key, r)
   for (int qi = 0; qi < k; ++qi) {
     int best = INT_MIN, br = INT_MAX;
@@ -1165,8 +1182,25 @@ __global__ __launch_bounds__(256) void topk_kernel(LigDev Lg, DockDev D, int n, 
       score[(size_t)lig * k + qi] = fs[rs];
       rid[(size_t)lig * k + qi] = rs;
     }
+  }
+}
+
+// The kept poses and pivots rebuilt from their recorded moves.  One wavefront per
+// pose: a replay is a chain of dependent moves, so the poses of a ligand side by
+// side take the time of one (64 ligands, 32 kept poses: 175 us one after another).
+template <int NSLOT>
+__global__ __launch_bounds__(256) void replay_kernel(LigDev Lg, DockDev D, int n, int k, const int32_t* rid, float* ox,
+                                                     float* oy, float* oz, float* opiv) {
+  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id();
+  for (long long w = (long long)blockIdx.x * nwaves + wave; w < (long long)n * k; w += (long long)gridDim.x * nwaves) {
+    const int lig = __builtin_amdgcn_readfirstlane((int)(w / k));
+    const int qi = __builtin_amdgcn_readfirstlane((int)(w - (long long)lig * k));
+    LigReg<NSLOT> L;
+    load_ligand(Lg, lig, L);
+    if (L.N > 64 * NSLOT) continue;   // cannot happen: the instance is sized for the largest ligand
+    const int r = min(max(__builtin_amdgcn_readfirstlane(rid[w]), 0), D.R - 1);
     PoseReg<NSLOT> p;
-    replay_restart(Lg, D, L, lig, rs, p);
+    replay_restart(Lg, D, L, lig, r, p);
     const size_t dst = (size_t)k * L.abase + (size_t)qi * L.N;
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) {
@@ -1178,7 +1212,7 @@ __global__ __launch_bounds__(256) void topk_kernel(LigDev Lg, DockDev D, int n, 
       }
     }
     const float pv = lane == 0 ? p.piv[0] : lane == 1 ? p.piv[1] : p.piv[2];
-    if (opiv && lane < 3) opiv[((size_t)lig * k + qi) * 3 + lane] = pv;
+    if (opiv && lane < 3) opiv[(size_t)w * 3 + lane] = pv;
   }
 }
 
@@ -1207,12 +1241,13 @@ hipError_t launch_dock_plain(int nslot, int wpb, const GridDev& G, const LigDev&
 #undef CALL
 }
 
-hipError_t launch_dock_bucket(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
-                              const QueueDev& Q, hipStream_t st) {
+hipError_t launch_dock_bucket(int nslot, bool lone, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
+                              const DockDev& D, const QueueDev& Q, hipStream_t st) {
 #define CALL(NS)                                                                                     \
   {                                                                                                  \
-    hipLaunchKernelGGL(dock_bucket_kernel<NS>, dim3(blocks), dim3(64 * wpb),                         \
-                       dock_lds_bytes(NS, wpb, G.tab_len, D.A), st, DockArgs{G, Lg, D}, Q);          \
+    hipLaunchKernelGGL((lone ? dock_bucket_kernel<NS, true> : dock_bucket_kernel<NS, false>),        \
+                       dim3(blocks), dim3(64 * wpb), dock_lds_bytes(NS, wpb, G.tab_len, D.A), st,    \
+                       DockArgs{G, Lg, D}, Q);                                                       \
     return hipGetLastError();                                                                        \
   }
   LG_DISPATCH(nslot, CALL)
@@ -1232,19 +1267,23 @@ hipError_t launch_dock_sites(int nslot, int wpb, int blocks, const GridDev& G, c
 }
 
 // Resident blocks per compute unit of a bucket kernel instance (the b of Eq. 1).
-hipError_t occupancy_dock_bucket(int nslot, int wpb, int tab_len, int angles, int* blocks_per_cu) {
-#define CALL(NS)                                                                                        \
-  {                                                                                                     \
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, dock_bucket_kernel<NS>, 64 * wpb, \
-                                                        dock_lds_bytes(NS, wpb, tab_len, angles));      \
+hipError_t occupancy_dock_bucket(int nslot, bool lone, int wpb, int tab_len, int angles, int* blocks_per_cu) {
+#define CALL(NS)                                                                                           \
+  {                                                                                                        \
+    const size_t lds = dock_lds_bytes(NS, wpb, tab_len, angles);                                           \
+    return lone ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, dock_bucket_kernel<NS, true>,  \
+                                                               64 * wpb, lds)                              \
+                : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, dock_bucket_kernel<NS, false>, \
+                                                               64 * wpb, lds);                             \
   }
   LG_DISPATCH(nslot, CALL)
 #undef CALL
 }
 
-hipError_t attributes_dock_bucket(int nslot, hipFuncAttributes* attr) {
-#define CALL(NS) \
-  { return hipFuncGetAttributes(attr, reinterpret_cast<const void*>(dock_bucket_kernel<NS>)); }
+hipError_t attributes_dock_bucket(int nslot, bool lone, hipFuncAttributes* attr) {
+#define CALL(NS)                                                                                             \
+  { return hipFuncGetAttributes(attr, lone ? reinterpret_cast<const void*>(dock_bucket_kernel<NS, true>)     \
+                                           : reinterpret_cast<const void*>(dock_bucket_kernel<NS, false>)); }
   LG_DISPATCH(nslot, CALL)
 #undef CALL
 }
@@ -1253,15 +1292,16 @@ hipError_t launch_topk(int nslot, const LigDev& Lg, const DockDev& D, int n, int
                        float* ox, float* oy, float* oz, float* all_scores, float* pivot, hipStream_t st) {
   if (n == 0) return hipSuccess;
   const int wpb = 4;
-  const dim3 grid((n + wpb - 1) / wpb), block(64 * wpb);
-  switch (nslot) {
-    case 1: hipLaunchKernelGGL(topk_kernel<1>, grid, block, 0, st, Lg, D, n, k, score, rid, ox, oy, oz, all_scores, pivot); break;
-    case 2: hipLaunchKernelGGL(topk_kernel<2>, grid, block, 0, st, Lg, D, n, k, score, rid, ox, oy, oz, all_scores, pivot); break;
-    case 3: hipLaunchKernelGGL(topk_kernel<3>, grid, block, 0, st, Lg, D, n, k, score, rid, ox, oy, oz, all_scores, pivot); break;
-    case 4: hipLaunchKernelGGL(topk_kernel<4>, grid, block, 0, st, Lg, D, n, k, score, rid, ox, oy, oz, all_scores, pivot); break;
-    default: return hipErrorInvalidValue;
+  hipLaunchKernelGGL(topk_kernel, dim3((n + wpb - 1) / wpb), dim3(64 * wpb), 0, st, D, n, k, score, rid, all_scores);
+  const long long poses = (long long)n * k;
+  const dim3 grid((unsigned)std::min<long long>((poses + wpb - 1) / wpb, 1 << 22)), block(64 * wpb);
+#define CALL(NS)                                                                                         \
+  {                                                                                                      \
+    hipLaunchKernelGGL(replay_kernel<NS>, grid, block, 0, st, Lg, D, n, k, rid, ox, oy, oz, pivot);      \
+    return hipGetLastError();                                                                            \
   }
-  return hipGetLastError();
+  LG_DISPATCH(nslot, CALL)
+#undef CALL
 }
 
 }  // namespace lg
