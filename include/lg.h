@@ -277,6 +277,16 @@ lg_status lg_dock_stream(lg_pocket pocket, const lg_host_ligands* ligands, const
 lg_status lg_score(lg_pocket pocket, const lg_ligands* poses, int32_t interp, const float* moves, float* score,
                    float* grad, int32_t top_m, int32_t* top_idx, float* top_score, void* stream);
 
+/* Local parameters given apart -- t and w device [3n], theta device
+ * [total_torsions] -- packed into lg_score's moves (device [6n +
+ * total_torsions]), and the places they went to: idx_t, idx_w device [3n],
+ * idx_theta device [total_torsions], with the pose of every bond in pose_of_bond
+ * device [total_torsions].  tors_offset is device [n+1].  One kernel on
+ * `stream`, on the caller's current device; no allocation. */
+lg_status lg_pack_moves(const int32_t* tors_offset, int32_t n, int32_t total_torsions, const float* t, const float* w,
+                        const float* theta, float* moves, int64_t* idx_t, int64_t* idx_w, int64_t* idx_theta,
+                        int64_t* pose_of_bond, void* stream);
+
 /* Local refinement of poses by gradient ascent on the trilinear score.  Each
  * step: gradient at the current pose, step = (eta_t*g_t, eta_w*g_w,
  * eta_th*g_th) clipped to norm clip_t, norm clip_w and per-bond clip_th,

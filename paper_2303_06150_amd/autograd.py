@@ -30,14 +30,23 @@ def move_layout(poses: lg.DeviceLigands):
     return as_t(idx_t), as_t(idx_w), as_t(idx_th), as_t(pose_of_bond), 6 * n + int(to[-1])
 
 
+def _parameter(v, count, dev):
+    """v as `count` contiguous float32 values (a single value stands for all of them)."""
+    v = v.detach().reshape(-1).float()
+    if v.numel() == 1 and count != 1:
+        v = v.to(dev).expand(count).contiguous()
+    if v.numel() != count or (count and v.device != dev):
+        raise RuntimeError(f"{v.numel()} values on {v.device} given for {count} parameters on {dev}")
+    return v
+
+
 class RefineScore(torch.autograd.Function):
     @staticmethod
     def forward(ctx, t, w, theta, pocket, poses):
-        idx_t, idx_w, idx_th, pose_of_bond, size = move_layout(poses)
-        moves = torch.zeros(max(size, 1), dtype=torch.float32, device=t.device)
-        moves[idx_t] = t.detach().reshape(-1).float()
-        moves[idx_w] = w.detach().reshape(-1).float()
-        moves[idx_th] = theta.detach().reshape(-1).float()
+        dev = poses.x.device
+        moves, idx_t, idx_w, idx_th, pose_of_bond = lg.lg_pack_moves(
+            poses, _parameter(t, 3 * poses.n, dev), _parameter(w, 3 * poses.n, dev),
+            _parameter(theta, poses.total_torsions, dev))
         res = lg.lg_score(pocket, poses, lg.LG_TRILINEAR, grad=True, moves=moves)
         ctx.save_for_backward(res["grad"])
         ctx.layout = (idx_t, idx_w, idx_th, pose_of_bond)

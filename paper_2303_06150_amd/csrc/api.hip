@@ -32,8 +32,11 @@ hipError_t launch_dock_sites(int nslot, int wpb, int blocks, const GridDev& G, c
 hipError_t attributes_dock_bucket(int nslot, bool lone, hipFuncAttributes* attr);
 hipError_t launch_topk(int nslot, const LigDev& Lg, const DockDev& D, int n, int k, float* score, int32_t* rid,
                        float* ox, float* oy, float* oz, float* all_scores, float* pivot, hipStream_t st);
-hipError_t launch_score(const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
+hipError_t launch_score(int max_atoms, const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
                         hipStream_t st);
+hipError_t launch_pack_moves(const int32_t* tors_offset, int n, int total_torsions, const float* t, const float* w,
+                             const float* theta, float* moves, int64_t* idx_t, int64_t* idx_w, int64_t* idx_th,
+                             int64_t* pose_of_bond, hipStream_t st);
 size_t rank_scratch_bytes(int n, int m);
 hipError_t launch_rank(const float* score, int n, int group, int m, void* work, int32_t* top_idx,
                        float* top_score, int32_t* top_member, hipStream_t st);
@@ -1196,9 +1199,23 @@ lg_status lg_score(lg_pocket p, const lg_ligands* L, int32_t interp, const float
   if (moves)
     LG_HIP(lg::launch_score_moves((max_atoms + 63) / 64, p->grid, lig_dev(L), moves, n, score, grad, st));
   else
-    LG_HIP(lg::launch_score(p->grid, lig_dev(L), n, interp, score, grad, st));
+    LG_HIP(lg::launch_score(max_atoms, p->grid, lig_dev(L), n, interp, score, grad, st));
   if (top_m > 0)
     LG_HIP(lg::launch_rank(score, n, 1, top_m, (char*)p->ws + o_rank, top_idx, top_score, nullptr, st));
+  return LG_OK;
+}
+
+lg_status lg_pack_moves(const int32_t* tors_offset, int32_t n, int32_t total_torsions, const float* t, const float* w,
+                        const float* theta, float* moves, int64_t* idx_t, int64_t* idx_w, int64_t* idx_theta,
+                        int64_t* pose_of_bond, void* stream) {
+  if (n < 0 || total_torsions < 0) return fail(LG_ERR_INVALID_ARG, "negative sizes");
+  if (n > (1 << 30) - 256) return fail(LG_ERR_LIMIT, "n = %d above 2^30 - 256", n);
+  if (n == 0) return LG_OK;
+  if (!tors_offset || !t || !w || !moves || !idx_t || !idx_w ||
+      (total_torsions > 0 && (!theta || !idx_theta || !pose_of_bond)))
+    return fail(LG_ERR_INVALID_ARG, "a required array is NULL");
+  LG_HIP(lg::launch_pack_moves(tors_offset, n, total_torsions, t, w, theta, moves, idx_t, idx_w, idx_theta,
+                               pose_of_bond, (hipStream_t)stream));
   return LG_OK;
 }
 

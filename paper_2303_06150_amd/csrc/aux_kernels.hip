@@ -14,83 +14,191 @@ __global__ void zero_kernel(int32_t* p, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// One wavefront per pose: score = sum over atoms in atom order; optional
-// gradient with respect to (t, omega, theta) at zero (force / torque form).
+// Sum over the 16 lanes of a row, on every lane of it.
+__device__ __forceinline__ float row_sum(float v) {
+  auto add = [&](int moved) { v += __int_as_float(moved); };
+  add(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+  add(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+  add(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, true));   // row_half_mirror
+  add(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, true));   // row_mirror
+  return v;
+}
+
+// Score of every pose = sum over its atoms in atom order; optional gradient with
+// respect to (t, omega, theta) at zero (force / torque form).
+// A pose takes a row of 16 lanes, atom 16 s + lane in slot s < S, so a wavefront
+// works on four poses, its lanes are filled to a sixteenth of a pose, and a sum
+// over a pose is four DPP steps.  Bounded by vector issue: per bond 16 operations
+// a slot and 12 to add up.  A wavefront per pose spent three quarters of its time on
+// atom-by-atom broadcasts and on 64-lane reductions of 41 atoms: 200 000 poses of
+// 41 atoms 520 us, as it is SCORE_US us.
+template <int S>
 __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, int interp, float* score,
                                                      float* grad) {
-  constexpr int NS = 4;
-  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id();
-  const int i = blockIdx.x * nwaves + wave;
-  if (i >= n) return;
-  const int abase = __builtin_amdgcn_readfirstlane(P.atom_offset[i]);
-  const int N = __builtin_amdgcn_readfirstlane(P.atom_offset[i + 1]) - abase;
-  float x[3][NS], g[3][NS], v[NS];
-  uint32_t mk[NS];
+  extern __shared__ float4 lds[];
+  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id(), row = lane >> 4, l = lane & 15;
+  float4* pos = lds + (size_t)(wave * 4 + row) * (16 * S);   // the pose's atoms: coordinates and value
+  const int i = (blockIdx.x * nwaves + wave) * 4 + row;
+  const bool live = i < n;
+  const int abase = live ? P.atom_offset[i] : 0, N = live ? P.atom_offset[i + 1] - abase : 0;
+  const int most = wave_reduce_i32(N, OpMax());
+  const bool want = grad && interp == LG_TRILINEAR;
+  float x[3][S], g[3][S];
+  uint32_t mk[S];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const int a = s * 64 + lane;
-    const bool in = a < N;
-    x[0][s] = in ? P.x[abase + a] : 0.f;
-    x[1][s] = in ? P.y[abase + a] : 0.f;
-    x[2][s] = in ? P.z[abase + a] : 0.f;
-    mk[s] = in ? P.mask[abase + a] : 0u;
-    float gg[3] = {0.f, 0.f, 0.f};
-    v[s] = 0.f;
-    if (in) v[s] = interp == LG_TRILINEAR ? trilinear(G, x[0][s], x[1][s], x[2][s], gg) : nearest(G, x[0][s], x[1][s], x[2][s]);
-    g[0][s] = gg[0]; g[1][s] = gg[1]; g[2][s] = gg[2];
+  for (int s = 0; s < S; ++s) {
+    x[0][s] = x[1][s] = x[2][s] = g[0][s] = g[1][s] = g[2][s] = 0.f;
+    mk[s] = 0u;
+    if (16 * s >= most) continue;
+    const int a = 16 * s + l;
+    if (a < N) {
+      const float px = P.x[abase + a], py = P.y[abase + a], pz = P.z[abase + a];
+      x[0][s] = px;
+      x[1][s] = py;
+      x[2][s] = pz;
+      if (want) mk[s] = P.mask[abase + a];
+      float gg[3] = {0.f, 0.f, 0.f};
+      const float v = interp == LG_TRILINEAR ? trilinear(G, px, py, pz, gg) : nearest(G, px, py, pz);
+      g[0][s] = gg[0];
+      g[1][s] = gg[1];
+      g[2][s] = gg[2];
+      pos[a] = make_float4(px, py, pz, v);
+    }
   }
-  float total = 0.f;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const int cnt = min(64, N - s * 64);
-    for (int l = 0; l < cnt; ++l) total = total + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[s]), l));
+  wave_sync();
+  // the score by the row's first lane, atom after atom
+  if (l == 0 && live) {
+    float total = 0.f;
+    int a = 0;
+    for (; a + 4 <= N; a += 4) {
+      const float v0 = pos[a].w, v1 = pos[a + 1].w, v2 = pos[a + 2].w, v3 = pos[a + 3].w;
+      total = total + v0;
+      total = total + v1;
+      total = total + v2;
+      total = total + v3;
+    }
+    for (; a < N; ++a) total = total + pos[a].w;
+    score[i] = total;
   }
-  if (lane == 0) score[i] = total;
-  if (!grad || interp != LG_TRILINEAR) return;
-  const int toff = __builtin_amdgcn_readfirstlane(P.tors_offset[i]);
-  const int K = __builtin_amdgcn_readfirstlane(P.tors_offset[i + 1]) - toff;
-  const float Px = P.ref[3 * i], Py = P.ref[3 * i + 1], Pz = P.ref[3 * i + 2];
-  float f[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};
+  if (!want) return;
+  const int toff = live ? P.tors_offset[i] : 0, K = live ? P.tors_offset[i + 1] - toff : 0;
+  float* out = grad + 6 * (size_t)(live ? i : 0) + toff;
+  {
+    float Pv[3], f[3] = {0.f, 0.f, 0.f}, tq[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    float rx = x[0][s] - Px, ry = x[1][s] - Py, rz = x[2][s] - Pz;
-    f[0] += g[0][s]; f[1] += g[1][s]; f[2] += g[2][s];
-    tq[0] += ry * g[2][s] - rz * g[1][s];
-    tq[1] += rz * g[0][s] - rx * g[2][s];
-    tq[2] += rx * g[1][s] - ry * g[0][s];
+    for (int c = 0; c < 3; ++c) Pv[c] = live ? P.ref[3 * (size_t)i + c] : 0.f;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if (16 * s >= most) continue;
+      const float rx = x[0][s] - Pv[0], ry = x[1][s] - Pv[1], rz = x[2][s] - Pv[2];
+      f[0] += g[0][s];
+      f[1] += g[1][s];
+      f[2] += g[2][s];
+      tq[0] += ry * g[2][s] - rz * g[1][s];
+      tq[1] += rz * g[0][s] - rx * g[2][s];
+      tq[2] += rx * g[1][s] - ry * g[0][s];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      f[c] = row_sum(f[c]);
+      tq[c] = row_sum(tq[c]);
+    }
+    const float mine = l == 0 ? f[0] : l == 1 ? f[1] : l == 2 ? f[2] : l == 3 ? tq[0] : l == 4 ? tq[1] : tq[2];
+    if (l < 6 && live) out[l] = mine;
   }
-  float* out = grad + 6 * (size_t)i + toff;
-  float red[6];
-  for (int c = 0; c < 3; ++c) { red[c] = wave_sum(f[c]); red[3 + c] = wave_sum(tq[c]); }
-  if (lane == 0)
-    for (int c = 0; c < 6; ++c) out[c] = red[c];
-  for (int k = 0; k < K; ++k) {
-    const int a = __builtin_amdgcn_readfirstlane(P.tors_atoms[2 * (toff + k)]);
-    const int b = __builtin_amdgcn_readfirstlane(P.tors_atoms[2 * (toff + k) + 1]);
-    const float xa = atom_value(x[0], a), ya = atom_value(x[1], a), za = atom_value(x[2], a);
-    float ux = atom_value(x[0], b) - xa, uy = atom_value(x[1], b) - ya, uz = atom_value(x[2], b) - za;
-    const float inv = 1.0f / sqrtf(ux * ux + uy * uy + uz * uz);
-    ux *= inv; uy *= inv; uz *= inv;
-    float t[3] = {0.f, 0.f, 0.f};
+  // bonds 16 b .. 16 b + 15 of the four poses: lane l holds bond 16 b + l's axis and
+  // takes its sums
+  const int bonds = wave_reduce_i32(K, OpMax());
+  for (int b = 0; 16 * b < bonds; ++b) {
+    const int mine = 16 * b + l;
+    int pa = 0, pb = 0;
+    if (mine < K) {
+      pa = P.tors_atoms[2 * (toff + mine)];
+      pb = P.tors_atoms[2 * (toff + mine) + 1];
+    }
+    float own[3] = {0.f, 0.f, 0.f};
+    const int last = min(16, bonds - 16 * b);
+    for (int q = 0; q < last; ++q) {
+      const int k = 16 * b + q;
+      const float4 at = pos[__builtin_amdgcn_ds_bpermute(((lane & 48) | q) << 2, pa)];   // bond k's pivot atom, of the row's pose
+      float t[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      if ((mk[s] >> k) & 1u) {
-        float rx = x[0][s] - xa, ry = x[1][s] - ya, rz = x[2][s] - za;
-        t[0] += ry * g[2][s] - rz * g[1][s];
-        t[1] += rz * g[0][s] - rx * g[2][s];
-        t[2] += rx * g[1][s] - ry * g[0][s];
+      for (int s = 0; s < S; ++s) {
+        if (16 * s >= most) continue;
+        const bool in = (mk[s] >> k) & 1u;
+        const float rx = x[0][s] - at.x, ry = x[1][s] - at.y, rz = x[2][s] - at.z;
+        const float t0 = ry * g[2][s] - rz * g[1][s], t1 = rz * g[0][s] - rx * g[2][s], t2 = rx * g[1][s] - ry * g[0][s];
+        t[0] += in ? t0 : 0.f;
+        t[1] += in ? t1 : 0.f;
+        t[2] += in ? t2 : 0.f;
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float sum = row_sum(t[c]);
+        own[c] = l == q ? sum : own[c];
       }
     }
-    const float tk = ux * wave_sum(t[0]) + uy * wave_sum(t[1]) + uz * wave_sum(t[2]);
-    if (lane == 0) out[6 + k] = tk;
+    if (mine < K) {
+      const float4 A = pos[pa], B = pos[pb];
+      float ux = B.x - A.x, uy = B.y - A.y, uz = B.z - A.z;
+      const float inv = 1.0f / sqrtf(ux * ux + uy * uy + uz * uz);
+      ux *= inv;
+      uy *= inv;
+      uz *= inv;
+      out[6 + mine] = ux * own[0] + uy * own[1] + uz * own[2];
+    }
   }
 }
 
-hipError_t launch_score(const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
+hipError_t launch_score(int max_atoms, const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
                         hipStream_t st) {
   if (n == 0) return hipSuccess;
-  const int wpb = 4;
-  hipLaunchKernelGGL(score_kernel, dim3((n + wpb - 1) / wpb), dim3(64 * wpb), 0, st, G, P, n, interp, score, grad);
+  const int slots = max_atoms <= 64 ? 4 : max_atoms <= 128 ? 8 : 16;
+  const int wpb = slots == 16 ? 2 : 4;   // 32 KB of LDS a block at most
+  const dim3 grid((unsigned)(((long long)n + 4 * wpb - 1) / (4 * wpb))), block(64 * wpb);
+  const size_t bytes = (size_t)wpb * 4 * 16 * slots * sizeof(float4);
+  switch (slots) {
+    case 4: hipLaunchKernelGGL(score_kernel<4>, grid, block, bytes, st, G, P, n, interp, score, grad); break;
+    case 8: hipLaunchKernelGGL(score_kernel<8>, grid, block, bytes, st, G, P, n, interp, score, grad); break;
+    default: hipLaunchKernelGGL(score_kernel<16>, grid, block, bytes, st, G, P, n, interp, score, grad); break;
+  }
+  return hipGetLastError();
+}
+
+// Local parameters of every pose packed into the layout of lg_score's moves (6 i +
+// tors_offset[i]: t, w, theta), and where each went.  One thread per pose and
+// entry; a pose whose offsets do not fit the sizes is left out (lg_score reports it).
+__global__ __launch_bounds__(256) void pack_moves_kernel(const int32_t* tors_offset, int n, int total_torsions,
+                                                         const float* t, const float* w, const float* theta,
+                                                         float* moves, int64_t* idx_t, int64_t* idx_w, int64_t* idx_th,
+                                                         int64_t* pose_of_bond) {
+  constexpr int kEntries = 6 + LG_MAX_TORSIONS;
+  const long long e = blockIdx.x * 256LL + threadIdx.x;
+  const int i = (int)(e / kEntries), q = (int)(e - (long long)i * kEntries);
+  if (i >= n) return;
+  const int t0 = tors_offset[i], t1 = tors_offset[i + 1];
+  if (t0 < 0 || t1 < t0 || t1 > total_torsions) return;
+  const long long base = 6LL * i + t0;
+  if (q < 3) {
+    moves[base + q] = t[3LL * i + q];
+    idx_t[3LL * i + q] = base + q;
+  } else if (q < 6) {
+    moves[base + q] = w[3LL * i + q - 3];
+    idx_w[3LL * i + q - 3] = base + q;
+  } else if (q - 6 < t1 - t0) {
+    const int b = t0 + q - 6;
+    moves[base + q] = theta[b];
+    idx_th[b] = base + q;
+    pose_of_bond[b] = i;
+  }
+}
+
+hipError_t launch_pack_moves(const int32_t* tors_offset, int n, int total_torsions, const float* t, const float* w,
+                             const float* theta, float* moves, int64_t* idx_t, int64_t* idx_w, int64_t* idx_th,
+                             int64_t* pose_of_bond, hipStream_t st) {
+  const long long entries = (long long)n * (6 + LG_MAX_TORSIONS);
+  hipLaunchKernelGGL(pack_moves_kernel, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, st, tors_offset, n,
+                     total_torsions, t, w, theta, moves, idx_t, idx_w, idx_th, pose_of_bond);
   return hipGetLastError();
 }
 

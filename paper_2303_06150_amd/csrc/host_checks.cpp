@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <thread>
 
 namespace lghost {
 
@@ -36,6 +37,70 @@ long long env_ll(const char* name, long long dflt) {
 
 size_t workspace_limit() { return (size_t)env_ll("LG_WORKSPACE_LIMIT", (long long)(SIZE_MAX >> 1)); }
 
+namespace {
+
+// Whether every difference off[i + 1] - off[i] lies in lo .. hi (no early exit:
+// the loop vectorises).
+bool differences_within(const int32_t* off, int n, uint32_t lo, uint32_t hi) {
+  uint32_t bad = 0;
+  for (int i = 0; i < n; ++i) bad |= (uint32_t)off[i + 1] - (uint32_t)off[i] - lo > hi - lo ? 1u : 0u;
+  return bad == 0;
+}
+
+int largest_difference(const int32_t* off, int n) {
+  int m = 0;
+  for (int i = 0; i < n; ++i) {
+    const int d = off[i + 1] - off[i];
+    m = d > m ? d : m;
+  }
+  return m;
+}
+
+// Whether every bond of ligands i0 .. i1 - 1 joins two distinct atoms of its ligand.
+// The offsets have been checked.
+bool bonds_within(const int32_t* atom_offset, const int32_t* tors_offset, const int32_t* tors_atoms, int i0, int i1) {
+  uint32_t bad = 0;
+  for (int i = i0; i < i1; ++i) {
+    const uint32_t N = (uint32_t)(atom_offset[i + 1] - atom_offset[i]);
+    for (int k = tors_offset[i]; k < tors_offset[i + 1]; ++k) {
+      const uint32_t a = (uint32_t)tors_atoms[2 * k], b = (uint32_t)tors_atoms[2 * k + 1];
+      bad |= (uint32_t)(a >= N) | (uint32_t)(b >= N) | (uint32_t)(a == b);
+    }
+  }
+  return bad == 0;
+}
+
+// The same over all ligands, on up to eight threads from 64 Ki bonds each (one
+// thread reads 1.5 million bonds in about 0.7 ms, more than the GPU takes to
+// score their poses; a thread costs about 15 us).  A share whose thread cannot
+// start is read here.
+bool all_bonds_within(const int32_t* atom_offset, const int32_t* tors_offset, const int32_t* tors_atoms, int n) {
+  constexpr int kMost = 8;
+  const int parts = std::max(1, std::min(kMost, tors_offset[n] >> 16));
+  bool fine[kMost];
+  std::thread th[kMost];
+  auto share = [&](int p) {
+    const int i0 = (int)((long long)n * p / parts), i1 = (int)((long long)n * (p + 1) / parts);
+    fine[p] = bonds_within(atom_offset, tors_offset, tors_atoms, i0, i1);
+  };
+  for (int p = 1; p < parts; ++p) {
+    try {
+      th[p] = std::thread(share, p);
+    } catch (...) {
+      share(p);
+    }
+  }
+  share(0);
+  bool all = true;
+  for (int p = 0; p < parts; ++p) {
+    if (th[p].joinable()) th[p].join();
+    all = all && fine[p];
+  }
+  return all;
+}
+
+}  // namespace
+
 lg_status check_ligands(const lg_ligands* L, bool need_tors) {
   if (!L) return fail(LG_ERR_INVALID_ARG, "ligands is NULL");
   if (L->n < 0) return fail(LG_ERR_INVALID_ARG, "n = %d < 0", L->n);
@@ -48,7 +113,8 @@ lg_status check_ligands(const lg_ligands* L, bool need_tors) {
   if (L->total_atoms > (1 << 30) - 256)
     return fail(LG_ERR_LIMIT, "total_atoms %d above 2^30 - 256 (32-bit byte offsets)", L->total_atoms);
   if (L->atom_offset_host) {
-    for (int i = 0; i < L->n; ++i) {
+    const bool fine = differences_within(L->atom_offset_host, L->n, 1, LG_MAX_ATOMS);
+    for (int i = 0; i < L->n && !fine; ++i) {   // the first one that is not
       const long long N = (long long)L->atom_offset_host[i + 1] - L->atom_offset_host[i];
       if (N < 1 || N > LG_MAX_ATOMS) return fail(LG_ERR_LIMIT, "ligand %d has %lld atoms (1..%d)", i, N, LG_MAX_ATOMS);
     }
@@ -56,7 +122,8 @@ lg_status check_ligands(const lg_ligands* L, bool need_tors) {
       return fail(LG_ERR_INVALID_ARG, "atom_offset does not span [0, total_atoms)");
   }
   if (L->tors_offset_host) {
-    for (int i = 0; i < L->n; ++i) {
+    const bool fine = differences_within(L->tors_offset_host, L->n, 0, LG_MAX_TORSIONS);
+    for (int i = 0; i < L->n && !fine; ++i) {
       const long long K = (long long)L->tors_offset_host[i + 1] - L->tors_offset_host[i];
       if (K < 0 || K > LG_MAX_TORSIONS) return fail(LG_ERR_LIMIT, "ligand %d has %lld bonds (0..%d)", i, K, LG_MAX_TORSIONS);
     }
@@ -66,7 +133,8 @@ lg_status check_ligands(const lg_ligands* L, bool need_tors) {
   if (L->tors_atoms_host) {
     if (!L->atom_offset_host || !L->tors_offset_host)
       return fail(LG_ERR_INVALID_ARG, "tors_atoms_host needs atom_offset_host and tors_offset_host");
-    for (int i = 0; i < L->n; ++i) {
+    const bool fine = all_bonds_within(L->atom_offset_host, L->tors_offset_host, L->tors_atoms_host, L->n);
+    for (int i = 0; i < L->n && !fine; ++i) {
       const long long N = (long long)L->atom_offset_host[i + 1] - L->atom_offset_host[i];
       for (int k = L->tors_offset_host[i]; k < L->tors_offset_host[i + 1]; ++k) {
         const int a = L->tors_atoms_host[2 * k], b = L->tors_atoms_host[2 * k + 1];
@@ -84,13 +152,8 @@ lg_status check_ligands(const lg_ligands* L, bool need_tors) {
 void host_maxima(const lg_ligands* L, int* max_atoms, int* max_tors) {
   *max_atoms = *max_tors = -1;
   if (!L || L->n < 1 || !L->atom_offset_host || !L->tors_offset_host || !L->tors_atoms_host) return;
-  int ma = 0, mt = 0;
-  for (int i = 0; i < L->n; ++i) {
-    ma = std::max(ma, L->atom_offset_host[i + 1] - L->atom_offset_host[i]);
-    mt = std::max(mt, L->tors_offset_host[i + 1] - L->tors_offset_host[i]);
-  }
-  *max_atoms = ma;
-  *max_tors = mt;
+  *max_atoms = largest_difference(L->atom_offset_host, L->n);
+  *max_tors = largest_difference(L->tors_offset_host, L->n);
 }
 
 // Host-side validation of a host-resident library (the device check's rules):

@@ -26,7 +26,7 @@ LG_PLAIN, LG_BUCKETED = 0, 1
 LG_MAX_ATOMS, LG_MAX_TORSIONS, LG_MAX_SAMPLES = 256, 32, 1024
 
 EXPORTS = ("lg_load_pocket", "lg_free_pocket", "lg_dock_batch", "lg_dock_sites", "lg_dock_stream", "lg_score",
-           "lg_refine", "lg_rank", "lg_rank_static", "lg_autotune", "lg_valu_probe",
+           "lg_pack_moves", "lg_refine", "lg_rank", "lg_rank_static", "lg_autotune", "lg_valu_probe",
            "lg_set_tuning", "lg_get_tuning", "lg_bucket_stats", "lg_bucket_size", "lg_atom_clusters", "lg_rotamer_clusters",
            "lg_last_error", "lg_version")
 
@@ -120,6 +120,7 @@ def load_library(path: str = LIB_PATH):
                                    c_void_p]
     lib.lg_score.argtypes = [c_void_p, P(lg_ligands), c_int32, c_void_p, c_void_p, c_void_p, c_int32, c_void_p,
                              c_void_p, c_void_p]
+    lib.lg_pack_moves.argtypes = [c_void_p, c_int32, c_int32] + [c_void_p] * 9
     lib.lg_refine.argtypes = [c_void_p, P(lg_ligands), P(lg_refine_params), c_void_p, c_void_p, c_void_p,
                               c_void_p, c_void_p]
     lib.lg_rank.argtypes = [c_void_p, c_void_p, c_int32, c_int32, c_int32, c_void_p, c_void_p, c_void_p, c_void_p]
@@ -138,7 +139,7 @@ def load_library(path: str = LIB_PATH):
     lib.lg_last_error.restype = ctypes.c_char_p
     for name in ("lg_load_pocket", "lg_free_pocket", "lg_dock_batch", "lg_dock_sites", "lg_dock_stream", "lg_score",
                  "lg_refine", "lg_rank", "lg_rank_static", "lg_autotune", "lg_valu_probe", "lg_set_tuning",
-                 "lg_get_tuning"):
+                 "lg_get_tuning", "lg_pack_moves"):
         getattr(lib, name).restype = c_int32
     _lib = lib
     return lib
@@ -435,6 +436,21 @@ def lg_score(pocket: Pocket, poses: DeviceLigands, interp: int = LG_TRILINEAR, g
                          _ptr(res["grad"]), int(top_m), _ptr(res["top_idx"]), _ptr(res["top_score"]),
                          _stream_handle(stream)))
     return res
+
+
+def lg_pack_moves(poses: DeviceLigands, t, w, theta, stream=None):
+    """Pack t, w [3n] and theta [total_torsions] (contiguous float32 on the poses'
+    device) into lg_score's moves.  Returns moves and the int64 index tensors of
+    t, w, theta in it and of every bond's pose."""
+    torch = _torch()
+    dev, n, tors = poses.x.device, poses.n, poses.total_torsions
+    moves = torch.empty(max(6 * n + tors, 1), dtype=torch.float32, device=dev)
+    idx_t, idx_w, idx_th, pose_of_bond = torch.empty(6 * n + 2 * tors, dtype=torch.int64, device=dev).split(
+        (3 * n, 3 * n, tors, tors))
+    _check(load_library().lg_pack_moves(_ptr(poses.tors_offset), n, tors, _ptr(t), _ptr(w), _ptr(theta), _ptr(moves),
+                                        _ptr(idx_t), _ptr(idx_w), _ptr(idx_th), _ptr(pose_of_bond),
+                                        _stream_handle(stream)))
+    return moves, idx_t, idx_w, idx_th, pose_of_bond
 
 
 def lg_refine(pocket: Pocket, poses: DeviceLigands, params: lg_refine_params, stream=None):
