@@ -31,7 +31,7 @@ __device__ __forceinline__ float row_sum(float v) {
 // over a pose is four DPP steps.  Bounded by vector issue: per bond 16 operations
 // a slot and 12 to add up.  A wavefront per pose spent three quarters of its time on
 // atom-by-atom broadcasts and on 64-lane reductions of 41 atoms: 200 000 poses of
-// 41 atoms 520 us, as it is SCORE_US us.
+// 41 atoms 520 us, as it is 231 us.
 template <int S>
 __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, int interp, float* score,
                                                      float* grad) {

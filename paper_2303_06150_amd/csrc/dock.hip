@@ -136,7 +136,7 @@ struct Samples {
   int GT, ngt;        // translations, in order of displacement
   int tsub;           // lanes that share a translation group in the bound pass (log2): 0, 1, 2
   int gt0;            // translation group of sample 0
-  bool bound_t;       // a translation group's samples span less than one node
+  bool bound_a, bound_t;   // rotations and torsions, translations: a bound pass pays (and is possible)
   float dlow;         // least displacement of the lane's translation group
   float radius;       // largest |(cos, sin)| of a sample (1 up to rounding)
   float chord;        // every sample of a group lies within chord of its centre, in (cos, sin)
@@ -150,6 +150,10 @@ __device__ __forceinline__ void load_samples(const GridDev& G, const DockDev& D,
   sm.A = D.A;
   sm.GA = (D.A + 63) >> 6;
   sm.nga = (D.A + sm.GA - 1) / sm.GA;
+  // the bound pass costs most of a scoring pass and can save all but one of GA: with
+  // two it does not pay (100 samples, 1 000 mixed ligands: 18.5 ms without, 20.5
+  // with); 130 to 1024 samples have three passes and more
+  sm.bound_a = sm.GA > 2;
   const int j0 = lane * sm.GA, cnt = min(sm.GA, D.A - j0);
   float far2 = 0.f, len2 = 0.f;
   bool odd = false;
@@ -314,14 +318,12 @@ __device__ __forceinline__ V ordered_sum(V acc, int n, F value) {
 }
 
 // The sum over n atoms of value(in, t): `in` says whether every node index is
-// known to lie inside the padded grid, so that none needs its clamp (the usual
-// case; the other one takes the plain loop).
+// known to lie inside the padded grid, so that none needs its clamp (two clamps of
+// an eighth of a rotation sample's vector cycles each).
 template <int U, class V, class F>
 __device__ __forceinline__ V scan_sum(bool inside, V acc, int n, F value) {
   if (inside) return ordered_sum<U>(acc, n, [&](int t) { return value(std::true_type{}, t); });
-#pragma unroll 1
-  for (int t = 0; t < n; ++t) acc += value(std::false_type{}, t);
-  return acc;
+  return ordered_sum<U>(acc, n, [&](int t) { return value(std::false_type{}, t); });
 }
 
 template <class In>
@@ -353,7 +355,7 @@ __device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, flo
   // monotone: when both ends of every atom's range, widened by four nodes
   // (rounding and the windows), map inside [-1, n], no sample and no window needs
   // the clamp of the node index.
-  bool inside = true, level = G.dil != nullptr && sm.GA > 1;
+  bool inside = true, level = sm.bound_a && G.dil != nullptr;
   const float fp = fmaf(pP, ih, cP), fq = fmaf(pQ, ih, cQ);
   const float ferr = fmaf(1e-6f * ih, fabsf(pP) + fabsf(pQ), 2e-3f);
   const float reach = fminf(fminf(fp + 1.f, fnP - fp), fminf(fq + 1.f, fnQ - fq)) - 4.f;
@@ -626,7 +628,7 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, ui
   // every place of a moving atom lies within |h u| + radius rho of a: when that
   // cube, widened by four nodes, is inside the padded grid, no node index needs
   // its clamp
-  bool inside = true, level = G.dil != nullptr && sm.GA > 1;
+  bool inside = true, level = sm.bound_a && G.dil != nullptr;
   const float ulen = prune_sqrt(fmaf(ux, ux, fmaf(uy, uy, uz * uz))) * 1.0001f;
   const float f0 = fmaf(xa, ih, cx), f1 = fmaf(ya, ih, cy), f2 = fmaf(za, ih, cz);
   const float reach = fminf(fminf(fminf(f0 + 1.f, G.fn[0] - f0), fminf(f1 + 1.f, G.fn[1] - f1)),
