@@ -50,6 +50,9 @@ hipError_t launch_bucketing(const int32_t* atom_offset, const int32_t* tors_offs
                             int32_t* cls, int32_t* counts, int32_t* start, int32_t* fill, int32_t* perm,
                             int32_t* cursors, hipStream_t st);
 hipError_t launch_refine(int nslot, const GridDev& G, const LigDev& P, const RefineDev& Rp, int n, hipStream_t st);
+hipError_t launch_refine_classes(int max_atoms, const GridDev& G, const LigDev& P, const RefineDev& Rp,
+                               const int32_t* perm, const int32_t* start, const ClusterBounds& cb, bool pairs,
+                               int poses, bool wide, hipStream_t st);
 hipError_t launch_refine_pair(const GridDev& G, const LigDev& P, const RefineDev& Rp, int n_lig, hipStream_t st);
 hipError_t launch_score_moves(int nslot, const GridDev& G, const LigDev& P, const float* moves, int n, float* score,
                               float* grad, hipStream_t st);
@@ -1332,6 +1335,20 @@ lg_status lg_refine(lg_pocket p, const lg_ligands* L, const lg_refine_params* rp
   int32_t* fill = start + nb + 1;
   int32_t* cursors = fill + nb;
   LG_HIP(lg::launch_bucketing(L->atom_offset, L->tors_offset, n, cb, cls, counts, start, fill, perm, cursors, st));
+  // at most four wavefronts per SIMD (four SIMDs per compute unit), what the
+  // combined kernel's registers allow at once: the poses of all classes together
+  // One launch for all classes while the tails of one launch per class weigh more
+  // than the registers that the combined kernel adds: 19 200 poses of up to 256 atoms
+  // 5.4 ms by class, 2.3 ms combined; 50 000 mixed poses 3.44 and 3.28; 128 000 7.3
+  // and 7.9.  The wide gradient tile up to 16 poses per compute unit: twice what its
+  // LDS allows at once, but pairs halve the wavefronts (4 000 poses 798 us, narrow
+  // 868; 8 000 poses 1 088 and 907).
+  const long long poses = (long long)n * kpl;
+  if (poses <= 256LL * p->cus) {
+    LG_HIP(lg::launch_refine_classes(max_atoms, p->grid, lig_dev(L), R, perm, start, cb, pairs, (int)poses,
+                                   poses <= 16LL * p->cus, st));
+    return LG_OK;
+  }
   int32_t hs[2 * (LG_MAX_ATOMS / 64 + 1) + 1];
   LG_HIP(hipMemcpyAsync(hs, start, (size_t)(nb + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   LG_HIP(hipStreamSynchronize(st));

@@ -155,6 +155,10 @@ __device__ void apply_move(MoveState<NSLOT>& p, const uint32_t (&mk)[NSLOT], int
   apply_rigid<NSLOT, LIB>(p, q);
 }
 
+__device__ __forceinline__ float of_lane(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
 // Bond k's axis at the pose held in pos, computed by lane k: pivot atom a_k and
 // unit direction (b_k - a_k) / |b_k - a_k| (the stored inverse length).
 struct LaneAxis {
@@ -198,11 +202,11 @@ __device__ __forceinline__ bool axes_fixed_under_torsions(const LigDev& P, int a
 // mv: per slot, the bonds that rotate the lane's atom (bit k of the fragment
 // mask, cleared for b_k itself and for lanes past the last atom).
 template <int NSLOT>
-__device__ void apply_torsions_table(MoveState<NSLOT>& p, const uint32_t (&mv)[NSLOT], int K, const float* th,
+__device__ void apply_torsions_table(MoveState<NSLOT>& p, const uint32_t (&mv)[NSLOT], uint32_t turns,
                                      const float4* mats) {
-  for (int k = K - 1; k >= 0; --k) {
-    const float ang = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(th[k])));
-    if (ang == 0.f) continue;
+  while (turns != 0u) {
+    const int k = 31 - __builtin_clz(turns);
+    turns &= ~(1u << k);
     const float4 r0 = mats[3 * k], r1 = mats[3 * k + 1], r2 = mats[3 * k + 2];
     const float m[9] = {r0.x, r0.y, r0.z, r1.x, r1.y, r1.z, r2.x, r2.y, r2.z};
 #pragma unroll
@@ -223,21 +227,47 @@ __device__ void apply_torsions_table(MoveState<NSLOT>& p, const uint32_t (&mv)[N
 // then lane c adds column c's values atom by atom, four per LDS read.  Each
 // column's sum runs over atoms 0..N-1 in order, like a sequential loop, but all
 // columns at once.
-constexpr int TILE_COLS = 16;                      // LDS per wavefront stays small (occupancy)
+// Columns of a pass: a pass runs as long for one column as for 64, but the tile is
+// most of a wavefront's LDS and a large launch lives from the wavefronts in
+// flight.  256 000 poses: 14.2 ms with 13 or 22 columns for the one-slot instance,
+// 13.9 with 16, 13.6 with 19, 15.8 with 28; larger instances have fewer wavefronts
+// in flight by their registers (19 200 poses of up to 256 atoms: 5.8 ms with 16,
+// 5.5 with 22 or 28).
+constexpr int tile_cols(int nslot) { return nslot == 1 ? 19 : 22; }
+constexpr int WIDE_COLS = 64;                      // launches that leave LDS and lanes idle: two passes at most
 constexpr int TILE_STRIDE = 68;                    // 16-byte aligned columns for 4-float reads
-constexpr int TILE_FLOATS = TILE_COLS * TILE_STRIDE;
+constexpr int tile_floats(int cols) { return cols * TILE_STRIDE; }
 constexpr int GRAD_COLS = 7 + 3 * 32;              // score, force, torque, 3 per bond
 constexpr int GRAD_RES_FLOATS = 104;               // GRAD_COLS rounded up to float4
-constexpr int GRAD_LDS_FLOAT4 = (TILE_FLOATS + GRAD_RES_FLOATS) / 4;
+constexpr int grad_lds_float4(int cols) { return (tile_floats(cols) + GRAD_RES_FLOATS) / 4; }
 static_assert(GRAD_RES_FLOATS >= GRAD_COLS && GRAD_RES_FLOATS % 4 == 0, "gradient results: every column, whole float4");
-static_assert(TILE_FLOATS >= 12 * 32, "the torsion matrices reuse the tile");
+
+// acc + the first n values of a column, in order; the values past n up to the next
+// multiple of 16 are zeros (a sum that starts at +0 does not change by adding
+// them).  Four reads in flight: with one, each four additions waited for their
+// read (256 000 poses: 15.4 ms, now 14.8; 100 leads 957 us, now 915).
+__device__ __forceinline__ float column_sum(const float* col, int n, float acc) {
+  for (int l = 0; l < n; l += 16) {
+    float4 q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const float4*>(col + l + 4 * u);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      acc = acc + q[u].x;
+      acc = acc + q[u].y;
+      acc = acc + q[u].z;
+      acc = acc + q[u].w;
+    }
+  }
+  return acc;
+}
 
 // Trilinear score and its gradient with respect to the local move at zero;
 // sums in atom order.  g_out: t[3], w[3], then theta[K] into th_grad.  Column
 // 0 is the score, 1..3 the force, 4..6 the torque about the pivot, 7 + 3k + d
 // component d of bond k's torque about its pivot atom over F_k.  pos holds the
 // pose p; lane k holds bond k's axis.
-template <int NSLOT>
+template <int NSLOT, int COLS>
 __device__ float move_gradient(const GridDev& G, const MoveState<NSLOT>& p, const uint32_t (&mk)[NSLOT], int N,
                                int K, const int2* tors, const float4* pos, const LaneAxis& ax, float* g_out,
                                float* th_grad, float* tile, float* res) {
@@ -252,7 +282,7 @@ __device__ float move_gradient(const GridDev& G, const MoveState<NSLOT>& p, cons
   // column chunks: the 7 pose columns with bonds 0..2, then 5 bonds per chunk
   for (int k0 = 0, first = 1; first || k0 < K; first = 0) {
     const int base = first ? 7 : 0;
-    const int nb = min(K - k0, (TILE_COLS - base) / 3);
+    const int nb = min(K - k0, (COLS - base) / 3);
     const int ncol = base + 3 * nb;
     const int col0 = first ? 0 : 7 + 3 * k0;
     float acc = 0.f;
@@ -266,15 +296,16 @@ __device__ float move_gradient(const GridDev& G, const MoveState<NSLOT>& p, cons
         tile[1 * TILE_STRIDE + lane] = g[0][s];
         tile[2 * TILE_STRIDE + lane] = g[1][s];
         tile[3 * TILE_STRIDE + lane] = g[2][s];
-        tile[4 * TILE_STRIDE + lane] = r1 * g[2][s] - r2 * g[1][s];
-        tile[5 * TILE_STRIDE + lane] = r2 * g[0][s] - r0 * g[2][s];
-        tile[6 * TILE_STRIDE + lane] = r0 * g[1][s] - r1 * g[0][s];
+        const bool in = lane < cnt;
+        tile[4 * TILE_STRIDE + lane] = in ? r1 * g[2][s] - r2 * g[1][s] : 0.f;
+        tile[5 * TILE_STRIDE + lane] = in ? r2 * g[0][s] - r0 * g[2][s] : 0.f;
+        tile[6 * TILE_STRIDE + lane] = in ? r0 * g[1][s] - r1 * g[0][s] : 0.f;
       }
       for (int kk = 0; kk < nb; ++kk) {
         const int k = k0 + kk;
-        const float4 pa = pos[tors[k].x];   // pivot atom a_k, the same address in every lane
+        const float ax0 = of_lane(ax.xa, k), ax1 = of_lane(ax.ya, k), ax2 = of_lane(ax.za, k);   // pivot atom a_k, held by lane k
         const bool in = (mk[s] >> k) & 1u;
-        const float r0 = p.x[0][s] - pa.x, r1 = p.x[1][s] - pa.y, r2 = p.x[2][s] - pa.z;
+        const float r0 = p.x[0][s] - ax0, r1 = p.x[1][s] - ax1, r2 = p.x[2][s] - ax2;
         float* t = tile + (base + 3 * kk) * TILE_STRIDE + lane;
         t[0] = in ? r1 * g[2][s] - r2 * g[1][s] : 0.f;
         t[TILE_STRIDE] = in ? r2 * g[0][s] - r0 * g[2][s] : 0.f;
@@ -282,16 +313,7 @@ __device__ float move_gradient(const GridDev& G, const MoveState<NSLOT>& p, cons
       }
       wave_sync();
       if (lane < ncol) {
-        const float* col = tile + lane * TILE_STRIDE;
-        int l = 0;
-        for (; l + 4 <= cnt; l += 4) {
-          const float4 q4 = *reinterpret_cast<const float4*>(col + l);
-          acc = acc + q4.x;
-          acc = acc + q4.y;
-          acc = acc + q4.z;
-          acc = acc + q4.w;
-        }
-        for (; l < cnt; ++l) acc = acc + col[l];
+        acc = column_sum(tile + lane * TILE_STRIDE, cnt, acc);
       }
       wave_sync();
     }
@@ -390,27 +412,31 @@ __device__ __forceinline__ void store_pose(float4* pos, const MoveState<NSLOT>& 
   }
 }
 
-// LDS of one refinement wavefront in float4: pose, gradient tile, bond atoms,
-// 1/lengths, bond steps, bond gradients, gradient results.  The clash pass's
-// copy of the first atoms runs from the pose into the tile's first 32 * nslot
-// float4; the torsion matrices sit in the tile after it.
-constexpr int refine_wave_float4(int nslot) { return 64 * nslot + 16 + 8 + 8 + 8 + GRAD_LDS_FLOAT4; }
-constexpr int refine_mats_float4(int nslot) { return 32 * nslot; }
-static_assert(refine_mats_float4(4) + 3 * 33 <= TILE_FLOATS / 4, "wrap copy and the matrices fit in the tile");
+// LDS of one refinement wavefront in float4: the pose with the clash pass's copy of
+// its first atoms and the torsion matrices behind it, and in the same place the
+// gradient tile (the pose is last read, for the bond axes, before the columns are
+// written, and stored again after the step); then bond atoms, 1/lengths, bond
+// steps, bond gradients, gradient results.
+constexpr int refine_mats_float4(int nslot) { return 96 * nslot; }
+constexpr int refine_shared_float4(int nslot, int cols) {
+  const int tile = tile_floats(cols) / 4, pose = refine_mats_float4(nslot) + 3 * 33;
+  return tile > pose ? tile : pose;
+}
+constexpr int refine_wave_float4(int nslot, int cols) {
+  return refine_shared_float4(nslot, cols) + 16 + 8 + 8 + 8 + GRAD_RES_FLOATS / 4;
+}
 
-template <int NSLOT>
-__global__ __launch_bounds__(256) void refine_kernel(GridDev G, LigDev P, RefineDev Rp, int n) {
-  extern __shared__ float4 lds[];
-  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id();
-  float4* pos = lds + (size_t)wave * refine_wave_float4(NSLOT);
-  float* tile = reinterpret_cast<float*>(pos + 64 * NSLOT);   // column sums of the gradient; then wrap copy + matrices
-  int2* tors = reinterpret_cast<int2*>(tile + TILE_FLOATS);   // 32 entries (16 float4)
+// Pose w of a launch: member w % kpl of its ligand w / kpl, by one wavefront with
+// refine_wave_float4(NSLOT, COLS) of LDS at pos.
+template <int NSLOT, int COLS>
+__device__ __forceinline__ void refine_pose(const GridDev& G, const LigDev& P, const RefineDev& Rp, float4* pos, int w) {
+  const int lane = lane_id();
+  float* tile = reinterpret_cast<float*>(pos);                // column sums of the gradient, over the pose
+  int2* tors = reinterpret_cast<int2*>(pos + refine_shared_float4(NSLOT, COLS));   // 32 entries (16 float4)
   float* inv_len = reinterpret_cast<float*>(tors + 32);       // 32 entries (8 float4)
   float* th = inv_len + 32;                                   // 32 bond steps (8 float4)
   float* thg = th + 32;                                       // 32 bond gradients (8 float4)
   float* res = thg + 32;                                      // gradient results
-  const int w = blockIdx.x * nwaves + wave;   // pose: member w % kpl of the launch's ligand w / kpl
-  if (w >= n) return;
   const int li = w / Rp.kpl, member = w - li * Rp.kpl;
   const int lig = Rp.lig_ids ? __builtin_amdgcn_readfirstlane(Rp.lig_ids[li]) : li;
   const int i = lig * Rp.kpl + member;        // pose index in the caller's layout
@@ -465,7 +491,8 @@ __global__ __launch_bounds__(256) void refine_kernel(GridDev G, LigDev P, Refine
   for (int step = 0; step < Rp.steps; ++step) {
     if (fresh) {
       ax = lane_axis(pos, tors, inv_len, K);
-      const float sc = move_gradient(G, cur, mk, N, K, tors, pos, ax, g, thg, tile, res);
+      wave_sync();
+      const float sc = move_gradient<NSLOT, COLS>(G, cur, mk, N, K, tors, pos, ax, g, thg, tile, res);
       wave_sync();
       if (pending && sc > best_s) {
         best_s = sc;
@@ -529,7 +556,7 @@ __global__ __launch_bounds__(256) void refine_kernel(GridDev G, LigDev P, Refine
         mats[3 * lane + 2] = make_float4(m[6], m[7], m[8], ax.za);
       }
       wave_sync();
-      apply_torsions_table(cand, mv, K, th, mats);
+      apply_torsions_table(cand, mv, (uint32_t)__ballot(thk != 0.f), mats);
       apply_rigid_table(cand, q, rot, mats + 3 * K);
     } else {
       wave_sync();
@@ -568,6 +595,15 @@ __global__ __launch_bounds__(256) void refine_kernel(GridDev G, LigDev P, Refine
   if (lane == 0) Rp.score[i] = best_s;
 }
 
+template <int NSLOT>
+__global__ __launch_bounds__(256) void refine_kernel(GridDev G, LigDev P, RefineDev Rp, int n) {
+  extern __shared__ float4 lds[];
+  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+  const int w = blockIdx.x * nwaves + wave;
+  if (w >= n) return;
+  refine_pose<NSLOT, tile_cols(NSLOT)>(G, P, Rp, lds + (size_t)wave * refine_wave_float4(NSLOT, tile_cols(NSLOT)), w);
+}
+
 // ---- two poses per wavefront (ligands of at most 32 atoms) -------------------
 // Poses 2m and 2m + 1 of one ligand share a wavefront: pose h = lane / 32 in
 // lanes 32 h .. 32 h + 31, atom a in lane 32 h + a.  Both halves have the same
@@ -578,7 +614,8 @@ __global__ __launch_bounds__(256) void refine_kernel(GridDev G, LigDev P, Refine
 // script, the same clash rule.  A wavefront without a second pose (odd k)
 // refines the first pose twice and stores it once.
 constexpr int PAIR_STRIDE = 36;                              // 32 atoms + pad, 16-byte aligned columns
-constexpr int PAIR_TILE_FLOATS = TILE_COLS * PAIR_STRIDE;    // per half
+constexpr int PAIR_COLS = 16;   // per half, of 32 lanes
+constexpr int PAIR_TILE_FLOATS = PAIR_COLS * PAIR_STRIDE;    // per half
 constexpr int PAIR_POS_FLOAT4 = 48;                          // 32 atoms + the clash pass's wrap copy
 static_assert(PAIR_TILE_FLOATS / 4 >= 3 * 32, "the matrices of 31 bonds and the rigid move fit in a half's tile");
 // LDS of one wavefront in float4: poses, tiles, bond atoms, 1/lengths, steps,
@@ -614,7 +651,7 @@ __device__ float pair_move_gradient(const GridDev& G, const PairPose& p, uint32_
   const float v = la < N ? trilinear(G, p.x[0], p.x[1], p.x[2], gg) : 0.f;
   for (int k0 = 0, first = 1; first || k0 < K; first = 0) {
     const int base = first ? 7 : 0;
-    const int nb = min(K - k0, (TILE_COLS - base) / 3);
+    const int nb = min(K - k0, (PAIR_COLS - base) / 3);
     const int ncol = base + 3 * nb;
     const int col0 = first ? 0 : 7 + 3 * k0;
     if (first) {
@@ -623,9 +660,10 @@ __device__ float pair_move_gradient(const GridDev& G, const PairPose& p, uint32_
       tile_h[1 * PAIR_STRIDE + la] = gg[0];
       tile_h[2 * PAIR_STRIDE + la] = gg[1];
       tile_h[3 * PAIR_STRIDE + la] = gg[2];
-      tile_h[4 * PAIR_STRIDE + la] = r1 * gg[2] - r2 * gg[1];
-      tile_h[5 * PAIR_STRIDE + la] = r2 * gg[0] - r0 * gg[2];
-      tile_h[6 * PAIR_STRIDE + la] = r0 * gg[1] - r1 * gg[0];
+      const bool in = la < N;
+      tile_h[4 * PAIR_STRIDE + la] = in ? r1 * gg[2] - r2 * gg[1] : 0.f;
+      tile_h[5 * PAIR_STRIDE + la] = in ? r2 * gg[0] - r0 * gg[2] : 0.f;
+      tile_h[6 * PAIR_STRIDE + la] = in ? r0 * gg[1] - r1 * gg[0] : 0.f;
     }
     for (int kk = 0; kk < nb; ++kk) {
       const int k = k0 + kk;
@@ -640,16 +678,7 @@ __device__ float pair_move_gradient(const GridDev& G, const PairPose& p, uint32_
     wave_sync();
     float acc = 0.f;
     if (la < ncol) {
-      const float* col = tile_h + la * PAIR_STRIDE;
-      int l = 0;
-      for (; l + 4 <= N; l += 4) {
-        const float4 q4 = *reinterpret_cast<const float4*>(col + l);
-        acc = acc + q4.x;
-        acc = acc + q4.y;
-        acc = acc + q4.z;
-        acc = acc + q4.w;
-      }
-      for (; l < N; ++l) acc = acc + col[l];
+      acc = column_sum(tile_h + la * PAIR_STRIDE, N, acc);
     }
     wave_sync();
     if (la < ncol) res_h[col0 + la] = acc;
@@ -721,11 +750,11 @@ __device__ __forceinline__ void pair_store_pose(float4* pos_h, const PairPose& p
   if (wrap && la < full) pos_h[N + la] = v;
 }
 
-__global__ __launch_bounds__(256) void refine_pair_kernel(GridDev G, LigDev P, RefineDev Rp, int n_pairs) {
-  extern __shared__ float4 lds[];
-  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id();
+// Pair w of a launch: members 2m, 2m + 1 of its ligand w / ppl, by one wavefront
+// with pair_wave_float4() of LDS at base4.
+__device__ __forceinline__ void refine_pair(const GridDev& G, const LigDev& P, const RefineDev& Rp, float4* base4, int w) {
+  const int lane = lane_id();
   const int h = lane >> 5, la = lane & 31;
-  float4* base4 = lds + (size_t)wave * pair_wave_float4();
   float4* pos_h = base4 + h * PAIR_POS_FLOAT4;
   float* tile_h = reinterpret_cast<float*>(base4 + 2 * PAIR_POS_FLOAT4) + h * PAIR_TILE_FLOATS;
   int2* tors = reinterpret_cast<int2*>(base4 + 2 * PAIR_POS_FLOAT4 + 2 * PAIR_TILE_FLOATS / 4);   // 32 entries
@@ -733,8 +762,6 @@ __global__ __launch_bounds__(256) void refine_pair_kernel(GridDev G, LigDev P, R
   float* th_h = inv_len + 32 + h * 32;        // bond steps of this half's pose
   float* thg_h = inv_len + 96 + h * 32;       // bond gradients
   float* res_h = inv_len + 160 + h * GRAD_RES_FLOATS;
-  const int w = blockIdx.x * nwaves + wave;   // pair w: members 2m, 2m + 1 of ligand w / ppl
-  if (w >= n_pairs) return;
   const int ppl = (Rp.kpl + 1) >> 1;
   const int li = w / ppl, m = w - li * ppl;
   const int lig = Rp.lig_ids ? __builtin_amdgcn_readfirstlane(Rp.lig_ids[li]) : li;
@@ -849,10 +876,12 @@ __global__ __launch_bounds__(256) void refine_pair_kernel(GridDev G, LigDev P, R
         mats[3 * la + 2] = make_float4(mm[6], mm[7], mm[8], ax.za);
       }
       wave_sync();
-      for (int k = K - 1; k >= 0; --k) {
-        const float ang = th_h[k];
-        if (!wave_any(ang != 0.f)) continue;
-        if (ang != 0.f && ((mv >> k) & 1u)) {
+      const uint64_t moved = __ballot(thk != 0.f);
+      const uint32_t mine = mv & (h ? (uint32_t)(moved >> 32) : (uint32_t)moved);
+      for (uint32_t turns = (uint32_t)moved | (uint32_t)(moved >> 32); turns != 0u;) {
+        const int k = 31 - __builtin_clz(turns);
+        turns &= ~(1u << k);
+        if ((mine >> k) & 1u) {
           const float4 r0 = mats[3 * k], r1 = mats[3 * k + 1], r2 = mats[3 * k + 2];
           const float mm[9] = {r0.x, r0.y, r0.z, r1.x, r1.y, r1.z, r2.x, r2.y, r2.z};
           float y0, y1, y2;
@@ -949,6 +978,50 @@ __global__ __launch_bounds__(256) void refine_pair_kernel(GridDev G, LigDev P, R
   }
 }
 
+__global__ __launch_bounds__(256) void refine_pair_kernel(GridDev G, LigDev P, RefineDev Rp, int n_pairs) {
+  extern __shared__ float4 lds[];
+  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+  const int w = blockIdx.x * nwaves + wave;
+  if (w >= n_pairs) return;
+  refine_pair(G, P, Rp, lds + (size_t)wave * pair_wave_float4(), w);
+}
+
+// Every size class of a batch in one launch, one wavefront per block, the largest
+// class first.  Launched one after another, each class waits for the slowest pose
+// of the one before (a pose's steps are a serial chain), and sizing the launches
+// waits for the class counts to come back to the host; here the blocks find their
+// pose from the bucket starts on the device.  WIDE: one or two passes over the
+// gradient's columns instead of LDS for more wavefronts.  10 poses a ligand, one
+// launch per class against this kernel: 100 ligands 1 511 us, 801 WIDE, 882 not;
+// 400 ligands 1 550, 798, 868; 800 ligands 1 660, 1 088, 907.
+template <int SLOTS, bool WIDE>
+__global__ __launch_bounds__(64) void refine_classes_kernel(GridDev G, LigDev P, RefineDev Rp, const int32_t* perm,
+                                                          const int32_t* start, ClusterBounds cb, int pairs) {
+  extern __shared__ float4 lds[];
+  int w = blockIdx.x;
+  const int ppl = (Rp.kpl + 1) >> 1;
+  for (int b = cb.na * cb.nr - 1; b >= 0; --b) {
+    const int b0 = __builtin_amdgcn_readfirstlane(start[b]), cnt = __builtin_amdgcn_readfirstlane(start[b + 1]) - b0;
+    const bool pair = pairs && b == 0;   // at most 32 atoms and 31 bonds
+    const int waves = cnt * (pair ? ppl : Rp.kpl);
+    if (w >= waves) {
+      w -= waves;
+      continue;
+    }
+    Rp.lig_ids = perm + b0;
+    const int slots = (cb.atom[b / cb.nr] + 63) / 64;
+    if (pair)
+      refine_pair(G, P, Rp, lds, w);
+    else if (slots == 1)
+      refine_pose<1, WIDE ? WIDE_COLS : tile_cols(1)>(G, P, Rp, lds, w);
+    else if (SLOTS >= 2 && slots == 2)
+      refine_pose<(SLOTS >= 2 ? 2 : 1), WIDE ? WIDE_COLS : tile_cols(2)>(G, P, Rp, lds, w);
+    else if (SLOTS >= 4 && slots <= 4)
+      refine_pose<(SLOTS >= 4 ? 4 : 1), WIDE ? WIDE_COLS : tile_cols(4)>(G, P, Rp, lds, w);
+    return;
+  }
+}
+
 // Score of poses moved by given local parameters, and the gradient with respect
 // to those parameters: each pose i is moved by q_i = (t, w, theta) (layout of
 // lg_score's gradient: 6 i + tors_offset[i]), scored (trilinear, atom order) and
@@ -961,12 +1034,12 @@ __global__ __launch_bounds__(256) void score_moves_kernel(GridDev G, LigDev P, c
                                                           float* score, float* grad) {
   extern __shared__ float4 lds[];
   const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id();
-  float4* pos = lds + (size_t)wave * (64 * NSLOT + 32 + GRAD_LDS_FLOAT4);
+  float4* pos = lds + (size_t)wave * (64 * NSLOT + 32 + grad_lds_float4(tile_cols(NSLOT)));
   int2* tors = reinterpret_cast<int2*>(pos + 64 * NSLOT);     // 32 entries
   float* inv_len = reinterpret_cast<float*>(tors + 32);       // 32 entries
   float* th = inv_len + 32;                                   // 32 entries
   float* tile = th + 32;
-  float* res = tile + TILE_FLOATS;
+  float* res = tile + tile_floats(tile_cols(NSLOT));
   const int i = blockIdx.x * nwaves + wave;
   if (i >= n) return;
   const int abase = __builtin_amdgcn_readfirstlane(P.atom_offset[i]);
@@ -1001,7 +1074,7 @@ __global__ __launch_bounds__(256) void score_moves_kernel(GridDev G, LigDev P, c
   float g[6];
   wave_sync();
   const LaneAxis ax = lane_axis(pos, tors, inv_len, K);
-  const float sc = move_gradient(G, p, mk, N, K, tors, pos, ax, g, th, tile, res);
+  const float sc = move_gradient<NSLOT, tile_cols(NSLOT)>(G, p, mk, N, K, tors, pos, ax, g, th, tile, res);
   wave_sync();
   if (lane == 0) score[i] = sc;
   if (!grad) return;
@@ -1039,7 +1112,7 @@ hipError_t launch_score_moves(int nslot, const GridDev& G, const LigDev& P, cons
   if (n == 0) return hipSuccess;
   const int wpb = 4;
   const dim3 grid((n + wpb - 1) / wpb), block(64 * wpb);
-  const size_t lds_bytes = (size_t)wpb * (64 * nslot + 32 + GRAD_LDS_FLOAT4) * sizeof(float4);
+  const size_t lds_bytes = (size_t)wpb * (64 * nslot + 32 + grad_lds_float4(tile_cols(nslot))) * sizeof(float4);
   switch (nslot) {
     case 1: hipLaunchKernelGGL(score_moves_kernel<1>, grid, block, lds_bytes, st, G, P, moves, n, score, grad); break;
     case 2: hipLaunchKernelGGL(score_moves_kernel<2>, grid, block, lds_bytes, st, G, P, moves, n, score, grad); break;
@@ -1050,14 +1123,14 @@ hipError_t launch_score_moves(int nslot, const GridDev& G, const LigDev& P, cons
   return hipGetLastError();
 }
 
-static size_t refine_lds(int nslot, int wpb) { return (size_t)wpb * refine_wave_float4(nslot) * sizeof(float4); }
+static size_t refine_lds(int nslot, int wpb) { return (size_t)wpb * refine_wave_float4(nslot, tile_cols(nslot)) * sizeof(float4); }
 
 // Two poses per wavefront for ligands of at most 32 atoms: n_lig ligands of the
 // launch (Rp.lig_ids, or 0..n_lig-1), ceil(kpl / 2) wavefronts each.
 hipError_t launch_refine_pair(const GridDev& G, const LigDev& P, const RefineDev& Rp, int n_lig, hipStream_t st) {
   const long long waves = (long long)n_lig * ((Rp.kpl + 1) / 2);
   if (waves == 0) return hipSuccess;
-  const int wpb = 4;
+  const int wpb = 2;
   const dim3 grid((unsigned)((waves + wpb - 1) / wpb)), block(64 * wpb);
   const size_t lds_bytes = (size_t)wpb * pair_wave_float4() * sizeof(float4);
   hipLaunchKernelGGL(refine_pair_kernel, grid, block, lds_bytes, st, G, P, Rp, (int)waves);
@@ -1066,7 +1139,7 @@ hipError_t launch_refine_pair(const GridDev& G, const LigDev& P, const RefineDev
 
 hipError_t launch_refine(int nslot, const GridDev& G, const LigDev& P, const RefineDev& Rp, int n, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  const int wpb = 4;
+  const int wpb = 2;
   const dim3 grid((n + wpb - 1) / wpb), block(64 * wpb);
   switch (nslot) {
     case 1: hipLaunchKernelGGL(refine_kernel<1>, grid, block, refine_lds(1, wpb), st, G, P, Rp, n); break;
@@ -1075,6 +1148,26 @@ hipError_t launch_refine(int nslot, const GridDev& G, const LigDev& P, const Ref
     case 4: hipLaunchKernelGGL(refine_kernel<4>, grid, block, refine_lds(4, wpb), st, G, P, Rp, n); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+// All classes of a batch whose buckets (perm, start: device) launch_bucketing made
+// with cb; the largest ligand has max_atoms atoms, poses: those of the whole batch.
+hipError_t launch_refine_classes(int max_atoms, const GridDev& G, const LigDev& P, const RefineDev& Rp,
+                               const int32_t* perm, const int32_t* start, const ClusterBounds& cb, bool pairs,
+                               int poses, bool wide, hipStream_t st) {
+  if (poses == 0) return hipSuccess;
+  const int slots = max_atoms <= 64 ? 1 : max_atoms <= 128 ? 2 : 4;
+  const size_t bytes =
+      (size_t)std::max(refine_wave_float4(slots, wide ? WIDE_COLS : tile_cols(slots)), pair_wave_float4()) * sizeof(float4);
+  const dim3 grid(poses), block(64);
+#define LG_CLASSES(S, W) hipLaunchKernelGGL((refine_classes_kernel<S, W>), grid, block, bytes, st, G, P, Rp, perm, start, cb, pairs)
+  if (wide) {
+    if (slots == 1) LG_CLASSES(1, true); else if (slots == 2) LG_CLASSES(2, true); else LG_CLASSES(4, true);
+  } else {
+    if (slots == 1) LG_CLASSES(1, false); else if (slots == 2) LG_CLASSES(2, false); else LG_CLASSES(4, false);
+  }
+#undef LG_CLASSES
   return hipGetLastError();
 }
 
