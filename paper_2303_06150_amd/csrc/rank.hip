@@ -18,10 +18,11 @@
 // counted in LDS, and the result goes straight to its place; larger m: a
 // descending bitonic sort of the m keys (tile sorts in LDS, global merge steps).
 //
-// What bounds it: the launches (nine of 2 to 6 us), then the read of the scores
-// (29 us for 32 MB).  One million groups of eight values, m = 1000, a whole call:
-// 156 us with byte digits (a histogram and a pick launch each, 64-bit keys read
-// up to nine times) and a sort of the candidates by one block, 59 us as it is.
+// What bounds it: the launches (nine of 2 to 6 us), then the read of the scores.
+// One million groups of eight values, m = 1000, a whole call: 156 us with byte
+// digits (a histogram and a pick launch each, 64-bit keys read up to nine times)
+// and a sort of the candidates by one block, 59 us with the keys' values staged
+// through LDS (29 us for 32 MB), 41 us as it is.
 // At most 4096 groups: one launch.
 #include "lg.h"
 #include "lg_internal.h"
@@ -82,34 +83,84 @@ __device__ __forceinline__ void add_bins(const uint32_t* lh, uint32_t* hist) {
     if (lh[b]) atomicAdd(&hist[b], lh[b]);
 }
 
-// Value words of all groups and the histogram of their top digit.  A block takes
-// 256 groups at a time: their values are one stretch, read coalesced into LDS
-// (groups of up to kStageGroup values; larger ones are long stretches themselves).
+// Value words of all groups and the histogram of their top digit.  Bound by the
+// read of the scores, so by the bytes in flight.  VEC (groups of whole, aligned
+// float4): a thread reads its groups' values itself, kGroupsInFlight groups at a
+// time; few large blocks, because each adds its histogram to the global one and
+// those additions are contended (a whole ranking of one million groups of eight:
+// 59 us through LDS, 43 with 512 blocks of 256, 41 with 256 of 1 024).  Otherwise a
+// block takes 256 groups at a time, whose values are one stretch, read coalesced
+// into LDS (groups of up to kStageGroup values; larger ones are long stretches
+// themselves).
 constexpr int kStageGroup = 24;
+constexpr int kGroupsInFlight = 2, kKeyThreads = 1024;
 
-__global__ __launch_bounds__(256) void rank_keys_kernel(const float* score, int n, int group, uint32_t* words,
-                                                        uint32_t* hist) {
+template <bool VEC>
+__global__ __launch_bounds__(VEC ? kKeyThreads : 256) void rank_keys_kernel(const float* score, int n, int group,
+                                                                            uint32_t* words, uint32_t* hist) {
   __shared__ uint32_t lh[kBins];
-  __shared__ float vals[256 * kStageGroup];
   for (int b = threadIdx.x; b < kBins; b += blockDim.x) lh[b] = 0;
   __syncthreads();
-  const bool stage = group <= kStageGroup;
-  for (long long g0 = blockIdx.x * 256LL; g0 < n; g0 += gridDim.x * 256LL) {
-    const int groups = (int)min(256LL, n - g0);
-    if (stage) {
-      const float* src = score + g0 * group;
-      for (int t = threadIdx.x; t < groups * group; t += 256) vals[t] = src[t];
-      __syncthreads();
+  auto put = [&](long long g, float v) {
+    const uint32_t w = (uint32_t)(rank_key(v, 0) >> 32);
+    words[g] = w;
+    atomicAdd(&lh[w >> 21], 1u);
+  };
+  if constexpr (VEC) {
+    constexpr int U = kGroupsInFlight;
+    for (long long g0 = blockIdx.x * ((long long)kKeyThreads * U); g0 < n; g0 += gridDim.x * ((long long)kKeyThreads * U)) {
+      const float4* src[U];
+      float best[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {   // past the last group: that one again, not stored
+        const long long g = min(g0 + kKeyThreads * u + threadIdx.x, n - 1LL);
+        src[u] = reinterpret_cast<const float4*>(score + g * group);
+      }
+      auto add = [&](float v, float& b) { b = v > b ? v : b; };
+      for (int t = 0; t < group / 4; t += 2) {
+        const int t1 = min(t + 1, group / 4 - 1);   // an odd count: the last four again, which changes nothing
+        float4 q[U], r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          q[u] = src[u][t];
+          r[u] = src[u][t1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (t == 0) best[u] = q[u].x;
+          add(q[u].x, best[u]);
+          add(q[u].y, best[u]);
+          add(q[u].z, best[u]);
+          add(q[u].w, best[u]);
+          add(r[u].x, best[u]);
+          add(r[u].y, best[u]);
+          add(r[u].z, best[u]);
+          add(r[u].w, best[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const long long g = g0 + kKeyThreads * u + threadIdx.x;
+        if (g < n) put(g, best[u]);
+      }
     }
-    if ((int)threadIdx.x < groups) {
-      int member;
-      const float v = stage ? group_best(vals + (int)threadIdx.x * group, group, &member)
-                            : group_best(score + (g0 + threadIdx.x) * group, group, &member);
-      const uint32_t w = (uint32_t)(rank_key(v, 0) >> 32);
-      words[g0 + threadIdx.x] = w;
-      atomicAdd(&lh[w >> 21], 1u);
+  } else {
+    __shared__ float vals[256 * kStageGroup];
+    const bool stage = group <= kStageGroup;
+    for (long long g0 = blockIdx.x * 256LL; g0 < n; g0 += gridDim.x * 256LL) {
+      const int groups = (int)min(256LL, n - g0);
+      if (stage) {
+        const float* src = score + g0 * group;
+        for (int t = threadIdx.x; t < groups * group; t += 256) vals[t] = src[t];
+        __syncthreads();
+      }
+      if ((int)threadIdx.x < groups) {
+        int member;
+        put(g0 + threadIdx.x, stage ? group_best(vals + (int)threadIdx.x * group, group, &member)
+                                    : group_best(score + (g0 + threadIdx.x) * group, group, &member));
+      }
+      if (stage) __syncthreads();
     }
-    if (stage) __syncthreads();
   }
   add_bins(lh, hist);
 }
@@ -166,6 +217,24 @@ __device__ __forceinline__ RankState rank_pick(RankState st, const uint32_t* his
   return out;
 }
 
+// Keys i0 .. i1 - 1 (i0 a multiple of 4) handed to f, four words a read and two
+// reads in flight, by thread `t` of `threads`.  The words' space is whole float4.
+template <class F>
+__device__ __forceinline__ void for_each_key(const uint32_t* words, long long i0, long long i1, int t, int threads, F f) {
+  const uint4* q = reinterpret_cast<const uint4*>(words);
+  const long long end = (i1 + 3) / 4;
+  for (long long j = i0 / 4 + t; j < end; j += 2LL * threads) {
+    const long long j2 = j + threads;
+    const uint4 a = q[j], b = q[min(j2, end - 1)];
+    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const long long i = 4 * (e < 4 ? j : j2) + (e & 3);
+      if (i < i1) f(((uint64_t)w[e] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i));
+    }
+  }
+}
+
 // Digit d - 1 picked, digit d counted among the keys that match it.
 __global__ __launch_bounds__(256) void rank_digit_kernel(const uint32_t* words, int n, RankState* states,
                                                          uint32_t* hist, int d, uint32_t room, uint32_t m) {
@@ -177,11 +246,9 @@ __global__ __launch_bounds__(256) void rank_digit_kernel(const uint32_t* words, 
   __syncthreads();
   const int shift = digit_shift(d);
   const uint32_t bins = digit_mask(d);
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint64_t k = ((uint64_t)words[i] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
+  for_each_key(words, 0, n, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, [&](uint64_t k) {
     if ((k & st.mask) == st.prefix) atomicAdd(&lh[(uint32_t)(k >> shift) & bins], 1u);
-  }
+  });
   add_bins(lh, hist + d * kBins);
 }
 
@@ -197,11 +264,10 @@ __global__ __launch_bounds__(256) void rank_compact_kernel(const uint32_t* words
   const uint64_t t = st.prefix;
   const long long per = ((n + (long long)gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
   const long long i0 = blockIdx.x * per, i1 = min((long long)n, i0 + per);
-  auto key = [&](long long i) { return ((uint64_t)words[i] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i); };
   if (threadIdx.x == 0) taken = 0;
   __syncthreads();
   uint32_t mine = 0;
-  for (long long i = i0 + threadIdx.x; i < i1; i += 256) mine += key(i) >= t ? 1u : 0u;
+  for_each_key(words, i0, i1, threadIdx.x, 256, [&](uint64_t k) { mine += k >= t ? 1u : 0u; });
   mine = (uint32_t)wave_reduce_i32((int)mine, OpAdd());
   if (lane_id() == 0 && mine) atomicAdd(&taken, mine);
   __syncthreads();
@@ -210,12 +276,11 @@ __global__ __launch_bounds__(256) void rank_compact_kernel(const uint32_t* words
     taken = 0;
   }
   __syncthreads();
-  for (long long i = i0 + threadIdx.x; i < i1; i += 256) {
-    const uint64_t k = key(i);
-    if (k < t) continue;
+  for_each_key(words, i0, i1, threadIdx.x, 256, [&](uint64_t k) {
+    if (k < t) return;
     const uint32_t at = base + atomicAdd(&taken, 1u);
     if (at < room) cand[at] = k;
-  }
+  });
   for (long long i = m + blockIdx.x * 256LL + threadIdx.x; i < fill; i += gridDim.x * 256LL) cand[i] = 0;
 }
 
@@ -390,14 +455,18 @@ hipError_t launch_rank(const float* score, int n, int group, int m, void* work, 
   // less than another digit); more: exactly the top m
   const bool one_tile = m <= kTile;
   const uint32_t room = one_tile ? (uint32_t)std::min(kTile, m + std::max(256, m / 4)) : (uint32_t)m;
-  // at most two blocks per compute unit (each adds its histogram to the global
-  // one), at least four groups per thread
+  // each block adds its histogram to the global one: at most one per compute unit
+  // (two where the keys come through LDS), at least four groups per thread
   const int blocks = (int)std::max<long long>(1, std::min<long long>(((long long)n + 1023) / 1024, 512));
+  const int few = std::min(blocks, 256);
   hipLaunchKernelGGL(rank_init_kernel, dim3(12), dim3(256), 0, st, states, hist, m);
-  hipLaunchKernelGGL(rank_keys_kernel, dim3(blocks), dim3(256), 0, st, score, n, group, words, hist);
+  if (group % 4 == 0 && (uintptr_t)score % 16 == 0)
+    hipLaunchKernelGGL(rank_keys_kernel<true>, dim3(few), dim3(kKeyThreads), 0, st, score, n, group, words, hist);
+  else
+    hipLaunchKernelGGL(rank_keys_kernel<false>, dim3(blocks), dim3(256), 0, st, score, n, group, words, hist);
   for (int d = 1; d < kDigits; ++d)
-    hipLaunchKernelGGL(rank_digit_kernel, dim3(blocks), dim3(256), 0, st, words, n, states, hist, d, room, (uint32_t)m);
-  hipLaunchKernelGGL(rank_compact_kernel, dim3(std::min(blocks, 256)), dim3(256), 0, st, words, n, states, hist, cand, room,
+    hipLaunchKernelGGL(rank_digit_kernel, dim3(few), dim3(256), 0, st, words, n, states, hist, d, room, (uint32_t)m);
+  hipLaunchKernelGGL(rank_compact_kernel, dim3(few), dim3(256), 0, st, words, n, states, hist, cand, room,
                      (uint32_t)m, one_tile ? 0LL : padded);
   if (one_tile) {
     hipLaunchKernelGGL(rank_place_kernel, dim3((room + kPlaces - 1) / kPlaces), dim3(256), 0, st, cand, states, score, n, group, m, top_idx,
