@@ -38,17 +38,15 @@ sys.path.insert(0, ROOT)
 PEAK_LANE_OPS = 256 * 4 * 32 * 2.4e9
 VALU_PROBE_MIX = 6   # lg_valu_probe kind: the nearest-node index sequence of a scan sample
 
-# VALU instructions per lane, per unit of work, in the inner loops of the docking
-# scans, counted in the gfx950 assembly of dock_bucket_kernel<1, 4> (four samples
-# per lane, loop control included), for the variants a scan takes when every
-# sample's node is inside the grid (the usual case): a loop pass of the rotation
-# scan handles two atoms x four samples in 91 (the lane's four quarter-turn
-# samples share one 2-D rotation), of the staged translation scan one atom x four
-# samples in 25 (node values read from LDS; the group gathers that stage them are
-# not counted), of the torsion scan two moving atoms x two samples in 132 (the
-# per-atom set-up of the clash-pair loop included, the pair tests themselves
-# not); each torsion sample's rotation matrix takes 13.  Placement and the final
-# trilinear score are counted from the op script (15 and 45 per atom and restart).
+# VALU instructions per lane, per unit of work, of scans that score every sample
+# four per lane, loop control included: a pass of the rotation loop over two atoms
+# and four samples (one 2-D rotation for the lane's quarter turns) 91, of the
+# translation loop over one atom and four samples 25 (node values from LDS), of the
+# torsion loop over two moving atoms and two samples 132, a torsion sample's matrix
+# 13; placement and the final trilinear score 15 and 45 per atom and restart.  The
+# kernel bounds groups of samples from above and scores only those that may win, so
+# it issues less than this: the count is the work of an exhaustive scan, a
+# yardstick for the rate and not a hardware fraction.
 ISA_ROT = 91 / 8         # per (rotation sample, atom)
 ISA_TRANS = 25 / 4       # per (translation sample, atom)
 ISA_TORS = 132 / 4       # per (torsion sample, moving atom)
@@ -98,9 +96,9 @@ def _per_ligand(n_atoms, frag_sizes_per_lig, fn):
 
 
 def isa_ops(n_atoms, frag_sizes_per_lig, R, A, T, S):
-    """VALU lane-ops of docking each ligand: every sample of every scan at the
-    inner loops' per-unit instruction counts (a lower bound of what the kernel
-    issues: per-scan work and the tests of pairs that can clash are left out)."""
+    """VALU lane-ops of docking each ligand with every sample of every scan scored,
+    at per-unit instruction counts (per-scan work and the tests of pairs that can
+    clash left out)."""
     return _per_ligand(n_atoms, frag_sizes_per_lig, lambda N, mv: R * (
         S * (3 * A * N * ISA_ROT + 3 * T * N * ISA_TRANS + A * mv.sum() * ISA_TORS + len(mv) * A * ISA_TMAT)
         + N * (OPS_PLACE + OPS_TRI)))
@@ -572,7 +570,7 @@ def main():
     dom_ms = float(np.mean(bucket_ms[dom["bucket"]]))
     sel = bid == dom["bucket"]
     dom_ops, dom_plain, dom_looks = float(ops[sel].sum()), float(plain_ops[sel].sum()), float(looks[sel].sum())
-    kernel = f"dock_bucket_kernel<{dom['slots']},{dom['samples_per_lane']}>"
+    kernel = f"dock_bucket_kernel<{dom['slots']},false>"
     tune_key = tuning_key(tuning)
     # HBM bytes and VALU issue of the dominant launch, from the committed rocprofv3
     # counter summaries, when they were taken on this kernel source and tuning
@@ -582,21 +580,30 @@ def main():
     valu_issue = read_profile_value(f"{kernel_tag(dom)}_{args.workload}_valu.txt", "valu_issue_per_simd_cycle",
                                     tune_key)
     l2_hit = read_profile_value(f"{kernel_tag(dom)}_{args.workload}_valu.txt", "l2_hit", tune_key)
-    achieved = dom_ops / (dom_ms * 1e-3)
+    valu_insts = read_profile_value(f"{kernel_tag(dom)}_{args.workload}_valu.txt", "valu_insts_per_dispatch", tune_key)
+    # 64 lane-ops per VALU instruction that the counters saw; the counted launch docks
+    # this workload, so a subset of it has no figure
+    counted = 64.0 * valu_insts if valu_insts is not None and n == w.n_ligands else None
+    achieved = counted / (dom_ms * 1e-3) if counted is not None else None
     # the sustained rate of the scans' index arithmetic on this device, beside the peak
     valu_meas = lg.lg_valu_probe(pocket, VALU_PROBE_MIX, 2000)
-    roofline = dict(bound="alu", achieved=round(achieved / 1e12, 3), peak=round(PEAK_LANE_OPS / 1e12, 3),
-                    unit="TOP/s", frac=round(achieved / PEAK_LANE_OPS, 4), traffic=traffic, kernel=kernel,
-                    kernel_ms=round(dom_ms, 3), ligands_in_launch=int(dom["ligands"]),
-                    ops_per_launch=dom_ops,
-                    ops_basis="VALU lane-ops of the scans' inner loops, every sample of every scan (gfx950 "
-                              "assembly count per unit; pair tests and per-scan work not counted)",
+    roofline = dict(bound="alu", achieved=round(achieved / 1e12, 3) if achieved is not None else None,
+                    peak=round(PEAK_LANE_OPS / 1e12, 3), unit="TOP/s",
+                    frac=round(achieved / PEAK_LANE_OPS, 4) if achieved is not None else None, traffic=traffic,
+                    kernel=kernel, kernel_ms=round(dom_ms, 3), ligands_in_launch=int(dom["ligands"]),
+                    ops_per_launch=counted,
+                    ops_basis="VALU instructions of the launch (rocprofv3 counters on this kernel source) x 64 lanes",
+                    every_sample=dict(ops_per_launch=dom_ops, rate=round(dom_ops / (dom_ms * 1e-3) / 1e12, 3),
+                                      ratio_to_peak=round(dom_ops / (dom_ms * 1e-3) / PEAK_LANE_OPS, 3),
+                                      gather_bw=round(4.0 * dom_looks / (dom_ms * 1e-3) / 1e9, 1), gather_unit="GB/s",
+                                      basis="lane-ops and grid values of scoring every sample of every scan, four per lane; the "
+                                            "kernel rules most groups of samples out by a bound, so this is no "
+                                            "hardware fraction"),
                     valu_busy=valu_busy,
                     # every VALU instruction the counters saw, against gfx950's issue limit of one
                     # wave64 VALU instruction per SIMD per two cycles (the 78.6 T lane-op peak)
                     valu_issue_frac=round(2.0 * valu_issue, 4) if valu_issue is not None else None,
                     l2_hit=l2_hit,   # TCC hits / (hits + misses) of the launch: the grid stays L2-resident
-                    gather_bw=round(4.0 * dom_looks / (dom_ms * 1e-3) / 1e9, 1), gather_unit="GB/s",
                     measured_valu_peak=round(valu_meas / 1e12, 3),
                     plain_method=dict(ops_per_launch=dom_plain,
                                       rate=round(dom_plain / (dom_ms * 1e-3) / 1e12, 3),
@@ -605,7 +612,7 @@ def main():
                                             "32/23/37 per rotation/translation/torsion sample and atom, a "
                                             "pair test (8) of every moving and static atom for every "
                                             "torsion sample; a ratio above 1 is the speed-up of exact pair "
-                                            "pruning, not a hardware fraction"))
+                                            "pruning and sample bounds, not a hardware fraction"))
     total_ops = float(ops.sum())
 
     # ---- side runs: plain per-ligand launches, single-bucket ablation

@@ -397,7 +397,7 @@ typedef struct {
   int32_t atom_bound;        /* atoms <= atom_bound */
   int32_t rot_bound;         /* bonds <= rot_bound */
   int32_t slots;             /* atom slots per lane of the kernel instance */
-  int32_t samples_per_lane;
+  int32_t samples_per_lane;  /* of a scan that scores every sample: max(A, T) / 64, up to a power of two */
   int32_t waves_per_block;
   int32_t vgprs;             /* architected VGPRs per lane of the instance */
   int32_t lds_bytes;         /* LDS per block */

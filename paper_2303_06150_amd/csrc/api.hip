@@ -474,10 +474,15 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
   const int spl = spl_for(D.A, D.T);
 
   if (P->mode == LG_PLAIN) {
-    // the plain method: one launch per ligand, kernel sized for the largest class
-    const int nslot = LG_MAX_ATOMS / 64;
-    for (int i = 0; i < n; ++i)
-      LG_HIP(lg::launch_dock_plain(nslot, tu.plain_waves_per_block, p->grid, Lg, D, i, st));
+    // The plain method: one launch per ligand, by the instance that fits it (the
+    // batch's largest where the host has no offsets; 400 mixed ligands 160 ms by the
+    // four-slot instance, 149 by the two-slot one, 143 by their own), one wavefront
+    // per block while the restarts leave compute units idle (137 ms).
+    const int wpb = R <= 8 * p->cus ? 1 : tu.plain_waves_per_block;
+    for (int i = 0; i < n; ++i) {
+      const int atoms = L->atom_offset_host ? L->atom_offset_host[i + 1] - L->atom_offset_host[i] : max_atoms;
+      LG_HIP(lg::launch_dock_plain((atoms + 63) / 64, wpb, p->grid, Lg, D, i, st));
+    }
     LG_HIP(lg::launch_topk(topk_slots, Lg, D, n, P->top_k, O->score, O->restart_id, O->x, O->y, O->z, O->all_scores,
                            O->pivot, st));
     return LG_OK;

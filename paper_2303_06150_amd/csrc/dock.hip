@@ -14,6 +14,13 @@
 // scores).  Torsion samples are tested for intramolecular clashes against a
 // pruned list of the pairs that can clash at some angle.
 //
+// What bounds it: no single unit; vector issue, the gather path (about 27 cache
+// accesses for 64 scattered lookups) and LDS are each busy for about 70 % of the
+// time.  Against scoring every sample, four per lane: 20 000 mixed ligands of 256
+// restarts and 256 samples, two restarts per item, 457 -> 417 ms; 4 000 ligands of
+// up to 160 atoms in the default tuning 160 -> 91 ms, one ligand 2.17 -> 0.28 ms (with
+// shorter items for small launches).
+//
 // Outputs.  Each restart records its final score and the selected sample of
 // every scan (a few bytes per scan); the per-ligand top-k then rebuilds the k
 // kept poses by replaying their moves with the same apply functions the scans
@@ -447,7 +454,8 @@ __device__ __forceinline__ float larger(float a, float b) {
 // the groups survive; 1.6, 1.25, 1.14 passes (sweeps 1, 2, 3) instead of 4.
 // Runs longer than a wavefront (very wide translation ranges) fall back to
 // direct gathers of every sample, and so does STAGE = false (the plain launch,
-// where a lone wavefront per SIMD would wait on every group's nodes).
+// where a lone wavefront per SIMD would wait on every group's nodes) unless the
+// bound saves it passes.
 template <int NSLOT, int E, bool STAGE, int U>
 __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, float4* scr, float* stage,
                                           const Samples& sm, const int* tab) {
@@ -489,7 +497,7 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
   auto index = [&](int pos) { return pos + mlo < 0 ? pos + mlo + D.T : pos + mlo; };   // position: order of displacement
   auto none = [](int, bool) { return false; };
   int j;
-  if (!STAGE || span > 63) {
+  if ((!STAGE && !(sm.bound_t && D.T > 128)) || span > 63) {
     j = select_sample<true>(
         all, __builtin_inff(), sm.GT, D.T, 0.f, index,
         [&](int js) {
@@ -1039,9 +1047,12 @@ __global__ __launch_bounds__(256) void dock_plain_kernel(DockArgs X, int lig) {
   LigReg<NSLOT> L;
   load_ligand(X.Lg, lig, L);
   store_masks(L, B.mkl);
-  // one wavefront per restart: the staged translation scan's read-then-use of
-  // each group's nodes would expose their latency, so the gathers stay direct
-  dock_restart<NSLOT, false, 4>(kernel_args(), sm, L, lig, r, B);
+  // One wavefront per SIMD or less: latency, so more fetches in flight (400 mixed
+  // ligands of 256 restarts and 256 samples: 133 ms, 137 with four).  The staged
+  // translation scan's read-then-use of each group's nodes pays only where its
+  // bound saves passes (129 ms); with two passes or fewer the gathers stay direct
+  // (100 samples, 64 restarts: 95 ms, 99 staged).
+  dock_restart<NSLOT, false, 8>(kernel_args(), sm, L, lig, r, B);
 }
 
 // Bucketed method: persistent; wavefronts pull (ligand, restart chunk) items of
