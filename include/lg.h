@@ -166,7 +166,10 @@ typedef struct {
 
 /* Load a docking site: copies the grid (host or device memory, per
  * grid_is_device) into a library-owned device copy kept for the handle's
- * life.  *out receives the handle; the call synchronises `stream`. */
+ * life.  Finite grids of at most 2^25 padded nodes also get copies that bound
+ * the scans' scores, about eight times the grid's bytes of device memory; without
+ * them (or the memory) docking selects the same samples, more slowly.  *out
+ * receives the handle; the call synchronises `stream`. */
 lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t grid_is_device,
                          void* stream, lg_pocket* out);
 
@@ -175,7 +178,7 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
 lg_status lg_free_pocket(lg_pocket pocket);
 
 /* Dock a batch of ligands (Sec. 2 "dock", Sec. 3 buckets).  LG_PLAIN launches
- * one kernel per ligand sized for the largest class; LG_BUCKETED classifies
+ * one kernel per ligand, by the class instance that fits it; LG_BUCKETED classifies
  * ligands on the device by (atoms, bonds) into size buckets, docks every bucket
  * in one persistent launch of its class kernel pulling (ligand, restart) items
  * from a device queue, and replays the whole sequence as one HIP graph.  Every
@@ -297,8 +300,9 @@ lg_status lg_pack_moves(const int32_t* tors_offset, int32_t n, int32_t total_tor
  * the input) is written to x/y/z_out in the layout of the input coordinates,
  * its score to score_out [n*k].  One wavefront refines one pose; with k >= 2,
  * ligands of at most 32 atoms are refined two poses per wavefront (same
- * arithmetic per pose).  When the batch mixes size classes the call reads the
- * class counts back, which synchronises `stream`. */
+ * arithmetic per pose).  A large batch (more than 256 poses per compute unit)
+ * that mixes size classes reads the class counts back, which synchronises
+ * `stream`. */
 typedef struct {
   int32_t steps;
   float eta_t, eta_w, eta_th;
@@ -347,7 +351,9 @@ lg_status lg_rank_static(const float* score, int32_t n_groups, int32_t group_siz
  * by the kernel instance for ceil(atom bound / 64) atom slots per lane, with
  * waves_per_block[slots-1] wavefronts per block; its persistent grid is
  * grid_scale times the resident blocks of Eq. 1.  Work items are chunks of
- * restart_chunk restarts of one ligand.  Results do not depend on the tuning. */
+ * restart_chunk restarts of one ligand.  Launches too small to fill the device
+ * use smaller chunks and blocks than asked for.  Results do not depend on the
+ * tuning. */
 typedef struct {
   int32_t n_atom_clusters;        /* 1..16 */
   int32_t atom_bounds[16];        /* increasing, each 1..LG_MAX_ATOMS */
