@@ -14,9 +14,10 @@
 // scores).  Torsion samples are tested for intramolecular clashes against a
 // pruned list of the pairs that can clash at some angle.
 //
-// What bounds it: no single unit; vector issue, the gather path (about 27 cache
-// accesses for 64 scattered lookups) and LDS are each busy for about 70 % of the
-// time.  Against scoring every sample, four per lane: 20 000 mixed ligands of 256
+// What bounds it: each scan's fixed part and the latency of its gathers.  Vector
+// issue runs at 0.53 of its limit, the address unit is busy 84 % of the time (about
+// 27 cache accesses for 64 scattered lookups), L2 hits 99.1 % (mixed library).
+// Against scoring every sample, four per lane: 20 000 mixed ligands of 256
 // restarts and 256 samples, two restarts per item, 457 -> 417 ms; 4 000 ligands of
 // up to 160 atoms in the default tuning 160 -> 91 ms, one ligand 2.17 -> 0.28 ms (with
 // shorter items for small launches).
