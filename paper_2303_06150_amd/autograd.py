@@ -31,13 +31,15 @@ def move_layout(poses: lg.DeviceLigands):
 
 
 def _parameter(v, count, dev):
-    """v as `count` contiguous float32 values (a single value stands for all of them)."""
+    """v as `count` contiguous float32 values (a single value stands for all of them).
+    Slices, matrix columns and expanded values come with strides of their own: reshape
+    and float keep them, the pack kernel reads densely."""
     v = v.detach().reshape(-1).float()
     if v.numel() == 1 and count != 1:
-        v = v.to(dev).expand(count).contiguous()
+        v = v.to(dev).expand(count)
     if v.numel() != count or (count and v.device != dev):
         raise RuntimeError(f"{v.numel()} values on {v.device} given for {count} parameters on {dev}")
-    return v
+    return v.contiguous()
 
 
 class RefineScore(torch.autograd.Function):

@@ -444,6 +444,11 @@ def lg_pack_moves(poses: DeviceLigands, t, w, theta, stream=None):
     t, w, theta in it and of every bond's pose."""
     torch = _torch()
     dev, n, tors = poses.x.device, poses.n, poses.total_torsions
+    for name, v, count in (("t", t, 3 * n), ("w", w, 3 * n), ("theta", theta, tors)):
+        # the kernel reads `count` floats from the tensor's address
+        if count and (v.numel() != count or v.dtype != torch.float32 or v.device != dev or not v.is_contiguous()):
+            raise ValueError(f"{name}: {count} contiguous float32 values on {dev} wanted, got {tuple(v.shape)} "
+                             f"{v.dtype} on {v.device}, strides {v.stride()}")
     moves = torch.empty(max(6 * n + tors, 1), dtype=torch.float32, device=dev)
     idx_t, idx_w, idx_th, pose_of_bond = torch.empty(6 * n + 2 * tors, dtype=torch.int64, device=dev).split(
         (3 * n, 3 * n, tors, tors))

@@ -1,0 +1,59 @@
+"""Parameter tensors on their way to the pack kernel (no GPU): every layout that
+torch allows arrives as dense float32 values, and the binding refuses the others."""
+import types
+
+import pytest
+import torch
+
+from paper_2303_06150_amd import lg
+from paper_2303_06150_amd.autograd import _parameter
+
+CPU = torch.device("cpu")
+
+
+def layouts(count):
+    """Tensors of `count` values (or one for all) with every kind of stride, and the values they stand for."""
+    base = torch.arange(6.0 * max(count, 1)) + 1
+    rows = base.reshape(-1, 6)
+    return {
+        "dense": (base[:count], base[:count]),
+        "slice": (base[:2 * count:2], base[:2 * count:2].clone()),
+        "column": (rows[:count, 5], rows[:count, 5].clone()),
+        "reversed": (base[:count].flip(0), base[:count].flip(0).clone()),
+        "expanded": (torch.full((1,), 2.5).expand(count), torch.full((count,), 2.5)),
+        "single": (torch.full((1, 1), 2.5), torch.full((count,), 2.5)),
+        "scalar": (torch.tensor(2.5), torch.full((count,), 2.5)),
+        "double": (base[:2 * count:2].double(), base[:2 * count:2].clone()),
+    }
+
+
+@pytest.mark.parametrize("count", [0, 1, 3, 17])
+@pytest.mark.parametrize("kind", list(layouts(1)))
+def test_parameters_arrive_dense(count, kind):
+    if count == 0 and kind in ("single", "scalar"):
+        v, want = layouts(0)[kind]
+        assert _parameter(v, 0, CPU).numel() == 0
+        return
+    v, want = layouts(count)[kind]
+    got = _parameter(v.requires_grad_(True) if v.is_leaf else v, count, CPU)
+    assert got.is_contiguous() and got.dtype == torch.float32 and not got.requires_grad
+    assert got.untyped_storage().nbytes() >= 4 * (got.storage_offset() + count)
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n", [1, 4])
+def test_parameters_of_poses_arrive_dense(n):
+    """t and w as [n, 3] views: a transposed matrix, an expanded row, a strided matrix."""
+    m = torch.arange(24.0 * n).reshape(3, -1)
+    for v in (m[:, :n].t(), torch.ones(1, 1).expand(n, 3), torch.arange(12.0 * n).reshape(n, 12)[:, ::4]):
+        got = _parameter(v, 3 * n, CPU)
+        assert got.is_contiguous() and torch.equal(got, v.clone().reshape(-1))
+
+
+def test_binding_refuses_what_the_kernel_cannot_read():
+    poses = types.SimpleNamespace(x=torch.zeros(1), n=2, total_torsions=3, tors_offset=torch.zeros(3, dtype=torch.int32))
+    t, w, th = torch.zeros(6), torch.zeros(6), torch.zeros(3)
+    for bad in ((torch.zeros(12)[::2], w, th), (t, torch.zeros(5), th), (t, w, torch.zeros(1).expand(3)),
+                (t, w, th.double()), (t.to("meta"), w, th)):
+        with pytest.raises(ValueError, match="contiguous float32"):
+            lg.lg_pack_moves(poses, *bad)
