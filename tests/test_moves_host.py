@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2303_06150_amd import lg
-from paper_2303_06150_amd.autograd import _parameter
+from paper_2303_06150_amd.autograd import RefineScore, _parameter
 
 CPU = torch.device("cpu")
 
@@ -57,3 +57,35 @@ def test_binding_refuses_what_the_kernel_cannot_read():
                 (t, w, th.double()), (t.to("meta"), w, th)):
         with pytest.raises(ValueError, match="contiguous float32"):
             lg.lg_pack_moves(poses, *bad)
+
+
+def test_forward_runs_on_the_poses_device(monkeypatch):
+    """Both library calls happen with the poses' device current, whatever the caller's is."""
+    current = []
+
+    class Device:
+        def __init__(self, dev):
+            self.dev = dev
+
+        def __enter__(self):
+            current.append(self.dev)
+
+        def __exit__(self, *exc):
+            current.pop()
+
+    calls = []
+
+    def pack(poses, t, w, theta):
+        calls.append(("pack", list(current)))
+        return (torch.zeros(9), *(torch.arange(3),) * 4)
+
+    def score(pocket, poses, interp, grad, moves):
+        calls.append(("score", list(current)))
+        return dict(score=torch.ones(1), grad=torch.ones(9))
+
+    monkeypatch.setattr(torch.cuda, "device", Device)
+    monkeypatch.setattr(lg, "lg_pack_moves", pack)
+    monkeypatch.setattr(lg, "lg_score", score)
+    poses = types.SimpleNamespace(x=torch.zeros(1), n=1, total_torsions=3)
+    RefineScore.apply(torch.zeros(1, 3), torch.zeros(1, 3), torch.zeros(3), None, poses)
+    assert calls == [("pack", [CPU]), ("score", [CPU])] and current == []
