@@ -40,10 +40,14 @@ size_t workspace_limit() { return (size_t)env_ll("LG_WORKSPACE_LIMIT", (long lon
 namespace {
 
 // Whether every difference off[i + 1] - off[i] lies in lo .. hi (no early exit:
-// the loop vectorises).
+// the loop vectorises).  The subtraction is modulo 2^32; a decrease is refused by
+// itself, or offsets that run past 2^31 and around to the total again would pass.
 bool differences_within(const int32_t* off, int n, uint32_t lo, uint32_t hi) {
   uint32_t bad = 0;
-  for (int i = 0; i < n; ++i) bad |= (uint32_t)off[i + 1] - (uint32_t)off[i] - lo > hi - lo ? 1u : 0u;
+  for (int i = 0; i < n; ++i) {
+    bad |= (uint32_t)off[i + 1] - (uint32_t)off[i] - lo > hi - lo ? 1u : 0u;
+    bad |= off[i + 1] < off[i] ? 1u : 0u;
+  }
   return bad == 0;
 }
 
