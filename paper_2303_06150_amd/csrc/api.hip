@@ -77,6 +77,9 @@ using lghost::guarded;
   } while (0)
 
 constexpr size_t kMaxDilated = (size_t)1 << 25;   // padded nodes of the largest grid with dilated copies
+// bits of 2^118: the largest |value| of a grid with bounds, 2^10 times below the largest float
+constexpr uint32_t kMaxBounded = (118u + 127u) << 23;
+static_assert(LG_MAX_ATOMS <= 512, "sums of values below 2^118 stay finite");
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -273,7 +276,9 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
     G.nb4[a] = (G.n[a] + 2 + 3) / 4;
   }
   // the dilated copies only save work: grids of more than 2^25 nodes, or a device
-  // short of memory, do without, and so do grids with values that are not finite
+  // short of memory, do without, and so do grids with values that are not finite or
+  // whose sums over a ligand's atoms may not be (a sum that ran to infinity on the
+  // way is above the bound on its total)
   size_t stride = (size_t)128 * G.nb4[0] * G.nb4[1] * G.nb4[2];
   for (int e = 0; e < 3; ++e)
     stride = std::max(stride, (size_t)128 * (G.n[e] + 2) * G.nb8[(e + 1) % 3] * G.nb8[(e + 2) % 3]);
@@ -291,7 +296,7 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
         s = fail(LG_ERR_DEVICE, "reading the grid's largest value failed");
     }
   }
-  const bool finite = vmax_bits < 0x7F800000u;
+  const bool finite = vmax_bits < kMaxBounded;
   G.vmax = HUGE_VALF;
   if (finite) std::memcpy(&G.vmax, &vmax_bits, sizeof G.vmax);
   G.bound_scale = finite && G.vmax > 1e-30f ? G.vmax / 32000.f : 1.f;
