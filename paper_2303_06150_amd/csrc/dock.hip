@@ -667,10 +667,12 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, ui
       const float rho = prune_sqrt(fmaxf(ax * ax + ay * ay + az * az, bx * bx + by * by + bz * bz)) * 1.0001f;
       inside = inside && fmaf(sm.radius, rho, ulen * fabsf(h)) * ih <= reach;
       const float arc = sm.chord * rho;
-      const float del = fmaf(arc + ferr, ih, 4e-3f);
+      // rounding of the position: of the axis atom's part and of the turned vector's
+      const float verr = fmaf(1e-6f, rho + ulen * fabsf(h), ferr);
+      const float del = fmaf(arc + verr, ih, 4e-3f);
       const int l = del <= 0.5f ? 0 : del <= 1.5f ? 1 : 2;
       level = level && del <= 2.5f;
-      const float gap = D.clash - arc - ferr - 2e-3f;
+      const float gap = D.clash - arc - verr - 2e-3f;
       scr[at] = make_float4(vx, vy, vz, 0.f);
       aux[at] = make_float4(h, r, gap > 0.f ? gap * gap : 0.f, __int_as_float(l << 24));
     }
