@@ -77,9 +77,6 @@ using lghost::guarded;
   } while (0)
 
 constexpr size_t kMaxDilated = (size_t)1 << 25;   // padded nodes of the largest grid with dilated copies
-// bits of 2^118: the largest |value| of a grid with bounds, 2^10 times below the largest float
-constexpr uint32_t kMaxBounded = (118u + 127u) << 23;
-static_assert(LG_MAX_ATOMS <= 512, "sums of values below 2^118 stay finite");
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -276,9 +273,7 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
     G.nb4[a] = (G.n[a] + 2 + 3) / 4;
   }
   // the dilated copies only save work: grids of more than 2^25 nodes, or a device
-  // short of memory, do without, and so do grids with values that are not finite or
-  // whose sums over a ligand's atoms may not be (a sum that ran to infinity on the
-  // way is above the bound on its total)
+  // short of memory, do without, and so do grids with values that are not finite
   size_t stride = (size_t)128 * G.nb4[0] * G.nb4[1] * G.nb4[2];
   for (int e = 0; e < 3; ++e)
     stride = std::max(stride, (size_t)128 * (G.n[e] + 2) * G.nb8[(e + 1) % 3] * G.nb8[(e + 2) % 3]);
@@ -296,7 +291,7 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
         s = fail(LG_ERR_DEVICE, "reading the grid's largest value failed");
     }
   }
-  const bool finite = vmax_bits < kMaxBounded;
+  const bool finite = vmax_bits < 0x7F800000u;
   G.vmax = HUGE_VALF;
   if (finite) std::memcpy(&G.vmax, &vmax_bits, sizeof G.vmax);
   G.bound_scale = finite && G.vmax > 1e-30f ? G.vmax / 32000.f : 1.f;
@@ -450,7 +445,6 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
 
   int max_atoms = host_max_atoms, max_tors = host_max_tors;
   if (max_atoms < 0) host_maxima(L, &max_atoms, &max_tors);
-  const bool host_sized = max_atoms >= 0 && L->atom_offset_host;   // else the host's offsets are not what was checked
   if (max_atoms < 0) {
     s = check_on_device(p, L, stats, st, &max_atoms, &max_tors);
     if (s != LG_OK) return s;
@@ -481,12 +475,12 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
 
   if (P->mode == LG_PLAIN) {
     // The plain method: one launch per ligand, by the instance that fits it (the
-    // batch's largest where the sizes were taken from the device; 400 mixed ligands 160 ms by the
+    // batch's largest where the host has no offsets; 400 mixed ligands 160 ms by the
     // four-slot instance, 149 by the two-slot one, 143 by their own), one wavefront
     // per block while the restarts leave compute units idle (137 ms).
     const int wpb = R <= 8 * p->cus ? 1 : tu.plain_waves_per_block;
     for (int i = 0; i < n; ++i) {
-      const int atoms = host_sized ? L->atom_offset_host[i + 1] - L->atom_offset_host[i] : max_atoms;
+      const int atoms = L->atom_offset_host ? L->atom_offset_host[i + 1] - L->atom_offset_host[i] : max_atoms;
       LG_HIP(lg::launch_dock_plain((atoms + 63) / 64, wpb, p->grid, Lg, D, i, st));
     }
     LG_HIP(lg::launch_topk(topk_slots, Lg, D, n, P->top_k, O->score, O->restart_id, O->x, O->y, O->z, O->all_scores,

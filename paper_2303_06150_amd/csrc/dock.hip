@@ -145,7 +145,6 @@ struct Samples {
   int tsub;           // lanes that share a translation group in the bound pass (log2): 0, 1, 2
   int gt0;            // translation group of sample 0
   bool bound_a, bound_t;   // rotations and torsions, translations: a bound pass pays (and is possible)
-  float tspan, treach;     // nodes that a translation group and that all displacements span, each way
   float dlow;         // least displacement of the lane's translation group
   float radius;       // largest |(cos, sin)| of a sample (1 up to rounding)
   float chord;        // every sample of a group lies within chord of its centre, in (cos, sin)
@@ -192,11 +191,9 @@ __device__ __forceinline__ void load_samples(const GridDev& G, const DockDev& D,
   sm.tsub = 2;
   for (;; --sm.tsub) {
     sm.GT = (D.T + (64 >> sm.tsub) - 1) >> (6 - sm.tsub);
-    sm.tspan = (float)(sm.GT - 1) * step;
-    sm.bound_t = sm.tspan <= 0.998f;
+    sm.bound_t = (float)(sm.GT - 1) * step <= 0.998f;
     if (sm.bound_t || sm.tsub == 0) break;
   }
-  sm.treach = 0.5f * (float)D.T * step;
   if (D.T <= 64) {   // one pass scores every sample
     sm.GT = 1;
     sm.bound_t = false;
@@ -363,13 +360,13 @@ __device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, flo
   const char* gk = G.gk;
   float s0 = 0.f;
   // An atom stays within its distance from the axis, and the node map is
-  // monotone: when both ends of every atom's range, widened by four nodes (the
-  // windows) and the rounding of positions far from the origin (ferr), map inside
-  // [-1, n], no sample and no window needs the clamp of the node index.
+  // monotone: when both ends of every atom's range, widened by four nodes
+  // (rounding and the windows), map inside [-1, n], no sample and no window needs
+  // the clamp of the node index.
   bool inside = true, level = sm.bound_a && G.dil != nullptr;
   const float fp = fmaf(pP, ih, cP), fq = fmaf(pQ, ih, cQ);
   const float ferr = fmaf(1e-6f * ih, fabsf(pP) + fabsf(pQ), 2e-3f);
-  const float reach = fminf(fminf(fp + 1.f, fnP - fp), fminf(fq + 1.f, fnQ - fq)) - 4.f - ferr;
+  const float reach = fminf(fminf(fp + 1.f, fnP - fp), fminf(fq + 1.f, fnQ - fq)) - 4.f;
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
     const int a = s * 64 + lane;
@@ -497,15 +494,11 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
   inside = !wave_any(!inside);
   wave_sync();
   const uint64_t all = sm.ngt < 64 ? (1ull << sm.ngt) - 1u : ~0ull;
-  // a group spans less than one node also after the rounding of x + d and of the
-  // displacements: |x| / h inside the grid is at most |c0| + n
-  const bool bound_t = sm.bound_t && fmaf(2.4e-7f, fabsf(cE) + fnE + sm.treach, sm.tspan) <= 0.998f;
-  // (one sample: no displacement, whose range `inside` and the runs were taken for)
-  auto displacement = [&](int j) { return D.delta * (float)(j < max(D.T / 2, 1) ? j : j - D.T); };
+  auto displacement = [&](int j) { return D.delta * (float)(j < D.T / 2 ? j : j - D.T); };
   auto index = [&](int pos) { return pos + mlo < 0 ? pos + mlo + D.T : pos + mlo; };   // position: order of displacement
   auto none = [](int, bool) { return false; };
   int j;
-  if ((!STAGE && !(bound_t && D.T > 128)) || span > 63) {
+  if ((!STAGE && !(sm.bound_t && D.T > 128)) || span > 63) {
     j = select_sample<true>(
         all, __builtin_inff(), sm.GT, D.T, 0.f, index,
         [&](int js) {
@@ -551,7 +544,7 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
     };
     float bound = __builtin_inff();
     uint64_t alive = all;
-    if (bound_t) {
+    if (sm.bound_t) {
       const int part = lane >> (6 - sm.tsub), step = 1 << sm.tsub;
       const float d = sm.dlow;
       float acc = 0.f;
@@ -642,14 +635,14 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, ui
   int m = 0;
   float s0 = 0.f;
   // every place of a moving atom lies within |h u| + radius rho of a: when that
-  // cube, widened by four nodes and the rounding of positions far from the origin
-  // (ferr), is inside the padded grid, no node index needs its clamp
+  // cube, widened by four nodes, is inside the padded grid, no node index needs
+  // its clamp
   bool inside = true, level = sm.bound_a && G.dil != nullptr;
   const float ulen = prune_sqrt(fmaf(ux, ux, fmaf(uy, uy, uz * uz))) * 1.0001f;
   const float f0 = fmaf(xa, ih, cx), f1 = fmaf(ya, ih, cy), f2 = fmaf(za, ih, cz);
-  const float ferr = 1e-6f * (fabsf(xa) + fabsf(ya) + fabsf(za));
   const float reach = fminf(fminf(fminf(f0 + 1.f, G.fn[0] - f0), fminf(f1 + 1.f, G.fn[1] - f1)),
-                            fminf(f2 + 1.f, G.fn[2] - f2)) - 4.f - ferr * ih;
+                            fminf(f2 + 1.f, G.fn[2] - f2)) - 4.f;
+  const float ferr = 1e-6f * (fabsf(xa) + fabsf(ya) + fabsf(za));   // rounding of positions far from the origin
   moving_atoms(mk, N, k, b, mv);
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
@@ -667,12 +660,10 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, ui
       const float rho = prune_sqrt(fmaxf(ax * ax + ay * ay + az * az, bx * bx + by * by + bz * bz)) * 1.0001f;
       inside = inside && fmaf(sm.radius, rho, ulen * fabsf(h)) * ih <= reach;
       const float arc = sm.chord * rho;
-      // rounding of the position: of the axis atom's part and of the turned vector's
-      const float verr = fmaf(1e-6f, rho + ulen * fabsf(h), ferr);
-      const float del = fmaf(arc + verr, ih, 4e-3f);
+      const float del = fmaf(arc + ferr, ih, 4e-3f);
       const int l = del <= 0.5f ? 0 : del <= 1.5f ? 1 : 2;
       level = level && del <= 2.5f;
-      const float gap = D.clash - arc - verr - 2e-3f;
+      const float gap = D.clash - arc - ferr - 2e-3f;
       scr[at] = make_float4(vx, vy, vz, 0.f);
       aux[at] = make_float4(h, r, gap > 0.f ? gap * gap : 0.f, __int_as_float(l << 24));
     }
@@ -1056,10 +1047,6 @@ __global__ __launch_bounds__(256) void dock_plain_kernel(DockArgs X, int lig) {
   load_samples(X.G, X.D, B.ang, sm);
   LigReg<NSLOT> L;
   load_ligand(X.Lg, lig, L);
-  if (L.N > 64 * NSLOT) {   // the host's sizes are not the device's: as in the bucket kernel
-    if (lane_id() == 0) X.D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
-    return;
-  }
   store_masks(L, B.mkl);
   // One wavefront per SIMD or less: latency, so more fetches in flight (400 mixed
   // ligands of 256 restarts and 256 samples: 133 ms, 137 with four).  The staged
