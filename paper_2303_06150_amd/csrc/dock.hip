@@ -494,7 +494,8 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
   inside = !wave_any(!inside);
   wave_sync();
   const uint64_t all = sm.ngt < 64 ? (1ull << sm.ngt) - 1u : ~0ull;
-  auto displacement = [&](int j) { return D.delta * (float)(j < D.T / 2 ? j : j - D.T); };
+  // (one sample: no displacement, whose range `inside` and the runs were taken for)
+  auto displacement = [&](int j) { return D.delta * (float)(j < max(D.T / 2, 1) ? j : j - D.T); };
   auto index = [&](int pos) { return pos + mlo < 0 ? pos + mlo + D.T : pos + mlo; };   // position: order of displacement
   auto none = [](int, bool) { return false; };
   int j;

@@ -1,0 +1,46 @@
+"""Docking scans where their shortcuts end: one sample, positions far from the
+origin, sums near the largest float, ligands far longer than the site, sizes known
+on the device only.  Every selected sample is the oracle's, or that of scans without
+bounds."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+from gpu_common import compare_ligand, device_ligands, device_pocket, dock_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+
+def moved(pk, by):
+    """The site somewhere else."""
+    by = np.asarray(by, np.float64)
+    return gen.Pocket(pk.grid, (pk.origin + by).astype(np.float32), pk.spacing, (pk.center + by).astype(np.float32),
+                      pk.out_value)
+
+
+def sized(sizes, first, seed=5):
+    n, k = (np.array([s[i] for s in sizes], np.int32) for i in (0, 1))
+    return gen.ligands_from_sizes(np.arange(len(sizes)) + first, seed, n, k)
+
+
+def against_oracle(pk, L, r32, a32, T, S, step, mode, label):
+    pocket = device_pocket(pk)
+    out = dock_gpu(pocket, L, r32, a32, T=T, S=S, top_k=1, mode=mode, trans_step=step)
+    for i in range(L.n):
+        ref = oracle.dock_ligand(L.ligand(i), pk, r32.astype(np.float64), a32.astype(np.float64), T, S, step,
+                                 oracle.CLASH2, bits=32)
+        compare_ligand(out, L, i, ref, np.arange(len(r32)), 1, len(r32), label)
+    pocket.free()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("step", [0.7, 7.0, 1e6])
+def test_one_translation_sample(mode, step):
+    """T = 1: no displacement, however long the step, for atoms on either side of the box faces."""
+    pk = gen.pocket(16, 0.375, 20, 100, 3)
+    L = sized([(1, 0), (20, 4), (70, 9)], 4_100_000)
+    r32, _ = gen.restarts(40, 2)
+    a32, _ = gen.angles(32)
+    say(f"T = 1, step {step}, mode {mode}")
+    against_oracle(pk, L, r32, a32, 1, 2, step, mode, f"step {step}")
