@@ -360,13 +360,13 @@ __device__ __forceinline__ int rot_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, flo
   const char* gk = G.gk;
   float s0 = 0.f;
   // An atom stays within its distance from the axis, and the node map is
-  // monotone: when both ends of every atom's range, widened by four nodes
-  // (rounding and the windows), map inside [-1, n], no sample and no window needs
-  // the clamp of the node index.
+  // monotone: when both ends of every atom's range, widened by four nodes (the
+  // windows) and the rounding of positions far from the origin (ferr), map inside
+  // [-1, n], no sample and no window needs the clamp of the node index.
   bool inside = true, level = sm.bound_a && G.dil != nullptr;
   const float fp = fmaf(pP, ih, cP), fq = fmaf(pQ, ih, cQ);
   const float ferr = fmaf(1e-6f * ih, fabsf(pP) + fabsf(pQ), 2e-3f);
-  const float reach = fminf(fminf(fp + 1.f, fnP - fp), fminf(fq + 1.f, fnQ - fq)) - 4.f;
+  const float reach = fminf(fminf(fp + 1.f, fnP - fp), fminf(fq + 1.f, fnQ - fq)) - 4.f - ferr;
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {
     const int a = s * 64 + lane;
@@ -636,14 +636,14 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, ui
   int m = 0;
   float s0 = 0.f;
   // every place of a moving atom lies within |h u| + radius rho of a: when that
-  // cube, widened by four nodes, is inside the padded grid, no node index needs
-  // its clamp
+  // cube, widened by four nodes and the rounding of positions far from the origin
+  // (ferr), is inside the padded grid, no node index needs its clamp
   bool inside = true, level = sm.bound_a && G.dil != nullptr;
   const float ulen = prune_sqrt(fmaf(ux, ux, fmaf(uy, uy, uz * uz))) * 1.0001f;
   const float f0 = fmaf(xa, ih, cx), f1 = fmaf(ya, ih, cy), f2 = fmaf(za, ih, cz);
+  const float ferr = 1e-6f * (fabsf(xa) + fabsf(ya) + fabsf(za));
   const float reach = fminf(fminf(fminf(f0 + 1.f, G.fn[0] - f0), fminf(f1 + 1.f, G.fn[1] - f1)),
-                            fminf(f2 + 1.f, G.fn[2] - f2)) - 4.f;
-  const float ferr = 1e-6f * (fabsf(xa) + fabsf(ya) + fabsf(za));   // rounding of positions far from the origin
+                            fminf(f2 + 1.f, G.fn[2] - f2)) - 4.f - ferr * ih;
   moving_atoms(mk, N, k, b, mv);
 #pragma unroll
   for (int s = 0; s < NSLOT; ++s) {

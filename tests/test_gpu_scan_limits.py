@@ -44,3 +44,16 @@ def test_one_translation_sample(mode, step):
     a32, _ = gen.angles(32)
     say(f"T = 1, step {step}, mode {mode}")
     against_oracle(pk, L, r32, a32, 1, 2, step, mode, f"step {step}")
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("angles", [64, 256])
+def test_positions_rounded_by_more_than_nodes(mode, angles):
+    """Coordinates past 2^24, two Angstrom apart, nodes of 0.12: a turned atom lands up to
+    eight nodes beyond its exact place."""
+    pk = moved(gen.pocket(128, 0.12, 60, 400, 3), (1.75e7, -1.76e7, 1.77e7))
+    L = sized([(1, 0), (2, 0), (3, 0), (4, 0)], 4_200_000)
+    r32, _ = gen.restarts(200, 2, 7.0)
+    a32, _ = gen.angles(angles)
+    say(f"far origin, {angles} angles, mode {mode}")
+    against_oracle(pk, L, r32, a32, 64, 2, 1.0, mode, f"{angles} angles")
