@@ -445,6 +445,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
 
   int max_atoms = host_max_atoms, max_tors = host_max_tors;
   if (max_atoms < 0) host_maxima(L, &max_atoms, &max_tors);
+  const bool host_sized = max_atoms >= 0 && L->atom_offset_host;   // else the host's offsets are not what was checked
   if (max_atoms < 0) {
     s = check_on_device(p, L, stats, st, &max_atoms, &max_tors);
     if (s != LG_OK) return s;
@@ -475,12 +476,12 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
 
   if (P->mode == LG_PLAIN) {
     // The plain method: one launch per ligand, by the instance that fits it (the
-    // batch's largest where the host has no offsets; 400 mixed ligands 160 ms by the
+    // batch's largest where the sizes were taken from the device; 400 mixed ligands 160 ms by the
     // four-slot instance, 149 by the two-slot one, 143 by their own), one wavefront
     // per block while the restarts leave compute units idle (137 ms).
     const int wpb = R <= 8 * p->cus ? 1 : tu.plain_waves_per_block;
     for (int i = 0; i < n; ++i) {
-      const int atoms = L->atom_offset_host ? L->atom_offset_host[i + 1] - L->atom_offset_host[i] : max_atoms;
+      const int atoms = host_sized ? L->atom_offset_host[i + 1] - L->atom_offset_host[i] : max_atoms;
       LG_HIP(lg::launch_dock_plain((atoms + 63) / 64, wpb, p->grid, Lg, D, i, st));
     }
     LG_HIP(lg::launch_topk(topk_slots, Lg, D, n, P->top_k, O->score, O->restart_id, O->x, O->y, O->z, O->all_scores,

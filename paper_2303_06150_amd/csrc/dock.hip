@@ -1048,6 +1048,10 @@ __global__ __launch_bounds__(256) void dock_plain_kernel(DockArgs X, int lig) {
   load_samples(X.G, X.D, B.ang, sm);
   LigReg<NSLOT> L;
   load_ligand(X.Lg, lig, L);
+  if (L.N > 64 * NSLOT) {   // the host's sizes are not the device's: as in the bucket kernel
+    if (lane_id() == 0) X.D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
+    return;
+  }
   store_masks(L, B.mkl);
   // One wavefront per SIMD or less: latency, so more fetches in flight (400 mixed
   // ligands of 256 restarts and 256 samples: 133 ms, 137 with four).  The staged

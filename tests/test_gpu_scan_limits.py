@@ -57,3 +57,29 @@ def test_positions_rounded_by_more_than_nodes(mode, angles):
     a32, _ = gen.angles(angles)
     say(f"far origin, {angles} angles, mode {mode}")
     against_oracle(pk, L, r32, a32, 64, 2, 1.0, mode, f"{angles} angles")
+
+
+def test_plain_sizes_known_on_the_device_only():
+    """Host offsets without the bond atoms: the batch is checked from the device copies,
+    and the plain launches are sized by those too."""
+    import torch
+    from paper_2303_06150_amd import lg
+    pk = gen.pocket(32, 0.5, 40, 300, 3)
+    L = sized([(10, 2), (130, 9), (64, 5), (65, 5)], 4_300_000)
+    r32, _ = gen.restarts(20, 2)
+    a32, _ = gen.angles(64)
+    pocket = device_pocket(pk)
+    outs = []
+    for trusted in (True, False):
+        dl = device_ligands(L)
+        if not trusted:
+            dl.atom_offset_host = np.array([0, 130, 140, 205, 269], np.int32)
+            dl.tors_atoms_host = None
+        say(f"plain, host sizes {'right' if trusted else 'of another order'}")
+        outs.append(lg.lg_dock_batch(pocket, dl, torch.from_numpy(r32).cuda(), torch.from_numpy(a32).cuda(), sweeps=2,
+                                     top_k=3, trans_samples=64, trans_step=0.0625, clash_dist2=oracle.CLASH2,
+                                     mode=lg.LG_PLAIN, want_all_scores=True))
+        torch.cuda.synchronize()
+    for key in outs[0]:
+        assert torch.equal(outs[0][key], outs[1][key]), key
+    pocket.free()
