@@ -145,6 +145,7 @@ struct Samples {
   int tsub;           // lanes that share a translation group in the bound pass (log2): 0, 1, 2
   int gt0;            // translation group of sample 0
   bool bound_a, bound_t;   // rotations and torsions, translations: a bound pass pays (and is possible)
+  float tspan, treach;     // nodes that a translation group and that all displacements span, each way
   float dlow;         // least displacement of the lane's translation group
   float radius;       // largest |(cos, sin)| of a sample (1 up to rounding)
   float chord;        // every sample of a group lies within chord of its centre, in (cos, sin)
@@ -191,9 +192,11 @@ __device__ __forceinline__ void load_samples(const GridDev& G, const DockDev& D,
   sm.tsub = 2;
   for (;; --sm.tsub) {
     sm.GT = (D.T + (64 >> sm.tsub) - 1) >> (6 - sm.tsub);
-    sm.bound_t = (float)(sm.GT - 1) * step <= 0.998f;
+    sm.tspan = (float)(sm.GT - 1) * step;
+    sm.bound_t = sm.tspan <= 0.998f;
     if (sm.bound_t || sm.tsub == 0) break;
   }
+  sm.treach = 0.5f * (float)D.T * step;
   if (D.T <= 64) {   // one pass scores every sample
     sm.GT = 1;
     sm.bound_t = false;
@@ -494,12 +497,15 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
   inside = !wave_any(!inside);
   wave_sync();
   const uint64_t all = sm.ngt < 64 ? (1ull << sm.ngt) - 1u : ~0ull;
+  // a group spans less than one node also after the rounding of x + d and of the
+  // displacements: |x| / h inside the grid is at most |c0| + n
+  const bool bound_t = sm.bound_t && fmaf(2.4e-7f, fabsf(cE) + fnE + sm.treach, sm.tspan) <= 0.998f;
   // (one sample: no displacement, whose range `inside` and the runs were taken for)
   auto displacement = [&](int j) { return D.delta * (float)(j < max(D.T / 2, 1) ? j : j - D.T); };
   auto index = [&](int pos) { return pos + mlo < 0 ? pos + mlo + D.T : pos + mlo; };   // position: order of displacement
   auto none = [](int, bool) { return false; };
   int j;
-  if ((!STAGE && !(sm.bound_t && D.T > 128)) || span > 63) {
+  if ((!STAGE && !(bound_t && D.T > 128)) || span > 63) {
     j = select_sample<true>(
         all, __builtin_inff(), sm.GT, D.T, 0.f, index,
         [&](int js) {
@@ -545,7 +551,7 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
     };
     float bound = __builtin_inff();
     uint64_t alive = all;
-    if (sm.bound_t) {
+    if (bound_t) {
       const int part = lane >> (6 - sm.tsub), step = 1 << sm.tsub;
       const float d = sm.dlow;
       float acc = 0.f;

@@ -83,3 +83,25 @@ def test_plain_sizes_known_on_the_device_only():
     for key in outs[0]:
         assert torch.equal(outs[0][key], outs[1][key]), key
     pocket.free()
+
+
+def spiky(nodes, spacing, seed):
+    """A site of independent values, multiples of 2^-10 in [-5, 5]: a window a node off shows."""
+    rng = np.random.default_rng(seed)
+    grid = (rng.integers(-5120, 5121, (nodes,) * 3) / 1024).astype(np.float32)
+    centre = np.array(gen.DEFAULT_CENTER, np.float32)
+    return gen.Pocket(grid, (centre - 0.5 * spacing * (nodes - 1)).astype(np.float32), float(np.float32(spacing)), centre)
+
+
+@pytest.mark.parametrize("far", [0.0, 1e4, 2e5])
+def test_translation_groups_far_from_the_origin(far):
+    """Steps that let a group of samples span just under one node: rounded positions may
+    take a sample into the node after the next."""
+    pk = moved(spiky(64, 0.365, 3), (far, -far, far))
+    L = sized([(1, 0), (2, 0), (3, 0)], 4_400_000)
+    r32, _ = gen.restarts(4000, 2)
+    a32, _ = gen.angles(64)
+    say(f"translations near {far}")
+    for T in (128, 256):                                     # 16 groups
+        step = 0.9975 / (T // 16 - 1) * 0.365
+        against_oracle(pk, L, r32, a32, T, 3, step, 1, f"T {T} far {far}")
