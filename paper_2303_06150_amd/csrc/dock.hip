@@ -275,6 +275,8 @@ __device__ __forceinline__ int select_sample(uint64_t alive, float bound, int G,
 
 // How far apart two FP32 sums of the same n grid values can be, whatever their
 // orders of addition (zero on grids whose sums are exact; the bound holds for all).
+// Infinite wherever n values can add up past the largest float, since n * n * vmax
+// does so first: a sum that ran to infinity on the way is above any finite bound.
 __device__ __forceinline__ float sum_slack(const GridDev& G, int n) { return G.vmax * (float)(n * n) * 4.8e-7f; }
 
 // A bound on the FP32 sum of n grid values from the sum of their dilated copies

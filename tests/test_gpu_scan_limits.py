@@ -105,3 +105,40 @@ def test_translation_groups_far_from_the_origin(far):
     for T in (128, 256):                                     # 16 groups
         step = 0.9975 / (T // 16 - 1) * 0.365
         against_oracle(pk, L, r32, a32, T, 3, step, 1, f"T {T} far {far}")
+
+
+def scattered(sizes, seed):
+    """Rigid ligands whose atoms lie anywhere within 6 A."""
+    rng = np.random.default_rng(seed)
+    n = np.array(sizes, np.int32)
+    total, zero = int(n.sum()), np.zeros(0)
+    xyz = rng.uniform(-6, 6, (total, 3))
+    x = xyz.astype(np.float32)
+    return gen.Ligands(np.arange(len(n)), n, 0 * n, np.concatenate([[0], n.cumsum()]).astype(np.int32),
+                       np.zeros(len(n) + 1, np.int32), x[:, 0].copy(), x[:, 1].copy(), x[:, 2].copy(), xyz,
+                       np.zeros(total, np.int32), np.zeros(total, np.uint32), zero.astype(np.int32),
+                       zero.astype(np.float32), zero, np.zeros(3 * len(n), np.float32), np.zeros(3 * len(n)))
+
+
+@pytest.mark.parametrize("largest", [3e35, 1e38, 3.4e38])
+def test_sums_that_overflow(largest):
+    """Finite values whose sums over a ligand are not, of one sign in blocks of 12 nodes: the
+    samples of scans without bounds (a NaN in a corner that no atom reaches switches
+    them off)."""
+    from paper_2303_06150_amd import lg
+    pk = gen.pocket(96, 0.375, 120, 900, 4)
+    signs = np.kron(np.random.default_rng(5).choice([-1.0, 1.0], (8, 8, 8)), np.ones((12, 12, 12)))
+    grid = (signs * largest).astype(np.float32)
+    L = scattered([3, 4, 5, 6, 8, 13, 64, 70], 6)
+    r32, _ = gen.restarts(500, 2)
+    a32, _ = gen.angles(256)
+    outs = []
+    for corner in (grid[0, 0, 0], np.float32("nan")):
+        g = grid.copy()
+        g[0, 0, 0] = corner
+        pocket = device_pocket(gen.Pocket(g, pk.origin, pk.spacing, pk.center, pk.out_value))
+        say(f"largest value {largest}, corner {corner}")
+        outs.append(dock_gpu(pocket, L, r32, a32, T=256, S=2, top_k=4, mode=lg.LG_BUCKETED))
+        pocket.free()
+    for key in outs[0]:
+        np.testing.assert_array_equal(outs[0][key], outs[1][key], err_msg=f"{largest}: {key}")
