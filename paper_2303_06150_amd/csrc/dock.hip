@@ -285,9 +285,11 @@ __device__ __forceinline__ float upper_bound(const GridDev& G, int n, int sum) {
   return fmaf((float)sum, G.bound_scale, sum_slack(G, n));
 }
 
-// Groups that may hold a sample better than s0 (a NaN bound or score keeps them all).
+// Groups that may hold a sample better than s0.  A NaN bound or score keeps them all, and
+// so does an infinite bound: there a sum can run to infinity, and the current pose's does
+// so in one order of addition (s0) and not in the other (its score as a sample).
 __device__ __forceinline__ uint64_t groups_above(float bound, float s0, int groups) {
-  return __ballot(lane_id() < groups && !(bound <= s0));
+  return __ballot(lane_id() < groups && (!(bound <= s0) || bound == __builtin_inff()));
 }
 
 // acc + value(0) + value(1) + ... + value(n - 1), added in that order; U values are

@@ -142,3 +142,43 @@ def test_sums_that_overflow(largest):
         pocket.free()
     for key in outs[0]:
         np.testing.assert_array_equal(outs[0][key], outs[1][key], err_msg=f"{largest}: {key}")
+
+
+def test_sums_that_run_to_infinity_in_one_order_only():
+    """Eight atoms and values of a third of the largest float, in blocks of either sign: the first
+    translation scan compares the sums in atom order (a sum of both infinities orders
+    lowest), also when the current pose's sum is infinite in another order."""
+    from paper_2303_06150_amd import lg
+    nodes, h, R, T, step = 128, np.float32(0.375), 500, 256, 1 / 16
+    centre = np.array(gen.DEFAULT_CENTER, np.float32)
+    signs = np.kron(np.random.default_rng(5).choice([-1.0, 1.0], (16, 16, 16)), np.ones((8, 8, 8)))
+    grid = (signs * 1e38).astype(np.float32)
+    pk = gen.Pocket(grid, (centre - 0.5 * h * (nodes - 1)).astype(np.float32), float(h), centre)
+    L = scattered([8] * 8, 8)
+    r32, _ = gen.restarts(R, 2)
+    pocket = device_pocket(pk)
+    say("sums infinite in one order only")
+    out = dock_gpu(pocket, L, r32, np.array([[1.0, 0.0]], np.float32), T=T, S=1, top_k=1, mode=lg.LG_BUCKETED,
+                   trans_step=step)
+    pocket.free()
+    inv = np.float64(pk.inv_spacing)
+    c0 = np.array([np.float32(0.5 - np.float64(o) * inv) for o in pk.origin], np.float64)
+    j = np.arange(T)
+    d = (np.float32(step) * np.where(j < T // 2, j, j - T).astype(np.float32)).astype(np.float32)
+    finite = 0
+    for i in range(L.n):
+        for r in range(R):
+            x, _ = oracle.place(L.ligand(i), r32[r].astype(np.float64), centre.astype(np.float64), bits=32)
+            pose = np.broadcast_to(x.astype(np.float32), (T, 8, 3)).copy()
+            pose[..., 0] += d[:, None]
+            node = np.floor((pose.astype(np.float64) * inv + c0).astype(np.float32)).astype(int)
+            assert node.min() >= 0 and node.max() < nodes
+            v = grid[node[..., 2], node[..., 1], node[..., 0]]
+            score = np.zeros(T, np.float32)
+            with np.errstate(all="ignore"):
+                for a in range(8):
+                    score = score + v[:, a]
+            order = np.where(np.isnan(score), -1e39, np.nan_to_num(score.astype(np.float64), posinf=1e39, neginf=-9e38))
+            finite += np.isfinite(score).any()
+            assert out["trace"][i, r, 0, 3] == np.argmax(order), (i, r, score[0])
+    assert finite > 100
