@@ -20,16 +20,16 @@
 #include "lg_internal.h"
 
 namespace lg {
-hipError_t launch_dock_plain(int nslot, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D, int lig,
+hipError_t launch_dock_plain(int nslot, int spl, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D, int lig,
                              hipStream_t st);
-hipError_t launch_dock_bucket(int nslot, bool lone, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
+hipError_t launch_dock_bucket(int nslot, int spl, bool lone, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
                               const DockDev& D, const QueueDev& Q, hipStream_t st);
 size_t dock_lds_bytes(int nslot, int wpb, int tab_len, int angles);
-hipError_t occupancy_dock_bucket(int nslot, bool lone, int wpb, int tab_len, int angles, int* blocks_per_cu);
+hipError_t occupancy_dock_bucket(int nslot, int spl, bool lone, int wpb, int tab_len, int angles, int* blocks_per_cu);
 hipError_t launch_valu_probe(int kind, int blocks, int iters, float* out, hipStream_t st);
-hipError_t launch_dock_sites(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
+hipError_t launch_dock_sites(int nslot, int spl, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
                              const QueueDev& Q, const SitesDev& Sd, hipStream_t st);
-hipError_t attributes_dock_bucket(int nslot, bool lone, hipFuncAttributes* attr);
+hipError_t attributes_dock_bucket(int nslot, int spl, bool lone, hipFuncAttributes* attr);
 hipError_t launch_topk(int nslot, const LigDev& Lg, const DockDev& D, int n, int k, float* score, int32_t* rid,
                        float* ox, float* oy, float* oz, float* all_scores, float* pivot, hipStream_t st);
 hipError_t launch_score(int max_atoms, const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
@@ -104,6 +104,29 @@ lg_tuning default_tuning() {
   t.use_graph = 1;
   t.lazy_clash = 0;
   return t;
+}
+
+// Samples per lane of the instance for a class of up to `atoms` atoms that scores every
+// sample, 0 for the one that bounds groups of samples first.  The line lies where the two
+// cross, in ms, bounded / every sample (256 restarts, two sweeps, nodes of 0.375 A where
+// none are given):
+//   more than 256 samples, or 129 atoms and more: bounded (2 000 ligands of 512 samples 41,
+//     of eight per lane 182; 600 ligands of 180 to 256 atoms 138 / 333)
+//   up to 64 atoms, up to 128 angles: no bound pass there.  17.9 / 16.2 at 64, 25.7 / 21.4
+//     at 128; fragments of up to 20 atoms 13.3 / 9.6 and 18.8 / 12.2
+//   up to 64 atoms, 129 to 256 angles: a grid without bounds (60 / 53), nodes too fine for
+//     windows (0.2 A 47.6 / 44.4, 0.1 A 192 / 143; 0.25 A 38.3 / 39.6) or too coarse for
+//     tight ones (0.75 A 32.0 / 31.7, 1 A 33.3 / 30.9; 0.6 A 31.1 / 32.0), or ligands too
+//     small to repay the bound pass (up to 20 atoms 21.2 / 17.4; 20 to 40 atoms 37.3 /
+//     36.9, 26.2 / 28.3 at 0.25 A)
+//   65 to 128 atoms: 19.6 / 19.6 at 64 angles, 27.8 / 23.6 at 128, 38.1 / 35.5 at 256; with
+//     half as many translations or fewer the lanes would idle there (25.5 / 27.5)
+int every_sample(const lg::GridDev& G, int atoms, int A, int T) {
+  const int spl = A <= 64 ? 1 : A <= 128 ? 2 : 4;
+  if (A > 256 || T > 64 * spl || atoms > 128) return 0;
+  if (atoms > 64) return A > 64 && T > 32 * spl ? spl : 0;
+  const bool windows = G.dil && G.inv_h > 1.4f && G.inv_h < 4.5f;
+  return A <= 128 || !windows || atoms <= 32 ? spl : 0;
 }
 
 int spl_for(int A, int T) {
@@ -480,9 +503,20 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
     // four-slot instance, 149 by the two-slot one, 143 by their own), one wavefront
     // per block while the restarts leave compute units idle (137 ms).
     const int wpb = R <= 8 * p->cus ? 1 : tu.plain_waves_per_block;
+    // Up to two wavefronts per SIMD wait for their fetches: one pass with several samples
+    // per lane beats the bounded scans' passes one after another (12 ligands, 1 024
+    // restarts, 256 samples 4.00 ms bounded, 3.65; 4 096 restarts 5.38, 5.64), and with
+    // one sample per lane the bounded scans' eight fetches in flight win (64 samples 2.00,
+    // 2.23).
+    auto plain_spl = [&](int atoms) {
+      if (D.A <= 64) return 0;
+      const int spl = every_sample(p->grid, atoms, D.A, D.T);
+      const bool few = R <= 8 * p->cus && atoms <= 64 && D.A > 128 && D.A <= 256 && D.T > 128 && D.T <= 256;
+      return spl == 0 && few ? 4 : spl;
+    };
     for (int i = 0; i < n; ++i) {
       const int atoms = host_sized ? L->atom_offset_host[i + 1] - L->atom_offset_host[i] : max_atoms;
-      LG_HIP(lg::launch_dock_plain((atoms + 63) / 64, wpb, p->grid, Lg, D, i, st));
+      LG_HIP(lg::launch_dock_plain((atoms + 63) / 64, plain_spl(atoms), wpb, p->grid, Lg, D, i, st));
     }
     LG_HIP(lg::launch_topk(topk_slots, Lg, D, n, P->top_k, O->score, O->restart_id, O->x, O->y, O->z, O->all_scores,
                            O->pivot, st));
@@ -525,18 +559,22 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
   // units' caches take part (one ligand of 256 restarts: 256 blocks, not 64)
   const long long items = (long long)n * R;
   const bool lone = items <= 8LL * p->cus;
+  auto bucket_spl = [&](int ca) {
+    return lone ? 0 : every_sample(p->grid, std::min(cb.atom[ca], max_atoms), D.A, D.T);
+  };
   auto plan = [&](std::vector<lg_bucket_stat>& launches) -> lg_status {
     // Eq. 1: resident blocks per CU of each instance give the persistent grid
     for (int ca = cb.na - 1; ca >= 0; --ca) {
       // the instance holds the cluster's largest possible ligand: its bound, or the
       // batch's largest ligand if that is smaller (the last bound is LG_MAX_ATOMS)
       const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
+      const int every = bucket_spl(ca), entries = p->grid.table_entries(every == 0);
       const int wpb = lone ? 1 : tu.waves_per_block[nslot - 1];
       int bpc = 0;
-      LG_HIP(lg::occupancy_dock_bucket(nslot, lone, wpb, p->grid.tab_len, D.A, &bpc));
+      LG_HIP(lg::occupancy_dock_bucket(nslot, every, lone, wpb, entries, D.A, &bpc));
       if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots, %d samples/lane) cannot be resident", nslot, spl);
       hipFuncAttributes attr;
-      LG_HIP(lg::attributes_dock_bucket(nslot, lone, &attr));
+      LG_HIP(lg::attributes_dock_bucket(nslot, every, lone, &attr));
       for (int cr = cb.nr - 1; cr >= 0; --cr) {
         lg_bucket_stat b;
         b.bucket = ca * cb.nr + cr;
@@ -546,7 +584,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
         b.samples_per_lane = spl;
         b.waves_per_block = wpb;
         b.vgprs = attr.numRegs;
-        b.lds_bytes = (int32_t)lg::dock_lds_bytes(nslot, wpb, p->grid.tab_len, D.A);
+        b.lds_bytes = (int32_t)lg::dock_lds_bytes(nslot, wpb, entries, D.A);
         b.blocks_per_cu = bpc;
         b.blocks = (int)std::min<long long>((long long)bpc * p->cus * tu.grid_scale, (items + wpb - 1) / wpb);
         b.ligands = -1;
@@ -578,7 +616,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
       lg::QueueDev Q{perm, start, cursors, b.bucket, tu.restart_chunk};
       const int ca = b.bucket / cb.nr;
       if (e == hipSuccess && (ca == 0 || cb.atom[ca - 1] < max_atoms))   // else no ligand of the batch is that large
-        e = lg::launch_dock_bucket(b.slots, lone, b.waves_per_block, b.blocks, p->grid, Lg, D, Q, cs);
+        e = lg::launch_dock_bucket(b.slots, bucket_spl(ca), lone, b.waves_per_block, b.blocks, p->grid, Lg, D, Q, cs);
       if (e == hipSuccess && timed) e = hipEventRecord(p->events[2 + 2 * l], cs);
     }
     if (e == hipSuccess && timed) e = hipEventRecord(p->events[1 + 2 * nl], cs);
@@ -967,6 +1005,9 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
   LG_HIP(hipMemcpyAsync(dsites, sites.data(), sites.size() * sizeof(lg::DockArgs), hipMemcpyHostToDevice, st));
   LG_HIP(hipStreamSynchronize(st));   // the table's host copy ends with this call
   lg::SitesDev Sd{dsites, n_sites, site_major ? 1 : 0};
+  lg::GridDev sites_grid = p->grid;   // with bounds if every site has them
+  for (int si = 0; si < n_sites; ++si)
+    if (!pockets[si]->grid.dil) sites_grid.dil = nullptr;
 
   lg::ClusterBounds cb;
   std::memset(&cb, 0, sizeof cb);
@@ -987,12 +1028,13 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
     const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
     const int wpb = tu.waves_per_block[nslot - 1];
     int bpc = 0;
-    LG_HIP(lg::occupancy_dock_bucket(nslot, false, wpb, p->grid.tab_len, D.A, &bpc));
+    const int every = every_sample(sites_grid, std::min(cb.atom[ca], max_atoms), D.A, D.T);
+    LG_HIP(lg::occupancy_dock_bucket(nslot, every, false, wpb, p->grid.table_entries(every == 0), D.A, &bpc));
     if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots) cannot be resident", nslot);
     if (ca > 0 && cb.atom[ca - 1] >= max_atoms) continue;   // no ligand of the batch is that large
     for (int cr = cb.nr - 1; cr >= 0; --cr) {
       lg::QueueDev Q{perm, start, cursors, ca * cb.nr + cr, tu.restart_chunk};
-      LG_HIP(lg::launch_dock_sites(nslot, wpb, bpc * p->cus * tu.grid_scale, p->grid, Lg, D, Q, Sd, st));
+      LG_HIP(lg::launch_dock_sites(nslot, every, wpb, bpc * p->cus * tu.grid_scale, p->grid, Lg, D, Q, Sd, st));
     }
   }
   const int topk_slots = std::max(1, (max_atoms + 63) / 64);

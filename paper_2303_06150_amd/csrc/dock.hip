@@ -842,6 +842,444 @@ __device__ __forceinline__ int tors_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, ui
   return j;
 }
 
+// ---- scans of every sample ------------------------------------------------------
+// Where no bound pass pays or is possible a scan scores every sample, SPL per lane
+// (lane + 64 q) in one pass over the atoms: the atom's data is read and its fixed part
+// done once for all of them, and the pass ends in one reduction.  Bounded scans without
+// their bound pass score one sample per lane and pass: 4 000 mixed ligands of 128
+// samples took 49.6 ms that way, 10 000 fragments of up to 20 atoms 37.5 ms, 2 000
+// ligands in a grid of 0.1 A nodes and 256 samples 191 ms; these take 41.5, 24.3 and 144.
+// What a launch's scans need to know of them, uniform but for `valid`; the (cos, sin)
+// of the lane's samples are read from LDS in each scan.
+template <int SPL>
+struct SampleReg {
+  uint32_t valid;      // bit q: sample lane + 64 q exists
+  bool half_turn;      // A = 64 SPL and sample j + A/2 is sample j turned by pi:
+                       // (cos, sin) of the two are exact negatives
+  bool quarter_turn;   // A = 64 SPL and samples j + A/4, j + A/2, j + 3A/4 are j turned
+                       // by pi/2, pi, 3pi/2: (-s, c), (-c, -s), (s, -c) exactly
+  bool unit;           // every sample has |cos| <= 1 and |sin| <= 1
+};
+
+// (cos, sin) of sample lane + 64 q, the last one past the end.
+__device__ __forceinline__ float2 lane_sample(const float2* ang, int A, int q) {
+  return ang[min(lane_id() + 64 * q, A - 1)];
+}
+
+template <int SPL>
+__device__ __forceinline__ void load_every_sample(const DockDev& D, const float2* ang, SampleReg<SPL>& sm) {
+  const int lane = lane_id();
+  sm.valid = 0u;
+  bool unit = true;
+  float c[SPL], s[SPL];
+#pragma unroll
+  for (int q = 0; q < SPL; ++q) {
+    const int j = lane + 64 * q;
+    const float2 cs = lane_sample(ang, D.A, q);
+    c[q] = cs.x;
+    s[q] = cs.y;
+    if (j < D.A) sm.valid |= 1u << q;
+    unit = unit && fabsf(cs.x) <= 1.f && fabsf(cs.y) <= 1.f;
+  }
+  sm.unit = !wave_any(!unit);
+  sm.half_turn = sm.quarter_turn = false;
+  if (SPL % 2 == 0 && D.A == 64 * SPL) {
+    bool pair = true;
+#pragma unroll
+    for (int q = 0; q < SPL / 2; ++q) pair = pair && c[q + SPL / 2] == -c[q] && s[q + SPL / 2] == -s[q];
+    sm.half_turn = !wave_any(!pair);
+  }
+  if (SPL % 4 == 0 && D.A == 64 * SPL) {
+    constexpr int Q4 = SPL / 4;
+    bool quad = sm.half_turn;
+#pragma unroll
+    for (int q = 0; q < Q4; ++q) quad = quad && c[q + Q4] == -s[q] && s[q + Q4] == c[q];
+    sm.quarter_turn = !wave_any(!quad);
+  }
+}
+
+// The sample of the largest score, the lowest index among equal ones.
+template <int SPL>
+__device__ __forceinline__ int wave_argmax(const float (&acc)[SPL], uint32_t alive) {
+  const int lane = lane_id();
+  int best = INT_MIN, bj = INT_MAX;
+#pragma unroll
+  for (int q = 0; q < SPL; ++q) {
+    const int k = orderable(acc[q]);
+    if (((alive >> q) & 1u) && k > best) {
+      best = k;
+      bj = lane + 64 * q;
+    }
+  }
+  const int wmax = wave_reduce_i32(best, OpMax());
+  return wave_reduce_i32(best == wmax ? bj : INT_MAX, OpMin());
+}
+
+// acc[q] += gather(t)[q] over t < n, with the gathers of atom t + 1 issued before the
+// values of atom t are added (two register buffers, no copies).
+template <int Q, int NA, class F>
+__device__ __forceinline__ void pipelined_sum(int n, F gather, float (&acc)[NA], int qoff = 0) {
+  float v0[Q], v1[Q];
+  auto add = [&](const float (&v)[Q]) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) acc[q + qoff] += v[q];
+  };
+  gather(0, v0);
+  int t = 1;
+  for (; t + 1 < n; t += 2) {
+    gather(t, v1);
+    __builtin_amdgcn_sched_barrier(0);   // keep the loads of atom t ahead of the sums of atom t - 1
+    add(v0);
+    gather(t + 1, v0);
+    __builtin_amdgcn_sched_barrier(0);
+    add(v1);
+  }
+  if (t < n) {
+    gather(t, v1);
+    add(v0);
+    add(v1);
+  } else {
+    add(v0);
+  }
+}
+
+// The rotation scan over every sample.  A 2-D rotation serves the two or four samples
+// of a lane that are turned by pi or pi/2: the rotated offsets are exact negatives or
+// exchanged (fma and products are sign-symmetric), and a zero's sign cannot change the
+// node.  With |cos|, |sin| <= 1 a rotated offset is at most |vp| + |vq| per axis (B
+// covers the rounding), and the node map is monotone: when both ends of every atom's
+// range map inside [-1, n], no sample needs the clamp of the node index.
+template <int NSLOT, int E, int SPL>
+__device__ __forceinline__ int rot_scan_all(ArgsPtr S, PoseReg<NSLOT>& p, int N, float4* scr,
+                                            const SampleReg<SPL>& sm, const float2* ang, const int* tab) {
+  const GridDev G = grid_of(S);
+  const int A = S->D.A;
+  constexpr int P = (E + 1) % 3, Q = (E + 2) % 3;
+  const int lane = lane_id();
+  const float pP = p.piv[P], pQ = p.piv[Q];
+  const float cP = G.c0[P], cQ = G.c0[Q], ih = G.inv_h, fnP = G.fn[P], fnQ = G.fn[Q];
+  const int* tP = tab + G.tab_base[P] + 1;
+  const int* tQ = tab + G.tab_base[Q] + 1;
+  const char* gk = G.gk;
+  float s0 = 0.f;
+  bool inside = sm.unit;
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s) {
+    const int a = s * 64 + lane;
+    if (a < N) {
+      const float vp = p.x[P][s] - pP, vq = p.x[Q][s] - pQ;
+      const int part = boff(tab + G.tab_base[E] + 1, clamp_node(fmaf(p.x[E][s], ih, G.c0[E]), G.fn[E]));
+      scr[a] = make_float4(vp, vq, __int_as_float(part), 0.f);
+      s0 += grid_at(gk, part + boff(tP, clamp_node(fmaf(p.x[P][s], ih, cP), fnP)) +
+                            boff(tQ, clamp_node(fmaf(p.x[Q][s], ih, cQ), fnQ)));
+      const float B = (fabsf(vp) + fabsf(vq)) * (1.f + 0x1p-20f);
+      inside = inside && fmaf(pP - B, ih, cP) >= -1.f && fmaf(pP + B, ih, cP) <= fnP &&
+               fmaf(pQ - B, ih, cQ) >= -1.f && fmaf(pQ + B, ih, cQ) <= fnQ;
+    }
+  }
+  inside = !wave_any(!inside);
+  s0 = wave_sum(s0);
+  wave_sync();
+  float acc[SPL];
+#pragma unroll
+  for (int q = 0; q < SPL; ++q) acc[q] = 0.f;
+  // TURNS samples of a lane from one rotation, sample q + SPL / TURNS a turn of 1 / TURNS on
+  auto sums = [&](auto turns, auto in) {
+    constexpr int TURNS = decltype(turns)::value, STEP = SPL / TURNS;
+    float2 cs[STEP];
+#pragma unroll
+    for (int q = 0; q < STEP; ++q) cs[q] = lane_sample(ang, A, q);
+    pipelined_sum<SPL>(N, [&](int t, float (&out)[SPL]) {
+      const float4 d = scr[t];
+      const int part = __float_as_int(d.z);
+#pragma unroll
+      for (int q = 0; q < STEP; ++q) {
+        const float np = fmaf(cs[q].x, d.x, -(cs[q].y * d.y));
+        const float nq = fmaf(cs[q].y, d.x, cs[q].x * d.y);
+        auto at = [&](float xp, float xq) {
+          return grid_at(gk, part + boff(tP, node_index(in, fmaf(xp, ih, cP), fnP)) +
+                                 boff(tQ, node_index(in, fmaf(xq, ih, cQ), fnQ)));
+        };
+        out[q] = at(pP + np, pQ + nq);
+        if (TURNS == 4) out[q + STEP] = at(pP - nq, pQ + np);
+        if (TURNS >= 2) out[q + SPL / 2] = at(pP - np, pQ - nq);
+        if (TURNS == 4) out[q + 3 * STEP] = at(pP + nq, pQ - np);
+      }
+    }, acc);
+  };
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, SPL % 2 == 0 ? 2 : 1> two{};
+  constexpr std::integral_constant<int, SPL % 4 == 0 ? 4 : 1> four{};
+  auto by_turns = [&](auto in) {
+    if (SPL % 4 == 0 && sm.quarter_turn)
+      sums(four, in);
+    else if (SPL % 2 == 0 && sm.half_turn)
+      sums(two, in);
+    else
+      sums(one, in);
+  };
+  if (inside)
+    by_turns(std::true_type{});
+  else
+    by_turns(std::false_type{});
+  if (lane == 0) acc[0] = s0;   // sample 0 is the current pose
+  const int j = wave_argmax(acc, sm.valid);
+  apply_rot<NSLOT, E>(ang[j], p, j);
+  wave_sync();
+  return j;
+}
+
+// The torsion scan over every sample.  The clash tests run in the scoring pass, on the
+// list of risky pairs; a scan with more pairs than the list holds takes them in
+// several lists of whole moving atoms, as the bounded scan does.
+template <int NSLOT, int SPL>
+__device__ __forceinline__ int tors_scan_all(ArgsPtr S, PoseReg<NSLOT>& p, int N, uint32_t ab, float inv_len, int k,
+                                             const uint32_t* mkl, float4* scr, float4* pairs, const SampleReg<SPL>& sm,
+                                             const float2* ang, const int* tab) {
+  const GridDev G = grid_of(S);
+  const DockDev D = dock_of(S);
+  constexpr int PAIR_CAP = pair_cap(NSLOT) + 64 * NSLOT;
+  const int lane = lane_id();
+  uint32_t mk[NSLOT];
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s) mk[s] = mkl[s * 64 + lane];
+  const BondAxis A = bond_axis(ab, inv_len, p, k);
+  const int a = A.a, b = A.b;
+  const float xa = A.xa, ya = A.ya, za = A.za, ux = A.ux, uy = A.uy, uz = A.uz;
+
+  // moving atoms of F_k other than b, compacted into scr; their current score; axial
+  // position and radius of every static atom about the bond axis
+  bool mv[NSLOT], st[NSLOT];
+  float hs[NSLOT], rs[NSLOT];
+  int m = 0;
+  float s0 = 0.f;
+  moving_atoms(mk, N, k, b, mv);
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s) {
+    const int at = s * 64 + lane;
+    st[s] = at < N && !((mk[s] >> k) & 1u) && at != a;
+    const float vx = p.x[0][s] - xa, vy = p.x[1][s] - ya, vz = p.x[2][s] - za;
+    hs[s] = vx * ux + vy * uy + vz * uz;
+    rs[s] = prune_sqrt(fmaxf(vx * vx + vy * vy + vz * vz - hs[s] * hs[s], 0.f));
+    const uint64_t bal = __ballot(mv[s]);
+    const int pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+    if (mv[s]) {
+      scr[m + pre] = make_float4(vx, vy, vz, 0.f);
+      s0 += nearest(G, p.x[0][s], p.x[1][s], p.x[2][s]);
+    }
+    m += __popcll(bal);
+  }
+  if (m == 0) return 0;
+  s0 = wave_sum(s0);
+  wave_sync();
+
+  // risky pairs of the moving atoms t0 .. t1 - 1; scr[t].w = first pair | count << 16.
+  // Returns t1: whole atoms until the next one's pairs would not fit (one atom's do).
+  auto list_pairs = [&](int t0) {
+    wave_sync();   // reads of an earlier list are done
+    int npairs = 0, t = t0;
+    for (; t < m; ++t) {
+      const float4 v = scr[t];
+      const float ht = v.x * ux + v.y * uy + v.z * uz;
+      const float rt = prune_sqrt(fmaxf(v.x * v.x + v.y * v.y + v.z * v.z - ht * ht, 0.f));
+      uint64_t bal[NSLOT];
+      int count = 0;
+#pragma unroll
+      for (int s = 0; s < NSLOT; ++s) {
+        const float dh = ht - hs[s], dr = rt - rs[s];
+        bal[s] = __ballot(st[s] && fmaf(dr, dr, dh * dh) < D.clash_r2);
+        count += __popcll(bal[s]);
+      }
+      if (npairs + count > PAIR_CAP) break;
+      if (lane == 0) reinterpret_cast<int*>(scr + t)[3] = npairs | (count << 16);
+#pragma unroll
+      for (int s = 0; s < NSLOT; ++s) {
+        const int pre =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[s] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal[s], 0u));
+        if ((bal[s] >> lane) & 1u) pairs[npairs + pre] = make_float4(p.x[0][s], p.x[1][s], p.x[2][s], 0.f);
+        npairs += __popcll(bal[s]);
+      }
+    }
+    wave_sync();
+    return t;
+  };
+
+  float acc[SPL];
+#pragma unroll
+  for (int q = 0; q < SPL; ++q) acc[q] = 0.f;
+  uint32_t clash = 0u;   // bit q: sample lane + 64 q clashes
+  constexpr int QG = SPL < 2 ? SPL : 2;   // samples whose matrices are held at once
+  const float ih = G.inv_h, clash2 = D.clash2;
+  const char* gk = G.gk;
+  const int* tX = tab + G.tab_base[0] + 1;
+  const int* tY = tab + G.tab_base[1] + 1;
+  const int* tZ = tab + G.tab_base[2] + 1;
+  for (int t0 = 0; t0 < m;) {
+    const int t1 = list_pairs(t0);
+#pragma unroll
+    for (int g = 0; g < SPL; g += QG) {
+      float M[QG][9];
+#pragma unroll
+      for (int q = 0; q < QG; ++q) {
+        const float2 cs = lane_sample(ang, D.A, g + q);
+        torsion_matrix(ux, uy, uz, cs.x, cs.y, M[q]);
+      }
+      pipelined_sum<QG>(t1 - t0, [&](int t, float (&out)[QG]) {
+        const float4 v = scr[t0 + t];
+        float X[QG], Y[QG], Z[QG];
+#pragma unroll
+        for (int q = 0; q < QG; ++q) {
+          float y0, y1, y2;
+          mat_apply(M[q], v.x, v.y, v.z, y0, y1, y2);
+          X[q] = xa + y0;
+          Y[q] = ya + y1;
+          Z[q] = za + y2;
+          const int ix = clamp_node(fmaf(X[q], ih, G.c0[0]), G.fn[0]);
+          const int iy = clamp_node(fmaf(Y[q], ih, G.c0[1]), G.fn[1]);
+          const int iz = clamp_node(fmaf(Z[q], ih, G.c0[2]), G.fn[2]);
+          out[q] = grid_at(gk, boff(tX, ix) + boff(tY, iy) + boff(tZ, iz));
+        }
+        // the segment is the same on every lane: a scalar loop; the least d^2 over the
+        // atom's pairs decides its clash bits (min is exact)
+        const int seg = __builtin_amdgcn_readfirstlane(__float_as_int(v.w));
+        const int p0 = seg & 0xFFFF, p1 = p0 + (seg >> 16);
+        if (p1 == p0) return;
+        float dmin[QG];
+#pragma unroll
+        for (int q = 0; q < QG; ++q) dmin[q] = __builtin_inff();
+        for (int pi = p0; pi < p1; ++pi) {
+          const float4 c = pairs[pi];
+#pragma unroll
+          for (int q = 0; q < QG; ++q) {
+            const float dx = X[q] - c.x, dy = Y[q] - c.y, dz = Z[q] - c.z;
+            dmin[q] = vmin(dmin[q], fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < QG; ++q)
+          if (dmin[q] < clash2) clash |= 1u << (g + q);
+      }, acc, g);
+    }
+    t0 = t1;
+  }
+  if (lane == 0) {
+    acc[0] = s0;        // sample 0 is the current pose,
+    clash &= ~1u;       // always admissible
+  }
+  const int j = wave_argmax(acc, sm.valid & ~clash);
+  if (j != 0) {
+    float Mj[9];
+    torsion_matrix(ux, uy, uz, ang[j].x, ang[j].y, Mj);
+    apply_tors(p, A, Mj, mv);
+  }
+  wave_sync();
+  return j;
+}
+
+// The translation scan over every sample: as in the bounded scan the wavefront reads
+// each atom's run of nodes once, here 64 / span atoms at a time into one of two
+// buffers (a group's stage is written while the previous one's reads are retired), and
+// every sample then takes its value from there.  At most 64 SPL samples.
+template <int NSLOT, int E, int SPL>
+__device__ __forceinline__ int trans_scan_all(ArgsPtr S, PoseReg<NSLOT>& p, int N, float4* scr, float* stage,
+                                              const int* tab) {
+  const GridDev G = grid_of(S);
+  const DockDev D = dock_of(S);
+  constexpr int P = (E + 1) % 3, Q = (E + 2) % 3;
+  const int lane = lane_id();
+  const float cE = G.c0[E], ih = G.inv_h, fnE = G.fn[E];
+  float shift[SPL];
+  uint32_t valid = 0u;
+#pragma unroll
+  for (int q = 0; q < SPL; ++q) {
+    const int j = lane + 64 * q;
+    shift[q] = j < D.T ? D.delta * (float)(j < max(D.T / 2, 1) ? j : j - D.T) : 0.f;
+    if (j < D.T) valid |= 1u << q;
+  }
+  const int mlo = D.T >= 2 ? D.T / 2 - D.T : 0, mhi = D.T >= 2 ? D.T / 2 - 1 : 0;
+  const float da = D.delta * (float)mlo, db = D.delta * (float)mhi;
+  const float dmin = fminf(da, db), dmax = fmaxf(da, db);
+  int span = 0;
+  bool inside = true;
+#pragma unroll
+  for (int s = 0; s < NSLOT; ++s) {
+    const int a = s * 64 + lane;
+    if (a < N) {
+      const int ip = clamp_node(fmaf(p.x[P][s], ih, G.c0[P]), G.fn[P]);
+      const int iq = clamp_node(fmaf(p.x[Q][s], ih, G.c0[Q]), G.fn[Q]);
+      const int part = boff(tab + G.tab_base[P] + 1, ip) + boff(tab + G.tab_base[Q] + 1, iq);
+      const int lo = clamp_node(fmaf(p.x[E][s] + dmin, ih, cE), fnE);
+      const int hi = clamp_node(fmaf(p.x[E][s] + dmax, ih, cE), fnE);
+      span = max(span, hi - lo + 1);
+      inside = inside && lo >= 0 && hi < G.n[E];   // every sample's f in [0, n): no clamp needed
+      scr[a] = make_float4(p.x[E][s], __int_as_float(part), __int_as_float(lo), 0.f);
+    }
+  }
+  span = wave_reduce_i32(span, OpMax());
+  inside = !wave_any(!inside);
+  wave_sync();
+  float acc[SPL];
+#pragma unroll
+  for (int q = 0; q < SPL; ++q) acc[q] = 0.f;
+  const int* tE = tab + G.tab_base[E] + 1;
+  const char* gk = G.gk;
+  if (span > 64) {   // runs longer than a wavefront: direct gathers
+    pipelined_sum<SPL>(N, [&](int t, float (&out)[SPL]) {
+      const float4 d = scr[t];
+#pragma unroll
+      for (int q = 0; q < SPL; ++q)
+        out[q] = grid_at(gk, __float_as_int(d.y) + boff(tE, clamp_node(fmaf(d.x + shift[q], ih, cE), fnE)));
+    }, acc);
+  } else {
+    const float rspan = __builtin_amdgcn_rcpf((float)span);
+    const int per = __builtin_amdgcn_readfirstlane(small_div(64, rspan));   // atoms whose runs one gather reads
+    const int tt = small_div(lane, rspan), ii = lane - tt * span;
+    const int imax = (int)fnE;
+    // lane (tt, ii): node lo + ii of atom t0 + tt (clamped into the grid; positions past
+    // an atom's own run are never read)
+    auto stage_load = [&](int t0) {
+      const int t = t0 + tt;
+      if (tt >= per || t >= N) return 0.f;
+      const float4 d = scr[t];
+      return grid_at(gk, __float_as_int(d.y) + boff(tE, min(__float_as_int(d.z) + ii, imax)));
+    };
+    auto staged = [&](auto in) {
+      float next = stage_load(0);
+      int b = 0;
+      for (int t0 = 0; t0 < N; t0 += per, b ^= 1) {
+        float* buf = stage + b * 64;
+        buf[lane] = next;
+        wave_sync();
+        const int t1 = min(N, t0 + per);
+        if (t1 < N) next = stage_load(t1);
+        for (int t = t0; t < t1; ++t) {
+          const float4 d = scr[t];
+          // LDS byte address of the atom's run, shifted so that node ie (in [lo, lo +
+          // span)) is at run + 4 ie: one base per atom, one shift-add per sample
+          uint32_t run = lds_addr(buf) + 4u * (uint32_t)((t - t0) * span - __float_as_int(d.z));
+          asm volatile("" : "+v"(run));
+          int ie[SPL];
+          float v[SPL];
+#pragma unroll
+          for (int q = 0; q < SPL; ++q) ie[q] = node_index(in, fmaf(d.x + shift[q], ih, cE), fnE);
+#pragma unroll
+          for (int q = 0; q < SPL; ++q) v[q] = lds_load(run + 4u * (uint32_t)ie[q]);
+#pragma unroll
+          for (int q = 0; q < SPL; ++q) acc[q] += v[q];
+        }
+      }
+    };
+    if (inside)
+      staged(std::true_type{});
+    else
+      staged(std::false_type{});
+  }
+  const int j = wave_argmax(acc, valid);
+  apply_trans<NSLOT, E>(D, p, j);
+  wave_sync();
+  return j;
+}
+
 template <int NSLOT>
 struct LigReg {
   int N, K, abase, toff;
@@ -933,9 +1371,10 @@ struct BlockLds {
 // One restart: placement, S sweeps, final trilinear score, outputs.
 // U: values in flight per buffer of the scans' sums (and half of it in the torsion
 // scans, whose fragments are small).
-template <int NSLOT, bool STAGE, int U>
-__device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const LigReg<NSLOT>& L, int lig, int r,
-                                             const BlockLds& B) {
+// SPL: 0, scans that bound groups of samples; else scans of every sample, SPL per lane.
+template <int NSLOT, bool STAGE, int U, int SPL>
+__device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const SampleReg<SPL ? SPL : 1>& every,
+                                             const LigReg<NSLOT>& L, int lig, int r, const BlockLds& B) {
   const int lane = lane_id();
   const int N = L.N;
   PoseReg<NSLOT> p;
@@ -944,12 +1383,21 @@ __device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const
   float* stage = reinterpret_cast<float*>(B.cand);
   for (int sw = 0; sw < sweeps; ++sw) {
     int j[6];
-    j[0] = rot_scan<NSLOT, 0, U>(S, p, N, B.scr, B.cand, sm, B.tab);
-    j[1] = rot_scan<NSLOT, 1, U>(S, p, N, B.scr, B.cand, sm, B.tab);
-    j[2] = rot_scan<NSLOT, 2, U>(S, p, N, B.scr, B.cand, sm, B.tab);
-    j[3] = trans_scan<NSLOT, 0, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
-    j[4] = trans_scan<NSLOT, 1, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
-    j[5] = trans_scan<NSLOT, 2, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
+    if constexpr (SPL > 0) {
+      j[0] = rot_scan_all<NSLOT, 0, SPL>(S, p, N, B.scr, every, B.ang, B.tab);
+      j[1] = rot_scan_all<NSLOT, 1, SPL>(S, p, N, B.scr, every, B.ang, B.tab);
+      j[2] = rot_scan_all<NSLOT, 2, SPL>(S, p, N, B.scr, every, B.ang, B.tab);
+      j[3] = trans_scan_all<NSLOT, 0, SPL>(S, p, N, B.scr, stage, B.tab);
+      j[4] = trans_scan_all<NSLOT, 1, SPL>(S, p, N, B.scr, stage, B.tab);
+      j[5] = trans_scan_all<NSLOT, 2, SPL>(S, p, N, B.scr, stage, B.tab);
+    } else {
+      j[0] = rot_scan<NSLOT, 0, U>(S, p, N, B.scr, B.cand, sm, B.tab);
+      j[1] = rot_scan<NSLOT, 1, U>(S, p, N, B.scr, B.cand, sm, B.tab);
+      j[2] = rot_scan<NSLOT, 2, U>(S, p, N, B.scr, B.cand, sm, B.tab);
+      j[3] = trans_scan<NSLOT, 0, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
+      j[4] = trans_scan<NSLOT, 1, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
+      j[5] = trans_scan<NSLOT, 2, STAGE, U>(S, p, N, B.scr, stage, sm, B.tab);
+    }
     const DockDev D = dock_of(S);
     uint16_t* mrow = move_record(D, lig, L.toff, L.K, r) + (size_t)sw * (6 + L.K);
     int16_t* trow = D.trace ? D.trace + (((size_t)lig * D.R + r) * (size_t)sweeps + sw) * D.trace_w : nullptr;
@@ -962,7 +1410,11 @@ __device__ __forceinline__ void dock_restart(ArgsPtr S, const Samples& sm, const
       }
     }
     for (int k = 0; k < L.K; ++k) {
-      const int jk = tors_scan<NSLOT, U / 2>(S, p, N, L.ab, L.il, k, B.mkl, B.scr, B.cand, sm, B.tab);
+      int jk;
+      if constexpr (SPL > 0)
+        jk = tors_scan_all<NSLOT, SPL>(S, p, N, L.ab, L.il, k, B.mkl, B.scr, B.cand, every, B.ang, B.tab);
+      else
+        jk = tors_scan<NSLOT, U / 2>(S, p, N, L.ab, L.il, k, B.mkl, B.scr, B.cand, sm, B.tab);
       if (lane == 0) {
         mrow[6 + k] = (uint16_t)jk;
         if (trow) trow[6 + k] = (int16_t)jk;
@@ -1032,30 +1484,34 @@ __device__ void replay_restart(const LigDev& Lg, const DockDev& D, const LigReg<
 __device__ __forceinline__ ArgsPtr kernel_args() { return (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); }
 
 // Plain method: one launch per ligand; wavefront w of the grid docks restart w.
-template <int NSLOT>
+template <int NSLOT, bool BOUNDS>
 __device__ __forceinline__ BlockLds block_lds(const GridDev& G, const DockDev& D, float4* lds) {
   BlockLds b;
   b.tab = reinterpret_cast<int*>(lds);
-  const int head = (G.tab_len + 3) / 4;
+  const int head = (G.table_entries(BOUNDS) + 3) / 4;
   b.ang = reinterpret_cast<float2*>(lds + head);
   b.scr = lds + head + (D.A + 1) / 2 + (size_t)(threadIdx.x >> 6) * dock_wave_float4(NSLOT);
   b.cand = b.scr + 64 * NSLOT;
   b.mkl = reinterpret_cast<uint32_t*>(b.scr + dock_wave_float4(NSLOT) - 16 * NSLOT);
-  fill_brick_tables(G, b.tab);
+  fill_brick_tables(G, b.tab, BOUNDS && G.tab_bounds);
   for (int j = threadIdx.x; j < D.A; j += blockDim.x) b.ang[j] = make_float2(D.angles[2 * j], D.angles[2 * j + 1]);
   __syncthreads();
   return b;
 }
 
-template <int NSLOT>
+template <int NSLOT, int SPL>
 __global__ __launch_bounds__(256) void dock_plain_kernel(DockArgs X, int lig) {
   extern __shared__ float4 lds[];
-  const BlockLds B = block_lds<NSLOT>(X.G, X.D, lds);
+  const BlockLds B = block_lds<NSLOT, SPL == 0>(X.G, X.D, lds);
   const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
   const int r = blockIdx.x * nwaves + wave;
   if (r >= X.D.R) return;
   Samples sm;
-  load_samples(X.G, X.D, B.ang, sm);
+  SampleReg<SPL ? SPL : 1> every;
+  if constexpr (SPL > 0)
+    load_every_sample(X.D, B.ang, every);
+  else
+    load_samples(X.G, X.D, B.ang, sm);
   LigReg<NSLOT> L;
   load_ligand(X.Lg, lig, L);
   if (L.N > 64 * NSLOT) {   // the host's sizes are not the device's: as in the bucket kernel
@@ -1068,14 +1524,19 @@ __global__ __launch_bounds__(256) void dock_plain_kernel(DockArgs X, int lig) {
   // translation scan's read-then-use of each group's nodes pays only where its
   // bound saves passes (129 ms); with two passes or fewer the gathers stay direct
   // (100 samples, 64 restarts: 95 ms, 99 staged).
-  dock_restart<NSLOT, false, 8>(kernel_args(), sm, L, lig, r, B);
+  dock_restart<NSLOT, false, 8, SPL>(kernel_args(), sm, every, L, lig, r, B);
 }
 
 // Bucketed method: persistent; wavefronts pull (ligand, restart chunk) items of
 // one size bucket from an atomic cursor until the bucket is drained.  Occupancy
-// target per instance (wavefronts per SIMD), chosen by measurement: 8 000 mixed
-// ligands take 163 ms at 5 per SIMD (96 VGPRs), 166 at 6, 174 at 7.
-constexpr int bucket_waves_per_simd(int nslot) { return nslot == 1 ? 5 : 4; }
+// target per instance (wavefronts per SIMD), chosen by measurement.  Bounded scans: 8 000
+// mixed ligands take 163 ms at 5 per SIMD (96 VGPRs), 166 at 6, 174 at 7.  Scans of every
+// sample (without the clamp-free variants and lists): 4 000 of them, 256 and 128 samples,
+// 68.8 and 44.9 ms at 5, 66.6 and 43.9 at 6, 70.7 and 44.9 at 7; 1 200 ligands of 65 to
+// 128 atoms 76.9 and 47.5 ms at 4, 74.7 and 44.2 at 5, 74.1 and 46.3 at 6.
+constexpr int bucket_waves_per_simd(int nslot, int spl) {
+  return spl > 0 ? (nslot == 1 ? 6 : 5) : nslot == 1 ? 5 : 4;
+}
 
 // LONE: the instance for launches of at most two wavefronts per SIMD, where a
 // wavefront waits for each of its fetches alone: more of them in flight, in the
@@ -1092,20 +1553,24 @@ __device__ __forceinline__ int restart_chunk(int chunk, long long restarts, int 
   return share < 1 ? 1 : share < chunk ? (int)share : chunk;
 }
 
-template <int NSLOT, bool LONE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LONE ? 2 : bucket_waves_per_simd(NSLOT))))
+template <int NSLOT, bool LONE, int SPL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LONE ? 2 : bucket_waves_per_simd(NSLOT, SPL))))
 void dock_bucket_kernel(DockArgs X, QueueDev Q) {
   extern __shared__ float4 lds[];
   const int b0 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket]);
   const int b1 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket + 1]);
   if (b0 == b1) return;   // no ligand of this class in the batch
-  const BlockLds B = block_lds<NSLOT>(X.G, X.D, lds);
+  const BlockLds B = block_lds<NSLOT, SPL == 0>(X.G, X.D, lds);
   const int lane = lane_id();
   const int chunk = restart_chunk(Q.chunk, (long long)(b1 - b0) * X.D.R, blockDim.x >> 6);
   const int nch = (X.D.R + chunk - 1) / chunk;
   const long long n_items = (long long)(b1 - b0) * nch;
   Samples sm;
-  load_samples(X.G, X.D, B.ang, sm);
+  SampleReg<SPL ? SPL : 1> every;
+  if constexpr (SPL > 0)
+    load_every_sample(X.D, B.ang, every);
+  else
+    load_samples(X.G, X.D, B.ang, sm);
   int cur_lig = -1;
   LigReg<NSLOT> L;
   for (;;) {
@@ -1127,21 +1592,21 @@ void dock_bucket_kernel(DockArgs X, QueueDev Q) {
       for (int r = r0 + lane; r < r1; r += 64) X.D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
       continue;
     }
-    for (int r = r0; r < r1; ++r) dock_restart<NSLOT, true, in_flight<LONE>()>(kernel_args(), sm, L, lig, r, B);
+    for (int r = r0; r < r1; ++r) dock_restart<NSLOT, true, in_flight<LONE>(), SPL>(kernel_args(), sm, every, L, lig, r, B);
   }
 }
 
 // Several docking sites: the bucket kernel's loop over items (site, ligand of
 // the bucket, restart chunk); each item works on its site's entry of the table.  The brick tables depend on the
 // grid dimensions only, shared by every site.
-template <int NSLOT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bucket_waves_per_simd(NSLOT))))
+template <int NSLOT, int SPL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bucket_waves_per_simd(NSLOT, SPL))))
 void dock_sites_kernel(DockArgs X, QueueDev Q, SitesDev Sd) {
   extern __shared__ float4 lds[];
   const int b0 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket]);
   const int b1 = __builtin_amdgcn_readfirstlane(Q.bucket_start[Q.bucket + 1]);
   if (b0 == b1) return;   // no ligand of this class in the batch
-  const BlockLds B = block_lds<NSLOT>(X.G, X.D, lds);
+  const BlockLds B = block_lds<NSLOT, SPL == 0>(X.G, X.D, lds);
   const int lane = lane_id();
   const int nlig = b1 - b0;
   const int chunk = restart_chunk(Q.chunk, (long long)nlig * X.D.R * Sd.n_sites, blockDim.x >> 6);
@@ -1149,7 +1614,11 @@ void dock_sites_kernel(DockArgs X, QueueDev Q, SitesDev Sd) {
   const long long per_site = (long long)nlig * nch;
   const long long n_items = per_site * Sd.n_sites;
   Samples sm;
-  load_samples(X.G, X.D, B.ang, sm);
+  SampleReg<SPL ? SPL : 1> every;
+  if constexpr (SPL > 0)
+    load_every_sample(X.D, B.ang, every);
+  else
+    load_samples(X.G, X.D, B.ang, sm);
   int cur_lig = -1;
   LigReg<NSLOT> L;
   for (;;) {
@@ -1181,7 +1650,7 @@ void dock_sites_kernel(DockArgs X, QueueDev Q, SitesDev Sd) {
       for (int r = r0 + lane; r < r1; r += 64) S->D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");
       continue;
     }
-    for (int r = r0; r < r1; ++r) dock_restart<NSLOT, true, 4>(S, sm, L, lig, r, B);
+    for (int r = r0; r < r1; ++r) dock_restart<NSLOT, true, 4, SPL>(S, sm, every, L, lig, r, B);
   }
 }
 
@@ -1250,72 +1719,84 @@ size_t dock_lds_bytes(int nslot, int wpb, int tab_len, int angles) {
   return ((size_t)(tab_len + 3) / 4 + (size_t)(angles + 1) / 2 + (size_t)wpb * dock_wave_float4(nslot)) * sizeof(float4);
 }
 
+// Instances: NSLOT atom slots per lane; bounded scans (SPL 0; in kernels of their own for
+// LONE launches), or scans of every sample, SPL per lane.
+#define LG_INSTANCES(nslot, spl, CALL)                                                     \
+  switch ((nslot) * 10 + (spl)) {                                                          \
+    case 10: CALL(1, 0); case 20: CALL(2, 0); case 30: CALL(3, 0); case 40: CALL(4, 0);    \
+    case 11: CALL(1, 1); case 12: CALL(1, 2); case 14: CALL(1, 4);                         \
+    case 22: CALL(2, 2); case 24: CALL(2, 4);                                              \
+    default: return hipErrorInvalidValue;                                                  \
+  }
+
+template <int NS, int SP>
+hipError_t plain_launch(int wpb, const DockArgs& X, int lig, hipStream_t st) {
+  if constexpr (SP == 1) {
+    return hipErrorInvalidValue;   // never the better one here: no such instance
+  } else {
+    hipLaunchKernelGGL((dock_plain_kernel<NS, SP>), dim3((X.D.R + wpb - 1) / wpb), dim3(64 * wpb),
+                       dock_lds_bytes(NS, wpb, X.G.table_entries(SP == 0), X.D.A), st, X, lig);
+    return hipGetLastError();
+  }
+}
+
+hipError_t launch_dock_plain(int nslot, int spl, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D, int lig,
+                             hipStream_t st) {
+#define CALL(NS, SP) return plain_launch<NS, SP>(wpb, DockArgs{G, Lg, D}, lig, st)
+  LG_INSTANCES(nslot, spl, CALL)
+#undef CALL
+}
+
+template <int NS, int SP>
+constexpr auto bucket_kernel(bool lone) {
+  return SP == 0 && lone ? dock_bucket_kernel<NS, true, 0> : dock_bucket_kernel<NS, false, SP>;
+}
+
+hipError_t launch_dock_bucket(int nslot, int spl, bool lone, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
+                              const DockDev& D, const QueueDev& Q, hipStream_t st) {
+#define CALL(NS, SP)                                                                                 \
+  {                                                                                                  \
+    hipLaunchKernelGGL((bucket_kernel<NS, SP>(lone)), dim3(blocks), dim3(64 * wpb),                  \
+                       dock_lds_bytes(NS, wpb, G.table_entries(SP == 0), D.A), st, DockArgs{G, Lg, D}, Q);          \
+    return hipGetLastError();                                                                        \
+  }
+  LG_INSTANCES(nslot, spl, CALL)
+#undef CALL
+}
+
+hipError_t launch_dock_sites(int nslot, int spl, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
+                             const QueueDev& Q, const SitesDev& Sd, hipStream_t st) {
+#define CALL(NS, SP)                                                                                 \
+  {                                                                                                  \
+    hipLaunchKernelGGL((dock_sites_kernel<NS, SP>), dim3(blocks), dim3(64 * wpb),                    \
+                       dock_lds_bytes(NS, wpb, G.table_entries(SP == 0), D.A), st, DockArgs{G, Lg, D}, Q, Sd);      \
+    return hipGetLastError();                                                                        \
+  }
+  LG_INSTANCES(nslot, spl, CALL)
+#undef CALL
+}
+
+// Resident blocks per compute unit of a bucket kernel instance (the b of Eq. 1).
+hipError_t occupancy_dock_bucket(int nslot, int spl, bool lone, int wpb, int tab_len, int angles, int* blocks_per_cu) {
+#define CALL(NS, SP)                                                                                           \
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, bucket_kernel<NS, SP>(lone), 64 * wpb,    \
+                                                      dock_lds_bytes(NS, wpb, tab_len, angles))
+  LG_INSTANCES(nslot, spl, CALL)
+#undef CALL
+}
+
+hipError_t attributes_dock_bucket(int nslot, int spl, bool lone, hipFuncAttributes* attr) {
+#define CALL(NS, SP) return hipFuncGetAttributes(attr, reinterpret_cast<const void*>(bucket_kernel<NS, SP>(lone)))
+  LG_INSTANCES(nslot, spl, CALL)
+#undef CALL
+}
+
 #define LG_DISPATCH(nslot, CALL)              \
   switch (nslot) {                            \
     case 1: CALL(1); case 2: CALL(2);         \
     case 3: CALL(3); case 4: CALL(4);         \
     default: return hipErrorInvalidValue;     \
   }
-
-hipError_t launch_dock_plain(int nslot, int wpb, const GridDev& G, const LigDev& Lg, const DockDev& D, int lig,
-                             hipStream_t st) {
-  const int blocks = (D.R + wpb - 1) / wpb;
-#define CALL(NS)                                                                                     \
-  {                                                                                                  \
-    hipLaunchKernelGGL(dock_plain_kernel<NS>, dim3(blocks), dim3(64 * wpb),                          \
-                       dock_lds_bytes(NS, wpb, G.tab_len, D.A), st, DockArgs{G, Lg, D}, lig);        \
-    return hipGetLastError();                                                                        \
-  }
-  LG_DISPATCH(nslot, CALL)
-#undef CALL
-}
-
-hipError_t launch_dock_bucket(int nslot, bool lone, int wpb, int blocks, const GridDev& G, const LigDev& Lg,
-                              const DockDev& D, const QueueDev& Q, hipStream_t st) {
-#define CALL(NS)                                                                                     \
-  {                                                                                                  \
-    hipLaunchKernelGGL((lone ? dock_bucket_kernel<NS, true> : dock_bucket_kernel<NS, false>),        \
-                       dim3(blocks), dim3(64 * wpb), dock_lds_bytes(NS, wpb, G.tab_len, D.A), st,    \
-                       DockArgs{G, Lg, D}, Q);                                                       \
-    return hipGetLastError();                                                                        \
-  }
-  LG_DISPATCH(nslot, CALL)
-#undef CALL
-}
-
-hipError_t launch_dock_sites(int nslot, int wpb, int blocks, const GridDev& G, const LigDev& Lg, const DockDev& D,
-                             const QueueDev& Q, const SitesDev& Sd, hipStream_t st) {
-#define CALL(NS)                                                                                     \
-  {                                                                                                  \
-    hipLaunchKernelGGL(dock_sites_kernel<NS>, dim3(blocks), dim3(64 * wpb),                          \
-                       dock_lds_bytes(NS, wpb, G.tab_len, D.A), st, DockArgs{G, Lg, D}, Q, Sd);      \
-    return hipGetLastError();                                                                        \
-  }
-  LG_DISPATCH(nslot, CALL)
-#undef CALL
-}
-
-// Resident blocks per compute unit of a bucket kernel instance (the b of Eq. 1).
-hipError_t occupancy_dock_bucket(int nslot, bool lone, int wpb, int tab_len, int angles, int* blocks_per_cu) {
-#define CALL(NS)                                                                                           \
-  {                                                                                                        \
-    const size_t lds = dock_lds_bytes(NS, wpb, tab_len, angles);                                           \
-    return lone ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, dock_bucket_kernel<NS, true>,  \
-                                                               64 * wpb, lds)                              \
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, dock_bucket_kernel<NS, false>, \
-                                                               64 * wpb, lds);                             \
-  }
-  LG_DISPATCH(nslot, CALL)
-#undef CALL
-}
-
-hipError_t attributes_dock_bucket(int nslot, bool lone, hipFuncAttributes* attr) {
-#define CALL(NS)                                                                                             \
-  { return hipFuncGetAttributes(attr, lone ? reinterpret_cast<const void*>(dock_bucket_kernel<NS, true>)     \
-                                           : reinterpret_cast<const void*>(dock_bucket_kernel<NS, false>)); }
-  LG_DISPATCH(nslot, CALL)
-#undef CALL
-}
 
 hipError_t launch_topk(int nslot, const LigDev& Lg, const DockDev& D, int n, int k, float* score, int32_t* rid,
                        float* ox, float* oy, float* oz, float* all_scores, float* pivot, hipStream_t st) {

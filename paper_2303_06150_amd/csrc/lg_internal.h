@@ -47,6 +47,8 @@ struct GridDev {
   int nb8[3], nb4[3];    // bricks of 8 and of 4 nodes per axis
   int tab_p, tab_q[3], tab_c[3];   // first entries of their offset tables (see fill_brick_tables)
   int tab_bounds;                  // the tables hold them
+  // entries of the LDS tables, with or without those of the bounds (which come last)
+  __host__ __device__ int table_entries(bool bounds) const { return bounds ? tab_len : tab_base[2] + n[2] + 2; }
 };
 
 constexpr int kDilated = 15;   // dilated copies
@@ -202,17 +204,17 @@ __device__ __forceinline__ float wave_sum(float v) { return __int_as_float(wave_
 //     every axis; second: (p>>3)*128*nb8[first] + (p&7)*16 at tab_q[axis]
 //   dilated cubes (4 x 4 x 4 of 16 bits) at tab_c:
 //     (p>>2)*128 + (p&3)*2, (p>>2)*128*nb4x + (p&3)*8, (p>>2)*128*nb4x*nb4y + (p&3)*32
-__device__ __forceinline__ void fill_brick_tables(const GridDev& G, int* tab) {
+__device__ __forceinline__ void fill_brick_tables(const GridDev& G, int* tab, bool bounds) {
   const int longest = max(G.n[0], max(G.n[1], G.n[2])) + 2;
   for (int p = threadIdx.x; p < longest; p += blockDim.x) {
-    if (G.tab_bounds) tab[G.tab_p + p] = (p >> 3) * 128 + (p & 7) * 2;
+    if (bounds) tab[G.tab_p + p] = (p >> 3) * 128 + (p & 7) * 2;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       if (p >= G.n[a] + 2) continue;
       tab[G.tab_base[a] + p] = a == 0   ? (p >> 2) * 128 + (p & 3) * 4
                                : a == 1 ? (p >> 2) * 128 * G.nb[0] + (p & 3) * 16
                                         : (p >> 1) * 128 * G.nb[0] * G.nb[1] + (p & 1) * 64;
-      if (!G.tab_bounds) continue;
+      if (!bounds) continue;
       tab[G.tab_q[a] + p] = (p >> 3) * 128 * G.nb8[(a + 2) % 3] + (p & 7) * 16;
       tab[G.tab_c[a] + p] = a == 0   ? (p >> 2) * 128 + (p & 3) * 2
                             : a == 1 ? (p >> 2) * 128 * G.nb4[0] + (p & 3) * 8
