@@ -119,13 +119,16 @@ lg_tuning default_tuning() {
 //     tight ones (0.75 A 32.0 / 31.7, 1 A 33.3 / 30.9; 0.6 A 31.1 / 32.0), or ligands too
 //     small to repay the bound pass (up to 20 atoms 21.2 / 17.4; 20 to 40 atoms 37.3 /
 //     36.9, 26.2 / 28.3 at 0.25 A)
-//   65 to 128 atoms: 19.6 / 19.6 at 64 angles, 27.8 / 23.6 at 128, 38.1 / 35.5 at 256; with
-//     half as many translations or fewer the lanes would idle there (25.5 / 27.5)
+//   65 to 128 atoms, 65 to 128 angles: 27.8 / 23.6; with half as many translations or fewer
+//     the lanes would idle there (25.5 / 27.5), and at 64 angles the two are alike (19.6)
+//   65 to 128 atoms, 129 to 256 angles: a grid without bounds (68.5 / 52.0), nodes too fine
+//     or too coarse (0.2 A 96.9 / 72.8); else alike, by the size of the launch (38.1 / 35.5
+//     for 800 ligands of this class alone; 47.7 / 49.8 for 2 000 of 12 to 160 atoms)
 int every_sample(const lg::GridDev& G, int atoms, int A, int T) {
   const int spl = A <= 64 ? 1 : A <= 128 ? 2 : 4;
   if (A > 256 || T > 64 * spl || atoms > 128) return 0;
-  if (atoms > 64) return A > 64 && T > 32 * spl ? spl : 0;
   const bool windows = G.dil && G.inv_h > 1.4f && G.inv_h < 4.5f;
+  if (atoms > 64) return A > 64 && T > 32 * spl && (A <= 128 || !windows) ? spl : 0;
   return A <= 128 || !windows || atoms <= 32 ? spl : 0;
 }
 
