@@ -145,13 +145,30 @@ struct Samples {
   int tsub;           // lanes that share a translation group in the bound pass (log2): 0, 1, 2
   int gt0;            // translation group of sample 0
   bool bound_a, bound_t;   // rotations and torsions, translations: a bound pass pays (and is possible)
-  float tspan, treach;     // nodes that a translation group and that all displacements span, each way
   float dlow;         // least displacement of the lane's translation group
   float radius;       // largest |(cos, sin)| of a sample (1 up to rounding)
   float chord;        // every sample of a group lies within chord of its centre, in (cos, sin)
   float cc, cs;       // centre of the lane's group: the mean of its two middle samples
   const float2* ang;  // (cos, sin) of every sample, in LDS
 };
+
+// How far apart two FP32 sums of the same n grid values can be, whatever their
+// orders of addition (zero on grids whose sums are exact; the bound holds for all).
+// Infinite wherever n values can add up past the largest float, since n * n * vmax
+// does so first: a sum that ran to infinity on the way is above any finite bound.
+__device__ __forceinline__ float sum_slack(const GridDev& G, int n) { return G.vmax * (float)(n * n) * 4.8e-7f; }
+
+// Whether translation samples, GT to a group, have bounds in a grid.  A group spans less
+// than one node, also after the rounding of x + d and of the displacements (T / 2 steps
+// at most): |x| / h inside the grid is at most |c0| + n.  And no sum overflows: the
+// current pose's could be infinite in one order of addition, across the lanes, and not
+// in the other, its score as a sample.
+__device__ __forceinline__ bool translation_bounds(const GridDev& G, const DockDev& D, int GT) {
+  const float far = fmaxf(fmaxf(fabsf(G.c0[0]) + G.fn[0], fabsf(G.c0[1]) + G.fn[1]), fabsf(G.c0[2]) + G.fn[2]);
+  const float steps = fmaf(1.2e-7f, (float)D.T, (float)(GT - 1));
+  return fmaf(fabsf(D.delta) * G.inv_h, steps, 2.4e-7f * far) <= 0.998f &&
+         sum_slack(G, LG_MAX_ATOMS) < __builtin_inff();
+}
 
 __device__ __forceinline__ void load_samples(const GridDev& G, const DockDev& D, const float2* ang, Samples& sm) {
   const int lane = lane_id();
@@ -188,15 +205,12 @@ __device__ __forceinline__ void load_samples(const GridDev& G, const DockDev& D,
   sm.chord = none ? __builtin_inff() : prune_sqrt(w2) * 1.0001f + 1e-6f;
   sm.radius = none ? __builtin_inff() : prune_sqrt(r2) * 1.0001f;
   // a group may not span a whole node: 16 groups where that holds, else 32 or 64
-  const float step = fabsf(D.delta) * G.inv_h;
   sm.tsub = 2;
   for (;; --sm.tsub) {
     sm.GT = (D.T + (64 >> sm.tsub) - 1) >> (6 - sm.tsub);
-    sm.tspan = (float)(sm.GT - 1) * step;
-    sm.bound_t = sm.tspan <= 0.998f;
+    sm.bound_t = translation_bounds(G, D, sm.GT);
     if (sm.bound_t || sm.tsub == 0) break;
   }
-  sm.treach = 0.5f * (float)D.T * step;
   if (D.T <= 64) {   // one pass scores every sample
     sm.GT = 1;
     sm.bound_t = false;
@@ -273,23 +287,15 @@ __device__ __forceinline__ int select_sample(uint64_t alive, float bound, int G,
   return bj;
 }
 
-// How far apart two FP32 sums of the same n grid values can be, whatever their
-// orders of addition (zero on grids whose sums are exact; the bound holds for all).
-// Infinite wherever n values can add up past the largest float, since n * n * vmax
-// does so first: a sum that ran to infinity on the way is above any finite bound.
-__device__ __forceinline__ float sum_slack(const GridDev& G, int n) { return G.vmax * (float)(n * n) * 4.8e-7f; }
-
 // A bound on the FP32 sum of n grid values from the sum of their dilated copies
 // (whole numbers below 2^24).
 __device__ __forceinline__ float upper_bound(const GridDev& G, int n, int sum) {
   return fmaf((float)sum, G.bound_scale, sum_slack(G, n));
 }
 
-// Groups that may hold a sample better than s0.  A NaN bound or score keeps them all, and
-// so does an infinite bound: there a sum can run to infinity, and the current pose's does
-// so in one order of addition (s0) and not in the other (its score as a sample).
+// Groups that may hold a sample better than s0 (a NaN bound or score keeps them all).
 __device__ __forceinline__ uint64_t groups_above(float bound, float s0, int groups) {
-  return __ballot(lane_id() < groups && (!(bound <= s0) || bound == __builtin_inff()));
+  return __ballot(lane_id() < groups && !(bound <= s0));
 }
 
 // acc + value(0) + value(1) + ... + value(n - 1), added in that order; U values are
@@ -501,15 +507,12 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
   inside = !wave_any(!inside);
   wave_sync();
   const uint64_t all = sm.ngt < 64 ? (1ull << sm.ngt) - 1u : ~0ull;
-  // a group spans less than one node also after the rounding of x + d and of the
-  // displacements: |x| / h inside the grid is at most |c0| + n
-  const bool bound_t = sm.bound_t && fmaf(2.4e-7f, fabsf(cE) + fnE + sm.treach, sm.tspan) <= 0.998f;
   // (one sample: no displacement, whose range `inside` and the runs were taken for)
   auto displacement = [&](int j) { return D.delta * (float)(j < max(D.T / 2, 1) ? j : j - D.T); };
   auto index = [&](int pos) { return pos + mlo < 0 ? pos + mlo + D.T : pos + mlo; };   // position: order of displacement
   auto none = [](int, bool) { return false; };
   int j;
-  if ((!STAGE && !(bound_t && D.T > 128)) || span > 63) {
+  if ((!STAGE && !(sm.bound_t && D.T > 128)) || span > 63) {
     j = select_sample<true>(
         all, __builtin_inff(), sm.GT, D.T, 0.f, index,
         [&](int js) {
@@ -555,7 +558,7 @@ __device__ __forceinline__ int trans_scan(ArgsPtr S, PoseReg<NSLOT>& p, int N, f
     };
     float bound = __builtin_inff();
     uint64_t alive = all;
-    if (bound_t) {
+    if (sm.bound_t) {
       const int part = lane >> (6 - sm.tsub), step = 1 << sm.tsub;
       const float d = sm.dlow;
       float acc = 0.f;
@@ -1645,6 +1648,7 @@ void dock_sites_kernel(DockArgs X, QueueDev Q, SitesDev Sd) {
       cur_lig = lig;
     }
     const ArgsPtr S = (ArgsPtr)(Sd.sites + __builtin_amdgcn_readfirstlane(site));
+    if constexpr (SPL == 0) sm.bound_t = X.D.T > 64 && translation_bounds(grid_of(S), X.D, sm.GT);   // the site's
     const int r0 = ch * chunk, r1 = min(X.D.R, r0 + chunk);
     if (L.N > 64 * NSLOT) {
       for (int r = r0 + lane; r < r1; r += 64) S->D.final_scores[(size_t)lig * X.D.R + r] = __builtin_nanf("");

@@ -100,11 +100,38 @@ def test_translation_groups_far_from_the_origin(far):
     pk = moved(spiky(64, 0.365, 3), (far, -far, far))
     L = sized([(1, 0), (2, 0), (3, 0)], 4_400_000)
     r32, _ = gen.restarts(4000, 2)
-    a32, _ = gen.angles(64)
+    a32, _ = gen.angles(200)                                 # bounded scans
     say(f"translations near {far}")
     for T in (128, 256):                                     # 16 groups
         step = 0.9975 / (T // 16 - 1) * 0.365
         against_oracle(pk, L, r32, a32, T, 3, step, 1, f"T {T} far {far}")
+
+
+def test_translation_groups_of_each_site():
+    """One launch for a site at the origin, whose translation groups have bounds, and one so
+    far away that they have none: each as docked alone."""
+    import torch
+    from paper_2303_06150_amd import lg
+    near = spiky(64, 0.365, 3)
+    L = sized([(1, 0), (2, 0), (3, 0)], 4_400_000)
+    r32, _ = gen.restarts(2000, 2)
+    a32, _ = gen.angles(200)
+    rt, at = torch.from_numpy(r32).cuda(), torch.from_numpy(a32).cuda()
+    kw = dict(sweeps=2, top_k=3, trans_samples=128, trans_step=0.9975 / 7 * 0.365, clash_dist2=oracle.CLASH2,
+              want_all_scores=True)
+    dl = device_ligands(L)
+    pockets = [device_pocket(moved(near, by)) for by in ((0, 0, 0), (2e5, -2e5, 2e5))]
+    for order in (pockets, pockets[::-1]):
+        say("translations at two sites")
+        outs = lg.lg_dock_sites(order, dl, rt, at, **kw)
+        torch.cuda.synchronize()
+        for p, o in zip(order, outs):
+            alone = lg.lg_dock_batch(p, dl, rt, at, **kw)
+            torch.cuda.synchronize()
+            for key in alone:
+                assert torch.equal(o[key], alone[key]), key
+    for p in pockets:
+        p.free()
 
 
 def scattered(sizes, seed):
