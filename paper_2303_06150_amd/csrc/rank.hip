@@ -23,7 +23,7 @@
 // digits (a histogram and a pick launch each, 64-bit keys read up to nine times)
 // and a sort of the candidates by one block, 59 us with the keys' values staged
 // through LDS (29 us for 32 MB), 41 us as it is.
-// At most 4096 groups: one launch.
+// At most 4096 groups: one launch or two.
 #include "lg.h"
 #include "lg_internal.h"
 
@@ -57,6 +57,29 @@ __device__ __forceinline__ float group_best(const float* s, int group, int* memb
     if (s[q] > best) { best = s[q]; bm = q; }
   *member = bm;
   return best;
+}
+
+// Best value of a group by a row of 16 lanes, on every lane of it: the first value's if
+// that is NaN, else the largest of those that are not (as group_best has it).
+__device__ __forceinline__ float row_best(const float* s, int group) {
+  float best = s[0];
+  if (best != best) return best;
+#pragma unroll 4
+  for (int q = threadIdx.x & 15; q < group; q += 16) best = s[q] > best ? s[q] : best;
+#pragma unroll
+  for (int o = 1; o < 16; o *= 2) {
+    const float other = __shfl_xor(best, o);
+    best = other > best ? other : best;
+  }
+  return best;
+}
+
+// Value words of long groups, a row of 16 lanes each.
+__global__ __launch_bounds__(256) void rank_words_kernel(const float* score, int n, int group, uint32_t* words) {
+  const int g = blockIdx.x * 16 + ((int)threadIdx.x >> 4);
+  if (g >= n) return;
+  const uint32_t w = (uint32_t)(rank_key(row_best(score + (long long)g * group, group), 0) >> 32);
+  if ((threadIdx.x & 15) == 0) words[g] = w;
 }
 
 // Digits of the 64-bit key from the top: 11, 11, 10 bits of the value word, then
@@ -325,15 +348,20 @@ __global__ __launch_bounds__(256) void rank_place_kernel(const uint64_t* cand, c
   rank_place(s, count, score, n, group, m, top_idx, top_score, top_member);
 }
 
-// The whole ranking of at most kTile groups in one launch: every block takes all
-// keys from the scores (n * group values out of the L2, a few microseconds, where
-// each launch of the selection costs about as much) and places kPlaces.
-__global__ __launch_bounds__(256) void rank_small_kernel(const float* score, int n, int group, int m,
+// The ranking of at most kTile groups: every block takes all keys and places kPlaces.
+// Without stored words it takes them from the scores, one launch for everything, up to
+// kSmallValues values: each block reads them all, out of the L2 (4 096 groups: 44 us for
+// groups of 8, 74 of 24, 117 of 32, 200 of 64; the same 64 k values in 1 000 groups 61 us).
+// More values are read once, into words, by a launch before it.
+constexpr long long kSmallValues = 1 << 16;
+
+__global__ __launch_bounds__(256) void rank_small_kernel(const uint32_t* words, const float* score, int n, int group, int m,
                                                          int32_t* top_idx, float* top_score, int32_t* top_member) {
   __shared__ uint64_t s[kTile];
   for (int t = threadIdx.x; t < n; t += 256) {
     int member;
-    s[t] = rank_key(group_best(score + (long long)t * group, group, &member), t);
+    s[t] = words ? (uint64_t)words[t] << 32 | (uint64_t)(0xFFFFFFFFu - (uint32_t)t)
+                 : rank_key(group_best(score + (long long)t * group, group, &member), t);
   }
   __syncthreads();
   rank_place(s, n, score, n, group, m, top_idx, top_score, top_member);
@@ -437,9 +465,11 @@ hipError_t rank_static_scratch(void** out, size_t* bytes) {
 hipError_t launch_rank(const float* score, int n, int group, int m, void* work, int32_t* top_idx,
                        float* top_score, int32_t* top_member, hipStream_t st) {
   if (n <= 0 || m <= 0) return hipSuccess;
-  if (n <= kTile && group <= 64) {   // a block's share of larger groups would outlast the launches it saves
-    hipLaunchKernelGGL(rank_small_kernel, dim3((n + kPlaces - 1) / kPlaces), dim3(256), 0, st, score, n, group, m, top_idx,
-                       top_score, top_member);
+  if (n <= kTile) {
+    uint32_t* words = (long long)n * group <= kSmallValues ? nullptr : (uint32_t*)work;
+    if (words) hipLaunchKernelGGL(rank_words_kernel, dim3((n + 15) / 16), dim3(256), 0, st, score, n, group, words);
+    hipLaunchKernelGGL(rank_small_kernel, dim3((n + kPlaces - 1) / kPlaces), dim3(256), 0, st, words, score, n, group, m,
+                       top_idx, top_score, top_member);
     return hipGetLastError();
   }
   char* w = (char*)work;
