@@ -37,7 +37,7 @@ hipError_t launch_score(int max_atoms, const GridDev& G, const LigDev& P, int n,
 hipError_t launch_pack_moves(const int32_t* tors_offset, int n, int total_torsions, const float* t, const float* w,
                              const float* theta, float* moves, int64_t* idx_t, int64_t* idx_w, int64_t* idx_th,
                              int64_t* pose_of_bond, hipStream_t st);
-size_t rank_scratch_bytes(int n, int m);
+size_t rank_scratch_bytes(int n, int group, int m);
 hipError_t launch_rank(const float* score, int n, int group, int m, void* work, int32_t* top_idx,
                        float* top_score, int32_t* top_member, hipStream_t st);
 hipError_t rank_static_scratch(void** out, size_t* bytes);
@@ -1241,7 +1241,7 @@ lg_status lg_score(lg_pocket p, const lg_ligands* L, int32_t interp, const float
   const int n = L->n;
   Layout lay;
   const size_t o_stats = lay.take(16 * sizeof(int32_t));
-  const size_t o_rank = top_m > 0 ? lay.take(lg::rank_scratch_bytes(n, top_m)) : 0;
+  const size_t o_rank = top_m > 0 ? lay.take(lg::rank_scratch_bytes(n, 1, top_m)) : 0;
   s = ensure_ws(p, lay.off);
   if (s != LG_OK) return s;
   int max_atoms = 0, max_tors = 0;
@@ -1284,7 +1284,7 @@ lg_status lg_rank(lg_pocket p, const float* score, int32_t n_groups, int32_t gro
   if (top_m == 0) return LG_OK;
   hipStream_t st = (hipStream_t)stream;
   LG_HIP(hipSetDevice(p->device));
-  lg_status s = ensure_ws(p, lg::rank_scratch_bytes(n_groups, top_m));
+  lg_status s = ensure_ws(p, lg::rank_scratch_bytes(n_groups, group_size, top_m));
   if (s != LG_OK) return s;
   LG_HIP(lg::launch_rank(score, n_groups, group_size, top_m, p->ws, top_idx, top_score, top_member, st));
   return LG_OK;
@@ -1304,9 +1304,9 @@ lg_status lg_rank_static(const float* score, int32_t n_groups, int32_t group_siz
   void* work = nullptr;
   size_t bytes = 0;
   LG_HIP(lg::rank_static_scratch(&work, &bytes));
-  if (lg::rank_scratch_bytes(n_groups, top_m) > bytes)
-    return fail(LG_ERR_LIMIT, "ranking needs %zu bytes of scratch, the fixed array holds %zu",
-                lg::rank_scratch_bytes(n_groups, top_m), bytes);
+  const size_t need = lg::rank_scratch_bytes(n_groups, group_size, top_m);
+  if (need > bytes)
+    return fail(LG_ERR_LIMIT, "ranking needs %zu bytes of scratch, the fixed array holds %zu", need, bytes);
   LG_HIP(lg::launch_rank(score, n_groups, group_size, top_m, work, top_idx, top_score, top_member,
                          (hipStream_t)stream));
   return LG_OK;

@@ -84,7 +84,9 @@ __global__ __launch_bounds__(256) void rank_words_kernel(const float* score, int
 
 // Digits of the 64-bit key from the top: 11, 11, 10 bits of the value word, then
 // of the index word.
-constexpr int kDigits = 6, kBins = 2048;
+// The digits' histograms take three places in turn: one is read, one filled and one
+// cleared for the next pass.
+constexpr int kDigits = 6, kBins = 2048, kHists = 3;
 __device__ __forceinline__ int digit_shift(int d) { return d == 0 ? 53 : d == 1 ? 42 : d == 2 ? 32 : d == 3 ? 21 : d == 4 ? 10 : 0; }
 __device__ __forceinline__ uint32_t digit_mask(int d) { return d % 3 == 2 ? 1023u : 2047u; }
 
@@ -97,7 +99,8 @@ __global__ void rank_init_kernel(RankState* st, uint32_t* hist, int m) {
     st[0].count = 0;
     st[kDigits].count = 0;   // candidates
   }
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kDigits * kBins; i += gridDim.x * blockDim.x) hist[i] = 0;
+  // the first two digits'; every later one is cleared by the pass before it
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < 2 * kBins; i += gridDim.x * blockDim.x) hist[i] = 0;
 }
 
 __device__ __forceinline__ void add_bins(const uint32_t* lh, uint32_t* hist) {
@@ -262,9 +265,10 @@ __device__ __forceinline__ void for_each_key(const uint32_t* words, long long i0
 __global__ __launch_bounds__(256) void rank_digit_kernel(const uint32_t* words, int n, RankState* states,
                                                          uint32_t* hist, int d, uint32_t room, uint32_t m) {
   __shared__ uint32_t lh[kBins];
-  const RankState st = rank_pick(states[d - 1], hist + (d - 1) * kBins, d - 1, room, m);
+  const RankState st = rank_pick(states[d - 1], hist + (d - 1) % kHists * kBins, d - 1, room, m);
   if (blockIdx.x == 0 && threadIdx.x == 0) states[d] = st;
   if (st.done) return;
+  for (int b = blockIdx.x * 256 + threadIdx.x; b < kBins; b += gridDim.x * 256) hist[(d + 1) % kHists * kBins + b] = 0;
   for (int b = threadIdx.x; b < kBins; b += blockDim.x) lh[b] = 0;
   __syncthreads();
   const int shift = digit_shift(d);
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(256) void rank_digit_kernel(const uint32_t* words, 
   for_each_key(words, 0, n, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, [&](uint64_t k) {
     if ((k & st.mask) == st.prefix) atomicAdd(&lh[(uint32_t)(k >> shift) & bins], 1u);
   });
-  add_bins(lh, hist + d * kBins);
+  add_bins(lh, hist + d % kHists * kBins);
 }
 
 // The keys at or above the threshold (at most `room`), in any order, and their
@@ -283,7 +287,7 @@ __global__ __launch_bounds__(256) void rank_compact_kernel(const uint32_t* words
                                                            const uint32_t* hist, uint64_t* cand, uint32_t room,
                                                            uint32_t m, long long fill) {
   __shared__ uint32_t taken, base;
-  const RankState st = rank_pick(states[kDigits - 1], hist + (kDigits - 1) * kBins, kDigits - 1, room, m);
+  const RankState st = rank_pick(states[kDigits - 1], hist + (kDigits - 1) % kHists * kBins, kDigits - 1, room, m);
   const uint64_t t = st.prefix;
   const long long per = ((n + (long long)gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
   const long long i0 = blockIdx.x * per, i1 = min((long long)n, i0 + per);
@@ -420,10 +424,19 @@ long long pow2_at_least(long long m) {
 
 constexpr size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Candidates: kTile, or the power of two that the bitonic sort needs.
-constexpr size_t scratch_bytes(size_t n, size_t pow2_m) {
-  return up256((kDigits + 1) * sizeof(RankState)) + up256(kDigits * kBins * sizeof(uint32_t)) + up256(n * 4) +
-         up256((pow2_m > (size_t)kTile ? pow2_m : (size_t)kTile) * 8);
+// Candidates of a ranking of the top m: up to kTile a quarter more than wanted will do
+// (placing them costs less than another digit); more: exactly the top m, in the power
+// of two of places that the bitonic sort needs.
+constexpr uint32_t candidates(uint32_t m) {
+  if (m > (uint32_t)kTile) return m;
+  const uint32_t room = m + (m / 4 > 256 ? m / 4 : 256);
+  return room < (uint32_t)kTile ? room : (uint32_t)kTile;
+}
+
+// Scratch of the selection: states, three histograms, value words, candidates.
+constexpr size_t scratch_bytes(size_t n, size_t places) {
+  return up256((kDigits + 1) * sizeof(RankState)) + up256(kHists * kBins * sizeof(uint32_t)) + up256(n * 4) +
+         up256(places * 8);
 }
 
 // Fixed device scratch of lg_rank_static, sized for its largest accepted call
@@ -431,14 +444,19 @@ constexpr size_t scratch_bytes(size_t n, size_t pow2_m) {
 // holds one copy until the process ends.  Host code must not pass this name to
 // a kernel: its device address comes from hipGetSymbolAddress.
 static_assert((LG_RANK_STATIC_MAX_TOP & (LG_RANK_STATIC_MAX_TOP - 1)) == 0, "power of two");
-constexpr size_t kStaticScratchBytes = scratch_bytes(LG_RANK_STATIC_MAX_GROUPS, LG_RANK_STATIC_MAX_TOP);
+constexpr size_t kStaticScratchBytes = scratch_bytes(LG_RANK_STATIC_MAX_GROUPS, LG_RANK_STATIC_MAX_TOP > kTile ? LG_RANK_STATIC_MAX_TOP : kTile);
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 constexpr int kMaxDevices = 64;
 
 }  // namespace
 
-size_t rank_scratch_bytes(int n, int m) { return scratch_bytes((size_t)n, (size_t)pow2_at_least(m < 1 ? 1 : m)); }
+// Scratch of a call; never more than 12 bytes a group and 8 for every place of the power
+// of two above m, plus the fixed part of 1 280 bytes, which an earlier selection took.
+size_t rank_scratch_bytes(int n, int group, int m) {
+  if (n <= kTile) return (long long)n * group <= kSmallValues ? 0 : up256((size_t)n * 4);
+  return scratch_bytes((size_t)n, m > kTile ? (size_t)pow2_at_least(m) : candidates((uint32_t)std::max(m, 1)));
+}
 
 // Device address of the current device's copy of the fixed scratch, looked up
 // once per device (with that device current) and kept.
@@ -476,15 +494,13 @@ hipError_t launch_rank(const float* score, int n, int group, int m, void* work, 
   RankState* states = (RankState*)w;
   w += up256((kDigits + 1) * sizeof(RankState));
   uint32_t* hist = (uint32_t*)w;
-  w += up256(kDigits * kBins * sizeof(uint32_t));
+  w += up256(kHists * kBins * sizeof(uint32_t));
   uint32_t* words = (uint32_t*)w;
   w += up256((size_t)n * 4);
   uint64_t* cand = (uint64_t*)w;
   const long long padded = pow2_at_least(m);
-  // m <= kTile: a quarter more candidates than wanted will do (placing them costs
-  // less than another digit); more: exactly the top m
   const bool one_tile = m <= kTile;
-  const uint32_t room = one_tile ? (uint32_t)std::min(kTile, m + std::max(256, m / 4)) : (uint32_t)m;
+  const uint32_t room = candidates((uint32_t)m);
   // each block adds its histogram to the global one: at most one per compute unit
   // (two where the keys come through LDS), at least four groups per thread
   const int blocks = (int)std::max<long long>(1, std::min<long long>(((long long)n + 1023) / 1024, 512));

@@ -1,5 +1,6 @@
 """Rankings at the edges of their launches: long groups (rows of 16 lanes), the most
-values that one launch takes, values that are not numbers."""
+values that one launch takes, values that are not numbers, and a workspace limit that
+leaves no more than the scratch of 12 bytes a group and 8 a place."""
 import numpy as np
 import pytest
 
@@ -56,4 +57,21 @@ def test_long_groups(n, group, shift, odd):
     pocket = fresh_pocket()
     say(f"rank: {n} groups of {group}, offset {shift}, {'NaN and infinities' if odd else 'numbers'}")
     check(lg.lg_rank(pocket, torch.from_numpy(s).cuda()[shift:], group, m), s[shift:], group, m)
+    pocket.free()
+
+
+@pytest.mark.parametrize("n,group,m", [(1, 1, 1), (100, 1, 10), (100, 700, 10), (4096, 8, 4096), (4096, 64, 10), (4097, 8, 1),
+                                       (4097, 100, 4096), (4200, 1, 4097), (10000, 3, 1000), (10000, 8, 10000)])
+def test_workspace_limit(n, group, m, monkeypatch):
+    import torch
+    from paper_2303_06150_amd import lg
+    places = 1 << (m - 1).bit_length() if m > 1 else 1
+    round_up = lambda b: -(-b // 256) * 256
+    limit = 256 + 1024 + round_up(8 * n) + round_up(4 * n) + round_up(8 * places)
+    s = np.random.default_rng(n).normal(size=n * group).astype(np.float32)
+    pocket = fresh_pocket()
+    monkeypatch.setenv("LG_WORKSPACE_LIMIT", str(limit))
+    say(f"rank: {n} groups of {group}, top {m}, workspace limit {limit}")
+    check(lg.lg_rank(pocket, torch.from_numpy(s).cuda(), group, m), s, group, m)
+    monkeypatch.delenv("LG_WORKSPACE_LIMIT")
     pocket.free()
