@@ -116,9 +116,10 @@ __device__ __forceinline__ void add_bins(const uint32_t* lh, uint32_t* hist) {
 // those additions are contended (a whole ranking of one million groups of eight:
 // 59 us through LDS, 43 with 512 blocks of 256, 41 with 256 of 1 024).  Otherwise a
 // block takes 256 groups at a time, whose values are one stretch, read coalesced
-// into LDS (groups of up to kStageGroup values; larger ones are long stretches
-// themselves).
-constexpr int kStageGroup = 24;
+// into LDS (groups of up to kStageGroup values); longer ones, and any from kLongGroup
+// values on, are read by rows of 16 lanes, 16 groups a block and time (50 000 groups of
+// 200: a thread a group leaves 25 blocks of work, 168 us a call; 92 so).
+constexpr int kStageGroup = 24, kLongGroup = 64;
 constexpr int kGroupsInFlight = 2, kKeyThreads = 1024;
 
 template <bool VEC>
@@ -172,20 +173,23 @@ __global__ __launch_bounds__(VEC ? kKeyThreads : 256) void rank_keys_kernel(cons
     }
   } else {
     __shared__ float vals[256 * kStageGroup];
-    const bool stage = group <= kStageGroup;
-    for (long long g0 = blockIdx.x * 256LL; g0 < n; g0 += gridDim.x * 256LL) {
-      const int groups = (int)min(256LL, n - g0);
-      if (stage) {
+    if (group > kStageGroup) {
+      for (long long g = blockIdx.x * 16LL + (threadIdx.x >> 4); g < n; g += gridDim.x * 16LL) {
+        const float best = row_best(score + g * group, group);
+        if ((threadIdx.x & 15) == 0) put(g, best);
+      }
+    } else {
+      for (long long g0 = blockIdx.x * 256LL; g0 < n; g0 += gridDim.x * 256LL) {
+        const int groups = (int)min(256LL, n - g0);
         const float* src = score + g0 * group;
         for (int t = threadIdx.x; t < groups * group; t += 256) vals[t] = src[t];
         __syncthreads();
+        if ((int)threadIdx.x < groups) {
+          int member;
+          put(g0 + threadIdx.x, group_best(vals + (int)threadIdx.x * group, group, &member));
+        }
+        __syncthreads();
       }
-      if ((int)threadIdx.x < groups) {
-        int member;
-        put(g0 + threadIdx.x, stage ? group_best(vals + (int)threadIdx.x * group, group, &member)
-                                    : group_best(score + (g0 + threadIdx.x) * group, group, &member));
-      }
-      if (stage) __syncthreads();
     }
   }
   add_bins(lh, hist);
@@ -501,15 +505,19 @@ hipError_t launch_rank(const float* score, int n, int group, int m, void* work, 
   const long long padded = pow2_at_least(m);
   const bool one_tile = m <= kTile;
   const uint32_t room = candidates((uint32_t)m);
-  // each block adds its histogram to the global one: at most one per compute unit
-  // (two where the keys come through LDS), at least four groups per thread
-  const int blocks = (int)std::max<long long>(1, std::min<long long>(((long long)n + 1023) / 1024, 512));
-  const int few = std::min(blocks, 256);
+  // each block adds its histogram to the global one: at most one per compute unit (two
+  // where the keys come through LDS or by rows), at least four groups per thread or row
+  const auto share = [](long long count, long long per, long long most) {
+    return (int)std::max<long long>(1, std::min<long long>((count + per - 1) / per, most));
+  };
+  const int few = share(n, 1024, 256);
   hipLaunchKernelGGL(rank_init_kernel, dim3(12), dim3(256), 0, st, states, hist, m);
-  if (group % 4 == 0 && (uintptr_t)score % 16 == 0)
-    hipLaunchKernelGGL(rank_keys_kernel<true>, dim3(few), dim3(kKeyThreads), 0, st, score, n, group, words, hist);
+  if (group % 4 == 0 && group < kLongGroup && (uintptr_t)score % 16 == 0)
+    hipLaunchKernelGGL(rank_keys_kernel<true>, dim3(share(n, kKeyThreads * kGroupsInFlight, 256)), dim3(kKeyThreads), 0, st,
+                       score, n, group, words, hist);
   else
-    hipLaunchKernelGGL(rank_keys_kernel<false>, dim3(blocks), dim3(256), 0, st, score, n, group, words, hist);
+    hipLaunchKernelGGL(rank_keys_kernel<false>, dim3(share(n, group > kStageGroup ? 64 : 1024, 512)), dim3(256), 0, st,
+                       score, n, group, words, hist);
   for (int d = 1; d < kDigits; ++d)
     hipLaunchKernelGGL(rank_digit_kernel, dim3(few), dim3(256), 0, st, words, n, states, hist, d, room, (uint32_t)m);
   hipLaunchKernelGGL(rank_compact_kernel, dim3(few), dim3(256), 0, st, words, n, states, hist, cand, room,
