@@ -32,8 +32,8 @@ hipError_t launch_dock_sites(int nslot, int spl, int wpb, int blocks, const Grid
 hipError_t attributes_dock_bucket(int nslot, int spl, bool lone, hipFuncAttributes* attr);
 hipError_t launch_topk(int nslot, const LigDev& Lg, const DockDev& D, int n, int k, float* score, int32_t* rid,
                        float* ox, float* oy, float* oz, float* all_scores, float* pivot, hipStream_t st);
-hipError_t launch_score(int max_atoms, const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
-                        hipStream_t st);
+hipError_t launch_score(int max_atoms, int total_atoms, const GridDev& G, const LigDev& P, int n, int interp, float* score,
+                        float* grad, hipStream_t st);
 hipError_t launch_pack_moves(const int32_t* tors_offset, int n, int total_torsions, const float* t, const float* w,
                              const float* theta, float* moves, int64_t* idx_t, int64_t* idx_w, int64_t* idx_th,
                              int64_t* pose_of_bond, hipStream_t st);
@@ -1253,7 +1253,7 @@ lg_status lg_score(lg_pocket p, const lg_ligands* L, int32_t interp, const float
   if (moves)
     LG_HIP(lg::launch_score_moves((max_atoms + 63) / 64, p->grid, lig_dev(L), moves, n, score, grad, st));
   else
-    LG_HIP(lg::launch_score(max_atoms, p->grid, lig_dev(L), n, interp, score, grad, st));
+    LG_HIP(lg::launch_score(max_atoms, L->total_atoms, p->grid, lig_dev(L), n, interp, score, grad, st));
   if (top_m > 0)
     LG_HIP(lg::launch_rank(score, n, 1, top_m, (char*)p->ws + o_rank, top_idx, top_score, nullptr, st));
   return LG_OK;

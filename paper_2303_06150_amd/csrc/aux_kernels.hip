@@ -14,8 +14,10 @@ __global__ void zero_kernel(int32_t* p, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// Sum over the 16 lanes of a row, on every lane of it.
+// Sum over the W lanes (16 or 64) of a row, on every lane of it.
+template <int W>
 __device__ __forceinline__ float row_sum(float v) {
+  if (W == 64) return wave_sum(v);
   auto add = [&](int moved) { v += __int_as_float(moved); };
   add(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
   add(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
@@ -26,19 +28,19 @@ __device__ __forceinline__ float row_sum(float v) {
 
 // Score of every pose = sum over its atoms in atom order; optional gradient with
 // respect to (t, omega, theta) at zero (force / torque form).
-// A pose takes a row of 16 lanes, atom 16 s + lane in slot s < S, so a wavefront
-// works on four poses, its lanes are filled to a sixteenth of a pose, and a sum
-// over a pose is four DPP steps.  Bounded by vector issue: per bond 16 operations
+// A pose takes a row of W lanes, atom W s + lane in slot s < S.  With rows of 16 a
+// wavefront works on four poses, its lanes are filled to a sixteenth of a pose, and a
+// sum over a pose is four DPP steps.  Bounded by vector issue: per bond 16 operations
 // a slot and 12 to add up.  A wavefront per pose spent three quarters of its time on
 // atom-by-atom broadcasts and on 64-lane reductions of 41 atoms: 200 000 poses of
 // 41 atoms 520 us, as it is 231 us.
-template <int S>
+template <int S, int W>
 __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, int interp, float* score,
                                                      float* grad) {
   extern __shared__ float4 lds[];
-  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id(), row = lane >> 4, l = lane & 15;
-  float4* pos = lds + (size_t)(wave * 4 + row) * (16 * S);   // the pose's atoms: coordinates and value
-  const int i = (blockIdx.x * nwaves + wave) * 4 + row;
+  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, lane = lane_id(), row = lane / W, l = lane % W;
+  float4* pos = lds + (size_t)(wave * (64 / W) + row) * (W * S);   // the pose's atoms: coordinates and value
+  const int i = (blockIdx.x * nwaves + wave) * (64 / W) + row;
   const bool live = i < n;
   const int abase = live ? P.atom_offset[i] : 0, N = live ? P.atom_offset[i + 1] - abase : 0;
   const int most = wave_reduce_i32(N, OpMax());
@@ -49,8 +51,8 @@ __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, 
   for (int s = 0; s < S; ++s) {
     x[0][s] = x[1][s] = x[2][s] = g[0][s] = g[1][s] = g[2][s] = 0.f;
     mk[s] = 0u;
-    if (16 * s >= most) continue;
-    const int a = 16 * s + l;
+    if (W * s >= most) continue;
+    const int a = W * s + l;
     if (a < N) {
       const float px = P.x[abase + a], py = P.y[abase + a], pz = P.z[abase + a];
       x[0][s] = px;
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, 
     for (int c = 0; c < 3; ++c) Pv[c] = live ? P.ref[3 * (size_t)i + c] : 0.f;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      if (16 * s >= most) continue;
+      if (W * s >= most) continue;
       const float rx = x[0][s] - Pv[0], ry = x[1][s] - Pv[1], rz = x[2][s] - Pv[2];
       f[0] += g[0][s];
       f[1] += g[1][s];
@@ -100,31 +102,31 @@ __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, 
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      f[c] = row_sum(f[c]);
-      tq[c] = row_sum(tq[c]);
+      f[c] = row_sum<W>(f[c]);
+      tq[c] = row_sum<W>(tq[c]);
     }
     const float mine = l == 0 ? f[0] : l == 1 ? f[1] : l == 2 ? f[2] : l == 3 ? tq[0] : l == 4 ? tq[1] : tq[2];
     if (l < 6 && live) out[l] = mine;
   }
-  // bonds 16 b .. 16 b + 15 of the four poses: lane l holds bond 16 b + l's axis and
-  // takes its sums
+  // bonds W b .. W b + W - 1 of the poses: lane l holds bond W b + l's axis and takes its
+  // sums
   const int bonds = wave_reduce_i32(K, OpMax());
-  for (int b = 0; 16 * b < bonds; ++b) {
-    const int mine = 16 * b + l;
+  for (int b = 0; W * b < bonds; ++b) {
+    const int mine = W * b + l;
     int pa = 0, pb = 0;
     if (mine < K) {
       pa = P.tors_atoms[2 * (toff + mine)];
       pb = P.tors_atoms[2 * (toff + mine) + 1];
     }
     float own[3] = {0.f, 0.f, 0.f};
-    const int last = min(16, bonds - 16 * b);
+    const int last = min(W, bonds - W * b);
     for (int q = 0; q < last; ++q) {
-      const int k = 16 * b + q;
-      const float4 at = pos[__builtin_amdgcn_ds_bpermute(((lane & 48) | q) << 2, pa)];   // bond k's pivot atom, of the row's pose
+      const int k = W * b + q;
+      const float4 at = pos[__builtin_amdgcn_ds_bpermute((row * W | q) << 2, pa)];   // bond k's pivot atom, of the row's pose
       float t[3] = {0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < S; ++s) {
-        if (16 * s >= most) continue;
+        if (W * s >= most) continue;
         const bool in = (mk[s] >> k) & 1u;
         const float rx = x[0][s] - at.x, ry = x[1][s] - at.y, rz = x[2][s] - at.z;
         const float t0 = ry * g[2][s] - rz * g[1][s], t1 = rz * g[0][s] - rx * g[2][s], t2 = rx * g[1][s] - ry * g[0][s];
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, 
       }
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const float sum = row_sum(t[c]);
+        const float sum = row_sum<W>(t[c]);
         own[c] = l == q ? sum : own[c];
       }
     }
@@ -150,18 +152,29 @@ __global__ __launch_bounds__(256) void score_kernel(GridDev G, LigDev P, int n, 
   }
 }
 
-hipError_t launch_score(int max_atoms, const GridDev& G, const LigDev& P, int n, int interp, float* score, float* grad,
-                        hipStream_t st) {
+// Instances by the batch's largest pose.  Above 128 atoms the 16 slots of a row of 16 take
+// a pose's chain four times as long as a wavefront of its own, which shows while few
+// poses leave the chip idle: wavefronts of their own up to 2 048 poses (64 poses of 180 to
+// 256 atoms 66 us by rows, 44 so; 1 000 75, 53), or 8 192 where they are small on average
+// (5 000 of 41 atoms with one of 200 among them 81, 66).  Many poses are faster by rows
+// (200 000 of 41 atoms 231 us against 520 by a wavefront each).
+hipError_t launch_score(int max_atoms, int total_atoms, const GridDev& G, const LigDev& P, int n, int interp, float* score,
+                        float* grad, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  const int slots = max_atoms <= 64 ? 4 : max_atoms <= 128 ? 8 : 16;
+  const bool own = max_atoms > 128 && n <= (total_atoms / n <= 64 ? 8192 : 2048);
+  const int slots = own ? 4 : max_atoms <= 64 ? 4 : max_atoms <= 128 ? 8 : 16;
   const int wpb = slots == 16 ? 2 : 4;   // 32 KB of LDS a block at most
-  const dim3 grid((unsigned)(((long long)n + 4 * wpb - 1) / (4 * wpb))), block(64 * wpb);
-  const size_t bytes = (size_t)wpb * 4 * 16 * slots * sizeof(float4);
-  switch (slots) {
-    case 4: hipLaunchKernelGGL(score_kernel<4>, grid, block, bytes, st, G, P, n, interp, score, grad); break;
-    case 8: hipLaunchKernelGGL(score_kernel<8>, grid, block, bytes, st, G, P, n, interp, score, grad); break;
-    default: hipLaunchKernelGGL(score_kernel<16>, grid, block, bytes, st, G, P, n, interp, score, grad); break;
-  }
+  const int rows = own ? 1 : 4, width = 64 / rows;
+  const dim3 grid((unsigned)(((long long)n + rows * wpb - 1) / (rows * wpb))), block(64 * wpb);
+  const size_t bytes = (size_t)wpb * rows * width * slots * sizeof(float4);
+  if (own)
+    hipLaunchKernelGGL((score_kernel<4, 64>), grid, block, bytes, st, G, P, n, interp, score, grad);
+  else if (slots == 4)
+    hipLaunchKernelGGL((score_kernel<4, 16>), grid, block, bytes, st, G, P, n, interp, score, grad);
+  else if (slots == 8)
+    hipLaunchKernelGGL((score_kernel<8, 16>), grid, block, bytes, st, G, P, n, interp, score, grad);
+  else
+    hipLaunchKernelGGL((score_kernel<16, 16>), grid, block, bytes, st, G, P, n, interp, score, grad);
   return hipGetLastError();
 }
 
