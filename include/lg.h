@@ -166,10 +166,13 @@ typedef struct {
 
 /* Load a docking site: copies the grid (host or device memory, per
  * grid_is_device) into a library-owned device copy kept for the handle's
- * life.  Finite grids of at most 2^25 padded nodes also get copies that bound
- * the scans' scores, about eight times the grid's bytes of device memory; without
- * them (or the memory) docking selects the same samples, more slowly.  *out
- * receives the handle; the call synchronises `stream`. */
+ * life.  *out receives the handle; the call synchronises `stream`.
+ * The first docking call of more than 64 translation samples reads the grid's
+ * largest value, and the first of more than 128 angle samples makes copies of the
+ * grid that bound the scans' scores, about eight times the grid's bytes of device
+ * memory; those calls wait for it (finite grids of at most 2^25 padded nodes; not
+ * on a stream that is being captured).  Without them, or the memory, docking
+ * selects the same samples, more slowly. */
 lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t grid_is_device,
                          void* stream, lg_pocket* out);
 

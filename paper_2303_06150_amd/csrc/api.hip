@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <thread>
 #include <vector>
@@ -106,6 +107,9 @@ lg_tuning default_tuning() {
   return t;
 }
 
+// Whether nodes are of a size for which the bounds' windows fit and are tight.
+bool windows_fit(const lg::GridDev& G) { return G.inv_h > 1.4f && G.inv_h < 4.5f; }
+
 // Samples per lane of the instance for a class of up to `atoms` atoms that scores every
 // sample, 0 for the one that bounds groups of samples first.  The line lies where the two
 // cross, in ms, bounded / every sample (256 restarts, two sweeps, nodes of 0.375 A where
@@ -127,7 +131,7 @@ lg_tuning default_tuning() {
 int every_sample(const lg::GridDev& G, int atoms, int A, int T) {
   const int spl = A <= 64 ? 1 : A <= 128 ? 2 : 4;
   if (A > 256 || T > 64 * spl || atoms > 128) return 0;
-  const bool windows = G.dil && G.inv_h > 1.4f && G.inv_h < 4.5f;
+  const bool windows = G.dil && windows_fit(G);
   if (atoms > 64) return A > 64 && T > 32 * spl && (A <= 128 || !windows) ? spl : 0;
   return A <= 128 || !windows || atoms <= 32 ? spl : 0;
 }
@@ -147,7 +151,11 @@ struct lg_pocket_s {
   lg_pocket_desc desc{};
   float* padded = nullptr;
   float* brick = nullptr;
-  char* dil = nullptr;             // dilated copies of the brick grid, then the grid's largest |value|
+  // what bounds the scans, from the first docking calls that use it: see docking_grid
+  std::mutex bounds_mu;
+  bool measured = false, copied = false;   // vmax read; dilated copies made, or tried to
+  float vmax = HUGE_VALF;
+  char* dil = nullptr;
   lg::GridDev grid{};
   void* ws = nullptr;
   size_t ws_bytes = 0;
@@ -193,6 +201,60 @@ lg_status ensure_ws(lg_pocket p, size_t bytes) {
   return LG_OK;
 }
 
+
+// The pocket's grid for a docking call: with its largest |value| where groups of samples
+// may have bounds, and with the copies for those where it has bounded scans of angles
+// (`lone`: a launch of the LONE instances, which has no others).  Both are made once, on
+// the handle's own stream, by the first call that uses them: a load would pay several
+// times its own cost for them, also for handles that only score, refine or rank (96^3
+// nodes 150 us alone, 447 with them; 256^3 790 and 6 640).  They only save work: grids of
+// more than 2^25 nodes or with values that are not finite do without, and so does a device
+// short of memory, and a call on a stream that is being captured, which can neither
+// allocate nor wait.
+lg::GridDev docking_grid(lg_pocket p, int max_atoms, int A, int T, bool lone, hipStream_t st) {
+  lg::GridDev G = p->grid;
+  if (!G.tab_bounds || (A <= 128 && T <= 64)) return G;
+  const bool copies = A > 128 && (lone || A > 256 || T > 256 || max_atoms > 64 || windows_fit(G));
+  std::lock_guard<std::mutex> lock(p->bounds_mu);   // several calls may use a handle as one of their sites
+  if (!p->measured || (copies && !p->copied)) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (st && (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+      (void)hipGetLastError();
+      return G;
+    }
+  }
+  if (!p->measured) {
+    const long long nodes = (long long)(G.n[0] + 2) * (G.n[1] + 2) * (G.n[2] + 2);
+    uint32_t* at = reinterpret_cast<uint32_t*>(p->padded + nodes);
+    uint32_t bits = 0xFFFFFFFFu;
+    if (lg::launch_grid_max(p->padded, nodes, at, p->capture) != hipSuccess ||
+        hipMemcpyAsync(&bits, at, sizeof bits, hipMemcpyDeviceToHost, p->capture) != hipSuccess ||
+        hipStreamSynchronize(p->capture) != hipSuccess) {
+      (void)hipGetLastError();
+      return G;
+    }
+    p->measured = true;
+    if (bits < 0x7F800000u) std::memcpy(&p->vmax, &bits, sizeof p->vmax);
+  }
+  G.vmax = p->vmax;
+  if (!std::isfinite(G.vmax)) return G;
+  if (G.vmax > 1e-30f) G.bound_scale = G.vmax / 32000.f;
+  if (copies && !p->copied) {
+    p->copied = true;
+    if (hipMalloc((void**)&p->dil, (size_t)lg::kDilated * G.dil_stride) != hipSuccess) {
+      p->dil = nullptr;
+    } else {
+      G.dil = p->dil;
+      if (lg::launch_dilate(G, p->padded, p->capture) != hipSuccess || hipStreamSynchronize(p->capture) != hipSuccess) {
+        (void)hipFree(p->dil);
+        p->dil = nullptr;
+      }
+    }
+    if (!p->dil) (void)hipGetLastError();
+  }
+  G.dil = p->dil;
+  return G;
+}
 
 // Device-side validation of offsets and bond ids (one small read-back).
 lg_status check_on_device(lg_pocket p, const lg_ligands* L, int32_t* dstats, hipStream_t st, int* max_atoms,
@@ -258,7 +320,7 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
   p->desc = *desc;
   const int nx = desc->nx, ny = desc->ny, nz = desc->nz;
   const size_t padded = (size_t)(nx + 2) * (ny + 2) * (nz + 2);
-  if (hipMalloc(&p->padded, padded * sizeof(float)) != hipSuccess) {
+  if (hipMalloc(&p->padded, (padded + 1) * sizeof(float)) != hipSuccess) {   // the grid, then its largest |value|
     (void)hipGetLastError();
     delete p;
     return fail(LG_ERR_OUT_OF_MEMORY, "grid allocation failed");
@@ -298,38 +360,16 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
     G.nb8[a] = (G.n[a] + 2 + 7) / 8;
     G.nb4[a] = (G.n[a] + 2 + 3) / 4;
   }
-  // the dilated copies only save work: grids of more than 2^25 nodes, or a device
-  // short of memory, do without, and so do grids with values that are not finite
+  if (s == LG_OK && hipStreamSynchronize(st) != hipSuccess) s = fail(LG_ERR_DEVICE, "stream synchronise failed");
+  G.vmax = HUGE_VALF;
+  G.bound_scale = 1.f;
   size_t stride = (size_t)128 * G.nb4[0] * G.nb4[1] * G.nb4[2];
   for (int e = 0; e < 3; ++e)
     stride = std::max(stride, (size_t)128 * (G.n[e] + 2) * G.nb8[(e + 1) % 3] * G.nb8[(e + 2) % 3]);
-  stride = align256(stride);
-  uint32_t vmax_bits = 0xFFFFFFFFu;
-  if (s == LG_OK && padded <= kMaxDilated) {
-    if (hipMalloc((void**)&p->dil, lg::kDilated * stride + 256) != hipSuccess) {
-      (void)hipGetLastError();
-      p->dil = nullptr;
-    } else {
-      uint32_t* vmax = reinterpret_cast<uint32_t*>(p->dil + lg::kDilated * stride);
-      if (lg::launch_grid_max(p->padded, (long long)padded, vmax, st) != hipSuccess ||
-          hipMemcpyAsync(&vmax_bits, vmax, sizeof vmax_bits, hipMemcpyDeviceToHost, st) != hipSuccess ||
-          hipStreamSynchronize(st) != hipSuccess)
-        s = fail(LG_ERR_DEVICE, "reading the grid's largest value failed");
-    }
-  }
-  const bool finite = vmax_bits < 0x7F800000u;
-  G.vmax = HUGE_VALF;
-  if (finite) std::memcpy(&G.vmax, &vmax_bits, sizeof G.vmax);
-  G.bound_scale = finite && G.vmax > 1e-30f ? G.vmax / 32000.f : 1.f;
-  G.dil = finite ? p->dil : nullptr;
-  G.dil_stride = (uint32_t)stride;
-  if (s == LG_OK && G.dil && lg::launch_dilate(G, p->padded, st) != hipSuccess)
-    s = fail(LG_ERR_DEVICE, "dilation kernel launch failed");
-  if (s == LG_OK && hipStreamSynchronize(st) != hipSuccess) s = fail(LG_ERR_DEVICE, "stream synchronise failed");
+  G.dil_stride = (uint32_t)align256(stride);
   if (s != LG_OK) {
     (void)hipFree(p->padded);
     if (p->brick) (void)hipFree(p->brick);
-    if (p->dil) (void)hipFree(p->dil);
     delete p;
     return s;
   }
@@ -367,7 +407,6 @@ lg_status lg_load_pocket(const lg_pocket_desc* desc, const float* grid, int32_t 
   if (hipStreamCreateWithFlags(&p->capture, hipStreamNonBlocking) != hipSuccess) {
     (void)hipFree(p->padded);
     (void)hipFree(p->brick);
-    if (p->dil) (void)hipFree(p->dil);
     delete p;
     return fail(LG_ERR_DEVICE, "stream creation failed");
   }
@@ -497,6 +536,12 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
   D.trace = O->trace;
   D.trace_w = 6 + (O->trace ? O->trace_kmax : 0);
   const lg::LigDev Lg = lig_dev(L);
+  // at most two wavefronts per SIMD (four SIMDs per compute unit): the instance
+  // with more fetches in flight, one wavefront per block, so that all compute
+  // units' caches take part (one ligand of 256 restarts: 256 blocks, not 64)
+  const long long items = (long long)n * R;
+  const bool lone = P->mode == LG_BUCKETED && items <= 8LL * p->cus;
+  const lg::GridDev grid = docking_grid(p, max_atoms, D.A, D.T, lone, st);
   const int topk_slots = std::max(1, (max_atoms + 63) / 64);   // replay instance for the largest ligand
   const int spl = spl_for(D.A, D.T);
 
@@ -513,13 +558,13 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
     // 2.23).
     auto plain_spl = [&](int atoms) {
       if (D.A <= 64) return 0;
-      const int spl = every_sample(p->grid, atoms, D.A, D.T);
+      const int spl = every_sample(grid, atoms, D.A, D.T);
       const bool few = R <= 8 * p->cus && atoms <= 64 && D.A > 128 && D.A <= 256 && D.T > 128 && D.T <= 256;
       return spl == 0 && few ? 4 : spl;
     };
     for (int i = 0; i < n; ++i) {
       const int atoms = host_sized ? L->atom_offset_host[i + 1] - L->atom_offset_host[i] : max_atoms;
-      LG_HIP(lg::launch_dock_plain((atoms + 63) / 64, plain_spl(atoms), wpb, p->grid, Lg, D, i, st));
+      LG_HIP(lg::launch_dock_plain((atoms + 63) / 64, plain_spl(atoms), wpb, grid, Lg, D, i, st));
     }
     LG_HIP(lg::launch_topk(topk_slots, Lg, D, n, P->top_k, O->score, O->restart_id, O->x, O->y, O->z, O->all_scores,
                            O->pivot, st));
@@ -547,6 +592,8 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
   fb[2] = (uint32_t)O->trace_kmax;
   for (uint32_t v : fb) key.push_back(v);
   key.push_back((uint64_t)max_atoms);   // sizes the kernel instances of the plan
+  key.push_back((uint64_t)(uintptr_t)grid.dil);
+  key.push_back(std::isfinite(grid.vmax) ? 1u : 0u);
 
   lg::ClusterBounds cb;
   std::memset(&cb, 0, sizeof cb);
@@ -557,13 +604,8 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
   // every atom cluster must fit its kernel instance: the last one takes the rest
   cb.atom[cb.na - 1] = LG_MAX_ATOMS;
 
-  // at most two wavefronts per SIMD (four SIMDs per compute unit): the instance
-  // with more fetches in flight, one wavefront per block, so that all compute
-  // units' caches take part (one ligand of 256 restarts: 256 blocks, not 64)
-  const long long items = (long long)n * R;
-  const bool lone = items <= 8LL * p->cus;
   auto bucket_spl = [&](int ca) {
-    return lone ? 0 : every_sample(p->grid, std::min(cb.atom[ca], max_atoms), D.A, D.T);
+    return lone ? 0 : every_sample(grid, std::min(cb.atom[ca], max_atoms), D.A, D.T);
   };
   auto plan = [&](std::vector<lg_bucket_stat>& launches) -> lg_status {
     // Eq. 1: resident blocks per CU of each instance give the persistent grid
@@ -571,7 +613,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
       // the instance holds the cluster's largest possible ligand: its bound, or the
       // batch's largest ligand if that is smaller (the last bound is LG_MAX_ATOMS)
       const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
-      const int every = bucket_spl(ca), entries = p->grid.table_entries(every == 0);
+      const int every = bucket_spl(ca), entries = grid.table_entries(every == 0);
       const int wpb = lone ? 1 : tu.waves_per_block[nslot - 1];
       int bpc = 0;
       LG_HIP(lg::occupancy_dock_bucket(nslot, every, lone, wpb, entries, D.A, &bpc));
@@ -619,7 +661,7 @@ lg_status dock_batch_impl(lg_pocket p, const lg_ligands* L, const lg_dock_params
       lg::QueueDev Q{perm, start, cursors, b.bucket, tu.restart_chunk};
       const int ca = b.bucket / cb.nr;
       if (e == hipSuccess && (ca == 0 || cb.atom[ca - 1] < max_atoms))   // else no ligand of the batch is that large
-        e = lg::launch_dock_bucket(b.slots, bucket_spl(ca), lone, b.waves_per_block, b.blocks, p->grid, Lg, D, Q, cs);
+        e = lg::launch_dock_bucket(b.slots, bucket_spl(ca), lone, b.waves_per_block, b.blocks, grid, Lg, D, Q, cs);
       if (e == hipSuccess && timed) e = hipEventRecord(p->events[2 + 2 * l], cs);
     }
     if (e == hipSuccess && timed) e = hipEventRecord(p->events[1 + 2 * nl], cs);
@@ -997,9 +1039,11 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
   D.trace_w = 6;
   const lg::LigDev Lg = lig_dev(L);
   std::vector<lg::DockArgs> sites((size_t)n_sites, lg::DockArgs{p->grid, Lg, D});
+  bool bounded = true;   // every site has bounds
   for (int si = 0; si < n_sites; ++si) {
     lg::DockArgs& x = sites[si];
-    x.G = pockets[si]->grid;
+    x.G = docking_grid(pockets[si], max_atoms, D.A, D.T, false, st);
+    bounded = bounded && x.G.dil;
     for (int a = 0; a < 3; ++a) x.D.c[a] = pockets[si]->desc.center[a];
     x.D.final_scores = D.final_scores + (size_t)si * n * R;
     x.D.moves = D.moves + (size_t)si * moves_per_site;
@@ -1008,9 +1052,8 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
   LG_HIP(hipMemcpyAsync(dsites, sites.data(), sites.size() * sizeof(lg::DockArgs), hipMemcpyHostToDevice, st));
   LG_HIP(hipStreamSynchronize(st));   // the table's host copy ends with this call
   lg::SitesDev Sd{dsites, n_sites, site_major ? 1 : 0};
-  lg::GridDev sites_grid = p->grid;   // with bounds if every site has them
-  for (int si = 0; si < n_sites; ++si)
-    if (!pockets[si]->grid.dil) sites_grid.dil = nullptr;
+  lg::GridDev grid = sites[0].G;
+  if (!bounded) grid.dil = nullptr;
 
   lg::ClusterBounds cb;
   std::memset(&cb, 0, sizeof cb);
@@ -1031,13 +1074,13 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
     const int nslot = std::max(1, (std::min(cb.atom[ca], max_atoms) + 63) / 64);
     const int wpb = tu.waves_per_block[nslot - 1];
     int bpc = 0;
-    const int every = every_sample(sites_grid, std::min(cb.atom[ca], max_atoms), D.A, D.T);
-    LG_HIP(lg::occupancy_dock_bucket(nslot, every, false, wpb, p->grid.table_entries(every == 0), D.A, &bpc));
+    const int every = every_sample(grid, std::min(cb.atom[ca], max_atoms), D.A, D.T);
+    LG_HIP(lg::occupancy_dock_bucket(nslot, every, false, wpb, grid.table_entries(every == 0), D.A, &bpc));
     if (bpc < 1) return fail(LG_ERR_DEVICE, "kernel instance (%d slots) cannot be resident", nslot);
     if (ca > 0 && cb.atom[ca - 1] >= max_atoms) continue;   // no ligand of the batch is that large
     for (int cr = cb.nr - 1; cr >= 0; --cr) {
       lg::QueueDev Q{perm, start, cursors, ca * cb.nr + cr, tu.restart_chunk};
-      LG_HIP(lg::launch_dock_sites(nslot, every, wpb, bpc * p->cus * tu.grid_scale, p->grid, Lg, D, Q, Sd, st));
+      LG_HIP(lg::launch_dock_sites(nslot, every, wpb, bpc * p->cus * tu.grid_scale, grid, Lg, D, Q, Sd, st));
     }
   }
   const int topk_slots = std::max(1, (max_atoms + 63) / 64);

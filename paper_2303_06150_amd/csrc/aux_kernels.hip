@@ -265,12 +265,17 @@ __device__ __forceinline__ int round_up_to(float v, float scale) {
   return q;
 }
 
-// One step of the dilated copies: the largest of the source's nodes at offsets lo
-// and hi along the copy's axes (two of a plane, all three of a cube), clamped to
-// the padded extent.  Windows of 2, 3, 4 and 6 nodes are built from those before
-// (2 of the grid's own values, 3 and 4 of twos, 6 of fours), four or eight reads
-// a node.
-__global__ void dilate_kernel(GridDev G, const float* padded, const char* src, int e, int lo, int hi, char* dst) {
+// One step of the dilated copies, of kind e = e0 + blockIdx.y (a plane across an axis,
+// or cubes): level `to` from level `from` (-1: the grid's own values), the largest of
+// the source's nodes at offsets lo and hi along the copy's axes (two of a plane, all
+// three of a cube), clamped to the padded extent.  Windows of 2, 3, 4 and 6 nodes are
+// built from those before (2 of the grid's own values, 3 and 4 of twos, 6 of fours),
+// four or eight reads a node.
+__global__ void dilate_kernel(GridDev G, const float* padded, int e0, int from, int to, int lo, int hi) {
+  const int e = e0 + (int)blockIdx.y;
+  char* copies = const_cast<char*>(G.dil) + (size_t)(4 * e) * G.dil_stride;
+  const char* src = from < 0 ? nullptr : copies + (size_t)from * G.dil_stride;
+  char* dst = copies + (size_t)to * G.dil_stride;
   const int px[3] = {G.n[0] + 2, G.n[1] + 2, G.n[2] + 2};
   const int total = px[0] * px[1] * px[2];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
@@ -290,25 +295,20 @@ __global__ void dilate_kernel(GridDev G, const float* padded, const char* src, i
   }
 }
 
-// G: the finished description of the grid, dil included.
+// G: the finished description of the grid, dil included.  Planes (e = 0, 1, 2) and cubes
+// (e = 3) that take the same step share a launch.
 hipError_t launch_dilate(const GridDev& G, const float* padded, hipStream_t st) {
-  char* dil = const_cast<char*>(G.dil);
-  auto copy = [&](int i) { return dil + (size_t)i * G.dil_stride; };
   const long long total = (long long)(G.n[0] + 2) * (G.n[1] + 2) * (G.n[2] + 2);
   const int blocks = (int)std::min<long long>((total + 255) / 256, 8192);
-  auto step = [&](int from, int e, int lo, int hi, int to) {
-    hipLaunchKernelGGL(dilate_kernel, dim3(blocks), dim3(256), 0, st, G, padded, from < 0 ? nullptr : copy(from), e, lo,
-                       hi, copy(to));
+  auto step = [&](int e0, int kinds, int from, int to, int lo, int hi) {
+    hipLaunchKernelGGL(dilate_kernel, dim3(blocks, kinds), dim3(256), 0, st, G, padded, e0, from, to, lo, hi);
   };
-  for (int e = 0; e < 3; ++e) {
-    step(-1, e, 0, 1, 4 * e);              // 2 x 2
-    step(4 * e, e, 0, 1, 4 * e + 1);       // 3 x 3
-    step(4 * e, e, 0, 2, 4 * e + 2);       // 4 x 4
-    step(4 * e + 2, e, 0, 2, 4 * e + 3);   // 6 x 6
-  }
-  step(-1, 3, 0, 1, 12);    // i .. i + 1
-  step(12, 3, -1, 1, 13);   // i - 1 .. i + 2
-  step(13, 3, -1, 1, 14);   // i - 2 .. i + 3
+  step(0, 4, -1, 0, 0, 1);   // planes 2 x 2, cubes i .. i + 1
+  step(0, 3, 0, 1, 0, 1);    // 3 x 3
+  step(0, 3, 0, 2, 0, 2);    // 4 x 4
+  step(0, 3, 2, 3, 0, 2);    // 6 x 6
+  step(3, 1, 0, 1, -1, 1);   // i - 1 .. i + 2
+  step(3, 1, 1, 2, -1, 1);   // i - 2 .. i + 3
   return hipGetLastError();
 }
 
