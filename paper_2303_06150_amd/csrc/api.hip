@@ -1429,16 +1429,15 @@ lg_status lg_refine(lg_pocket p, const lg_ligands* L, const lg_refine_params* rp
   int32_t* fill = start + nb + 1;
   int32_t* cursors = fill + nb;
   LG_HIP(lg::launch_bucketing(L->atom_offset, L->tors_offset, n, cb, cls, counts, start, fill, perm, cursors, st));
-  // at most four wavefronts per SIMD (four SIMDs per compute unit), what the
-  // combined kernel's registers allow at once: the poses of all classes together
   // One launch for all classes while the tails of one launch per class weigh more
   // than the registers that the combined kernel adds: 19 200 poses of up to 256 atoms
   // 5.4 ms by class, 2.3 ms combined; 50 000 mixed poses 3.44 and 3.28; 128 000 7.3
-  // and 7.9.  The wide gradient tile up to 16 poses per compute unit: twice what its
-  // LDS allows at once, but pairs halve the wavefronts (4 000 poses 798 us, narrow
-  // 868; 8 000 poses 1 088 and 907).
+  // and 7.9.  Up to 64 atoms there are two classes and less of a tail: 64 000 poses of 12 to
+  // 60 atoms without bonds 1.96 ms by class, 2.09 combined; 32 000 1.17 and 1.12.  The wide
+  // gradient tile up to 16 poses per compute unit: twice what its LDS allows at once, but
+  // pairs halve the wavefronts (4 000 poses 798 us, narrow 868; 8 000 poses 1 088 and 907).
   const long long poses = (long long)n * kpl;
-  if (poses <= 256LL * p->cus) {
+  if (poses <= (max_atoms <= 64 ? 128LL : 256LL) * p->cus) {
     LG_HIP(lg::launch_refine_classes(max_atoms, p->grid, lig_dev(L), R, perm, start, cb, pairs, (int)poses,
                                    poses <= 16LL * p->cus, st));
     return LG_OK;
