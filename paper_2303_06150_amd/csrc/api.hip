@@ -159,6 +159,8 @@ struct lg_pocket_s {
   lg::GridDev grid{};
   void* ws = nullptr;
   size_t ws_bytes = 0;
+  lg::DockArgs* sites = nullptr;   // table of the sites of a call with this handle first
+  int sites_room = 0;
   lg_tuning tuning = default_tuning();
   hipGraphExec_t gexec = nullptr;
   std::vector<uint64_t> gkey;
@@ -421,6 +423,7 @@ lg_status lg_free_pocket(lg_pocket p) {
   if (p->capture) (void)hipStreamDestroy(p->capture);
   for (hipEvent_t e : p->events) (void)hipEventDestroy(e);
   if (p->ws) (void)hipFree(p->ws);
+  if (p->sites) (void)hipFree(p->sites);
   if (p->padded) (void)hipFree(p->padded);
   if (p->brick) (void)hipFree(p->brick);
   if (p->dil) (void)hipFree(p->dil);
@@ -1013,7 +1016,6 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
   const size_t o_cls = lay.take((size_t)n * sizeof(int32_t));
   const size_t o_perm = lay.take((size_t)n * sizeof(int32_t));
   const size_t o_cnt = lay.take((size_t)(4 * B + 1) * sizeof(int32_t));
-  const size_t o_sites = lay.take((size_t)n_sites * sizeof(lg::DockArgs));
   s = ensure_ws(p, lay.off);
   if (s != LG_OK) return s;
   char* ws = (char*)p->ws;
@@ -1048,7 +1050,20 @@ lg_status dock_sites_impl(const lg_pocket* pockets, int32_t n_sites, const lg_li
     x.D.final_scores = D.final_scores + (size_t)si * n * R;
     x.D.moves = D.moves + (size_t)si * moves_per_site;
   }
-  lg::DockArgs* dsites = (lg::DockArgs*)(ws + o_sites);
+  // the table has a buffer of its own: under a workspace limit it may take more than the
+  // workspace of a small call (about half a kilobyte a site)
+  if (n_sites > p->sites_room) {
+    LG_HIP(hipFree(p->sites));   // waits for the calls before
+    p->sites = nullptr;
+    p->sites_room = 0;
+    if (hipMalloc((void**)&p->sites, (size_t)n_sites * sizeof(lg::DockArgs)) != hipSuccess) {
+      (void)hipGetLastError();
+      p->sites = nullptr;
+      return fail(LG_ERR_OUT_OF_MEMORY, "table of %d sites could not be allocated", n_sites);
+    }
+    p->sites_room = n_sites;
+  }
+  lg::DockArgs* dsites = p->sites;
   LG_HIP(hipMemcpyAsync(dsites, sites.data(), sites.size() * sizeof(lg::DockArgs), hipMemcpyHostToDevice, st));
   LG_HIP(hipStreamSynchronize(st));   // the table's host copy ends with this call
   lg::SitesDev Sd{dsites, n_sites, site_major ? 1 : 0};
