@@ -570,7 +570,9 @@ def main():
     dom_ms = float(np.mean(bucket_ms[dom["bucket"]]))
     sel = bid == dom["bucket"]
     dom_ops, dom_plain, dom_looks = float(ops[sel].sum()), float(plain_ops[sel].sum()), float(looks[sel].sum())
-    kernel = f"dock_bucket_kernel<{dom['slots']},false>"
+    # third argument: samples per lane of scans of every sample, 0 for bounded scans
+    spl = 0 if w.angle_samples > 128 or dom["slots"] > 2 else 1 if w.angle_samples <= 64 else 2
+    kernel = f"dock_bucket_kernel<{dom['slots']},false,{spl}>"
     tune_key = tuning_key(tuning)
     # HBM bytes and VALU issue of the dominant launch, from the committed rocprofv3
     # counter summaries, when they were taken on this kernel source and tuning

@@ -334,7 +334,7 @@ lg_status lg_rank(lg_pocket pocket, const float* score, int32_t n_groups, int32_
 /* lg_rank for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): same
  * arguments and results as lg_rank, no pocket handle, and no allocation of any
- * kind.  Its scratch is a fixed device array in the library (about 12 MiB,
+ * kind.  Its scratch is a fixed device array in the library (about 4 MiB,
  * one copy per device, held until the process ends), looked up on the first
  * call on each device; the device is the caller's current device, which must
  * own `stream` and the buffers.  Limits: n_groups <= LG_RANK_STATIC_MAX_GROUPS

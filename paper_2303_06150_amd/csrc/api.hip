@@ -175,8 +175,6 @@ struct lg_pocket_s {
 
 namespace {
 
-
-
 lg_status ensure_ws(lg_pocket p, size_t bytes) {
   if (bytes <= p->ws_bytes) return LG_OK;
   const size_t limit = workspace_limit();

@@ -8,8 +8,6 @@
 
 namespace lg {
 
-
-
 __global__ void zero_kernel(int32_t* p, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
 }

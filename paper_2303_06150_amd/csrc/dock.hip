@@ -6,10 +6,10 @@
 // score of every group of neighbouring samples (one group per lane) from above,
 // then scores the samples of the groups whose bound exceeds the current pose's
 // score, one sample per lane: the selected sample is that of a scan over every
-// sample, at about half the lookups.  Each lane loops over the atoms of the
-// scan, reading per-atom scan data that the wavefront staged in LDS (broadcast
-// reads), and accumulates nearest-voxel values gathered from the L2-resident
-// grid.  The pose lives in registers, atom a = 64 s + lane in slot s < NSLOT.
+// sample, at about half the lookups.  Where no bound pass pays or is possible, scans
+// score every sample, several per lane.  Each lane loops over the atoms of the scan,
+// reading per-atom scan data that the wavefront staged in LDS (broadcast reads), and
+// accumulates nearest-voxel values gathered from the L2-resident grid.  The pose lives in registers, atom a = 64 s + lane in slot s < NSLOT.
 // The best sample comes from a DPP/readlane reduction (lowest index among equal
 // scores).  Torsion samples are tested for intramolecular clashes against a
 // pruned list of the pairs that can clash at some angle.

@@ -126,18 +126,19 @@ struct SitesDev {
   int site_major;           // 1: site by site; 0: every site of a ligand in turn
 };
 
-// Persistent work source of one bucket: items are (ligand of the bucket,
-// chunk of `chunk` restarts), pulled from `cursor` by whole wavefronts.
 // LDS of a docking wavefront, in float4: scan data of 64*nslot atoms, risky
 // torsion pairs, data of the moving atoms, the ligand's fragment masks (one
 // 32-bit word per atom).  The two middle regions together hold the bound-pass
 // data of a rotation scan (two float4 per atom) or the staged nodes of a
-// translation scan.  The pair list takes what leaves the instances their
-// occupancy (a list holds at least every pair of one atom).
+// translation scan; in scans of every sample the pair list takes both.  The bounded
+// scans' list takes what leaves the instances their occupancy (a list holds at least
+// every pair of one atom).
 constexpr int pair_cap(int nslot) { return nslot == 1 ? 128 : 64 * nslot; }
 constexpr int dock_wave_float4(int nslot) { return 2 * 64 * nslot + pair_cap(nslot) + 16 * nslot; }
 constexpr int stage_floats(int nslot) { return 4 * (pair_cap(nslot) + 64 * nslot); }
 
+// Persistent work source of one bucket: items are (ligand of the bucket,
+// chunk of `chunk` restarts), pulled from `cursor` by whole wavefronts.
 struct QueueDev {
   const int32_t* perm;          // ligand ids grouped by bucket
   const int32_t* bucket_start;  // [B+1]

@@ -265,12 +265,11 @@ __device__ __forceinline__ float column_sum(const float* col, int n, float acc) 
 // Trilinear score and its gradient with respect to the local move at zero;
 // sums in atom order.  g_out: t[3], w[3], then theta[K] into th_grad.  Column
 // 0 is the score, 1..3 the force, 4..6 the torque about the pivot, 7 + 3k + d
-// component d of bond k's torque about its pivot atom over F_k.  pos holds the
-// pose p; lane k holds bond k's axis.
+// component d of bond k's torque about its pivot atom over F_k.  Lane k holds bond
+// k's axis.
 template <int NSLOT, int COLS>
 __device__ float move_gradient(const GridDev& G, const MoveState<NSLOT>& p, const uint32_t (&mk)[NSLOT], int N,
-                               int K, const int2* tors, const float4* pos, const LaneAxis& ax, float* g_out,
-                               float* th_grad, float* tile, float* res) {
+                               int K, const LaneAxis& ax, float* g_out, float* th_grad, float* tile, float* res) {
   const int lane = lane_id();
   float v[NSLOT], g[3][NSLOT];
 #pragma unroll
@@ -279,7 +278,7 @@ __device__ float move_gradient(const GridDev& G, const MoveState<NSLOT>& p, cons
     v[s] = (s * 64 + lane < N) ? trilinear(G, p.x[0][s], p.x[1][s], p.x[2][s], gg) : 0.f;
     g[0][s] = gg[0]; g[1][s] = gg[1]; g[2][s] = gg[2];
   }
-  // column chunks: the 7 pose columns with bonds 0..2, then 5 bonds per chunk
+  // column chunks: the 7 pose columns with the first bonds, then as many bonds as fit
   for (int k0 = 0, first = 1; first || k0 < K; first = 0) {
     const int base = first ? 7 : 0;
     const int nb = min(K - k0, (COLS - base) / 3);
@@ -492,7 +491,7 @@ __device__ __forceinline__ void refine_pose(const GridDev& G, const LigDev& P, c
     if (fresh) {
       ax = lane_axis(pos, tors, inv_len, K);
       wave_sync();
-      const float sc = move_gradient<NSLOT, COLS>(G, cur, mk, N, K, tors, pos, ax, g, thg, tile, res);
+      const float sc = move_gradient<NSLOT, COLS>(G, cur, mk, N, K, ax, g, thg, tile, res);
       wave_sync();
       if (pending && sc > best_s) {
         best_s = sc;
@@ -1074,7 +1073,7 @@ __global__ __launch_bounds__(256) void score_moves_kernel(GridDev G, LigDev P, c
   float g[6];
   wave_sync();
   const LaneAxis ax = lane_axis(pos, tors, inv_len, K);
-  const float sc = move_gradient<NSLOT, tile_cols(NSLOT)>(G, p, mk, N, K, tors, pos, ax, g, th, tile, res);
+  const float sc = move_gradient<NSLOT, tile_cols(NSLOT)>(G, p, mk, N, K, ax, g, th, tile, res);
   wave_sync();
   if (lane == 0) score[i] = sc;
   if (!grad) return;
