@@ -49,10 +49,11 @@ class RefineScore(torch.autograd.Function):
         # the pack kernel runs on the current device, and both calls on its current
         # stream: the poses' device, whichever one the caller has current
         with torch.cuda.device(dev):
+            stream = torch.cuda.current_stream()
             moves, idx_t, idx_w, idx_th, pose_of_bond = lg.lg_pack_moves(
                 poses, _parameter(t, 3 * poses.n, dev), _parameter(w, 3 * poses.n, dev),
-                _parameter(theta, poses.total_torsions, dev))
-            res = lg.lg_score(pocket, poses, lg.LG_TRILINEAR, grad=True, moves=moves)
+                _parameter(theta, poses.total_torsions, dev), stream=stream)
+            res = lg.lg_score(pocket, poses, lg.LG_TRILINEAR, grad=True, moves=moves, stream=stream)
         ctx.save_for_backward(res["grad"])
         ctx.layout = (idx_t, idx_w, idx_th, pose_of_bond)
         ctx.n = poses.n

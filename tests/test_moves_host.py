@@ -60,7 +60,8 @@ def test_binding_refuses_what_the_kernel_cannot_read():
 
 
 def test_forward_runs_on_the_poses_device(monkeypatch):
-    """Both library calls happen with the poses' device current, whatever the caller's is."""
+    """Both library calls happen with the poses' device current, whatever the caller's is,
+    and on its current stream."""
     current = []
 
     class Device:
@@ -75,17 +76,18 @@ def test_forward_runs_on_the_poses_device(monkeypatch):
 
     calls = []
 
-    def pack(poses, t, w, theta):
-        calls.append(("pack", list(current)))
+    def pack(poses, t, w, theta, stream):
+        calls.append(("pack", list(current), stream))
         return (torch.zeros(9), *(torch.arange(3),) * 4)
 
-    def score(pocket, poses, interp, grad, moves):
-        calls.append(("score", list(current)))
+    def score(pocket, poses, interp, grad, moves, stream):
+        calls.append(("score", list(current), stream))
         return dict(score=torch.ones(1), grad=torch.ones(9))
 
     monkeypatch.setattr(torch.cuda, "device", Device)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: f"stream of {current[-1]}")
     monkeypatch.setattr(lg, "lg_pack_moves", pack)
     monkeypatch.setattr(lg, "lg_score", score)
     poses = types.SimpleNamespace(x=torch.zeros(1), n=1, total_torsions=3)
     RefineScore.apply(torch.zeros(1, 3), torch.zeros(1, 3), torch.zeros(3), None, poses)
-    assert calls == [("pack", [CPU]), ("score", [CPU])] and current == []
+    assert calls == [("pack", [CPU], "stream of cpu"), ("score", [CPU], "stream of cpu")] and current == []
